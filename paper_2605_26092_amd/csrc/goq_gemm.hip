@@ -42,6 +42,7 @@
 #include <type_traits>
 #include "goq_layout.h"
 #include "goq_decode.h"
+#include "goq_activations.h"
 #include "goq_internal.h"
 
 namespace {
@@ -249,7 +250,6 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     // Register staging (ACT >= 2): integer activations pass through registers and are unpacked /
     // widened on their way into LDS.  A thread moves NPS 16-byte pieces per slab; a piece holds
     // 16 int8 or 32 int4 activations and becomes OUTP 16-byte pieces of the LDS row.
-    // int -> fp16 without a conversion instruction: 0x6400 | u is the fp16 number 1024 + u.
     // (int6 / int3: a source piece is 24 / 12 bytes = 32 activations = two 16-byte LDS pieces of
     // int8, fetched as three 8-byte / 4-byte loads)
     constexpr int SRCROW = X4 ? GOQ_N / 2 : X6 ? GOQ_N * 3 / 4 : X3 ? GOQ_N * 3 / 8 : GOQ_N;   // bytes of a slab row in memory
@@ -285,37 +285,6 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
             }
         }
     };
-    // four int8 -> two registers of two fp16
-    auto widen_i8 = [](uint32_t d, uint32_t &h0, uint32_t &h1) {
-        const goq_half2 off = {(_Float16)1152.f, (_Float16)1152.f};
-        const uint32_t u = d ^ 0x80808080u;                        // x + 128
-        h0 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(goq_half2, goq_perm(0x64646464u, u, 0x04010400u)) - off);
-        h1 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(goq_half2, goq_perm(0x64646464u, u, 0x04030402u)) - off);
-    };
-    // eight int4 (element i in nibble i) -> two registers of four int8
-    auto unpack_i4 = [](uint32_t d, uint32_t &b0, uint32_t &b1) {
-        auto sext = [](uint32_t v) {      // per byte: low nibble, two's complement -> int8
-            return ((((v ^ 0x08080808u) | 0x80808080u) - 0x08080808u) ^ 0x80808080u);
-        };
-        const uint32_t ev = sext(d & 0x0F0F0F0Fu);                 // elements 0, 2, 4, 6
-        const uint32_t od = sext((d >> 4) & 0x0F0F0F0Fu);          // elements 1, 3, 5, 7
-        b0 = goq_perm(od, ev, 0x05010400u);                        // elements 0, 1, 2, 3
-        b1 = goq_perm(od, ev, 0x07030602u);                        // elements 4, 5, 6, 7
-    };
-    // four int6 (24 bits, element i in bits 6 i .. 6 i + 5) -> one register of four int8
-    auto unpack_i6 = [](uint32_t v) {
-        const uint32_t b = (v & 0x3Fu) | ((v << 2) & 0x3F00u) | ((v << 4) & 0x3F0000u) | ((v << 6) & 0x3F000000u);
-        return ((((b ^ 0x20202020u) | 0x80808080u) - 0x20202020u) ^ 0x80808080u);   // per byte: 6 -> 8 bits, signed
-    };
-    // eight int3 (24 bits, element i in bits 3 i .. 3 i + 2) -> two registers of four int8
-    auto unpack_i3 = [](uint32_t v, uint32_t &b0, uint32_t &b1) {
-        auto spread = [](uint32_t t) {
-            const uint32_t b = (t & 0x7u) | ((t << 5) & 0x700u) | ((t << 10) & 0x70000u) | ((t << 15) & 0x7000000u);
-            return ((((b ^ 0x04040404u) | 0x80808080u) - 0x04040404u) ^ 0x80808080u);   // per byte: 3 -> 8 bits, signed
-        };
-        b0 = spread(v);
-        b1 = spread(v >> 12);
-    };
     auto write_x = [&](int g, const uint4 (&r)[NPS * NQ]) {
         unsigned char *buf = xsb[g % NBUF];
 #pragma unroll
@@ -329,23 +298,21 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 const uint32_t w[6] = {r[i * 2].x, r[i * 2].y, r[i * 2].z, r[i * 2].w, r[i * 2 + 1].x, r[i * 2 + 1].y};
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const int dwi = (24 * j) >> 5, sh = (24 * j) & 31;
-                    const uint32_t v = sh == 0 ? w[dwi] : sh == 8 ? (w[dwi] >> 8) : __builtin_amdgcn_alignbit(w[dwi + 1], w[dwi], sh);
-                    const uint32_t b = unpack_i6(v);
+                    const uint32_t v = goq_bits24(w, j);
+                    const uint32_t b = goq_unpack_i6(v);
                     if constexpr (I8OUT) o[j] = b;
-                    else widen_i8(b, o[2 * j], o[2 * j + 1]);
+                    else goq_widen_i8(b, o[2 * j], o[2 * j + 1]);
                 }
             } else if constexpr (X3) {
                 // 3 dwords = 4 groups of 24 bits = 32 activations
                 const uint32_t w[3] = {r[i].x, r[i].y, r[i].z};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int dwi = (24 * j) >> 5, sh = (24 * j) & 31;
-                    const uint32_t v = sh == 0 ? w[dwi] : sh == 8 ? (w[dwi] >> 8) : __builtin_amdgcn_alignbit(w[dwi + 1], w[dwi], sh);
+                    const uint32_t v = goq_bits24(w, j);
                     uint32_t b0, b1;
-                    unpack_i3(v, b0, b1);
+                    goq_unpack_i3(v, b0, b1);
                     if constexpr (I8OUT) { o[2 * j] = b0; o[2 * j + 1] = b1; }
-                    else { widen_i8(b0, o[4 * j], o[4 * j + 1]); widen_i8(b1, o[4 * j + 2], o[4 * j + 3]); }
+                    else { goq_widen_i8(b0, o[4 * j], o[4 * j + 1]); goq_widen_i8(b1, o[4 * j + 2], o[4 * j + 3]); }
                 }
             }
             const uint32_t d[4] = {r[i * NQ].x, r[i * NQ].y, r[i * NQ].z, r[i * NQ].w};
@@ -353,17 +320,17 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 (void)d;
             } else if constexpr (ACT == 2) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) widen_i8(d[k], o[2 * k], o[2 * k + 1]);
+                for (int k = 0; k < 4; ++k) goq_widen_i8(d[k], o[2 * k], o[2 * k + 1]);
             } else if constexpr (ACT == 3) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) unpack_i4(d[k], o[2 * k], o[2 * k + 1]);
+                for (int k = 0; k < 4; ++k) goq_unpack_i4(d[k], o[2 * k], o[2 * k + 1]);
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     uint32_t b0, b1;
-                    unpack_i4(d[k], b0, b1);
-                    widen_i8(b0, o[4 * k], o[4 * k + 1]);
-                    widen_i8(b1, o[4 * k + 2], o[4 * k + 3]);
+                    goq_unpack_i4(d[k], b0, b1);
+                    goq_widen_i8(b0, o[4 * k], o[4 * k + 1]);
+                    goq_widen_i8(b1, o[4 * k + 2], o[4 * k + 3]);
                 }
             }
             unsigned char *dst = buf + row * ROWB;
@@ -622,8 +589,20 @@ int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, 
 
 int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
 {
+    // Every problem goes to the kernel its own token count asks for, whatever it is batched with: a
+    // batch returns the bits of single calls.
     GemmBatch b;
-    for (int i = 0; i < n; ++i) b.p[i] = make_args(descs[i]);
+    goq_gemm_desc few[GOQ_MAX_BATCH];
+    int nfew = 0, nmany = 0;
+    for (int i = 0; i < n; ++i) {
+        if (descs[i].tokens <= GOQ_SMALL_TOKENS) few[nfew++] = descs[i];
+        else b.p[nmany++] = make_args(descs[i]);
+    }
+    if (nfew) {
+        const int rc = goq_launch_gemm_small(st, bw, act, nfew, few);
+        if (rc || !nmany) return rc;
+    }
+    n = nmany;
     if (bw == 3 && act == GOQ_A16) return launch<3, 0>(st, b, n);
     if (bw == 3 && act == GOQ_A8) return launch<3, 1>(st, b, n);
     if (bw == 4 && act == GOQ_A16) return launch<4, 0>(st, b, n);

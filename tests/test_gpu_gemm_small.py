@@ -1,0 +1,91 @@
+"""goq_gemm with a few tokens (the kernel of up to 32 tokens): edges of its 16-token and 16-row tiles, wavefronts without
+a slab of their own, one and two row tiles per workgroup; against the oracle, and batch against single calls."""
+import numpy as np
+import pytest
+
+import goq_inputs
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+PACKERS = {"A8": None, "A4": (4, "pack_int4"), "A6": (6, "pack_int6"), "A3": (3, "pack_int3")}
+
+
+def _inputs(goq, act, tokens, inn):
+    """(device x, sx, host fp64 x or int8 x, host sx)"""
+    if act == "A16":
+        x = goq_inputs.activations_a16(tokens, inn, config_id=61, tensor_id=100 + tokens, outlier_frac=0.01)
+        return gu.to_dev(x), None, x, None
+    if act == "A8":
+        x, sx = goq_inputs.activations_a8(tokens, inn, config_id=61, tensor_id=200 + tokens)
+        return gu.to_dev(x), gu.to_dev(sx), x, sx
+    bits, packer = PACKERS[act]
+    x, sx = goq_inputs.activations_int(tokens, inn, bits, config_id=61, tensor_id=200 + tokens)
+    return gu.to_dev(getattr(goq_inputs, packer)(x)), gu.to_dev(sx), x, sx
+
+
+def _run(goq, bw, act, q, tokens, xd, sxd, ytype, partials=False):
+    torch = gu.torch_cuda()
+    out, inn = q["codes"].shape
+    packed = gu.pack_layer(goq, q)
+    Y = torch.full((tokens, out), float("nan"), dtype=torch.float32 if ytype == goq.F32 else torch.float16, device="cuda")
+    P = torch.full((tokens, out, inn // 128, 2), -7777, dtype=torch.int32, device="cuda") if partials else None
+    goq.gemm(bw, getattr(goq, act), tokens, out, inn, packed, xd, sxd, Y, ytype, partials=P)
+    torch.cuda.synchronize()
+    return Y, P
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,out,inn", [(1, 1, 128), (2, 17, 896), (15, 16, 1024), (16, 63, 1152), (17, 65, 2176),
+                                            (31, 48, 256), (32, 8209, 384), (33, 100, 640)])
+def test_few_tokens_a16(oracle, bw, tokens, out, inn):
+    """fp32 results within 2e-6 of the sum of absolute products (2^-24 per rounding, at most some
+    ten of them on a path from a product to y), fp16 results one rounding (2^-11) more."""
+    import paper_2605_26092_amd as goq
+    print("few tokens a16 bw=%d %dx%dx%d" % (bw, tokens, out, inn), flush=True)
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=60, tensor_id=tokens)
+    xd, _, x, _ = _inputs(goq, "A16", tokens, inn)
+    ref = oracle.gemm_a16(q, x, threads=8)
+    scale = np.abs(x.astype(np.float64)) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
+    y = _run(goq, bw, "A16", q, tokens, xd, None, goq.F32)[0].cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(y - ref) / scale) <= 2e-6
+    h = _run(goq, bw, "A16", q, tokens, xd, None, goq.F16)[0].float().cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(h - ref) <= 2e-6 * scale + 2.0 ** -11 * np.abs(ref) + 2.0 ** -25)
+
+
+@pytest.mark.parametrize("act", sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,out,inn", [(3, 33, 128), (16, 20, 1152), (32, 8200, 256), (19, 64, 2304)])
+def test_few_tokens_integers(oracle, act, bw, tokens, out, inn):
+    """int32 slab partials bit for bit; y from them; y without the partials the same bits."""
+    import paper_2605_26092_amd as goq
+    print("few tokens %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=62, tensor_id=tokens)
+    xd, sxd, x, sx = _inputs(goq, act, tokens, inn)
+    ref, pref = oracle.gemm_a8(q, x, sx, threads=8, want_partials=True)
+    Y, P = _run(goq, bw, act, q, tokens, xd, sxd, goq.F32, partials=True)
+    assert np.array_equal(P.cpu().numpy(), pref)
+    scale = (np.abs(x.astype(np.float64)) * sx[:, None]) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
+    assert np.max(np.abs(Y.cpu().numpy().astype(np.float64) - ref) / scale) <= 2e-6
+    assert gu.torch_cuda().equal(_run(goq, bw, act, q, tokens, xd, sxd, goq.F32)[0], Y)
+
+
+@pytest.mark.parametrize("act", ["A16", "A8"])
+def test_batch_of_few_and_many_tokens(act):
+    """A batch that mixes problems of either kernel, of one and of two token tiles, and with enough
+    rows for two row tiles per workgroup: the bits of single calls."""
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    probs, single = [], []
+    for i, (tokens, out, inn) in enumerate([(5, 8300, 256), (40, 200, 384), (32, 64, 2048), (100, 130, 128), (16, 70, 1280)]):
+        q = goq_inputs.canonical_random(3, out, inn, config_id=63, tensor_id=i)
+        packed = gu.pack_layer(goq, q)
+        xd, sxd, _, _ = _inputs(goq, act, tokens, inn)
+        ya, yb = (torch.full((tokens, out), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+        goq.gemm(3, getattr(goq, act), tokens, out, inn, packed, xd, sxd, ya, goq.F32)
+        probs.append((tokens, out, inn, packed, xd, sxd, yb, goq.F32))
+        single.append((ya, yb))
+    goq.gemm_batch(3, getattr(goq, act), probs)
+    torch.cuda.synchronize()
+    for ya, yb in single:
+        assert torch.equal(ya, yb)
