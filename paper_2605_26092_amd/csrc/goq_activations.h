@@ -4,6 +4,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "goq_decode.h"
+#include "../../include/goq.h"
+
+// bytes of a macro-block of activations
+template <int ACT>
+constexpr int goq_block_bytes() { return ACT == GOQ_A16 ? 256 : ACT == GOQ_A8 ? 128 : ACT == GOQ_A4 ? 64 : ACT == GOQ_A6 ? 96 : 48; }
 
 // four int8 -> two registers of two fp16, without a conversion instruction: 0x6400 | u is the
 // fp16 number 1024 + u

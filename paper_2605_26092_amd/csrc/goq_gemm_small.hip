@@ -1,5 +1,5 @@
-// goq_gemm / goq_gemm_batch for a few tokens (batched decode, verification of draft tokens):
-// Y[tokens][out] = X[tokens][in] * W^T (Eq. 4) with tokens <= GOQ_SMALL_TOKENS.
+// goq_gemm / goq_gemm_batch for a few tokens (batched decode, verification of draft tokens, short
+// prompts on narrow layers): Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
 //
 // What bounds it: the packed weights are read once for a handful of tokens, so the floor is the
 // weight stream; the work per weight that has to hide behind it is the decode on the vector ALU
@@ -7,18 +7,21 @@
 // many tokens (64 tokens x 128 outputs, one workgroup walks the whole depth) starts out / 128
 // workgroups: 32 for a 4096-wide layer, an eighth of the chip, one slab at a time.
 //
-// Split: a workgroup owns 16 RT output rows and ALL tokens; its eight wavefronts take the
-// macro-blocks round-robin (wavefront w: slabs w, w + 8, ..), so a 4096 x 4096 layer is 256
+// Split: a workgroup owns 16 RT output rows and a block of up to 32 tokens; its eight wavefronts take
+// the macro-blocks round-robin (wavefront w: slabs w, w + 8, ..), so a 4096 x 4096 layer is 256
 // workgroups with four slabs per wavefront, and the eight partial tiles meet in LDS in a fixed
-// order: no scratch memory, no atomics, one launch.
+// order: no scratch memory, no atomics, one launch.  More rows per workgroup (RT) share one fetch of
+// the activations, which is what limits large launches (64 bytes per CU and cycle).
 //   B operand (weights): v_mfma_f32_16x16x32_f16, lane (c = l % 16, q = l / 16) holds the quad
 //       (chunk q, row c) of the packed layout, micro-block 4 q + t in k-step t.
 //   A operand (activations): lane (token = l % 16, q) holds the same k, 32 q + 8 t .. + 7: the 32
 //       consecutive activations of its token that its quad multiplies.  They are read straight
 //       from global memory (every workgroup reads all of X, which L2 holds), so nothing is
 //       staged and no barrier stands before the final sum.
-// Measured against the tile kernel (one launch, us, weights of three copies in turn): 4096 x 4096, 5 tokens, W4/A16:
-// 38.2 -> 7.1; the seven matrices of a LLaMA-2-7B block, 16 tokens, W3/A16: 105.0 -> 37.5.
+// Measured against the tile kernel (one launch, us, weights of three copies in turn): 4096 x 4096, 5 tokens,
+// W4/A16: 38.2 -> 7.1; the seven matrices of a LLaMA-2-7B block, 16 tokens, W3/A16: 105.6 -> 33.2.
+// (Tried: activations through LDS in whole rows, 36 us for the block; micro-block 4 t + q per lane, so that
+// lanes of a load lie side by side but weights come in dwords: 52 us; four wavefronts: no gain.)
 // Integer activations are widened to fp16 in registers; int8 values and powers of two down to 2^-7
 // are exact in fp16 and a slab sum needs at most 22 bits, so the fp32 slab sums P1, P2 are exact.
 // The coefficient pair is applied once per slab in fp32, as everywhere in this library.
@@ -51,7 +54,7 @@ struct SmallArgs {
     const float *sx;
     void *Y;
     int32_t *partials;
-    int tokens, out, gn, ytype;
+    int tokens, out, gn, ytype, mblocks;
 };
 // workgroups first[i] .. first[i + 1] - 1 own problem i (unused problems start at INT_MAX)
 struct SmallBatch {
@@ -113,14 +116,11 @@ __device__ __forceinline__ void as_half(const uint32_t (&x)[XW], f16x8 (&A)[4])
     }
 }
 
-// bytes of an activation row of `gn` macro-blocks, and of 32 activations
-template <int ACT> constexpr int row_bytes_per_block() { return ACT == GOQ_A16 ? 256 : ACT == GOQ_A8 ? 128 : ACT == GOQ_A4 ? 64 : ACT == GOQ_A6 ? 96 : 48; }
-
-template <int BW, int ACT, int MT, int RT>
-__global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(SmallBatch batch)
+template <int BW, int ACT, int MT, int RT, bool PART>
+__global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel(SmallBatch batch)
 {
     constexpr int CH = (BW == 3) ? 4 : 5;
-    constexpr int XROW = row_bytes_per_block<ACT>();
+    constexpr int XROW = goq_block_bytes<ACT>();
     using SlabT = Slab<BW, ACT, MT, RT>;
     __shared__ __attribute__((aligned(256))) unsigned char vtab[64 * VS];
     __shared__ __attribute__((aligned(16))) float red[WAVES][MT * RT][256];
@@ -135,7 +135,10 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
     for (int i = 1; i < GOQ_MAX_BATCH; ++i) pi += ((int)blockIdx.x >= batch.first[i]) ? 1 : 0;
     pi = __builtin_amdgcn_readfirstlane(pi);
     const SmallArgs &a = batch.p[pi];
-    const int rt0 = ((int)blockIdx.x - batch.first[pi]) * RT;       // first 16-row tile; RT divides 4: one row block
+    // workgroups of a problem: token blocks of 16 MT tokens inside, row tiles outside
+    const int job = (int)blockIdx.x - batch.first[pi];
+    const int m0 = (job % a.mblocks) * (16 * MT);
+    const int rt0 = (job / a.mblocks) * RT;                         // first 16-row tile; RT divides 4: one row block
     const int gn = a.gn;
 
     // rows: lane (c, q) reads chunk q of row 16 (rt0 + r) % 64 + c (rows past `out` lie in the padding)
@@ -144,8 +147,8 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
     // tokens: rows past the end repeat the last one, their results are not stored
     uint32_t xoff[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xoff[m] = (uint32_t)(min(16 * m + c, a.tokens - 1) * gn) * XROW + q * (XROW / 4);
-    gbytes xbase = (gbytes)a.X;
+    for (int m = 0; m < MT; ++m) xoff[m] = (uint32_t)(min(16 * m + c, a.tokens - 1 - m0) * gn) * XROW + q * (XROW / 4);
+    gbytes xbase = (gbytes)a.X + (int64_t)m0 * gn * XROW;
 
     auto load = [&](int g, SlabT &s) {
         gptr base = wbase + (int64_t)g * (CH * GOQ_ROWS * 4);
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[r][m][v] = fmaf(c2, P2[m][v], fmaf(c1, P1[m][v], acc[r][m][v]));
-            if constexpr (ACT != GOQ_A16) {
+            if constexpr (PART) {
                 // exact int32 slab partials [tokens][out][in/128][2] (verification output)
                 if (a.partials) {
                     constexpr float UNIT = (float)(1 << ((1 << (BW - 1)) - 1));
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
                     for (int m = 0; m < MT; ++m)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const int token = 16 * m + 4 * q + v;
+                            const int token = m0 + 16 * m + 4 * q + v;
                             if (token < a.tokens && row < a.out)
                                 *reinterpret_cast<int2 *>(a.partials + (((int64_t)token * a.out + row) * gn + g) * 2) =
                                     make_int2((int)(P1[m][v] * UNIT), (int)(P2[m][v] * UNIT));
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
     __syncthreads();
     for (int i = tid; i < MT * RT * 256; i += NT) {
         const int tile = i >> 8, e = i & 255;
-        const int token = 16 * (tile / RT) + (e >> 4);
+        const int token = m0 + 16 * (tile / RT) + (e >> 4);
         const int row = 16 * (rt0 + tile % RT) + (e & 15);
         float y = 0.f;
 #pragma unroll
@@ -299,40 +302,60 @@ __global__ __launch_bounds__(NT, MT * RT > 2 ? 2 : 4) void gemm_small_kernel(Sma
 }
 
 template <int BW, int ACT, int MT, int RT>
-int launch(hipStream_t st, const SmallBatch &b, int grid)
+int launch(hipStream_t st, const SmallBatch &b, int grid, bool part)
 {
-    hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT>), dim3((unsigned)grid), dim3(NT), 0, st, b);
+    if (ACT != GOQ_A16 && part)
+        hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, ACT != GOQ_A16>), dim3((unsigned)grid), dim3(NT), 0, st, b);
+    else
+        hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, false>), dim3((unsigned)grid), dim3(NT), 0, st, b);
     return goq_check_launch("goq_gemm");
 }
 
 template <int BW, int ACT>
-int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt)
+int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part)
 {
-    if (mt == 1) return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid) : launch<BW, ACT, 1, 2>(st, b, grid);
-    return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid) : launch<BW, ACT, 2, 2>(st, b, grid);
+    if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part) : launch<BW, ACT, 2, 2>(st, b, grid, part);
+    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part)
+         : rt == 2 ? launch<BW, ACT, 1, 2>(st, b, grid, part) : launch<BW, ACT, 1, 4>(st, b, grid, part);
 }
 
 template <int BW>
-int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt)
+int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt, bool part)
 {
-    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt);
-    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt);
-    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt);
-    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt);
-    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt);
+    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt, part);
+    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt, part);
+    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt, part);
+    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt, part);
+    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt, part);
 }
 
 }  // namespace
 
+// Up to 32 tokens always; beyond that as long as the tile kernel (64 tokens x 128 outputs per
+// workgroup, whole depth) would fill at most half of the 256 CUs.  Both sides measured (us, this kernel /
+// tile kernel, W3/A16): 4096 x 4096: 64 tokens 19 / 42, 128: 23 / 42, 256 (128 tiles): 44 / 43, 384: 63 / 44;
+// 11008 x 4096: 64 tokens (86 tiles) 31 / 42, 96 (172): 50 / 44; 8192 x 8192: 128 (128): 75 / 78, 192: 112 / 78;
+// 768 x 768: 512 tokens (48) 8 / 13; 3072 x 768: 192 (72): 12 / 13, 256 (96): 13 / 13.
+bool goq_gemm_small_takes(int64_t tokens, int64_t out)
+{
+    return tokens <= 32 || (tokens + 63) / 64 * ((out + 127) / 128) <= 128;
+}
+
 int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
 {
     int64_t tiles16 = 0, most = 0;
+    bool part = false;
     for (int i = 0; i < n; ++i) {
-        tiles16 += (descs[i].out + 15) / 16;
+        tiles16 += (descs[i].out + 15) / 16 * ((descs[i].tokens + 31) / 32);
         most = descs[i].tokens > most ? descs[i].tokens : most;
+        part = part || descs[i].partials;
     }
-    const int rt = tiles16 > 512 ? 2 : 1;
+    // Row tiles per workgroup: one until the chip is full (two workgroups per CU), then two; four
+    // for launches of many row tiles, with 16 tokens and bw = 3 (the 7B block, 16 tokens: 2656 row
+    // tiles, RT = 1, 2, 4: 54.8, 37.9, 34.7 us; bw = 4 and two token tiles have no registers for four).
+    // (Neither choice changes a result: a row's sums are the same in every tile.)
     const int mt = most > 16 ? 2 : 1;
+    const int rt = tiles16 <= 512 ? 1 : mt == 2 || bw == 4 || tiles16 <= 2048 ? 2 : 4;
     // the problems with the deepest rows first: the launch should end with short ones
     int order[GOQ_MAX_BATCH];
     for (int i = 0; i < n; ++i) {
@@ -346,8 +369,9 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
         if (i >= n) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; continue; }
         const goq_gemm_desc &d = descs[order[i]];
         b.first[i] = (int)grid;
-        grid += (d.out + 16 * rt - 1) / (16 * rt);               // out <= 2^24: the sum stays below 2^24
         SmallArgs &a = b.p[i];
+        a.mblocks = (int)((d.tokens + 16 * mt - 1) / (16 * mt));
+        grid += (d.out + 16 * rt - 1) / (16 * rt) * a.mblocks;
         a.packed = (const uint32_t *)d.packed;
         a.X = d.X;
         a.sx = d.sx;
@@ -358,5 +382,5 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
         a.gn = (int)(d.in / GOQ_N);
         a.ytype = d.ytype;
     }
-    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt) : launch_act<4>(st, act, b, (int)grid, mt, rt);
+    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt, part) : launch_act<4>(st, act, b, (int)grid, mt, rt, part);
 }

@@ -1,4 +1,4 @@
-"""goq_gemm with a few tokens (the kernel of up to 32 tokens): edges of its 16-token and 16-row tiles, wavefronts without
+"""goq_gemm with a few tokens or outputs (the kernel that splits the depth over wavefronts): edges of its 16-token and 16-row tiles, wavefronts without
 a slab of their own, one and two row tiles per workgroup; against the oracle, and batch against single calls."""
 import numpy as np
 import pytest
@@ -37,7 +37,8 @@ def _run(goq, bw, act, q, tokens, xd, sxd, ytype, partials=False):
 
 @pytest.mark.parametrize("bw", [3, 4])
 @pytest.mark.parametrize("tokens,out,inn", [(1, 1, 128), (2, 17, 896), (15, 16, 1024), (16, 63, 1152), (17, 65, 2176),
-                                            (31, 48, 256), (32, 8209, 384), (33, 100, 640)])
+                                            (31, 48, 256), (32, 8209, 384), (33, 100, 640),
+                                            (3, 32800, 128), (65, 257, 1024), (129, 100, 384), (257, 3328, 256), (257, 3329, 256)])
 def test_few_tokens_a16(oracle, bw, tokens, out, inn):
     """fp32 results within 2e-6 of the sum of absolute products (2^-24 per rounding, at most some
     ten of them on a path from a product to y), fp16 results one rounding (2^-11) more."""
@@ -55,7 +56,7 @@ def test_few_tokens_a16(oracle, bw, tokens, out, inn):
 
 @pytest.mark.parametrize("act", sorted(PACKERS))
 @pytest.mark.parametrize("bw", [3, 4])
-@pytest.mark.parametrize("tokens,out,inn", [(3, 33, 128), (16, 20, 1152), (32, 8200, 256), (19, 64, 2304)])
+@pytest.mark.parametrize("tokens,out,inn", [(3, 33, 128), (16, 20, 1152), (32, 8200, 256), (19, 64, 2304), (70, 130, 640)])
 def test_few_tokens_integers(oracle, act, bw, tokens, out, inn):
     """int32 slab partials bit for bit; y from them; y without the partials the same bits."""
     import paper_2605_26092_amd as goq
@@ -77,7 +78,7 @@ def test_batch_of_few_and_many_tokens(act):
     import paper_2605_26092_amd as goq
     torch = gu.torch_cuda()
     probs, single = [], []
-    for i, (tokens, out, inn) in enumerate([(5, 8300, 256), (40, 200, 384), (32, 64, 2048), (100, 130, 128), (16, 70, 1280)]):
+    for i, (tokens, out, inn) in enumerate([(5, 8300, 256), (40, 200, 384), (32, 64, 2048), (1100, 1000, 128), (16, 70, 1280)]):
         q = goq_inputs.canonical_random(3, out, inn, config_id=63, tensor_id=i)
         packed = gu.pack_layer(goq, q)
         xd, sxd, _, _ = _inputs(goq, act, tokens, inn)
