@@ -95,3 +95,23 @@ def test_pack_matches_the_documented_layout(bw, shape):
     q = goq_inputs.canonical_random(bw, out, inn, config_id=23, tensor_id=out)
     packed = gu.pack_layer(goq, q).cpu().numpy().view(np.uint32)
     assert np.array_equal(packed, _pack_by_the_book(q))
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("shift", [0, 1, 4])
+@pytest.mark.parametrize("shape", [(64, 1024), (67, 1152), (3, 2176)])
+def test_pack_groups_and_alignment(bw, shape, shift):
+    """A workgroup takes eight macro-blocks: full, one over, and partial groups; canonical arrays at
+    any byte address (the wide loads need codes at 16, pattern and signs at 4 bytes)."""
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    out, inn = shape
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=24, tensor_id=out)
+    dev = []
+    for k in ("codes", "pattern", "signs"):
+        t = torch.zeros(q[k].size + 16, dtype=torch.uint8, device="cuda")
+        t[shift:shift + q[k].size] = gu.to_dev(q[k]).reshape(-1)
+        dev.append(t[shift:])
+    packed = torch.full((goq.packed_bytes(bw, out, inn),), 255, dtype=torch.uint8, device="cuda")
+    goq.pack(bw, out, inn, *dev, gu.to_dev(q["c1"]), gu.to_dev(q["c2"]), packed)
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), _pack_by_the_book(q))
