@@ -5,33 +5,43 @@
 // macro-blocks per wavefront.  Everything that belongs to a micro-block -- nearest states, the 16
 // cross terms of the four exchange patterns, scores, argmax, pair signs, the exchange itself -- is
 // lane-local and lives in registers; what belongs to the macro-block -- the norm s_norm and the
-// four sums of Eq. 1 and Eq. 2 -- is reduced across the 16 lanes of a row with data-parallel-
-// primitive (DPP) moves, which stay inside a row by construction.  No LDS, no barriers.  The
-// arithmetic is laid out around what is exact:
+// sums of Eq. 1 and Eq. 2 -- is reduced across the 16 lanes of a row with data-parallel-primitive
+// (DPP) moves, which stay inside a row by construction.  No LDS, no barriers.  It is bound by
+// vector-ALU issue (about 440 instructions per micro-block), so the arithmetic is laid out around what is
+// exact and need not be computed twice:
 //
-//   products    A lattice state is a signed power of two, so every product with a state (w b1,
-//               w b2, c b1, x r) is exact in fp64.
+//   products    A lattice state is a signed power of two, so every product with a state is exact
+//               in fp64.
 //   sums        <w, b1> and <w, b2> (Eq. 1, Eq. 2) are sums of multiples of 2^-31 below 2^23: every
 //               partial sum is exactly representable in fp64 whatever the order (always for
 //               bw = 3; for bw = 4 unless |<w, b>| reaches 2^22, i.e. more than 64 weights of the
-//               block at the fp16 maximum), so the reduction tree is free.  ||b1||^2 and ||b2||^2
-//               are small integers (units of 4^-(E-1)).
+//               block at the fp16 maximum), so the reduction tree is free.  ||b1||^2 = ||b2||^2 is a
+//               multiple of 2^-14 of at most 128: exact in fp32.
 //   nearest     Q(v), v = w / s_norm (Sec. 3.2), is decided without the division: |v| lies above
 //               the midpoint 0.75 * 2^-k of the states 2^-k and 2^-(k+1) exactly when
 //               |w| > 0.75 * 2^-k * s_norm, and above the midpoint to zero, 2^-(emin+1), when
 //               |w| > 2^-(emin+1) * s_norm.  The thresholds fall with k, so the exponent of the
 //               nearest state is the NUMBER of thresholds |w| does not exceed, and that number is
-//               a difference of fp64 exponent fields (see the loop); an exact tie goes to the
+//               a difference of fp32 exponent fields (see the loop); an exact tie goes to the
 //               smaller magnitude.
-//   roundings   Only what the method defines as real arithmetic rounds: the projection
-//               coefficient <w,b1> / ||b1||^2 (one correctly rounded division of two exact
-//               numbers), the residual r = w - c b1 (Eq. 1; one rounding), the cross terms
-//               t = x_i r_j - x_j r_i (Sec. 3.3; one rounding) and the four-term score
-//               A_s = |t_0| + |t_1| + |t_2| + |t_3|, added in pair order.  eta = sgn(t)
-//               (+1 at zero), s* = argmax A_s (ties: smallest s).
+//   cross terms The method's cross term of a pair is t = x_i r_j - x_j r_i with the residual
+//               r = w - c b1, c = <w,b1> / ||b1||^2 (Eq. 1, Sec. 3.3), x = b1.  The c terms cancel:
+//               in real arithmetic t = u = x_i w_j - x_j w_i, and u is EXACT in fp64 (a multiple of
+//               2^-31 below 2^18).  A sequential fp64 evaluation rounds r and t, which moves t by less
+//               than 2^-50 s_norm; it has the sign of u, because a nonzero u is at least 2^-31 (and where
+//               u = 0 the states and weights of the pair are proportional by a power of two, or
+//               zero, and so are the rounded residuals: t = 0).  So eta = sgn(u) (+1 at zero), the
+//               scores A_s = sum |t| equal the exact U_s = sum |u| within 2^-46 s_norm, and s* =
+//               argmax U_s unless two scores lie closer than that.  Only then (equal scores, a few per
+//               million of real micro-blocks) the wavefront evaluates residuals and t as the method
+//               writes them, to let their roundings decide as the sequential evaluation does
+//               (ties: smallest s).  The pair's share of <w, b2> under the Theorem 1 exchange
+//               (b2_i = -eta x_j for the lower index, +eta x_i for the upper one) is eta u = |u|:
+//               U_s* is <w, b2> of the micro-block.
 //
 // The results are a pure function of the weights and equal those of a sequential fp64 evaluation
 // of the same formulas bit for bit under the condition on the sums stated above.
+// Measured, 4096 x 11008, bw = 3: 77 us (residuals and cross terms of every micro-block in fp64: 98 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "goq_layout.h"
@@ -72,12 +82,14 @@ __device__ __forceinline__ double row_sum(double v)
     v += dpp_double<ROW_MIRROR>(v);
     return v;
 }
-__device__ __forceinline__ uint32_t row_sum(uint32_t v)
+template <int CTRL>
+__device__ __forceinline__ float dpp_float(float v) { return __uint_as_float(dpp32<CTRL>(__float_as_uint(v))); }
+__device__ __forceinline__ float row_sum(float v)
 {
-    v += dpp32<QUAD_SWAP1>(v);
-    v += dpp32<QUAD_SWAP2>(v);
-    v += dpp32<ROW_HALF_MIRROR>(v);
-    v += dpp32<ROW_MIRROR>(v);
+    v += dpp_float<QUAD_SWAP1>(v);
+    v += dpp_float<QUAD_SWAP2>(v);
+    v += dpp_float<ROW_HALF_MIRROR>(v);
+    v += dpp_float<ROW_MIRROR>(v);
     return v;
 }
 __device__ __forceinline__ uint32_t row_max(uint32_t v)
@@ -89,8 +101,38 @@ __device__ __forceinline__ uint32_t row_max(uint32_t v)
     return v;
 }
 
-// 2^-e as fp64, e >= 0 small
-__device__ __forceinline__ double pow2_neg(int e) { return __longlong_as_double((long long)(1023 - e) << 52); }
+// lower index of the p-th pair of pattern s, pairs in ascending lower index
+__device__ __forceinline__ constexpr int pair_lower(int s, int p)
+{
+    return s == 1 ? 2 * p : s == 4 ? p : ((p & 1) | ((p >> 1) << 2));
+}
+
+// Pattern and signs of a micro-block as Sec. 3.3 writes them: residuals r = w - c x, cross terms and
+// scores in fp64 in pair order; sets s - 1 and the sign bits.
+__device__ __forceinline__ void choose_by_residual(const double (&wv)[8], const double (&x)[8], double c,
+                                                   uint32_t &best, uint32_t &best_signs)
+{
+    double r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = wv[i] - c * x[i];
+    double bestA = -1.0;
+#pragma unroll
+    for (int s = 1; s <= 4; ++s) {
+        double A = 0.0;
+        uint32_t sg = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int i = pair_lower(s, p), j = i ^ s;
+            const double t = x[i] * r[j] - x[j] * r[i];
+            A = (p == 0) ? fabs(t) : A + fabs(t);
+            sg |= (t < 0.0 ? 1u : 0u) << p;
+        }
+        const bool better = A > bestA;                               // ties: the smaller s stays
+        bestA = better ? A : bestA;
+        best = better ? (uint32_t)(s - 1) : best;
+        best_signs = better ? sg : best_signs;
+    }
+}
 
 template <int BW>
 __global__ __launch_bounds__(64 * QW) void quantize_kernel(const uint4 *__restrict__ w, int64_t nblocks,
@@ -110,100 +152,90 @@ __global__ __launch_bounds__(64 * QW) void quantize_kernel(const uint4 *__restri
         const int64_t mb = valid ? mb_raw : nblocks - 1;
         const uint4 q = w[mb * 16 + m];
         const uint32_t pk[4] = {q.x, q.y, q.z, q.w};
-        uint32_t h[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { h[2 * i] = pk[i] & 0xffffu; h[2 * i + 1] = pk[i] >> 16; }
 
         // macro-block normalisation s_norm = ||w||_inf: magnitude bits order like magnitudes
         uint32_t amax = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) amax = max(amax, h[i] & 0x7fffu);
+        for (int i = 0; i < 4; ++i) amax = max(amax, max(pk[i] & 0x7fffu, (pk[i] >> 16) & 0x7fffu));
         amax = row_max(amax);
         const bool zero_block = amax == 0;           // nothing to represent: zero codes, c1 = c2 = 0
-        const double sn = half_bits_to_double(amax);
+        const float sn = (float)__builtin_bit_cast(_Float16, (unsigned short)amax);
 
         // nearest states.  Thresholds common to both signs: 0.75 2^-k s_norm, k = 0 .. E-3; then a
         // negative weight has the state 2^-(E-1) (midpoints 0.75 2^-(E-2) s_norm and, to zero,
         // 2^-E s_norm), a positive one ends at 2^-(E-2) (midpoint to zero 2^-(E-1) s_norm).
-        const int T075 = __double2hiint(0.75 * sn), Tsn = __double2hiint(sn);
+        const int T075 = (int)__float_as_uint(0.75f * sn);
+        const int Tzero = (int)__float_as_uint(sn) - ((E - 1) << 23);
         double wv[8], x[8];
-        uint32_t code_lo = 0, code_hi = 0, n1 = 0;
-        double s1 = 0.0;
+        uint32_t code_lo = 0, code_hi = 0;
+        double s1 = 0.0, n1 = 0.0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            wv[i] = half_bits_to_double(h[i]);
-            const double wa = fabs(wv[i]);
-            const uint32_t neg = h[i] >> 15;                         // 1 for a negative weight
+            const float wf = (float)__builtin_bit_cast(_Float16, (unsigned short)(pk[i >> 1] >> (16 * (i & 1))));
+            wv[i] = (double)wf;
+            const uint32_t bits = __float_as_uint(wf);
+            const int neg = (int)(bits >> 31);                       // 1 for a negative weight
             // Number of thresholds |w| does not exceed.  |w| (11 significant bits) and 0.75 s_norm
-            // (13) are positive fp64 numbers whose low words are zero, so they order like their high
-            // words, and a factor 2^k is k units of the exponent field (bit 20 of the high word):
-            // |w| 2^k <= 0.75 s_norm  <=>  A + (k << 20) <= T.  That holds for k = 0 .. (T - A) >> 20
-            // when T >= A and for no k otherwise; a negative weight has E - 1 such thresholds, a
-            // positive one E - 2, and the midpoint to zero is one more comparison.
-            const int A = __double2hiint(wa);
-            const int nth = min(max(((T075 - A) >> 20) + 1, 0), E - 2 + (int)neg);
-            const int e = nth + ((A <= Tsn - ((E - 1 + (int)neg) << 20)) ? 1 : 0);
-            const bool is_zero = zero_block || e == E - 1 + (int)neg;
-            const uint32_t code = is_zero ? (uint32_t)(E - 1) : ((neg << (BW - 1)) | (uint32_t)e);
+            // (13) are exact in fp32 and order like their bits, and a factor 2^k is k units of the
+            // exponent field: |w| 2^k <= 0.75 s_norm  <=>  A + (k << 23) <= T.  That holds for
+            // k = 0 .. (T - A) >> 23 when T >= A and for no k otherwise; a negative weight has E - 1
+            // such thresholds, a positive one E - 2, and below the midpoint to zero it is zero.
+            const int A = (int)(bits & 0x7fffffffu);
+            const int e = min(max(((T075 - A) >> 23) + 1, 0), E - 2 + neg);
+            const bool is_zero = A <= Tzero - (neg << 23) || zero_block;
+            const uint32_t code = is_zero ? (uint32_t)(E - 1) : (((uint32_t)neg << (BW - 1)) | (uint32_t)e);
             if (i < 4) code_lo |= code << (8 * i);
             else code_hi |= code << (8 * (i - 4));
             // b1_i = (-1)^neg 2^-e assembled from sign and exponent field (low word zero)
-            const uint32_t xhi = is_zero ? 0u : (((uint32_t)(1023 - e) << 20) | (neg << 31));
+            const uint32_t xhi = is_zero ? 0u : ((uint32_t)((1023 - e) << 20) | (bits & 0x80000000u));
             x[i] = __hiloint2double((int)xhi, 0);
-            s1 += wa * fabs(x[i]);                                  // a weight and its state share the sign
-            n1 += is_zero ? 0u : (1u << (2 * (E - 1 - e)));         // |b1_i|^2 in units of 4^-(E-1)
+            s1 = fma(wv[i], x[i], s1);                              // a weight and its state share the sign
+            n1 = fma(x[i], x[i], n1);
         }
         if (valid) codes[mb * 16 + m] = make_uint2(code_lo, code_hi);
         const double S1 = row_sum(s1);
-        const uint32_t N1 = row_sum(n1);             // > 0 unless the block is zero: the largest weight maps to +-1
-        // projection coefficient <w,b1> / ||b1||^2 and the residual r = w - c b1 (Eq. 1)
-        const double proj = zero_block ? 0.0 : S1 / ((double)N1 * pow2_neg(2 * (E - 1)));
-        double r[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] = wv[i] - proj * x[i];
+        const double N1 = (double)row_sum((float)n1);    // > 0 unless the block is zero: the largest weight maps to +-1
 
-        // Sec. 3.3: the four patterns s, pairs (i, i xor s) in ascending lower index; cross term,
-        // score in pair order, sign bits (eta = -1 where t < 0).  The pair's share of <w, b2> under
-        // the Theorem 1 exchange (b2_i = -eta x_j for the lower index, b2_j = +eta x_i for the upper
-        // one) is eta (w_j x_i - w_i x_j): exact, and summed for every pattern alongside its score,
-        // so that choosing the pattern chooses the sum.
-        int best_s = 1;
-        uint32_t best_signs = 0;
-        double bestA = -1.0, best_d = 0.0;
+        // the four patterns: exact cross terms, scores and sign bits
+        double U[4];
+        uint32_t sg[4];
 #pragma unroll
         for (int s = 1; s <= 4; ++s) {
-            double A = 0.0, d = 0.0;
-            uint32_t sg = 0;
+            double sum = 0.0;
+            uint32_t bit = 0;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int i = (s == 1) ? 2 * p : (s == 4) ? p : ((p & 1) | ((p >> 1) << 2));
-                const int j = i ^ s;
-                const double t = x[i] * r[j] - x[j] * r[i];
-                const double u = wv[j] * x[i] - wv[i] * x[j];
-                const bool eta_neg = t < 0.0;
-                A = (p == 0) ? fabs(t) : A + fabs(t);
-                sg |= (eta_neg ? 1u : 0u) << p;
-                d += eta_neg ? -u : u;
+            for (int p = 3; p >= 0; --p) {
+                const int i = pair_lower(s, p), j = i ^ s;
+                const double u = fma(x[i], wv[j], -(x[j] * wv[i]));
+                sum += fabs(u);
+                bit = bit + bit + (u < 0.0 ? 1u : 0u);
             }
-            const bool better = A > bestA;                           // ties: the smaller s stays
-            bestA = better ? A : bestA;
-            best_s = better ? s : best_s;
-            best_signs = better ? sg : best_signs;
-            best_d = better ? d : best_d;
+            U[s - 1] = sum;
+            sg[s - 1] = bit;
         }
-        if (zero_block) { best_s = 1; best_signs = 0; }
+        const double top = fmax(fmax(U[0], U[1]), fmax(U[2], U[3]));
+        const double limit = fma((double)sn, -0x1p-44, top);
+        const bool k0 = U[0] >= limit, k1 = U[1] >= limit, k2 = U[2] >= limit, k3 = U[3] >= limit;
+        uint32_t best = k0 ? 0u : k1 ? 1u : k2 ? 2u : 3u;
+        uint32_t best_signs = k0 ? sg[0] : k1 ? sg[1] : k2 ? sg[2] : sg[3];
+        // scores too close to tell without their roundings (all zero: the first pattern, no signs)
+        const bool close = ((k0 && (k1 || k2 || k3)) || (k1 && (k2 || k3)) || (k2 && k3)) && top > 0.0;
+        if (__any(close)) {
+            uint32_t b = 0, bs = 0;
+            choose_by_residual(wv, x, S1 / N1, b, bs);
+            if (close) { best = b; best_signs = bs; }
+        }
         if (valid) {
-            pattern[mb * 16 + m] = (uint8_t)(best_s - 1);
+            pattern[mb * 16 + m] = (uint8_t)best;
             signs[mb * 16 + m] = (uint8_t)best_signs;
         }
-        // <w, b2> of the macro-block; ||b2||^2 = ||b1||^2 (b2 is a signed permutation of b1)
-        const double S2 = row_sum(best_d);
-        const uint32_t N2 = N1;
-        if (valid && m == 0) {
-            // GEO coefficients, Eq. 2 (the normal equations are diagonal: <b1, b2> = 0)
-            const double c2v = N2 ? S2 / ((double)N2 * pow2_neg(2 * (E - 1))) : 0.0;
-            c1[mb] = (uint16_t)double_to_half_bits(proj);
-            c2[mb] = (uint16_t)double_to_half_bits(c2v);
+        // <w, b2> of the chosen pattern, and the GEO coefficients, Eq. 2 (the normal equations are
+        // diagonal: <b1, b2> = 0): lane 0 of the row divides for c1, lane 1 for c2
+        double d = best == 0 ? U[0] : best == 1 ? U[1] : best == 2 ? U[2] : U[3];
+        const double S2 = row_sum(d);
+        if (valid && m < 2) {
+            const double c = zero_block ? 0.0 : (m == 0 ? S1 : S2) / N1;
+            (m == 0 ? c1 : c2)[mb] = (uint16_t)double_to_half_bits(c);
         }
     }
 }

@@ -82,3 +82,20 @@ def test_quantize_llama_shape_and_pack_gemv(oracle):
     yref = oracle.gemm_a16(ref, x, threads=8)[0]
     e1, _ = gu.a16_errors(y.cpu().numpy(), yref, None)
     assert e1 <= 1e-3, e1
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+def test_quantize_close_scores(oracle, bw):
+    """Micro-blocks whose pattern scores tie, or lie closer than their roundings: weights from a
+    handful of values (many equal scores), equal up to a power of two, negative zeros, and a block
+    that mixes the largest with subnormal weights."""
+    import paper_2605_26092_amd as goq
+    r = np.random.default_rng(11)
+    rows = [r.choice([0.3, -0.3, 0.15, -0.15, 0.0, -0.0], size=1024),
+            r.choice([0.7, 0.1, -0.1], size=1024),
+            r.choice([1.0, -1.0], size=1024) * 2.0 ** r.integers(-9, 1, size=1024) * 0.8,
+            np.where(r.random(1024) < 0.9, 0.0, r.normal(0, 1, 1024)),
+            np.where(r.random(1024) < 0.02, 65504.0, r.normal(0, 1e-6, 1024)),
+            np.round(r.normal(0, 2, 1024)) / 8]
+    w = np.stack(rows).astype(np.float16)
+    _same(_run(goq, bw, w), oracle.quantize_geo(bw, w, threads=1))
