@@ -7,10 +7,17 @@
 // all output channels share:
 //     A^T A = [b1 b2]^T S_g [b1 b2],   A^T Y = [b1 b2]^T S_g w,
 // so the tokens are reduced once per macro-block (kernel 1) instead of once per output channel, and
-// kernel 2 needs, per (o, g), the two products S_g b1 and S_g b2 and five dot products.  Everything
-// is fp64 with fixed summation orders (tokens ascending; columns, then rows ascending), so the
-// result is a pure function of the inputs.  It differs from a token-by-token evaluation of Eq. 3
-// only by fp64 rounding, far below the fp16 quantum of the stored coefficients.
+// kernel 2 needs, per (o, g), the two products S_g b1 and S_g b2 and five dot products.  Both are
+// fp64 contractions and run on v_mfma_f64_16x16x4: it has the rate of the vector ALU (one 16 x 16 x 4
+// product in 64 cycles) but takes one operand register pair per 16 fused multiply-adds of a lane, so that
+// loads, conversions and address arithmetic hide behind it, which bound the same sums on the vector ALU
+// (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now TIMES).  Everything is fp64 with
+// fixed summation orders (tokens ascending; columns, then rows), so the result is a pure function of
+// the inputs.  It differs from a token-by-token evaluation of Eq. 3 only by fp64 rounding, far below
+// the fp16 quantum of the stored coefficients.
+//
+// Operand layout of the instruction: A lane l holds A[l % 16][l / 16], B lane l holds
+// B[l / 16][l % 16], element v of D is D[4 v + l / 16][l % 16].
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "goq_layout.h"
@@ -19,73 +26,76 @@
 
 namespace {
 
-constexpr int RT = 256;                  // threads per workgroup (both kernels)
-constexpr int TT = 16;                   // tokens per LDS tile of the Gram kernel
-constexpr int OPT = 2;                   // output channels per thread of the solve kernel
-constexpr int OB = 32 * OPT;             // output channels per workgroup of the solve kernel
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// ---- kernel 1: S_g = X_q^T X_q, one workgroup per macro-block, thread (ti, tj) owns the 8 x 8
-// block of rows 8 ti .., columns 8 tj ..
+constexpr int RT = 256;                  // threads per workgroup (both kernels): four wavefronts
+constexpr int TT = 64;                   // tokens per LDS tile of the Gram kernel
+constexpr int XP = GOQ_N + 16;           // halfs per LDS row: the four tokens of an operand in different banks
+constexpr int OB = 64;                   // output channels per workgroup of the solve kernel, 16 per wavefront
+constexpr int TILES = 36;                // 16 x 16 tiles of S_g on and below the diagonal
+
+__device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ double half_to_double(_Float16 h) { return (double)(float)h; }
+
+// ---- kernel 1: S_g = X_q^T X_q.  Workgroup (g, y): wavefront w owns tile 4 y + w of the lower triangle
+// over all tokens, so that 32 macro-blocks already fill the chip with one tile per SIMD; the tile's
+// mirror image is stored beside it.
 __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X, int tokens, int64_t in,
                                                   double *__restrict__ S)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t xt[TT][GOQ_N];
+    __shared__ __attribute__((aligned(16))) _Float16 xt[TT][XP];
     const int g = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int ti = tid >> 4, tj = tid & 15;
-    double acc[8][8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = lane & 15, k = lane >> 4;
+    const int tile = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (tid >> 6));
+    int ti = 0;
+    while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
+    const int tj = tile - ti * (ti + 1) / 2;
+    // 64 tokens x 128 halfs = 1024 pieces of 16 bytes, four per thread; rows past the end are zero
+    auto load = [&](int t0, uint4 (&v)[4]) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
-    for (int t0 = 0; t0 < tokens; t0 += TT) {
-        // 16 tokens x 128 halfs = 256 pieces of 16 bytes; rows past the end are zero
-        const int r = tid >> 4, c = tid & 15;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (t0 + r < tokens) v = *reinterpret_cast<const uint4 *>(X + (int64_t)(t0 + r) * in + (int64_t)g * GOQ_N + c * 8);
-        __syncthreads();                                       // the previous tile has been used
-        *reinterpret_cast<uint4 *>(&xt[r][c * 8]) = v;
-        __syncthreads();
-        const int nt = min(TT, tokens - t0);
-        for (int t = 0; t < nt; ++t) {
-            const uint4 ra = *reinterpret_cast<const uint4 *>(&xt[t][8 * ti]);
-            const uint4 rb = *reinterpret_cast<const uint4 *>(&xt[t][8 * tj]);
-            const uint32_t wa[4] = {ra.x, ra.y, ra.z, ra.w}, wb[4] = {rb.x, rb.y, rb.z, rb.w};
-            double a[8], b[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                a[k] = half_bits_to_double((wa[k >> 1] >> (16 * (k & 1))) & 0xffffu);
-                b[k] = half_bits_to_double((wb[k >> 1] >> (16 * (k & 1))) & 0xffffu);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+        for (int i = 0; i < 4; ++i) {
+            const int t = t0 + 16 * i + (tid >> 4);
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (t < tokens) v[i] = *reinterpret_cast<const uint4 *>(X + (int64_t)t * in + (int64_t)g * GOQ_N + (tid & 15) * 8);
         }
+    };
+    uint4 v[4];
+    load(0, v);
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int t0 = 0; t0 < tokens; t0 += TT) {
+        __syncthreads();                                       // the previous tile has been used
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(&xt[16 * i + (tid >> 4)][(tid & 15) * 8]) = v[i];
+        __syncthreads();
+        if (t0 + TT < tokens) load(t0 + TT, v);
+#pragma unroll
+        for (int t = 0; t < TT; t += 4)
+            acc = mfma(half_to_double(xt[t + k][16 * ti + n]), half_to_double(xt[t + k][16 * tj + n]), acc);
     }
     double *Sg = S + (int64_t)g * GOQ_N * GOQ_N;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; j += 2)
-            *reinterpret_cast<double2 *>(Sg + (8 * ti + i) * GOQ_N + 8 * tj + j) = make_double2(acc[i][j], acc[i][j + 1]);
+    for (int e = 0; e < 4; ++e) {
+        const int i = 16 * ti + 4 * e + k, j = 16 * tj + n;
+        Sg[i * GOQ_N + j] = acc[e];
+        if (ti != tj) Sg[j * GOQ_N + i] = acc[e];
+    }
 }
 
-// ---- kernel 2: per (g, block of OB output channels).  Thread (oo = tid % 32, ic = tid / 32) forms
-// rows 16 ic .. 16 ic + 15 of u1 = S_g b1 and u2 = S_g b2 of the output channels oo, oo + 32, ..
-// (S_g is symmetric, so column j of S_g is read as the contiguous row j, and one read serves all of
-// a thread's channels), then its share of the five dot products; the eight shares of an output
-// channel are added in order and the 2 x 2 system is solved.  b1, b2 and w are staged as fp16,
-// which holds them exactly.
+// ---- kernel 2: per (g, block of OB output channels).  A wavefront forms u1 = S_g b1 and u2 = S_g b2 of
+// its 16 output channels (columns of B), all 128 rows: eight 16-row tiles and two bases of
+// accumulators, one read of a row of S_g (symmetric: column j is read as the contiguous row j, from
+// L2, the next four rows in flight) for all of them.  Then its share of the five dot products per lane, the four
+// lanes of a channel are added in order and the 2 x 2 system is solved.  b1, b2 and w are staged as
+// fp16, which holds them exactly.
 template <int BW>
-__global__ __launch_bounds__(RT) void ref_solve_kernel(const uint16_t *__restrict__ w, const uint8_t *__restrict__ codes,
+__global__ __launch_bounds__(RT, 2) void ref_solve_kernel(const uint16_t *__restrict__ w, const uint8_t *__restrict__ codes,
                                                        const uint8_t *__restrict__ pattern, const uint8_t *__restrict__ signs,
                                                        const double *__restrict__ S, int64_t out, int64_t in, double lambda,
                                                        double *__restrict__ craw, uint16_t *__restrict__ c1,
                                                        uint16_t *__restrict__ c2)
 {
     __shared__ _Float16 vb1[OB][GOQ_N + 2], vb2[OB][GOQ_N + 2], vw[OB][GOQ_N + 2];
-    __shared__ double red[8][OB][5];
     const int tid = threadIdx.x;
     const int g = blockIdx.x;
     const int64_t o0 = (int64_t)blockIdx.y * OB;
@@ -127,53 +137,56 @@ __global__ __launch_bounds__(RT) void ref_solve_kernel(const uint16_t *__restric
     }
     __syncthreads();
 
-    const int o32 = tid & 31, ic = tid >> 5;
-    const double *Sg = S + (int64_t)g * GOQ_N * GOQ_N;
-    double u1[OPT][16], u2[OPT][16];
+    const int lane = tid & 63, n = lane & 15, k = lane >> 4;
+    const int oo = (tid >> 6) * 16 + n;                        // this lane's channel
+    const double *Sg = S + (int64_t)g * GOQ_N * GOQ_N + k * GOQ_N + n;
+    f64x4 u1[8], u2[8];
 #pragma unroll
-    for (int c = 0; c < OPT; ++c)
+    for (int i = 0; i < 8; ++i) { u1[i] = f64x4{0.0, 0.0, 0.0, 0.0}; u2[i] = f64x4{0.0, 0.0, 0.0, 0.0}; }
+    // rows 4 t + k of S_g, column 16 i + n
+    auto load = [&](int t, double (&a)[8]) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { u1[c][r] = 0.0; u2[c][r] = 0.0; }
-    for (int j = 0; j < GOQ_N; ++j) {
-        double bj1[OPT], bj2[OPT];
+        for (int i = 0; i < 8; ++i) a[i] = Sg[4 * t * GOQ_N + 16 * i];
+    };
+    auto products = [&](int t, const double (&a)[8]) {
+        const double b1 = half_to_double(vb1[oo][4 * t + k]), b2 = half_to_double(vb2[oo][4 * t + k]);
 #pragma unroll
-        for (int c = 0; c < OPT; ++c) { bj1[c] = (double)(float)vb1[o32 + 32 * c][j]; bj2[c] = (double)(float)vb2[o32 + 32 * c][j]; }
-        const double *row = Sg + j * GOQ_N + 16 * ic;           // S[j][16 ic ..] = S[16 ic ..][j]
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            const double2 sv = *reinterpret_cast<const double2 *>(row + r);
-#pragma unroll
-            for (int c = 0; c < OPT; ++c) {
-                u1[c][r] = fma(sv.x, bj1[c], u1[c][r]);
-                u1[c][r + 1] = fma(sv.y, bj1[c], u1[c][r + 1]);
-                u2[c][r] = fma(sv.x, bj2[c], u2[c][r]);
-                u2[c][r + 1] = fma(sv.y, bj2[c], u2[c][r + 1]);
-            }
+        for (int i = 0; i < 8; ++i) {
+            u1[i] = mfma(a[i], b1, u1[i]);
+            u2[i] = mfma(a[i], b2, u2[i]);
         }
+    };
+    double a0[8], a1[8];
+    load(0, a0);
+    for (int t = 0; t < 30; t += 2) {
+        load(t + 1, a1);
+        products(t, a0);
+        load(t + 2, a0);
+        products(t + 1, a1);
     }
+    load(31, a1);
+    products(30, a0);
+    products(31, a1);
+
+    double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < OPT; ++c) {
-        const int oo = o32 + 32 * c;
-        double g11 = 0.0, g12 = 0.0, g22 = 0.0, r1 = 0.0, r2 = 0.0;
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 16 * ic + r;
-            const double b1i = (double)(float)vb1[oo][i], b2i = (double)(float)vb2[oo][i], wi = (double)(float)vw[oo][i];
-            g11 = fma(b1i, u1[c][r], g11);
-            g12 = fma(b2i, u1[c][r], g12);
-            g22 = fma(b2i, u2[c][r], g22);
-            r1 = fma(wi, u1[c][r], r1);
-            r2 = fma(wi, u2[c][r], r2);
+        for (int e = 0; e < 4; ++e) {
+            const int r = 16 * i + 4 * e + k;
+            const double b1 = half_to_double(vb1[oo][r]), b2 = half_to_double(vb2[oo][r]), wr = half_to_double(vw[oo][r]);
+            q[0] = fma(b1, u1[i][e], q[0]);
+            q[1] = fma(b2, u1[i][e], q[1]);
+            q[2] = fma(b2, u2[i][e], q[2]);
+            q[3] = fma(wr, u1[i][e], q[3]);
+            q[4] = fma(wr, u2[i][e], q[4]);
         }
-        red[ic][oo][0] = g11; red[ic][oo][1] = g12; red[ic][oo][2] = g22; red[ic][oo][3] = r1; red[ic][oo][4] = r2;
-    }
-    __syncthreads();
-    for (int oo = tid; oo < OB; oo += RT) {
-        if (o0 + oo >= out) continue;
-        double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int c = 0; c < 8; ++c)
 #pragma unroll
-            for (int k = 0; k < 5; ++k) q[k] += red[c][oo][k];
+    for (int c = 0; c < 5; ++c) {
+        q[c] += __shfl_xor(q[c], 16);
+        q[c] += __shfl_xor(q[c], 32);
+    }
+    if (k == 0 && o0 + oo < out) {
         const double a11 = q[0] + lambda, a22 = q[2] + lambda, a12 = q[1];
         const double det = a11 * a22 - a12 * a12;
         double s1 = 0.0, s2 = 0.0;
@@ -199,7 +212,7 @@ int goq_launch_ref(hipStream_t st, int bw, int64_t tokens, int64_t out, int64_t 
     if (gn > 0x7fffffff || ob > 65535 || tokens > 0x7fffffff)
         return goq_set_error(GOQ_ESHAPE, "goq_ref_coefficients: layer too large for one launch");
     double *S = reinterpret_cast<double *>(workspace);
-    hipLaunchKernelGGL(gram_kernel, dim3((unsigned)gn), dim3(RT), 0, st, X, (int)tokens, in, S);
+    hipLaunchKernelGGL(gram_kernel, dim3((unsigned)gn, TILES / 4), dim3(RT), 0, st, X, (int)tokens, in, S);
     int rc = goq_check_launch("goq_ref_coefficients");
     if (rc) return rc;
     if (bw == 3)
