@@ -1,14 +1,7 @@
-// fp64 helpers shared by the calibration-time kernels (quantizer, REF coefficients): exact
-// fp16 -> fp64 conversion, fp64 -> fp16 rounding and the value of a canonical lattice code.
+// fp64 -> fp16 rounding, shared by the calibration-time kernels (quantizer, REF coefficients).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-// fp16 -> fp64 is exact; the two hardware conversions (fp16 -> fp32 -> fp64) keep subnormals
-__device__ __forceinline__ double half_bits_to_double(uint32_t h)
-{
-    return (double)(float)__builtin_bit_cast(_Float16, (unsigned short)h);
-}
 
 // fp64 -> IEEE binary16 bits, round to nearest even, straight from the bit pattern (no
 // intermediate fp32): the 53-bit significand is cut at the binary16 quantum of its binade (2^-24
@@ -36,16 +29,3 @@ __device__ __forceinline__ uint32_t double_to_half_bits(double d)
     const uint32_t base = (e < -14) ? 0u : (uint32_t)(e + 14) << 10;
     return sign | (base + (uint32_t)q + up);
 }
-
-// value of one canonical code: (-1)^sign 2^-e, (sign 0, e = E - 1) is exact zero (Sec. 3.2)
-template <int BW>
-__device__ __forceinline__ double code_value(int code)
-{
-    constexpr int E = 1 << (BW - 1);
-    const int sign = (code >> (BW - 1)) & 1;
-    const int e = code & (E - 1);
-    if (!sign && e == E - 1) return 0.0;
-    // 2^-e assembled from its exponent field
-    return __longlong_as_double(((long long)sign << 63) | ((long long)(1023 - e) << 52));
-}
-

@@ -11,7 +11,7 @@
 // fp64 contractions and run on v_mfma_f64_16x16x4: it has the rate of the vector ALU (one 16 x 16 x 4
 // product in 64 cycles) but takes one operand register pair per 16 fused multiply-adds of a lane, so that
 // loads, conversions and address arithmetic hide behind it, which bound the same sums on the vector ALU
-// (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now TIMES).  Everything is fp64 with
+// (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now 16 and 141).  Everything is fp64 with
 // fixed summation orders (tokens ascending; columns, then rows), so the result is a pure function of
 // the inputs.  It differs from a token-by-token evaluation of Eq. 3 only by fp64 rounding, far below
 // the fp16 quantum of the stored coefficients.
@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "goq_layout.h"
+#include "goq_decode.h"
 #include "goq_internal.h"
 #include "goq_f64.h"
 
@@ -95,45 +96,49 @@ __global__ __launch_bounds__(RT, 2) void ref_solve_kernel(const uint16_t *__rest
                                                        double *__restrict__ craw, uint16_t *__restrict__ c1,
                                                        uint16_t *__restrict__ c2)
 {
-    __shared__ _Float16 vb1[OB][GOQ_N + 2], vb2[OB][GOQ_N + 2], vw[OB][GOQ_N + 2];
+    // (rows of 130 halfs: the 16 channels of an operand read fall into different banks)
+    constexpr int VP = GOQ_N + 2;
+    __shared__ __attribute__((aligned(16))) _Float16 vb1[OB][VP], vb2[OB][VP], vw[OB][VP];
+    __shared__ __attribute__((aligned(16))) uint4 xtab[64];                 // exchange table
     const int tid = threadIdx.x;
     const int g = blockIdx.x;
     const int64_t o0 = (int64_t)blockIdx.y * OB;
     const int64_t gn = in / GOQ_N;
 
-    // stage b1, b2 (Theorem 1 exchange from pattern and pair signs) and w of the OB channels
+    if (tid < 64) xtab[tid] = goq_exchange_entry<0x80u>(tid);
+    __syncthreads();
+    // stage b1, b2 (Theorem 1 exchange from pattern and pair signs) and w of the OB channels: a
+    // micro-block at a time, as fp16 high bytes until they are written
+    const bool wide = ((uintptr_t)w & 15) == 0;
+#pragma unroll
     for (int it = tid; it < OB * 16; it += RT) {
         const int oo = it >> 4, m = it & 15;
         const int64_t o = min(o0 + oo, out - 1);               // channels past the end repeat the last one
         const int64_t k0 = o * in + (int64_t)g * GOQ_N + m * GOQ_G;
         const uint2 cw = *reinterpret_cast<const uint2 *>(codes + k0);
-        const int s = pattern[k0 / GOQ_G] + 1;
-        const int sg = signs[k0 / GOQ_G];
-        float x[GOQ_G], y[GOQ_G];
+        const uint32_t v = (pattern[k0 / GOQ_G] & 3u) | ((signs[k0 / GOQ_G] & 15u) << 2);
+        uint32_t wd[4];
+        if (wide) {
+            const uint4 t = *reinterpret_cast<const uint4 *>(w + k0);
+            wd[0] = t.x; wd[1] = t.y; wd[2] = t.z; wd[3] = t.w;
+        } else {
 #pragma unroll
-        for (int i = 0; i < GOQ_G; ++i) x[i] = (float)code_value<BW>((int)(((i < 4 ? cw.x : cw.y) >> (8 * (i & 3))) & 0xffu));
-        int p = 0;
-#pragma unroll
-        for (int i = 0; i < GOQ_G; ++i) {
-            y[i] = 0.f;
+            for (int i = 0; i < 4; ++i) wd[i] = w[k0 + 2 * i] | (uint32_t)w[k0 + 2 * i + 1] << 16;
         }
+        // the dword of the packed layout without its metadata
+        const uint32_t d = BW == 3 ? (cw.x & 0x07070707u) | ((cw.y & 0x07070707u) << 3)
+                                   : (cw.x & 0x0f0f0f0fu) | ((cw.y & 0x0f0f0f0fu) << 4);
+        uint32_t lo, hi;
+        goq_decode_bytes<BW, 0>(d, lo, hi);
+        const uint4 e = xtab[v];
+        const uint32_t xlo = goq_perm(hi, lo, e.x) ^ e.z, xhi = goq_perm(hi, lo, e.y) ^ e.w;
+        uint32_t *p1 = reinterpret_cast<uint32_t *>(&vb1[oo][m * GOQ_G]);
+        uint32_t *p2 = reinterpret_cast<uint32_t *>(&vb2[oo][m * GOQ_G]);
+        uint32_t *pw = reinterpret_cast<uint32_t *>(&vw[oo][m * GOQ_G]);
+        p1[0] = goq_widen01(lo); p1[1] = goq_widen23(lo); p1[2] = goq_widen01(hi); p1[3] = goq_widen23(hi);
+        p2[0] = goq_widen01(xlo); p2[1] = goq_widen23(xlo); p2[2] = goq_widen01(xhi); p2[3] = goq_widen23(xhi);
 #pragma unroll
-        for (int i = 0; i < GOQ_G; ++i) {
-            const int j = i ^ s;
-            if (i < j) {
-                const float eta = ((sg >> p) & 1) ? -1.f : 1.f;
-                y[i] = -eta * x[j];
-                y[j] = eta * x[i];
-                ++p;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < GOQ_G; ++i) { vb1[oo][m * GOQ_G + i] = (_Float16)x[i]; vb2[oo][m * GOQ_G + i] = (_Float16)y[i]; }
-    }
-    for (int it = tid; it < OB * GOQ_N; it += RT) {
-        const int oo = it >> 7, k = it & 127;
-        const int64_t o = min(o0 + oo, out - 1);
-        vw[oo][k] = __builtin_bit_cast(_Float16, w[o * in + (int64_t)g * GOQ_N + k]);
+        for (int i = 0; i < 4; ++i) pw[i] = wd[i];
     }
     __syncthreads();
 

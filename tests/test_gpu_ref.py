@@ -48,6 +48,29 @@ def test_ref_matches_oracle(oracle, bw, shape):
     _compare(*_run(goq, q, W, X, 1e-4), ref, rc)
 
 
+@pytest.mark.parametrize("tokens", [64, 65])
+def test_ref_tile_edges_and_weights_at_any_address(oracle, tokens):
+    """One and just over one token tile, one and just over one block of 64 channels; weights at an
+    address that is only 2-byte aligned give the bits of aligned ones."""
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    out, inn = tokens, 256
+    W = goq_inputs.weights(out, inn, config_id=53, tensor_id=tokens)
+    q = oracle.quantize_geo(4, W, threads=4)
+    X = goq_inputs.activations_a16(tokens, inn, config_id=53, tensor_id=100, outlier_frac=0.01)
+    ref, rc = oracle.ref_coefficients(q, W, X, lam=1e-4, threads=4)
+    aligned = _run(goq, q, W, X, 1e-4)
+    _compare(*aligned, ref, rc)
+    shifted = torch.zeros(out * inn + 1, dtype=torch.int16, device="cuda")
+    shifted[1:] = gu.to_dev(W.view(np.uint16)).reshape(-1)
+    ws = torch.empty(goq.ref_workspace_bytes(inn), dtype=torch.uint8, device="cuda")
+    c1, c2 = (torch.zeros((out, inn // 128), dtype=torch.int16, device="cuda") for _ in range(2))
+    goq.ref_coefficients(4, tokens, out, inn, shifted[1:], gu.to_dev(q["codes"]), gu.to_dev(q["pattern"]),
+                         gu.to_dev(q["signs"]), gu.to_dev(X.view(np.uint16)), 1e-4, ws, None, c1, c2)
+    assert np.array_equal(c1.cpu().numpy().view(np.uint16), aligned[1])
+    assert np.array_equal(c2.cpu().numpy().view(np.uint16), aligned[2])
+
+
 def test_ref_special_cases(oracle):
     """identity inputs with and without a ridge (the GEO coefficients), weights in the span of the
     bases (exact recovery), a single token (rank-one system, ridge only), an all-zero macro-block."""
