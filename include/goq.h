@@ -244,9 +244,11 @@ int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kerne
  *                  +128, which is no int8; the int8 activations are widened to fp16 on their way
  *                  into LDS and the fp16 MFMA is used -- every product is exact and a slab sum
  *                  needs at most 22 bits, so the fp32 accumulators hold the same exact integers.
- *   act = GOQ_A4 : X packed int4 [tokens][in / 2 bytes], sx fp32 [tokens]; unpacked to int8 (bw = 3)
- *                  or widened to fp16 (bw = 4) on the way into LDS, then as GOQ_A8.
- *   act = GOQ_A6 : X packed int6 [tokens][3 in / 4 bytes], otherwise as GOQ_A4.
+ *   act = GOQ_A4 : X packed int4 [tokens][in / 2 bytes], sx fp32 [tokens]; integers of four bits and
+ *                  PoT weights are exact 8-bit floats (E5M2) and go to the 8-bit-float MFMA, with
+ *                  exact slab sums.
+ *   act = GOQ_A6 : X packed int6 [tokens][3 in / 4 bytes]; unpacked to int8 (bw = 3) or widened to
+ *                  fp16 (bw = 4) on the way into LDS, then as GOQ_A8.
  *   act = GOQ_A3 : X packed int3 [tokens][3 in / 8 bytes], otherwise as GOQ_A4.
  *   partials (optional, integer activations only, else NULL): int32 [tokens][out][in/128][2] receives
  *   the exact slab partials P_1, P_2 (in units of 2^-(E-1)). */

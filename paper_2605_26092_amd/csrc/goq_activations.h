@@ -50,6 +50,31 @@ __device__ __forceinline__ void goq_unpack_i3(uint32_t v, uint32_t &b0, uint32_t
     b1 = spread(v >> 12);
 }
 
+// eight int4 / int3 as eight 8-bit floats (E5M2), elements 0..3 in b0 and 4..7 in b1: 0..7 are
+// 00 3C 40 42 44 45 46 47, negative numbers have the sign bit, -8 is C8
+__device__ __forceinline__ void goq_e5m2_i4(uint32_t d, uint32_t &b0, uint32_t &b1)
+{
+    // both halves are looked up by the low three bits, then picked by the sign bit (selector byte i = i
+    // or 4 + i)
+    auto four = [](uint32_t n, uint32_t pick) {
+        const uint32_t e = n & 0x07070707u;
+        return goq_perm(goq_perm(0xBCC0C2C4u, 0xC5C6C7C8u, e), goq_perm(0x47464544u, 0x42403C00u, e), pick | 0x03020100u);
+    };
+    const uint32_t ev = four(d, (d >> 1) & 0x04040404u);           // elements 0, 2, 4, 6
+    const uint32_t od = four(d >> 4, (d >> 5) & 0x04040404u);      // elements 1, 3, 5, 7
+    b0 = goq_perm(od, ev, 0x05010400u);
+    b1 = goq_perm(od, ev, 0x07030602u);
+}
+__device__ __forceinline__ void goq_e5m2_i3(uint32_t v, uint32_t &b0, uint32_t &b1)
+{
+    auto four = [](uint32_t t) {
+        const uint32_t e = (t & 0x7u) | ((t << 5) & 0x700u) | ((t << 10) & 0x70000u) | ((t << 15) & 0x7000000u);
+        return goq_perm(0xBCC0C2C4u, 0x42403C00u, e);
+    };
+    b0 = four(v);
+    b1 = four(v >> 12);
+}
+
 // the j-th group of 24 bits of a little-endian bit string of dwords
 template <int NW>
 __device__ __forceinline__ uint32_t goq_bits24(const uint32_t (&w)[NW], int j)

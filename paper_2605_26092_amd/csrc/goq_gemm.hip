@@ -7,6 +7,11 @@
 //        fp16 on their way into LDS and the fp16 instruction is used: int8 values and powers of
 //        two down to 2^-7 are exact in fp16, every product is exact, and a slab sum needs at most
 //        22 bits, so the fp32 accumulators hold the exact integers (in units of 2^-7).
+//   A4, A3: v_mfma_scale_f32_32x32x64_f8f6f4.  Integers of up to four bits and powers of two are exact
+//        8-bit floats (E5M2, the high byte of the fp16 number), so neither side is widened; a product has
+//        at most ten binary places, the instruction adds on a grid of thirteen, and a slab sum needs
+//        at most 18 bits: exact again.  Half the matrix cycles of the fp16 form and half its LDS bytes
+//        (ViT-B block, 1576 tokens, W4/A4: 64.6 -> 59.4 us).
 // The weight side is the MFMA B operand.  Its register layout -- lane (n = lane % 32,
 // kg = lane / 32) holds 8 (fp16) or 16 (int8) consecutive k of output channel n -- is one (two)
 // 8-weight micro-block(s) of one row, which is the unit the packed layout stores in a dword.  A
@@ -51,6 +56,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 #ifndef GOQ_GEMM_TM
 #define GOQ_GEMM_TM 64
@@ -145,23 +151,23 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     const int tile = (int)blockIdx.x - batch.first[pi];
     static_assert(!FOLD || (ACT == 0 && !PART), "the folded product exists for fp16 activations only");
     constexpr int CH = (BW == 3) ? 4 : 5;
-    // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x unpacked to
-    // int8, int8 MFMA; 4 packed int4 x widened to fp16; 5 packed int6 x unpacked to int8, int8
-    // MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x unpacked to int8, int8 MFMA; 8 packed
-    // int3 x widened to fp16.  2..8 stage x through registers.
-    constexpr bool F16 = (ACT == 0 || ACT == 2 || ACT == 4 || ACT == 6 || ACT == 8);   // fp16 MFMA
+    // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x as 8-bit floats;
+    // 5 packed int6 x unpacked to int8, int8 MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x
+    // as 8-bit floats.  2..7 stage x through registers.
+    constexpr bool F16 = (ACT == 0 || ACT == 2 || ACT == 6);       // fp16 MFMA
+    constexpr bool F8 = (ACT == 3 || ACT == 7);                    // 8-bit-float MFMA
     constexpr bool REGSTAGE = (ACT >= 2);
-    constexpr bool X4 = (ACT == 3 || ACT == 4);                    // two activations per byte
+    constexpr bool X4 = (ACT == 3);                                // two activations per byte
     constexpr bool X6 = (ACT == 5 || ACT == 6);                    // four activations per three bytes
-    constexpr bool X3 = (ACT == 7 || ACT == 8);                    // eight activations per three bytes
-    constexpr bool I8OUT = (ACT == 3 || ACT == 5 || ACT == 7);     // staged as int8 (else widened to fp16)
-    constexpr int WACT = F16 ? 0 : 1;                  // how the weights are decoded
+    constexpr bool X3 = (ACT == 7);                                // eight activations per three bytes
+    constexpr bool I8OUT = (ACT == 5);                             // staged as int8 (else 8-bit floats or widened to fp16)
+    constexpr int WACT = F16 || F8 ? 0 : 1;            // how the weights are decoded
     constexpr int XB = F16 ? 2 : 1;                    // bytes per activation in LDS
     constexpr int ROWB = GOQ_N * XB;                   // LDS row stride (XOR-swizzled, not padded)
-    constexpr int KSTEPS = F16 ? 8 : 4;                // MFMA k-steps per slab (16 / 32 k each)
+    constexpr int KSTEPS = F16 ? 8 : F8 ? 2 : 4;       // MFMA k-steps per slab (16 / 64 / 32 k each)
     constexpr int NBUF = 3;                            // activation slabs resident in LDS
-    using AccT = typename std::conditional<F16, f32x16, i32x16>::type;
-    using OpT = typename std::conditional<F16, f16x8, i32x4>::type;          // one MFMA operand
+    using AccT = typename std::conditional<F16 || F8, f32x16, i32x16>::type;
+    using OpT = typename std::conditional<F16, f16x8, typename std::conditional<F8, i32x8, i32x4>::type>::type;   // one MFMA operand
 
     __shared__ __attribute__((aligned(16))) unsigned char xsb[NBUF][TM * ROWB];
     __shared__ __attribute__((aligned(16))) unsigned char xtab[64 * 16];        // exchange table
@@ -309,10 +315,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t v = goq_bits24(w, j);
-                    uint32_t b0, b1;
-                    goq_unpack_i3(v, b0, b1);
-                    if constexpr (I8OUT) { o[2 * j] = b0; o[2 * j + 1] = b1; }
-                    else { goq_widen_i8(b0, o[4 * j], o[4 * j + 1]); goq_widen_i8(b1, o[4 * j + 2], o[4 * j + 3]); }
+                    goq_e5m2_i3(v, o[2 * j], o[2 * j + 1]);
                 }
             }
             const uint32_t d[4] = {r[i * NQ].x, r[i * NQ].y, r[i * NQ].z, r[i * NQ].w};
@@ -323,15 +326,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 for (int k = 0; k < 4; ++k) goq_widen_i8(d[k], o[2 * k], o[2 * k + 1]);
             } else if constexpr (ACT == 3) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) goq_unpack_i4(d[k], o[2 * k], o[2 * k + 1]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    uint32_t b0, b1;
-                    goq_unpack_i4(d[k], b0, b1);
-                    goq_widen_i8(b0, o[4 * k], o[4 * k + 1]);
-                    goq_widen_i8(b1, o[4 * k + 2], o[4 * k + 3]);
-                }
+                for (int k = 0; k < 4; ++k) goq_e5m2_i4(d[k], o[2 * k], o[2 * k + 1]);
             }
             unsigned char *dst = buf + row * ROWB;
 #pragma unroll
@@ -350,6 +345,15 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
             B1 = widen8(l1, h1);
             B2 = widen8(l2, h2);
             if constexpr (FOLD) B1 = cf1 * B1 + cf2 * B2;
+        } else if constexpr (F8) {
+            // the quad of 32 consecutive k: decoded bytes are the 8-bit floats
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t l1, h1, l2, h2;
+                decode_pair<BW, WACT>(word_of(w, 4 * t + k), w.meta, 4 * t + k, vt, l1, h1, l2, h2);
+                B1[2 * k] = (int)l1; B1[2 * k + 1] = (int)h1;
+                B2[2 * k] = (int)l2; B2[2 * k + 1] = (int)h2;
+            }
         } else {
             uint32_t l1, h1, l2, h2, l3, h3, l4, h4;
             decode_pair<BW, WACT>(word_of(w, 2 * t), w.meta, 2 * t, vt, l1, h1, l2, h2);
@@ -364,7 +368,12 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
         const int piece = KSTEPS * kg + t;
 #pragma unroll
         for (int i = 0; i < MS; ++i)
-            A[i] = *reinterpret_cast<const OpT *>(xs + (32 * i + ln) * ROWB + ((piece ^ swz(32 * i + ln)) * 16));
+            if constexpr (F8) {
+                const unsigned char *row = xs + (32 * i + ln) * ROWB;
+                const i32x4 a0 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece) ^ swz(32 * i + ln)) * 16));
+                const i32x4 a1 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece + 1) ^ swz(32 * i + ln)) * 16));
+                A[i] = i32x8{a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+            } else A[i] = *reinterpret_cast<const OpT *>(xs + (32 * i + ln) * ROWB + ((piece ^ swz(32 * i + ln)) * 16));
     };
     // coefficient pair of this lane's output channel
     auto coefficients = [&](const Weights &w, float &c1, float &c2) {
@@ -464,6 +473,10 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 } else if constexpr (F16) {
                     P1[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[i], B1c, t == 0 ? z : P1[i], 0, 0, 0);
                     P2[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[i], B2c, t == 0 ? z : P2[i], 0, 0, 0);
+                } else if constexpr (F8) {
+                    // E5M2 x E5M2, block scales 2^0
+                    P1[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ac[i], B1c, t == 0 ? z : P1[i], 1, 1, 0, 127, 0, 127);
+                    P2[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ac[i], B2c, t == 0 ? z : P2[i], 1, 1, 0, 127, 0, 127);
                 } else {
                     P1[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ac[i], B1c, t == 0 ? z : P1[i], 0, 0, 0);
                     P2[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ac[i], B2c, t == 0 ? z : P2[i], 0, 0, 0);
@@ -489,7 +502,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                     const int m = m0 + 32 * i + 8 * (v / 4) + 4 * kg + (v % 4);
                     if (m < a.tokens && n < a.out && a.partials)
                         *reinterpret_cast<int2 *>(a.partials + (((int64_t)m * a.out + n) * a.gn + g) * 2) =
-                            F16 ? make_int2((int)((float)P1[i][v] * (float)(1 << ((1 << (BW - 1)) - 1))),
+                            F16 || F8 ? make_int2((int)((float)P1[i][v] * (float)(1 << ((1 << (BW - 1)) - 1))),
                                             (int)((float)P2[i][v] * (float)(1 << ((1 << (BW - 1)) - 1))))
                                 : make_int2((int)P1[i][v], (int)P2[i][v]);
                 }
@@ -507,8 +520,8 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
             const int m = m0 + 32 * i + 8 * (v / 4) + 4 * kg + (v % 4);
             if (m >= a.tokens || n >= a.out) continue;
             float y = Yacc[i][v];
-            if constexpr (ACT != 0 && !F16) y *= a.sx[m] * (1.f / (float)(1 << ((1 << (BW - 1)) - 1)));
-            if constexpr (ACT != 0 && F16) y *= a.sx[m];
+            if constexpr (ACT != 0 && !F16 && !F8) y *= a.sx[m] * (1.f / (float)(1 << ((1 << (BW - 1)) - 1)));
+            if constexpr (ACT != 0 && (F16 || F8)) y *= a.sx[m];
             if (a.ytype == GOQ_F32) reinterpret_cast<float *>(a.Y)[(int64_t)m * a.out + n] = y;
             else reinterpret_cast<__half *>(a.Y)[(int64_t)m * a.out + n] = __float2half(y);
         }
@@ -608,9 +621,9 @@ int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc 
     if (bw == 4 && act == GOQ_A16) return launch<4, 0>(st, b, n);
     if (bw == 4 && act == GOQ_A8) return launch<4, 2>(st, b, n);
     if (bw == 3 && act == GOQ_A4) return launch<3, 3>(st, b, n);
-    if (bw == 4 && act == GOQ_A4) return launch<4, 4>(st, b, n);
+    if (bw == 4 && act == GOQ_A4) return launch<4, 3>(st, b, n);
     if (bw == 3 && act == GOQ_A6) return launch<3, 5>(st, b, n);
     if (bw == 4 && act == GOQ_A6) return launch<4, 6>(st, b, n);
     if (bw == 3 && act == GOQ_A3) return launch<3, 7>(st, b, n);
-    return launch<4, 8>(st, b, n);
+    return launch<4, 7>(st, b, n);
 }

@@ -90,3 +90,28 @@ def test_batch_of_few_and_many_tokens(act):
     torch.cuda.synchronize()
     for ya, yb in single:
         assert torch.equal(ya, yb)
+
+
+@pytest.mark.parametrize("act", sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,out,inn", [(1089, 1025, 128), (700, 2050, 384)])
+def test_many_tokens_integers(oracle, act, bw, tokens, out, inn):
+    """The tile kernel with every integer type, ragged in both directions, one and three slabs: int32
+    slab partials bit for bit, with the extremes of the type in the first tokens, y from them, and y
+    without the partials the same bits."""
+    import paper_2605_26092_amd as goq
+    print("many tokens %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=64, tensor_id=tokens)
+    q["codes"][:40] = 0                                            # all +1
+    bits, packer = PACKERS[act] or (8, None)
+    x, sx = goq_inputs.activations_int(tokens, inn, bits, config_id=64, tensor_id=200)
+    top = 1 << (bits - 1)
+    x[0], x[1], x[2, ::2] = -top, top - 1, -top
+    xd = gu.to_dev(getattr(goq_inputs, packer)(x) if packer else x)
+    rows = np.r_[0:8, tokens // 2:tokens // 2 + 8, tokens - 8:tokens]
+    ref, pref = oracle.gemm_a8(q, x[rows], sx[rows], threads=8, want_partials=True)
+    Y, P = _run(goq, bw, act, q, tokens, xd, gu.to_dev(sx), goq.F32, partials=True)
+    assert np.array_equal(P.cpu().numpy()[rows], pref)
+    scale = (np.abs(x[rows].astype(np.float64)) * sx[rows][:, None]) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
+    assert np.max(np.abs(Y.cpu().numpy()[rows].astype(np.float64) - ref) / scale) <= 2e-6
+    assert gu.torch_cuda().equal(_run(goq, bw, act, q, tokens, xd, gu.to_dev(sx), goq.F32)[0], Y)
