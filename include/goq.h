@@ -233,10 +233,9 @@ int goq_gemv_select(int kernel);
  * Only out and in of the descriptors are read; nothing is launched and no device is touched. */
 int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kernel, int *workgroups);
 
-/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Few tokens (up to
- * 32, or 64-token x 128-output tiles for at most 128 workgroups) go to a kernel that splits the
- * depth over the wavefronts of a workgroup and widens integer activations to fp16 (exact: see
- * bw = 4 below); the others:
+/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Up to 32 tokens
+ * go to a kernel that splits the depth over the wavefronts of a workgroup and widens integer
+ * activations to fp16 (exact: see bw = 4 below); the others:
  *   act = GOQ_A16: X fp16, sx NULL; PoT codes are decoded to fp16 operands of the fp16 MFMA,
  *                  fp32 accumulation.
  *   act = GOQ_A8 : X int8, sx fp32 [tokens].  bw = 3: PoT codes are decoded to int8 (b * 2^(E-1))
@@ -244,9 +243,9 @@ int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kerne
  *                  +128, which is no int8; the int8 activations are widened to fp16 on their way
  *                  into LDS and the fp16 MFMA is used -- every product is exact and a slab sum
  *                  needs at most 22 bits, so the fp32 accumulators hold the same exact integers.
- *   act = GOQ_A4 : X packed int4 [tokens][in / 2 bytes], sx fp32 [tokens]; integers of four bits and
- *                  PoT weights are exact 8-bit floats (E5M2) and go to the 8-bit-float MFMA, with
- *                  exact slab sums.
+ *   act = GOQ_A4 : X packed int4 [tokens][in / 2 bytes], sx fp32 [tokens]; bw = 3: unpacked to int8 on the
+ *                  way into LDS, then as GOQ_A8; bw = 4: integers of four bits and PoT weights are
+ *                  exact 8-bit floats (E5M2) and go to the 8-bit-float MFMA, with exact slab sums.
  *   act = GOQ_A6 : X packed int6 [tokens][3 in / 4 bytes]; unpacked to int8 (bw = 3) or widened to
  *                  fp16 (bw = 4) on the way into LDS, then as GOQ_A8.
  *   act = GOQ_A3 : X packed int3 [tokens][3 in / 8 bytes], otherwise as GOQ_A4.
@@ -258,8 +257,8 @@ int goq_gemm(void *stream, int bw, int act, int64_t tokens, int64_t out, int64_t
 
 /* Several independent many-token layers in ONE launch (e.g. q, k, v or gate, up of a decoder block,
  * which share X): the tiles of all problems form one grid, so a small matrix does not leave the
- * chip half empty and there is one tail instead of n (a batch that mixes problems of a few
- * tokens, see goq_gemm, with larger ones is two launches on the stream).  descs is a HOST array of n <= GOQ_MAX_BATCH
+ * chip half empty and there is one tail instead of n (a batch that mixes problems of up to 32
+ * tokens with larger ones is two launches on the stream).  descs is a HOST array of n <= GOQ_MAX_BATCH
  * descriptors with the arguments of goq_gemm; all share bw and act.  Results are those of n
  * goq_gemm calls, bit for bit. */
 typedef struct goq_gemm_desc {

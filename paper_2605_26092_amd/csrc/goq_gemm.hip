@@ -7,11 +7,14 @@
 //        fp16 on their way into LDS and the fp16 instruction is used: int8 values and powers of
 //        two down to 2^-7 are exact in fp16, every product is exact, and a slab sum needs at most
 //        22 bits, so the fp32 accumulators hold the exact integers (in units of 2^-7).
-//   A4, A3: v_mfma_scale_f32_32x32x64_f8f6f4.  Integers of up to four bits and powers of two are exact
-//        8-bit floats (E5M2, the high byte of the fp16 number), so neither side is widened; a product has
-//        at most ten binary places, the instruction adds on a grid of thirteen, and a slab sum needs
-//        at most 18 bits: exact again.  Half the matrix cycles of the fp16 form and half its LDS bytes
-//        (ViT-B block, 1576 tokens, W4/A4: 64.6 -> 59.4 us).
+//   A6, A4, A3 are unpacked to int8 on their way into LDS (bw = 3); with bw = 4 A6 goes the way of A8, and
+//   A4, A3 with bw = 4: v_mfma_scale_f32_32x32x64_f8f6f4.  Integers of up to four bits and powers of
+//        two are exact 8-bit floats (E5M2, the high byte of the fp16 number), so neither side is widened;
+//        a product has at most ten binary places, the instruction adds on a grid of thirteen, and a slab
+//        sum needs at most 18 bits: exact again.  Half the matrix cycles of the fp16 form and half its LDS
+//        bytes (us, fp16 form / this: ViT-B block, W4/A4, 1576 tokens 66 / 56; 7B block, 2048 tokens
+//        1589 / 1250).  With bw = 3 the int8 form stays: 2304 x 768, 12608 tokens 95 / 107, three
+//        wavefronts per SIMD against two.
 // The weight side is the MFMA B operand.  Its register layout -- lane (n = lane % 32,
 // kg = lane / 32) holds 8 (fp16) or 16 (int8) consecutive k of output channel n -- is one (two)
 // 8-weight micro-block(s) of one row, which is the unit the packed layout stores in a dword.  A
@@ -23,7 +26,7 @@
 // takes micro-block 8 kg + t of lane group kg.  The activation tile of the slab is staged in LDS
 // (XOR-swizzled 16-byte pieces against bank conflicts) and read as the MFMA A operand.
 //
-// Tiling: workgroup = 4 wavefronts, tile 64 tokens x 128 outputs; each wavefront owns 64 tokens x
+// Tiling: workgroup = 4 wavefronts, tile 64 (or 32) tokens x 128 outputs; each wavefront owns 64 tokens x
 // 32 outputs = two MFMA tiles of 32 x 32, with three accumulator sets: the slab partials P1, P2
 // (restarted every slab by feeding C = 0 to the slab's first MFMA) and the output Y.  That fits
 // three wavefronts per SIMD.  Measured on this chip with a probe of the same instruction mix:
@@ -36,7 +39,11 @@
 // it measured slower.
 // Pipeline: activations of slab g + 2 are requested (global_load_lds, straight into one of three
 // LDS buffers) and the weights of slab g + 1 (registers) at the start of slab g; inside a slab
-// every k-step's MFMAs run on operands prepared during the previous k-step; one barrier per slab.
+// every k-step's MFMAs run on operands prepared during the previous k-step; one barrier per slab, which
+// waits for slab g + 1's activations only.  (With a request under a run-time condition or a plain
+// __syncthreads() the compiler waited for everything, slab g + 2 included, once per slab: a launch with
+// one workgroup per CU took 1.3 us a slab.)
+// Launches of few tiles use 32-token tiles (narrow_tiles below): 4096 x 4096, 64 tokens, W3/A16 40 -> 27 us.
 // One launch covers up to GOQ_MAX_BATCH layers (goq_gemm_batch): their tiles form one grid, the
 // layers with the deepest rows first, so that a block of matrices has one tail, not one per matrix.
 // Coefficient rescale (H5) once per slab: Y += c1[n,g] * P1 + c2[n,g] * P2 in fp32, after the
@@ -58,13 +65,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-#ifndef GOQ_GEMM_TM
-#define GOQ_GEMM_TM 64
-#endif
-constexpr int TM = GOQ_GEMM_TM;   // tokens per workgroup tile
 constexpr int TN = 128;       // outputs per workgroup tile
 constexpr int WN = 32;        // outputs per wavefront
-constexpr int MS = TM / 32;   // MFMA tiles along tokens per wavefront
 
 struct GemmArgs {
     const uint32_t *packed;
@@ -82,28 +84,28 @@ struct GemmBatch {
     GemmArgs p[GOQ_MAX_BATCH];
 };
 
-// LDS address of the exchange table entry of a micro-block: vt + 16 * (pattern | signs << 2)
+// offset of the exchange table entry of a micro-block: 16 * (pattern | signs << 2)
 template <int BW>
-__device__ __forceinline__ uint32_t exchange_address(uint32_t w, const uint4 &meta, int m, uint32_t vt)
+__device__ __forceinline__ uint32_t exchange_offset(uint32_t w, const uint4 &meta, int m)
 {
     if constexpr (BW == 3) {
         // a_0 (bits 6..7), a_1 (14..15), a_2 (22..23) -> contiguous 6-bit index at bits 18..23
         const uint32_t u = __umul24(w & 0x00C0C0C0u, 0x1041u);
-        return vt + ((u >> 14) & 0x3F0u);
+        return (u >> 14) & 0x3F0u;
     } else {
         // meta.x, meta.y: the metadata dwords of this lane's two chunks (6 bits per micro-block)
         const uint32_t md = m < 4 ? meta.x : meta.y;
-        return vt + (((md >> (6 * (m & 3))) & 63u) << 4);
+        return ((md >> (6 * (m & 3))) & 63u) << 4;
     }
 }
 
 // Decode one micro-block dword into the bytes of b1 and b2 (elements 0..3 in lo, 4..7 in hi).
 template <int BW, int ACT>
-__device__ __forceinline__ void decode_pair(uint32_t w, const uint4 &meta, int m, uint32_t vt,
+__device__ __forceinline__ void decode_pair(uint32_t w, const uint4 &meta, int m, const unsigned char *xtab,
                                             uint32_t &b1lo, uint32_t &b1hi, uint32_t &b2lo, uint32_t &b2hi)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 e = *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>(exchange_address<BW>(w, meta, m, vt));
+    const u32x4 e = *reinterpret_cast<const u32x4 *>(xtab + exchange_offset<BW>(w, meta, m));
     if constexpr (ACT == 0) {
         // fp16 high bytes: exchange the decoded bytes, flip sign bits
         goq_decode_bytes<BW, ACT>(w, b1lo, b1hi);
@@ -132,16 +134,14 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
     return __builtin_bit_cast(f16x8, v);
 }
 
-#ifndef GOQ_GEMM_MINWAVES
-#define GOQ_GEMM_MINWAVES 2
-#endif
 // FOLD (fp16 activations only) is the ablation of the method's two-basis product: the decoded
 // operands are combined in registers to the fp16 weight c1 b1 + c2 b2 (two packed fp16 operations
 // per register) and ONE matrix instruction per k-step and tile accumulates straight into Y.  Half
 // the matrix instructions and no rescale, but the operand is no power of two any more: every
 // weight is rounded to fp16 (2^-11 relative), which the two-basis path avoids.
-template <int BW, int ACT, bool PART, bool FOLD = false>
-__global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch batch)
+// MS: MFMA tiles along tokens per wavefront (the workgroup's tile has 32 MS tokens).
+template <int BW, int ACT, bool PART, bool FOLD, int MS>
+__global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm_kernel(GemmBatch batch)
 {
     int pi = 0;
 #pragma unroll
@@ -151,25 +151,30 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     const int tile = (int)blockIdx.x - batch.first[pi];
     static_assert(!FOLD || (ACT == 0 && !PART), "the folded product exists for fp16 activations only");
     constexpr int CH = (BW == 3) ? 4 : 5;
-    // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x as 8-bit floats;
-    // 5 packed int6 x unpacked to int8, int8 MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x
-    // as 8-bit floats.  2..7 stage x through registers.
+    constexpr int TM = 32 * MS;
+    // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x unpacked to
+    // int8, int8 MFMA; 4 packed int4 x as 8-bit floats; 5 packed int6 x unpacked to int8, int8
+    // MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x unpacked to int8, int8 MFMA; 8 packed
+    // int3 x as 8-bit floats.  2..8 stage x through registers.
     constexpr bool F16 = (ACT == 0 || ACT == 2 || ACT == 6);       // fp16 MFMA
-    constexpr bool F8 = (ACT == 3 || ACT == 7);                    // 8-bit-float MFMA
+    constexpr bool F8 = (ACT == 4 || ACT == 8);                    // 8-bit-float MFMA
     constexpr bool REGSTAGE = (ACT >= 2);
-    constexpr bool X4 = (ACT == 3);                                // two activations per byte
+    constexpr bool X4 = (ACT == 3 || ACT == 4);                    // two activations per byte
     constexpr bool X6 = (ACT == 5 || ACT == 6);                    // four activations per three bytes
-    constexpr bool X3 = (ACT == 7);                                // eight activations per three bytes
-    constexpr bool I8OUT = (ACT == 5);                             // staged as int8 (else 8-bit floats or widened to fp16)
+    constexpr bool X3 = (ACT == 7 || ACT == 8);                    // eight activations per three bytes
+    constexpr bool I8OUT = (ACT == 3 || ACT == 5 || ACT == 7);     // staged as int8 (else 8-bit floats or widened to fp16)
     constexpr int WACT = F16 || F8 ? 0 : 1;            // how the weights are decoded
     constexpr int XB = F16 ? 2 : 1;                    // bytes per activation in LDS
     constexpr int ROWB = GOQ_N * XB;                   // LDS row stride (XOR-swizzled, not padded)
     constexpr int KSTEPS = F16 ? 8 : F8 ? 2 : 4;       // MFMA k-steps per slab (16 / 64 / 32 k each)
-    constexpr int NBUF = 3;                            // activation slabs resident in LDS
     using AccT = typename std::conditional<F16 || F8, f32x16, i32x16>::type;
     using OpT = typename std::conditional<F16, f16x8, typename std::conditional<F8, i32x8, i32x4>::type>::type;   // one MFMA operand
 
-    __shared__ __attribute__((aligned(16))) unsigned char xsb[NBUF][TM * ROWB];
+    // three activation slabs (arrays of their own: the compiler makes a read of an array wait for the
+    // loads that fill it, and two slabs are on their way while the third is read)
+    __shared__ __attribute__((aligned(16))) unsigned char xs0[TM * ROWB];
+    __shared__ __attribute__((aligned(16))) unsigned char xs1[TM * ROWB];
+    __shared__ __attribute__((aligned(16))) unsigned char xs2[TM * ROWB];
     __shared__ __attribute__((aligned(16))) unsigned char xtab[64 * 16];        // exchange table
 
     const int tid = threadIdx.x;
@@ -185,7 +190,6 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     const int n0 = nt * TN + wave * WN;
 
     if (tid < 64) *reinterpret_cast<uint4 *>(xtab + tid * 16) = goq_exchange_entry<(WACT == 0 ? 0x80u : 0xFFu)>(tid);
-    const uint32_t vt = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)xtab;
 
     f32x16 Yacc[MS];
 #pragma unroll
@@ -227,31 +231,26 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     // instruction fills 64 consecutive 16-byte LDS slots, one per lane, from per-lane addresses.
     // Slot (row, cs) holds k-piece cs ^ f(row): the XOR swizzle makes the 16 rows a quarter of an
     // MFMA A operand read touches fall into 16 different bank groups (row stride 256 / 128 bytes).
-    // The per-thread byte offsets (inside the token tile) of the pieces a thread requests are
-    // constant over the slabs: a slab's request is one uniform base plus these 32-bit offsets.
+    // The swizzle repeats over the pieces of a thread, so one byte offset serves them all: a request
+    // is that offset plus a uniform one.
     constexpr int PIECES = TM * GOQ_N * XB / 16;
     constexpr int PER_ROW = GOQ_N * XB / 16;
     constexpr int NP = PIECES / 256;
     auto swz = [](int row) { return F16 ? (row & 15) : ((row >> 1) & 7); };
-    uint32_t xoff[NP];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int S = i * 256 + tid;
-        const int row = S / PER_ROW, cs = S % PER_ROW;
-        const int c = cs ^ swz(row);
-        int m = m0 + row;
-        m = m < a.tokens ? m : a.tokens - 1;          // rows past the end are never stored
-        xoff[i] = (uint32_t)(m - m0) * (uint32_t)a.in * XB + c * 16;
-    }
+    const int row0 = tid / PER_ROW;                   // piece i of a thread: token row0 + i 256 / PER_ROW
+    const uint32_t xline = (uint32_t)a.in * XB;
+    const uint32_t xoff = (uint32_t)row0 * xline + (uint32_t)((tid % PER_ROW) ^ swz(row0)) * 16u;
     const unsigned char *xtile = reinterpret_cast<const unsigned char *>(a.X) + (int64_t)m0 * a.in * XB;
-    auto stage_x = [&](int g) {          // exactly NP vector-memory instructions
-        const unsigned char *base = xtile + (int64_t)g * GOQ_N * XB;
-        unsigned char *buf = xsb[g % NBUF];
+    // (tokens past the end are out of the buffer's range and read as zeros)
+    const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char *>(xtile), 0, (int)(uint32_t)min((uint64_t)(a.tokens - m0) * xline, (uint64_t)0xffffffffu), 0x00020000);
+    auto stage_x = [&](int g, unsigned char *buf) {          // exactly NP vector-memory instructions
+        const uint32_t at = g < a.gn ? (uint32_t)(g * GOQ_N * XB) : 0xC0000000u;
 #pragma unroll
         for (int i = 0; i < NP; ++i)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(base + xoff[i]),
-                (__attribute__((address_space(3))) void *)(buf + (i * 256 + wave * 64) * 16), 16, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                xrsrc, (__attribute__((address_space(3))) void *)(buf + (i * 256 + wave * 64) * 16), 16, (int)xoff,
+                (int)((uint32_t)(i * (256 / PER_ROW)) * xline + at), 0, 0);
     };
     // Register staging (ACT >= 2): integer activations pass through registers and are unpacked /
     // widened on their way into LDS.  A thread moves NPS 16-byte pieces per slab; a piece holds
@@ -291,8 +290,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
             }
         }
     };
-    auto write_x = [&](int g, const uint4 (&r)[NPS * NQ]) {
-        unsigned char *buf = xsb[g % NBUF];
+    auto write_x = [&](unsigned char *buf, const uint4 (&r)[NPS * NQ]) {
 #pragma unroll
         for (int i = 0; i < NPS; ++i) {
             const int S = i * 256 + tid;
@@ -315,7 +313,8 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t v = goq_bits24(w, j);
-                    goq_e5m2_i3(v, o[2 * j], o[2 * j + 1]);
+                    if constexpr (I8OUT) goq_unpack_i3(v, o[2 * j], o[2 * j + 1]);
+                    else goq_e5m2_i3(v, o[2 * j], o[2 * j + 1]);
                 }
             }
             const uint32_t d[4] = {r[i * NQ].x, r[i * NQ].y, r[i * NQ].z, r[i * NQ].w};
@@ -325,6 +324,9 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
 #pragma unroll
                 for (int k = 0; k < 4; ++k) goq_widen_i8(d[k], o[2 * k], o[2 * k + 1]);
             } else if constexpr (ACT == 3) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) goq_unpack_i4(d[k], o[2 * k], o[2 * k + 1]);
+            } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) goq_e5m2_i4(d[k], o[2 * k], o[2 * k + 1]);
             }
@@ -341,7 +343,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     auto decode_step = [&](const Weights &w, int t, OpT &B1, OpT &B2) {
         if constexpr (F16) {
             uint32_t l1, h1, l2, h2;
-            decode_pair<BW, WACT>(word_of(w, t), w.meta, t, vt, l1, h1, l2, h2);
+            decode_pair<BW, WACT>(word_of(w, t), w.meta, t, xtab, l1, h1, l2, h2);
             B1 = widen8(l1, h1);
             B2 = widen8(l2, h2);
             if constexpr (FOLD) B1 = cf1 * B1 + cf2 * B2;
@@ -350,14 +352,14 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 uint32_t l1, h1, l2, h2;
-                decode_pair<BW, WACT>(word_of(w, 4 * t + k), w.meta, 4 * t + k, vt, l1, h1, l2, h2);
+                decode_pair<BW, WACT>(word_of(w, 4 * t + k), w.meta, 4 * t + k, xtab, l1, h1, l2, h2);
                 B1[2 * k] = (int)l1; B1[2 * k + 1] = (int)h1;
                 B2[2 * k] = (int)l2; B2[2 * k + 1] = (int)h2;
             }
         } else {
             uint32_t l1, h1, l2, h2, l3, h3, l4, h4;
-            decode_pair<BW, WACT>(word_of(w, 2 * t), w.meta, 2 * t, vt, l1, h1, l2, h2);
-            decode_pair<BW, WACT>(word_of(w, 2 * t + 1), w.meta, 2 * t + 1, vt, l3, h3, l4, h4);
+            decode_pair<BW, WACT>(word_of(w, 2 * t), w.meta, 2 * t, xtab, l1, h1, l2, h2);
+            decode_pair<BW, WACT>(word_of(w, 2 * t + 1), w.meta, 2 * t + 1, xtab, l3, h3, l4, h4);
             B1 = i32x4{(int)l1, (int)h1, (int)l3, (int)h3};
             B2 = i32x4{(int)l2, (int)h2, (int)l4, (int)h4};
         }
@@ -393,19 +395,19 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
     };
 
     // Prologue: slabs 0 and 1 are requested and waited for.
-    Weights wd, wn;
+    Weights wA, wB, wC;
     uint4 xr[NPS * NQ];
-    load_weights(0, wd);
+    load_weights(0, wA);
     if constexpr (REGSTAGE) {
         fetch_x(0, xr);
-        write_x(0, xr);
+        write_x(xs0, xr);
         if (a.gn > 1) {
             fetch_x(1, xr);
-            write_x(1, xr);
+            write_x(xs1, xr);
         }
     } else {
-        stage_x(0);
-        if (a.gn > 1) stage_x(1);
+        stage_x(0, xs0);
+        if (a.gn > 1) stage_x(1, xs1);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -417,21 +419,28 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
         for (int k = 0; k < 8; ++k) { cf1[k] = (_Float16)c1; cf2[k] = (_Float16)c2; }
     };
     OpT B1, B2, A[MS];
-    if constexpr (FOLD) fold_coefficients(wd);
-    decode_step(wd, 0, B1, B2);
-    read_a(xsb[0], 0, A);
+    if constexpr (FOLD) fold_coefficients(wA);
+    decode_step(wA, 0, B1, B2);
+    read_a(xs0, 0, A);
 
-    for (int g = 0; g < a.gn; ++g) {
-        const unsigned char *xs = xsb[g % NBUF];
-        const bool more2 = g + 2 < a.gn;
-        // (the weight request is unconditional, on a clamped slab index: past the last slab the
-        // result is not used; the activation request comes last so that the wait below is exact)
+    // One slab: its weights wd and activations xs, the next slab's weights wn (requested here) and
+    // activations xn (requested a slab ago), and the buffer xf that slab g + 2 is requested into.
+    auto slab = [&](int g, const Weights &wd, Weights &wn, const unsigned char *xs, const unsigned char *xn, unsigned char *xf) {
+        // (The weight request is on a clamped slab index, past the last slab the result is not used; the
+        // activation request comes last and is unconditional -- past the last slab it lies outside the
+        // buffer and touches no memory -- so that the wait below and the compiler's own for the weights
+        // are exact: under a run-time condition it waits for everything.)
         load_weights(min(g + 1, a.gn - 1), wn);
         if constexpr (REGSTAGE) {
-            if (more2) fetch_x(g + 2, xr);
+            // (8-bit floats: unconditional too, unpacking a slab too much at the end costs less than the waits)
+            if (F8 || g + 2 < a.gn) fetch_x(min(g + 2, a.gn - 1), xr);
         } else {
-            if (more2) stage_x(g + 2);
+            stage_x(g + 2, xf);
         }
+        // The requests stay here; moved near their use they would not be in flight long enough.  (64
+        // tokens and fp16 operands: the compiler keeps them here by itself and schedules the slab better
+        // without the barrier: 7B block, 2048 tokens, W3/A16 1400 us with, 1365 without; int8 1048 / 1084.)
+        if constexpr (MS == 1 || !F16) __builtin_amdgcn_sched_barrier(0);
 
         float c1 = 0.f, c2 = 0.f;
         if constexpr (!FOLD) coefficients(wd, c1, c2);
@@ -453,15 +462,18 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 if constexpr (REGSTAGE) {
                     // (register path: slab g + 2 is written here; its buffer was last read before
                     // the previous slab's barrier, and it is first read after the next one)
-                    if (more2) write_x(g + 2, xr);
+                    if (F8 || g + 2 < a.gn) write_x(xf, xr);
                 } else {
-                    if (more2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
-                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
                 }
-                __syncthreads();
+                // (not __syncthreads(): it would wait for the activations just requested as well.  This
+                // wavefront's LDS operations are done when it arrives.)
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
                 if constexpr (FOLD) fold_coefficients(wn);
                 decode_step(wn, 0, B1, B2);
-                read_a(xsb[min(g + 1, a.gn - 1) % NBUF], 0, A);
+                read_a(xn, 0, A);
             }
 #pragma unroll
             for (int i = 0; i < MS; ++i) {
@@ -508,8 +520,17 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
                 }
             }
         }
-        wd = wn;
+    };
+    for (int g = 0;;) {
+        slab(g, wA, wB, xs0, xs1, xs2);
+        if (++g == a.gn) break;
+        slab(g, wB, wC, xs1, xs2, xs0);
+        if (++g == a.gn) break;
+        slab(g, wC, wA, xs2, xs0, xs1);
+        if (++g == a.gn) break;
     }
+    // no load may still be on its way into LDS when the workgroup ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // ---- store the tile (H6)
     const int n = n0 + ln;
@@ -529,7 +550,7 @@ __global__ __launch_bounds__(256, GOQ_GEMM_MINWAVES) void gemm_kernel(GemmBatch 
 
 // tiles of the problems, in launch order; returns the grid size (0: too large).  The problems with
 // the deepest rows go first: their tiles take longest, and the launch should end with short ones.
-int64_t lay_out(GemmBatch &b, int n)
+int64_t lay_out(GemmBatch &b, int n, int tm)
 {
     for (int i = 1; i < n; ++i)
         for (int j = i; j > 0 && b.p[j].gn > b.p[j - 1].gn; --j) {
@@ -541,32 +562,64 @@ int64_t lay_out(GemmBatch &b, int n)
     for (int i = 0; i < GOQ_MAX_BATCH; ++i) {
         if (i >= n) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; continue; }
         b.first[i] = (int)tiles;
-        tiles += (int64_t)((b.p[i].tokens + TM - 1) / TM) * ((b.p[i].out + TN - 1) / TN);
+        tiles += (int64_t)((b.p[i].tokens + tm - 1) / tm) * ((b.p[i].out + TN - 1) / TN);
         if (tiles > 0x3fffffff) return 0;
     }
     return tiles;
 }
 
-template <int BW, int ACT>
-int launch(hipStream_t st, GemmBatch &b, int n)
+template <int BW, int ACT, int MS>
+int launch_ms(hipStream_t st, GemmBatch &b, int n)
 {
-    const int64_t grid = lay_out(b, n);
+    const int64_t grid = lay_out(b, n, 32 * MS);
     if (!grid) return goq_set_error(GOQ_ESHAPE, "goq_gemm: too much work for one launch");
     bool part = false;
     for (int i = 0; i < n; ++i) part = part || b.p[i].partials;
     if (ACT != 0 && part)
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, (ACT != 0)>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, (ACT != 0), false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
     else
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm");
+}
+
+// Tokens per tile.  32-token tiles do a token's decode twice as often as 64-token ones, but a launch that
+// leaves CUs without a workgroup lasts as long as one workgroup walks its slabs, and that is where
+// half the work per slab counts.  Estimated time per slab in units of what one more resident 64-token
+// workgroup costs, from the workgroups per CU; fitted to 4096 x 4096, 11008 x 4096, 4096 x 11008 and the 7B, 70B
+// and ViT-B blocks at 40 .. 1024 tokens (us, 32 / 64 tokens per tile, W3/A16: 4096 x 4096, 64 tokens 27 / 40, 256
+// tokens 30 / 45, 512 tokens 44 / 48, 1024 tokens 79 / 71; 7B block, 64 tokens 84 / 115, 128 tokens 125 / 131).
+// bw = 4 spends more on decode, activations that pass through registers (staged) on unpacking.  Results do
+// not depend on the choice.
+bool narrow_tiles(int bw, bool staged, const GemmBatch &b, int n)
+{
+    int64_t w1 = 0, w2 = 0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t nt = (b.p[i].out + TN - 1) / TN;
+        w1 += (b.p[i].tokens + 31) / 32 * nt;
+        w2 += (b.p[i].tokens + 63) / 64 * nt;
+    }
+    if (w2 > 768) return false;
+    // beyond the first workgroup of a CU; up to two the fullest CU counts, then the average
+    auto more = [](int64_t w) { return w <= 512 ? (double)((w + 255) / 256 - 1) : (double)w / 256.0 - 1.0; };
+    const double narrow = staged ? 1.0 + 0.8 * more(w1) : bw == 3 ? 0.88 + 0.52 * more(w1) : 0.95 + 0.7 * more(w1);
+    return narrow <= 1.4 + more(w2);
+}
+
+template <int BW, int ACT>
+int launch(hipStream_t st, GemmBatch &b, int n)
+{
+    // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
+    if constexpr (ACT != 4 && ACT != 8)
+        if (narrow_tiles(BW, ACT >= 2, b, n)) return launch_ms<BW, ACT, 1>(st, b, n);
+    return launch_ms<BW, ACT, 2>(st, b, n);
 }
 
 template <int BW>
 int launch_folded(hipStream_t st, GemmBatch &b, int n)
 {
-    const int64_t grid = lay_out(b, n);
+    const int64_t grid = lay_out(b, n, 64);
     if (!grid) return goq_set_error(GOQ_ESHAPE, "goq_gemm_folded: too much work for one launch");
-    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true>), dim3((unsigned)grid), dim3(256), 0, st, b);
+    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm_folded");
 }
 
@@ -602,13 +655,13 @@ int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, 
 
 int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
 {
-    // Every problem goes to the kernel its own shape asks for, whatever it is batched with: a
+    // Every problem goes to the kernel its own token count asks for, whatever it is batched with: a
     // batch returns the bits of single calls.
     GemmBatch b;
     goq_gemm_desc few[GOQ_MAX_BATCH];
     int nfew = 0, nmany = 0;
     for (int i = 0; i < n; ++i) {
-        if (goq_gemm_small_takes(descs[i].tokens, descs[i].out)) few[nfew++] = descs[i];
+        if (goq_gemm_small_takes(descs[i].tokens)) few[nfew++] = descs[i];
         else b.p[nmany++] = make_args(descs[i]);
     }
     if (nfew) {
@@ -621,9 +674,9 @@ int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc 
     if (bw == 4 && act == GOQ_A16) return launch<4, 0>(st, b, n);
     if (bw == 4 && act == GOQ_A8) return launch<4, 2>(st, b, n);
     if (bw == 3 && act == GOQ_A4) return launch<3, 3>(st, b, n);
-    if (bw == 4 && act == GOQ_A4) return launch<4, 3>(st, b, n);
+    if (bw == 4 && act == GOQ_A4) return launch<4, 4>(st, b, n);
     if (bw == 3 && act == GOQ_A6) return launch<3, 5>(st, b, n);
     if (bw == 4 && act == GOQ_A6) return launch<4, 6>(st, b, n);
     if (bw == 3 && act == GOQ_A3) return launch<3, 7>(st, b, n);
-    return launch<4, 7>(st, b, n);
+    return launch<4, 8>(st, b, n);
 }

@@ -1,5 +1,5 @@
-// goq_gemm / goq_gemm_batch for a few tokens (batched decode, verification of draft tokens, short
-// prompts on narrow layers): Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
+// goq_gemm / goq_gemm_batch for up to 32 tokens (batched decode, verification of draft tokens):
+// Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
 //
 // What bounds it: the packed weights are read once for a handful of tokens, so the floor is the
 // weight stream; the work per weight that has to hide behind it is the decode on the vector ALU
@@ -7,7 +7,7 @@
 // many tokens (64 tokens x 128 outputs, one workgroup walks the whole depth) starts out / 128
 // workgroups: 32 for a 4096-wide layer, an eighth of the chip, one slab at a time.
 //
-// Split: a workgroup owns 16 RT output rows and a block of up to 32 tokens; its eight wavefronts take
+// Split: a workgroup owns 16 RT output rows and all tokens; its eight wavefronts take
 // the macro-blocks round-robin (wavefront w: slabs w, w + 8, ..), so a 4096 x 4096 layer is 256
 // workgroups with four slabs per wavefront, and the eight partial tiles meet in LDS in a fixed
 // order: no scratch memory, no atomics, one launch.  More rows per workgroup (RT) share one fetch of
@@ -54,7 +54,7 @@ struct SmallArgs {
     const float *sx;
     void *Y;
     int32_t *partials;
-    int tokens, out, gn, ytype, mblocks;
+    int tokens, out, gn, ytype;
 };
 // workgroups first[i] .. first[i + 1] - 1 own problem i (unused problems start at INT_MAX)
 struct SmallBatch {
@@ -135,10 +135,7 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
     for (int i = 1; i < GOQ_MAX_BATCH; ++i) pi += ((int)blockIdx.x >= batch.first[i]) ? 1 : 0;
     pi = __builtin_amdgcn_readfirstlane(pi);
     const SmallArgs &a = batch.p[pi];
-    // workgroups of a problem: token blocks of 16 MT tokens inside, row tiles outside
-    const int job = (int)blockIdx.x - batch.first[pi];
-    const int m0 = (job % a.mblocks) * (16 * MT);
-    const int rt0 = (job / a.mblocks) * RT;                         // first 16-row tile; RT divides 4: one row block
+    const int rt0 = ((int)blockIdx.x - batch.first[pi]) * RT;       // first 16-row tile; RT divides 4: one row block
     const int gn = a.gn;
 
     // rows: lane (c, q) reads chunk q of row 16 (rt0 + r) % 64 + c (rows past `out` lie in the padding)
@@ -147,8 +144,8 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
     // tokens: rows past the end repeat the last one, their results are not stored
     uint32_t xoff[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xoff[m] = (uint32_t)(min(16 * m + c, a.tokens - 1 - m0) * gn) * XROW + q * (XROW / 4);
-    gbytes xbase = (gbytes)a.X + (int64_t)m0 * gn * XROW;
+    for (int m = 0; m < MT; ++m) xoff[m] = (uint32_t)(min(16 * m + c, a.tokens - 1) * gn) * XROW + q * (XROW / 4);
+    gbytes xbase = (gbytes)a.X;
 
     auto load = [&](int g, SlabT &s) {
         gptr base = wbase + (int64_t)g * (CH * GOQ_ROWS * 4);
@@ -252,7 +249,7 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
                     for (int m = 0; m < MT; ++m)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const int token = m0 + 16 * m + 4 * q + v;
+                            const int token = 16 * m + 4 * q + v;
                             if (token < a.tokens && row < a.out)
                                 *reinterpret_cast<int2 *>(a.partials + (((int64_t)token * a.out + row) * gn + g) * 2) =
                                     make_int2((int)(P1[m][v] * UNIT), (int)(P2[m][v] * UNIT));
@@ -288,7 +285,7 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
     __syncthreads();
     for (int i = tid; i < MT * RT * 256; i += NT) {
         const int tile = i >> 8, e = i & 255;
-        const int token = m0 + 16 * (tile / RT) + (e >> 4);
+        const int token = 16 * (tile / RT) + (e >> 4);
         const int row = 16 * (rt0 + tile % RT) + (e & 15);
         float y = 0.f;
 #pragma unroll
@@ -331,22 +328,19 @@ int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, i
 
 }  // namespace
 
-// Up to 32 tokens always; beyond that as long as the tile kernel (64 tokens x 128 outputs per
-// workgroup, whole depth) would fill at most half of the 256 CUs.  Both sides measured (us, this kernel /
-// tile kernel, W3/A16): 4096 x 4096: 64 tokens 19 / 42, 128: 23 / 42, 256 (128 tiles): 44 / 43, 384: 63 / 44;
-// 11008 x 4096: 64 tokens (86 tiles) 31 / 42, 96 (172): 50 / 44; 8192 x 8192: 128 (128): 75 / 78, 192: 112 / 78;
-// 768 x 768: 512 tokens (48) 8 / 13; 3072 x 768: 192 (72): 12 / 13, 256 (96): 13 / 13.
-bool goq_gemm_small_takes(int64_t tokens, int64_t out)
-{
-    return tokens <= 32 || (tokens + 63) / 64 * ((out + 127) / 128) <= 128;
-}
+// Up to 32 tokens.  Its sums are not those of the tile kernel bit for bit, and a batch returns the bits of
+// single calls, so the line can depend on the problem alone: up to 32 tokens this kernel is the faster one
+// in a launch of its own and as part of a block (us, this kernel / tile kernel, W3/A16: 4096 x 4096, 32 tokens
+// 10 / 40; 7B block, 24 tokens 60 / 111).  With 64 tokens a 4096 x 4096 layer takes 19 / 27, but the block
+// 125 / 83: the weights are decoded once per 32 tokens here, and the tiles of a block fill the chip.
+bool goq_gemm_small_takes(int64_t tokens) { return tokens <= 32; }
 
 int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
 {
     int64_t tiles16 = 0, most = 0;
     bool part = false;
     for (int i = 0; i < n; ++i) {
-        tiles16 += (descs[i].out + 15) / 16 * ((descs[i].tokens + 31) / 32);
+        tiles16 += (descs[i].out + 15) / 16;
         most = descs[i].tokens > most ? descs[i].tokens : most;
         part = part || descs[i].partials;
     }
@@ -370,8 +364,7 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
         const goq_gemm_desc &d = descs[order[i]];
         b.first[i] = (int)grid;
         SmallArgs &a = b.p[i];
-        a.mblocks = (int)((d.tokens + 16 * mt - 1) / (16 * mt));
-        grid += (d.out + 16 * rt - 1) / (16 * rt) * a.mblocks;
+        grid += (d.out + 16 * rt - 1) / (16 * rt);               // out <= 2^24: the sum stays below 2^24
         a.packed = (const uint32_t *)d.packed;
         a.X = d.X;
         a.sx = d.sx;

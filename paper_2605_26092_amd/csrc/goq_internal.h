@@ -31,8 +31,8 @@ int goq_gemv_plan_launch(int n, const goq_gemv_desc *descs, int *kernel, int *wo
 int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, int64_t in, const void *packed,
                            const void *X, void *Y, int ytype);
 int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs);
-// few tokens or few outputs: kernel of its own (goq_gemm_small.hip)
-bool goq_gemm_small_takes(int64_t tokens, int64_t out);
+// few tokens: kernel of its own (goq_gemm_small.hip)
+bool goq_gemm_small_takes(int64_t tokens);
 int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs);
 int goq_launch_mfma_probe(hipStream_t st, int32_t *report);
 int goq_launch_read_probe(hipStream_t st, const void *buf, size_t bytes, uint32_t *sink);

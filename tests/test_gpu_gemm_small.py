@@ -1,4 +1,4 @@
-"""goq_gemm with a few tokens or outputs (the kernel that splits the depth over wavefronts): edges of its 16-token and 16-row tiles, wavefronts without
+"""goq_gemm with up to 32 tokens (the kernel that splits the depth over wavefronts) and just beyond: edges of its 16-token and 16-row tiles, wavefronts without
 a slab of their own, one and two row tiles per workgroup; against the oracle, and batch against single calls."""
 import numpy as np
 import pytest
@@ -38,7 +38,8 @@ def _run(goq, bw, act, q, tokens, xd, sxd, ytype, partials=False):
 @pytest.mark.parametrize("bw", [3, 4])
 @pytest.mark.parametrize("tokens,out,inn", [(1, 1, 128), (2, 17, 896), (15, 16, 1024), (16, 63, 1152), (17, 65, 2176),
                                             (31, 48, 256), (32, 8209, 384), (33, 100, 640),
-                                            (3, 32800, 128), (65, 257, 1024), (129, 100, 384), (257, 3328, 256), (257, 3329, 256)])
+                                            (3, 32800, 128), (65, 257, 1024), (129, 100, 384), (257, 2432, 256), (257, 2433, 256),
+                                            (257, 2433, 384), (1025, 1920, 128), (1025, 2049, 256)])
 def test_few_tokens_a16(oracle, bw, tokens, out, inn):
     """fp32 results within 2e-6 of the sum of absolute products (2^-24 per rounding, at most some
     ten of them on a path from a product to y), fp16 results one rounding (2^-11) more."""
@@ -94,7 +95,7 @@ def test_batch_of_few_and_many_tokens(act):
 
 @pytest.mark.parametrize("act", sorted(PACKERS))
 @pytest.mark.parametrize("bw", [3, 4])
-@pytest.mark.parametrize("tokens,out,inn", [(1089, 1025, 128), (700, 2050, 384)])
+@pytest.mark.parametrize("tokens,out,inn", [(1089, 1025, 128), (700, 2050, 384), (65, 130, 256), (1100, 9000, 128)])
 def test_many_tokens_integers(oracle, act, bw, tokens, out, inn):
     """The tile kernel with every integer type, ragged in both directions, one and three slabs: int32
     slab partials bit for bit, with the extremes of the type in the first tokens, y from them, and y
