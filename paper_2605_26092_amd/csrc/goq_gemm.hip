@@ -466,11 +466,18 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
                 } else {
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
                 }
-                // (not __syncthreads(): it would wait for the activations just requested as well.  This
-                // wavefront's LDS operations are done when it arrives.)
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
+                if constexpr (ACT == 1 && MS == 2) {
+                    // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
+                    // CU: nothing is gained by looking further ahead (ViT-B block, 12608 tokens: 313.5 us, 319
+                    // with the barrier below)
+                    __syncthreads();
+                } else {
+                    // (not __syncthreads(): it would wait for the activations just requested as well.
+                    // This wavefront's LDS operations are done when it arrives.)
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                }
                 if constexpr (FOLD) fold_coefficients(wn);
                 decode_step(wn, 0, B1, B2);
                 read_a(xn, 0, A);
