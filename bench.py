@@ -310,7 +310,7 @@ def gemv_kernel_name(bw, shapes):
     """The kernel the library launches for these layers in one goq_gemv_batch call (goq_gemv_plan)."""
     import paper_2605_26092_amd as goq
     kernel, _ = goq.gemv_plan(bw, goq.A16, [(out, inn) for _, out, inn in shapes])
-    return ("gemv_rows_kernel<%d,0>" if kernel == goq.GEMV_ROWS else "gemv_kernel<%d,0>") % bw
+    return ("gemm_small_kernel<%d,0,1,1>" if kernel == goq.GEMV_ROWS else "gemv_kernel<%d,0>") % bw
 
 
 def bench_gemm_block(args, shapes, bw, act, packed, tokens, steps=10, warmup=2, folded=False):

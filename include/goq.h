@@ -121,13 +121,14 @@ int goq_unpack(void *stream, int bw, int64_t out, int64_t in, const void *packed
  *   act = GOQ_A4 : x is packed int4 [in / 2 bytes], sx as for GOQ_A8.
  *   act = GOQ_A6 : x is packed int6 [3 in / 4 bytes], sx as for GOQ_A8.
  *   act = GOQ_A3 : x is packed int3 [3 in / 8 bytes], sx as for GOQ_A8.
- *   y is [out] of ytype.  The PoT codes are decoded to 8-bit floats (a power of two is exact in
- *   E5M2) and b2 is rebuilt from b1 by a byte permute and a sign flip; the two slab dot products
- *   run on the 8-bit-float matrix instruction against x written as block fixed point (24 bits
- *   below the largest exponent of each 32-activation block: exact for int8 x, and for fp16 x up
- *   to a truncation at 2^-24 of the block maximum), accumulate in fp32; coefficients are applied
- *   per slab in fp32.  Results are deterministic (no floating-point atomics).  x must be finite
- *   (Inf / NaN inputs give unspecified finite or non-finite outputs).
+ *   y is [out] of ytype.  Large launches stream (see goq_gemv_select): the PoT codes are decoded to
+ *   8-bit floats (a power of two is exact in E5M2) and b2 is rebuilt from b1 by a byte permute and a
+ *   sign flip; the two slab dot products run on the 8-bit-float matrix instruction against x written
+ *   as block fixed point (24 bits below the largest exponent of each 32-activation block: exact for
+ *   int8 x, and for fp16 x up to a truncation at 2^-24 of the block maximum) and accumulate in fp32.
+ *   Small launches hand x to the fp16 matrix instruction as it is.  Coefficients are applied per slab
+ *   in fp32.  Results are deterministic (no floating-point atomics).  x must be finite (Inf / NaN
+ *   inputs give unspecified finite or non-finite outputs).
  *   Row groups split over several workgroups are combined through one of the library's 8 static
  *   scratch regions on the device (2.1 MB each), one region per stream: launches on one stream run
  *   one after the other and may follow each other without limit.  A 9th stream takes over the
@@ -223,7 +224,8 @@ int goq_mfma_rate_probe(void *stream, int kind, int workgroups, int iters, float
  *   GOQ_GEMV_STREAM the streaming kernel: equal contiguous pieces of the launch's weight bytes
  *                   per workgroup, split row groups combined through the scratch area;
  *   GOQ_GEMV_ROWS   the row-owner kernel: one workgroup per 16 output rows over the whole depth,
- *                   partial sums combined in LDS (no scratch).
+ *                   partial sums combined in LDS (no scratch).  It is the kernel of goq_gemm with few
+ *                   tokens: x goes to the fp16 matrix instruction as it is (integers widened, exact).
  * Returns GOQ_EINVAL for any other value. */
 enum { GOQ_GEMV_AUTO = 0, GOQ_GEMV_STREAM = 1, GOQ_GEMV_ROWS = 2 };
 int goq_gemv_select(int kernel);

@@ -672,7 +672,7 @@ int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc 
         else b.p[nmany++] = make_args(descs[i]);
     }
     if (nfew) {
-        const int rc = goq_launch_gemm_small(st, bw, act, nfew, few);
+        const int rc = goq_launch_gemm_small(st, bw, act, nfew, few, 0, "goq_gemm");
         if (rc || !nmany) return rc;
     }
     n = nmany;

@@ -1,5 +1,5 @@
-// goq_gemm / goq_gemm_batch for up to 32 tokens (batched decode, verification of draft tokens):
-// Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
+// goq_gemm / goq_gemm_batch for up to 32 tokens (batched decode, verification of draft tokens), and
+// goq_gemv / goq_gemv_batch of small layers as one token: Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
 //
 // What bounds it: the packed weights are read once for a handful of tokens, so the floor is the
 // weight stream; the work per weight that has to hide behind it is the decode on the vector ALU
@@ -299,31 +299,31 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
 }
 
 template <int BW, int ACT, int MT, int RT>
-int launch(hipStream_t st, const SmallBatch &b, int grid, bool part)
+int launch(hipStream_t st, const SmallBatch &b, int grid, bool part, const char *what)
 {
     if (ACT != GOQ_A16 && part)
         hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, ACT != GOQ_A16>), dim3((unsigned)grid), dim3(NT), 0, st, b);
     else
         hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, false>), dim3((unsigned)grid), dim3(NT), 0, st, b);
-    return goq_check_launch("goq_gemm");
+    return goq_check_launch(what);
 }
 
 template <int BW, int ACT>
-int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part)
+int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part, const char *what)
 {
-    if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part) : launch<BW, ACT, 2, 2>(st, b, grid, part);
-    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part)
-         : rt == 2 ? launch<BW, ACT, 1, 2>(st, b, grid, part) : launch<BW, ACT, 1, 4>(st, b, grid, part);
+    if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part, what) : launch<BW, ACT, 2, 2>(st, b, grid, part, what);
+    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part, what)
+         : rt == 2 ? launch<BW, ACT, 1, 2>(st, b, grid, part, what) : launch<BW, ACT, 1, 4>(st, b, grid, part, what);
 }
 
 template <int BW>
-int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt, bool part)
+int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt, bool part, const char *what)
 {
-    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt, part);
-    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt, part);
-    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt, part);
-    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt, part);
-    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt, part);
+    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt, part, what);
+    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt, part, what);
+    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt, part, what);
+    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt, part, what);
+    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt, part, what);
 }
 
 }  // namespace
@@ -335,7 +335,7 @@ int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, i
 // 125 / 83: the weights are decoded once per 32 tokens here, and the tiles of a block fill the chip.
 bool goq_gemm_small_takes(int64_t tokens) { return tokens <= 32; }
 
-int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
+int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs, int row_tiles, const char *what)
 {
     int64_t tiles16 = 0, most = 0;
     bool part = false;
@@ -349,7 +349,7 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
     // tiles, RT = 1, 2, 4: 54.8, 37.9, 34.7 us; bw = 4 and two token tiles have no registers for four).
     // (Neither choice changes a result: a row's sums are the same in every tile.)
     const int mt = most > 16 ? 2 : 1;
-    const int rt = tiles16 <= 512 ? 1 : mt == 2 || bw == 4 || tiles16 <= 2048 ? 2 : 4;
+    const int rt = row_tiles ? row_tiles : tiles16 <= 512 ? 1 : mt == 2 || bw == 4 || tiles16 <= 2048 ? 2 : 4;
     // the problems with the deepest rows first: the launch should end with short ones
     int order[GOQ_MAX_BATCH];
     for (int i = 0; i < n; ++i) {
@@ -375,5 +375,5 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
         a.gn = (int)(d.in / GOQ_N);
         a.ytype = d.ytype;
     }
-    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt, part) : launch_act<4>(st, act, b, (int)grid, mt, rt, part);
+    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt, part, what) : launch_act<4>(st, act, b, (int)grid, mt, rt, part, what);
 }
