@@ -63,7 +63,7 @@ constexpr int ROW_MIRROR = 0x140;                                   // i -> 15 -
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_double(double v)
@@ -165,38 +165,45 @@ __global__ __launch_bounds__(64 * QW) void quantize_kernel(const uint4 *__restri
         // negative weight has the state 2^-(E-1) (midpoints 0.75 2^-(E-2) s_norm and, to zero,
         // 2^-E s_norm), a positive one ends at 2^-(E-2) (midpoint to zero 2^-(E-1) s_norm).
         const int T075 = (int)__float_as_uint(0.75f * sn);
-        const int Tzero = (int)__float_as_uint(sn) - ((E - 1) << 23);
+        const int Tzero = zero_block ? 0x7f000000 : (int)__float_as_uint(sn) - ((E - 1) << 23);
         double wv[8], x[8];
-        uint32_t code_lo = 0, code_hi = 0;
+        int codes_lo = 0, codes_hi = 0;                              // minus the codes, byte i
         double s1 = 0.0, n1 = 0.0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float wf = (float)__builtin_bit_cast(_Float16, (unsigned short)(pk[i >> 1] >> (16 * (i & 1))));
             wv[i] = (double)wf;
             const uint32_t bits = __float_as_uint(wf);
-            const int neg = (int)(bits >> 31);                       // 1 for a negative weight
+            const int neg = (int)bits >> 31;                         // -1 for a negative weight
             // Number of thresholds |w| does not exceed.  |w| (11 significant bits) and 0.75 s_norm
             // (13) are exact in fp32 and order like their bits, and a factor 2^k is k units of the
             // exponent field: |w| 2^k <= 0.75 s_norm  <=>  A + (k << 23) <= T.  That holds for
             // k = 0 .. (T - A) >> 23 when T >= A and for no k otherwise; a negative weight has E - 1
             // such thresholds, a positive one E - 2, and below the midpoint to zero it is zero.
+            // ne is minus that number (-((T - A) >> 23) - 1 = (A - T - 1) >> 23): the state's exponent,
+            // which goes into the exponent field and the code by shift-and-add.
             const int A = (int)(bits & 0x7fffffffu);
-            const int e = min(max(((T075 - A) >> 23) + 1, 0), E - 2 + neg);
-            const bool is_zero = A <= Tzero - (neg << 23) || zero_block;
-            const uint32_t code = is_zero ? (uint32_t)(E - 1) : (((uint32_t)neg << (BW - 1)) | (uint32_t)e);
-            if (i < 4) code_lo |= code << (8 * i);
-            else code_hi |= code << (8 * (i - 4));
-            // b1_i = (-1)^neg 2^-e assembled from sign and exponent field (low word zero)
-            const uint32_t xhi = is_zero ? 0u : ((uint32_t)((1023 - e) << 20) | (bits & 0x80000000u));
-            x[i] = __hiloint2double((int)xhi, 0);
+            int ne;
+            asm("v_med3_i32 %0, %1, 0, %2" : "=v"(ne) : "v"((A - T075 - 1) >> 23), "v"(neg - (E - 2)));
+            const bool is_zero = A <= Tzero + (neg << 23);
+            int nc = is_zero ? 1 - E : (neg << (BW - 1)) + ne;       // minus the code
+            asm("" : "+v"(nc));                                      // keeps the shift below out of the selection
+            if (i < 4) codes_lo += nc << (8 * i);
+            else codes_hi += nc << (8 * (i - 4));
+            // b1_i = +-2^ne assembled from sign and exponent field (low word zero); a zero keeps the
+            // weight's sign, so that x_i w_j and x_j w_i share a sign for every pair
+            const int mag = is_zero ? 0 : (ne << 20) + (1023 << 20);
+            x[i] = __hiloint2double((int)((uint32_t)mag | (bits & 0x80000000u)), 0);
             s1 = fma(wv[i], x[i], s1);                              // a weight and its state share the sign
             n1 = fma(x[i], x[i], n1);
         }
+        const uint32_t code_lo = (uint32_t)-codes_lo, code_hi = (uint32_t)-codes_hi;
         if (valid) codes[mb * 16 + m] = make_uint2(code_lo, code_hi);
         const double S1 = row_sum(s1);
         const double N1 = (double)row_sum((float)n1);    // > 0 unless the block is zero: the largest weight maps to +-1
 
-        // the four patterns: exact cross terms, scores and sign bits
+        // the four patterns: exact cross terms, scores and sign bits.  u is never -0 (the difference of
+        // two equal numbers is +0, of two zeros of one sign too), so its sign bit says u < 0.
         double U[4];
         uint32_t sg[4];
 #pragma unroll
@@ -208,7 +215,7 @@ __global__ __launch_bounds__(64 * QW) void quantize_kernel(const uint4 *__restri
                 const int i = pair_lower(s, p), j = i ^ s;
                 const double u = fma(x[i], wv[j], -(x[j] * wv[i]));
                 sum += fabs(u);
-                bit = bit + bit + (u < 0.0 ? 1u : 0u);
+                bit = __builtin_amdgcn_alignbit(bit, (uint32_t)__double2hiint(u), 31);    // 2 bit + sign of u
             }
             U[s - 1] = sum;
             sg[s - 1] = bit;

@@ -99,3 +99,17 @@ def test_quantize_close_scores(oracle, bw):
             np.round(r.normal(0, 2, 1024)) / 8]
     w = np.stack(rows).astype(np.float16)
     _same(_run(goq, bw, w), oracle.quantize_geo(bw, w, threads=1))
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+def test_quantize_signs_of_zero(oracle, bw):
+    """Zeros and weights below the smallest state, of either sign, among generic ones: their states are
+    zero, so cross terms of two zeros and of equal products occur in patterns whose scores differ."""
+    import paper_2605_26092_amd as goq
+    r = np.random.default_rng(23)
+    kind = r.random((40, 1024))
+    w = r.normal(0, 1, kind.shape)
+    sign = np.where(r.random(kind.shape) < 0.5, -1.0, 1.0)
+    w = np.where(kind < 0.4, sign * 0.0, np.where(kind < 0.6, sign * 2.0 ** r.integers(-24, -8, kind.shape), w))
+    w = w.astype(np.float16)
+    _same(_run(goq, bw, w), oracle.quantize_geo(bw, w, threads=4))
