@@ -7,7 +7,7 @@
 // lane-local and lives in registers; what belongs to the macro-block -- the norm s_norm and the
 // sums of Eq. 1 and Eq. 2 -- is reduced across the 16 lanes of a row with data-parallel-primitive
 // (DPP) moves, which stay inside a row by construction.  No LDS, no barriers.  It is bound by
-// vector-ALU issue (about 440 instructions per micro-block), so the arithmetic is laid out around what is
+// vector-ALU issue (391 instructions per micro-block, 76 % of the SIMD cycles), so the arithmetic is laid out around what is
 // exact and need not be computed twice:
 //
 //   products    A lattice state is a signed power of two, so every product with a state is exact
@@ -41,7 +41,9 @@
 //
 // The results are a pure function of the weights and equal those of a sequential fp64 evaluation
 // of the same formulas bit for bit under the condition on the sums stated above.
-// Measured, 4096 x 11008, bw = 3: 77 us (residuals and cross terms of every micro-block in fp64: 98 us).
+// Measured, 11008 x 4096, bw = 3: 64 us (with states and signs by compare and select 77 us, with residuals and
+// cross terms of every micro-block in fp64 98 us).  No gain: the next group's weights requested one iteration
+// ahead (65 us), a finer or coarser grid (64 - 66 us); six wavefronts per SIMD spill (122 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "goq_layout.h"
