@@ -224,8 +224,9 @@ int goq_mfma_rate_probe(void *stream, int kind, int workgroups, int iters, float
  *   GOQ_GEMV_STREAM the streaming kernel: equal contiguous pieces of the launch's weight bytes
  *                   per workgroup, split row groups combined through the scratch area;
  *   GOQ_GEMV_ROWS   the row-owner kernel: one workgroup per 16 output rows over the whole depth,
- *                   partial sums combined in LDS (no scratch).  It is the kernel of goq_gemm with few
- *                   tokens: x goes to the fp16 matrix instruction as it is (integers widened, exact).
+ *                   partial sums combined in LDS (no scratch).  fp16 and int8 activations: the kernel
+ *                   of goq_gemm with few tokens, x goes to the fp16 matrix instruction as it is
+ *                   (int8 widened, exact); packed int6, int4, int3: x as digits, as in the streaming kernel.
  * Returns GOQ_EINVAL for any other value. */
 enum { GOQ_GEMV_AUTO = 0, GOQ_GEMV_STREAM = 1, GOQ_GEMV_ROWS = 2 };
 int goq_gemv_select(int kernel);

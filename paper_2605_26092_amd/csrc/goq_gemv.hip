@@ -30,7 +30,8 @@
 // per row and slab, after the slab's dot products.
 //
 // (Launches of a few hundred 16-row tiles at most -- single layers -- go to the kernel of few-token GEMMs,
-// goq_gemm_small.hip: one workgroup per 16 rows over the whole depth, no combine.)
+// goq_gemm_small.hip, or, with packed activations, to gemv_rows_kernel of this file: one workgroup per 16 rows
+// over the whole depth, no combine.)
 //
 // Where a piece boundary falls inside a row group, each wavefront publishes the partial sums of
 // its 64 rows to a workspace and the LAST wavefront to arrive (an atomic counter per boundary
@@ -107,7 +108,8 @@ struct GemvProblem {
     int rbn;         // row blocks
     int rgroups;     // row groups
     int begin;       // first unit of this problem in the linear unit sequence
-    int pad[2];
+    int bb;          // first 16-row block of this problem in the grid of gemv_rows_kernel
+    int pad;
 };
 
 struct GemvArgs {
@@ -821,6 +823,123 @@ __global__ __launch_bounds__(256) void workspace_init_kernel(Region *ws)
 constexpr int ROWS_MAX_TILES = 512;      // automatic choice: largest grid ...
 constexpr int ROWS_MAX_SLICES = 24576;   // ... and most (tile, macro-block) slices per launch
 
+// Packed activations (int6, int4, int3) keep a kernel of that split on the digits, gemv_rows_kernel: in the
+// few-token kernel all 16 token lanes of an operand unpack the one token there is, here a thread unpacks a run of 8
+// once per workgroup (us, digits / few-token kernel: W3/A6 8192 x 4096 7.6 / 9.4, 4096 x 4096 5.7 / 6.3, 1024 x 29952
+// 22.9 / 28.1; W3/A4 8192 x 4096 7.5 / 8.2; W4/A3 2048 x 16384 17.5 / 18.5; only W4/A4 gains at some depths, 4096 x
+// 11008 14.6 / 12.2, and loses at full grids, three layers of 444 tiles 8.9 / 9.4).
+constexpr int RW = NT / 16;              // macro-blocks staged per window: one run per thread
+constexpr int RS = RW / WAVES;           // slices per wavefront and window
+struct Slice {
+    uint4 q;
+    uint32_t md;
+};
+
+template <int BW, int ACT>
+__global__ __launch_bounds__(NT)
+void gemv_rows_kernel(GemvArgs a)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char xtab[XZ + RW * XG];
+    __shared__ __attribute__((aligned(16))) unsigned char stab[RW * 4];
+    __shared__ __attribute__((aligned(16))) unsigned char vtab[64 * VS];
+    __shared__ __attribute__((aligned(16))) unsigned char cwx[WAVES * 256];
+    __shared__ float red[NT];
+    constexpr int CH = (BW == 3) ? 4 : 5;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, q = lane >> 4;
+
+    int pi = 0;
+#pragma unroll
+    for (int i = 1; i < GOQ_MAX_BATCH; ++i) pi += ((int)blockIdx.x >= a.p[i].bb) ? 1 : 0;   // unused: INT_MAX
+    pi = __builtin_amdgcn_readfirstlane(pi);
+    const GemvProblem &P = a.p[pi];
+    const int lb = (int)blockIdx.x - P.bb;
+    const int R = lb >> 2, j = lb & 3;
+    const int gn = P.gn;
+
+    typedef const __attribute__((address_space(1))) uint32_t *gptr;
+    typedef const __attribute__((address_space(1))) u32x4 *gptr4;
+    gptr rowbase = (gptr)P.packed + (int64_t)R * gn * (CH * GOQ_ROWS * 4) + (16 * j + c) * 4;
+    // slices of macro-blocks w0 + wave + WAVES i (past the end: the last one again, not used)
+    auto request = [&](int w0, Slice (&s)[RS]) {
+#pragma unroll
+        for (int i = 0; i < RS; ++i) {
+            const int g = min(w0 + wave + WAVES * i, gn - 1);
+            gptr base = rowbase + (int64_t)g * (CH * GOQ_ROWS * 4);
+            const u32x4 v = __builtin_nontemporal_load((gptr4)(base + q * (GOQ_ROWS * 4)));
+            s[i].q = make_uint4(v.x, v.y, v.z, v.w);
+            s[i].md = 0u;
+            if constexpr (BW == 4) s[i].md = __builtin_nontemporal_load(base + 4 * (GOQ_ROWS * 4) + q);
+        }
+    };
+    Slice cur[RS], nxt[RS];
+    request(0, cur);
+
+    for (int t = tid; t < 64 * VC; t += NT) *reinterpret_cast<uint4 *>(vtab + t * 16) = goq_exchange_entry<0x80u>(t / VC);
+    if (tid < XZ / 4) reinterpret_cast<uint32_t *>(xtab)[tid] = 0u;
+
+    // A operand of this lane, as in the kernel above
+    const bool arow_live = (c & 3) < 2;
+    const int digit = 2 * (c >> 2) + (c & 1);
+    const uint32_t abase = arow_live ? (uint32_t)(XZ + q * 256 + digit * 32) : 0u;
+    const uint32_t amask = arow_live ? ~0u : 0u;
+    const uint32_t vt_lane = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)vtab + (lane % VC) * 16;
+    unsigned char *cw = cwx + wave * 256;
+
+    float acc = 0.f;
+    for (int w0 = 0; w0 < gn; w0 += RW) {
+        if (w0) __syncthreads();                               // everyone is done with the old window
+        if (tid < min(RW, gn - w0) * 16)
+            stage_run<ACT>(xtab + XZ + (tid >> 4) * XG, stab + (tid >> 4) * 4, P.x, w0 + (tid >> 4), tid & 15);
+        __syncthreads();
+        if (w0 + RW < gn) request(w0 + RW, nxt);
+#pragma unroll
+        for (int i = 0; i < RS; ++i)
+            cw[i * 64 + c * 4 + coefficient_byte_position<BW>(q)] = (unsigned char)coefficient_byte<BW>(cur[i].q, cur[i].md);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < RS; ++i) {
+            const int slot = wave + WAVES * i;
+            if (w0 + slot < gn) {
+                const v8i A = *reinterpret_cast<const v8i *>(xtab + abase + ((uint32_t)(slot * XG) & amask));
+                const uint32_t sc = *reinterpret_cast<const uint32_t *>(stab + slot * 4);
+                const int sa = (int)((sc >> (8 * q)) & 0xFFu) - 3 * digit;
+                v4f D1, D2;
+                slice_products<BW>(cur[i].q, cur[i].md, vt_lane, A, sa, D1, D2);
+                acc = rescale(*reinterpret_cast<const uint32_t *>(cw + i * 64 + c * 4), D1, D2, acc);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RS; ++i) cur[i] = nxt[i];
+    }
+    // H6: the 32 partial sums of row c, in wavefront and lane-group order
+    red[tid] = acc;
+    __syncthreads();
+    if (tid < 16) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < NT / 16; ++i) s += red[i * 16 + tid];
+        if constexpr (ACT != 0) s *= ((const __attribute__((address_space(1))) float *)P.sx)[0];
+        const int row = R * GOQ_ROWS + 16 * j + tid;
+        if (row < P.out) {
+            // (global-memory pointers, said explicitly: a generic store may hit LDS as far as the
+            // compiler knows, and every later LDS read would wait for it)
+            if (P.ytype == GOQ_F32) ((__attribute__((address_space(1))) float *)P.y)[row] = s;
+            else ((__attribute__((address_space(1))) unsigned short *)P.y)[row] = __half_as_ushort(__float2half(s));
+        }
+    }
+}
+
+template <int BW, int ACT>
+int launch_rows(hipStream_t st, const GemvArgs &a, int nblocks)
+{
+    hipLaunchKernelGGL((gemv_rows_kernel<BW, ACT>), dim3(nblocks), dim3(NT), 0, st, a);
+    return goq_check_launch("goq_gemv");
+}
+
 template <int BW, int ACT>
 int launch(hipStream_t st, const GemvArgs &a, int nwg)
 {
@@ -922,7 +1041,8 @@ void fill_problem(GemvProblem &P, const goq_gemv_desc &d)
     P.rbn = (int)goq_row_blocks(d.out);
     P.rgroups = (P.rbn + WAVES - 1) / WAVES;
     P.begin = 0;
-    P.pad[0] = P.pad[1] = 0;
+    P.bb = 0;
+    P.pad = 0;
 }
 
 }  // namespace
@@ -964,8 +1084,8 @@ int goq_launch_gemv(hipStream_t st, int bw, int act, int n, const goq_gemv_desc 
     int kernel = 0, workgroups = 0;
     int rc = goq_gemv_plan_launch(n, descs, &kernel, &workgroups);
     if (rc) return rc;
-    // Small launches: no workspace.
-    if (kernel == GOQ_GEMV_ROWS) {
+    // Small launches: no workspace.  Packed activations: gemv_rows_kernel, below.
+    if (kernel == GOQ_GEMV_ROWS && (act == GOQ_A16 || act == GOQ_A8)) {
         goq_gemm_desc rows[GOQ_MAX_BATCH];
         for (int i = 0; i < n; ++i) {
             const goq_gemv_desc &d = descs[i];
@@ -976,16 +1096,26 @@ int goq_launch_gemv(hipStream_t st, int bw, int act, int n, const goq_gemv_desc 
     GemvArgs a;
     a.n = n;
     a.scratch = nullptr;
-    int64_t total = 0;
+    int64_t total = 0, blocks = 0;
     for (int i = 0; i < n; ++i) {
         GemvProblem &P = a.p[i];
         fill_problem(P, descs[i]);
         P.begin = (int)total;
         total += (int64_t)P.rgroups * P.gn;
+        P.bb = (int)blocks;
+        blocks += (descs[i].out + 15) / 16;
     }
-    for (int i = n; i < GOQ_MAX_BATCH; ++i) { a.p[i] = a.p[0]; a.p[i].begin = 0x7fffffff; }
+    for (int i = n; i < GOQ_MAX_BATCH; ++i) { a.p[i] = a.p[0]; a.p[i].begin = 0x7fffffff; a.p[i].bb = 0x7fffffff; }
     a.total = (int)total;
     a.pq = a.pr = 0;
+    if (kernel == GOQ_GEMV_ROWS) {
+        if (bw == 3 && act == GOQ_A6) return launch_rows<3, 3>(st, a, workgroups);
+        if (bw == 4 && act == GOQ_A6) return launch_rows<4, 3>(st, a, workgroups);
+        if (bw == 3 && act == GOQ_A4) return launch_rows<3, 2>(st, a, workgroups);
+        if (bw == 4 && act == GOQ_A4) return launch_rows<4, 2>(st, a, workgroups);
+        if (bw == 3) return launch_rows<3, 4>(st, a, workgroups);
+        return launch_rows<4, 4>(st, a, workgroups);
+    }
     a.scratch = reinterpret_cast<Region *>(workspace);
     if (!a.scratch) {
         a.scratch = region_of_stream(st, &rc);
