@@ -466,10 +466,10 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
                 } else {
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
                 }
-                if constexpr (ACT == 1 && MS == 2) {
+                if constexpr ((ACT == 1 || ACT == 3 || ACT == 5 || ACT == 7) && MS == 2) {
                     // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
                     // CU: nothing is gained by looking further ahead (ViT-B block, 12608 tokens: 313.5 us, 319
-                    // with the barrier below)
+                    // with the barrier below; int4 on its way to int8, 4096 x 11008, 300 tokens: 102.4 / 104.1, int6 110.5 / 112.5)
                     __syncthreads();
                 } else {
                     // (not __syncthreads(): it would wait for the activations just requested as well.
@@ -595,8 +595,11 @@ int launch_ms(hipStream_t st, GemmBatch &b, int n)
 // workgroup costs, from the workgroups per CU; fitted to 4096 x 4096, 11008 x 4096, 4096 x 11008 and the 7B, 70B
 // and ViT-B blocks at 40 .. 1024 tokens (us, 32 / 64 tokens per tile, W3/A16: 4096 x 4096, 64 tokens 27 / 40, 256
 // tokens 30 / 45, 512 tokens 44 / 48, 1024 tokens 79 / 71; 7B block, 64 tokens 84 / 115, 128 tokens 125 / 131).
-// bw = 4 spends more on decode, activations that pass through registers (staged) on unpacking.  Results do
-// not depend on the choice.
+// bw = 4 spends more on decode, activations that pass through registers (staged) on unpacking.  A single
+// layer whose 64-token tiles give every CU one and some a second has equally long tiles, nothing that short ones
+// could fill, and takes the 64-token tiles earlier (32 / 64 tokens per tile: 2304 x 768, 1576 tokens, W3/A16, 450
+// tiles of 64: 18.9 / 17.2; W4/A16 8192 x 4096, 300 tokens, 320 tiles: 66.0 / 58.9, 4096 x 4096, 600 tokens 65.0 /
+// 59.2; at 320 tiles W3 is faster with short ones).  Results do not depend on the choice.
 bool narrow_tiles(int bw, bool staged, const GemmBatch &b, int n)
 {
     int64_t w1 = 0, w2 = 0;
@@ -605,7 +608,7 @@ bool narrow_tiles(int bw, bool staged, const GemmBatch &b, int n)
         w1 += (b.p[i].tokens + 31) / 32 * nt;
         w2 += (b.p[i].tokens + 63) / 64 * nt;
     }
-    if (w2 > 768) return false;
+    if (w2 > (n > 1 ? 768 : bw == 3 ? 384 : 256)) return false;
     // beyond the first workgroup of a CU; up to two the fullest CU counts, then the average
     auto more = [](int64_t w) { return w <= 512 ? (double)((w + 255) / 256 - 1) : (double)w / 256.0 - 1.0; };
     const double narrow = staged ? 1.0 + 0.8 * more(w1) : bw == 3 ? 0.88 + 0.52 * more(w1) : 0.95 + 0.7 * more(w1);
