@@ -56,6 +56,7 @@
 #include "goq_decode.h"
 #include "goq_activations.h"
 #include "goq_internal.h"
+#include "goq_request.h"
 
 namespace {
 
@@ -231,26 +232,29 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     // instruction fills 64 consecutive 16-byte LDS slots, one per lane, from per-lane addresses.
     // Slot (row, cs) holds k-piece cs ^ f(row): the XOR swizzle makes the 16 rows a quarter of an
     // MFMA A operand read touches fall into 16 different bank groups (row stride 256 / 128 bytes).
-    // The swizzle repeats over the pieces of a thread, so one byte offset serves them all: a request
-    // is that offset plus a uniform one.
+    // A slab is a window of its own (goq_request.h); the offsets in it are the same for every slab and the whole of
+    // them is per-lane, which the range check counts.
     constexpr int PIECES = TM * GOQ_N * XB / 16;
     constexpr int PER_ROW = GOQ_N * XB / 16;
     constexpr int NP = PIECES / 256;
     auto swz = [](int row) { return F16 ? (row & 15) : ((row >> 1) & 7); };
-    const int row0 = tid / PER_ROW;                   // piece i of a thread: token row0 + i 256 / PER_ROW
     const uint32_t xline = (uint32_t)a.in * XB;
-    const uint32_t xoff = (uint32_t)row0 * xline + (uint32_t)((tid % PER_ROW) ^ swz(row0)) * 16u;
-    const unsigned char *xtile = reinterpret_cast<const unsigned char *>(a.X) + (int64_t)m0 * a.in * XB;
-    // (tokens past the end are out of the buffer's range and read as zeros)
-    const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<unsigned char *>(xtile), 0, (int)(uint32_t)min((uint64_t)(a.tokens - m0) * xline, (uint64_t)0xffffffffu), 0x00020000);
+    uint32_t xoff[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int row = i * (256 / PER_ROW) + tid / PER_ROW;
+        xoff[i] = goq_piece_offset(row, (tid % PER_ROW) ^ swz(row), xline);
+    }
+    const uint64_t xtile = (uint64_t)(uintptr_t)a.X + (uint64_t)m0 * xline;
+    uint32_t xbytes = goq_tile_bytes(a.tokens - m0, TM, xline);
+    asm("" : "+s"(xbytes));                           // (uniform: a descriptor in vector registers would be read lane by lane)
     auto stage_x = [&](int g, unsigned char *buf) {          // exactly NP vector-memory instructions
-        const uint32_t at = g < a.gn ? (uint32_t)(g * GOQ_N * XB) : 0xC0000000u;
+        const GoqWindow win = goq_slab_window(xbytes, g, a.gn, GOQ_N * XB);
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(xtile + win.begin), 0, (int)win.records, 0x00020000);
 #pragma unroll
         for (int i = 0; i < NP; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                xrsrc, (__attribute__((address_space(3))) void *)(buf + (i * 256 + wave * 64) * 16), 16, (int)xoff,
-                (int)((uint32_t)(i * (256 / PER_ROW)) * xline + at), 0, 0);
+                rsrc, (__attribute__((address_space(3))) void *)(buf + (i * 256 + wave * 64) * 16), 16, (int)xoff[i], 0, 0, 0);
     };
     // Register staging (ACT >= 2): integer activations pass through registers and are unpacked /
     // widened on their way into LDS.  A thread moves NPS 16-byte pieces per slab; a piece holds
