@@ -559,9 +559,17 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         }
 }
 
-// tiles of the problems, in launch order; returns the grid size (0: too large).  The problems with
-// the deepest rows go first: their tiles take longest, and the launch should end with short ones.
-int64_t lay_out(GemmBatch &b, int n, int tm)
+// Too many tiles for one grid?  (64-token tiles: 32-token ones are for a few hundred.)
+bool too_large(const GemmBatch &b, int n)
+{
+    int64_t tiles = 0;                                                        // below 8 * 2^35
+    for (int i = 0; i < n; ++i) tiles += (int64_t)((b.p[i].tokens + 63) / 64) * ((b.p[i].out + TN - 1) / TN);
+    return tiles > 0x3fffffff;
+}
+
+// tiles of the problems, in launch order; returns the grid size.  The problems with the deepest rows go
+// first: their tiles take longest, and the launch should end with short ones.
+int lay_out(GemmBatch &b, int n, int tm)
 {
     for (int i = 1; i < n; ++i)
         for (int j = i; j > 0 && b.p[j].gn > b.p[j - 1].gn; --j) {
@@ -569,12 +577,11 @@ int64_t lay_out(GemmBatch &b, int n, int tm)
             b.p[j] = b.p[j - 1];
             b.p[j - 1] = t;
         }
-    int64_t tiles = 0;
+    int tiles = 0;
     for (int i = 0; i < GOQ_MAX_BATCH; ++i) {
         if (i >= n) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; continue; }
-        b.first[i] = (int)tiles;
-        tiles += (int64_t)((b.p[i].tokens + tm - 1) / tm) * ((b.p[i].out + TN - 1) / TN);
-        if (tiles > 0x3fffffff) return 0;
+        b.first[i] = tiles;
+        tiles += ((b.p[i].tokens + tm - 1) / tm) * ((b.p[i].out + TN - 1) / TN);
     }
     return tiles;
 }
@@ -582,8 +589,7 @@ int64_t lay_out(GemmBatch &b, int n, int tm)
 template <int BW, int ACT, int MS>
 int launch_ms(hipStream_t st, GemmBatch &b, int n)
 {
-    const int64_t grid = lay_out(b, n, 32 * MS);
-    if (!grid) return goq_set_error(GOQ_ESHAPE, "goq_gemm: too much work for one launch");
+    const int grid = lay_out(b, n, 32 * MS);
     bool part = false;
     for (int i = 0; i < n; ++i) part = part || b.p[i].partials;
     if (ACT != 0 && part)
@@ -631,8 +637,7 @@ int launch(hipStream_t st, GemmBatch &b, int n)
 template <int BW>
 int launch_folded(hipStream_t st, GemmBatch &b, int n)
 {
-    const int64_t grid = lay_out(b, n, 64);
-    if (!grid) return goq_set_error(GOQ_ESHAPE, "goq_gemm_folded: too much work for one launch");
+    const int grid = lay_out(b, n, 64);
     hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm_folded");
 }
@@ -664,6 +669,7 @@ int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, 
     d.ytype = ytype; d.partials = nullptr;
     GemmBatch b;
     b.p[0] = make_args(d);
+    if (too_large(b, 1)) return goq_set_error(GOQ_ESHAPE, "goq_gemm_folded: too much work for one launch");
     return bw == 3 ? launch_folded<3>(st, b, 1) : launch_folded<4>(st, b, 1);
 }
 
@@ -678,6 +684,8 @@ int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc 
         if (goq_gemm_small_takes(descs[i].tokens)) few[nfew++] = descs[i];
         else b.p[nmany++] = make_args(descs[i]);
     }
+    // before the first launch: a refused batch has done nothing
+    if (too_large(b, nmany)) return goq_set_error(GOQ_ESHAPE, "goq_gemm: too much work for one launch");
     if (nfew) {
         const int rc = goq_launch_gemm_small(st, bw, act, nfew, few, 0, "goq_gemm");
         if (rc || !nmany) return rc;

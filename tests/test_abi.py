@@ -72,6 +72,19 @@ def test_host_side_argument_errors(goq):
         goq.packed_bytes(3, 64, 64)
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="relies on the missing device: made-up pointers")
+def test_batch_with_too_much_work_is_refused_whole(goq):
+    """A batch is two launches where it mixes problems of up to 32 tokens with larger ones; one that is
+    refused for its size starts neither (a launch here would report the missing device instead)."""
+    from paper_2605_26092_amd import binding as b
+    fake = 0x10000
+    large = (1 << 24, 1 << 24, 128, fake, fake, None, fake, goq.F32)      # 2^35 tiles
+    few = (4, 64, 128, fake, fake, None, fake, goq.F32)
+    for probs in ([large], [few, large], [large, few]):
+        assert goq.lib().goq_gemm_batch(None, 3, goq.A16, len(probs), b.make_gemm_descs(probs)) == b.ESHAPE, probs
+        assert "too much work" in goq.last_error()
+
+
 def test_gemv_plan_follows_the_documented_choice(goq):
     """Host logic of the automatic kernel choice (include/goq.h): at most 512 tiles of 16 rows and
     24576 (tile, macro-block) pairs -> row-owner kernel, one workgroup per tile; else the streaming
