@@ -116,3 +116,60 @@ def test_many_tokens_integers(oracle, act, bw, tokens, out, inn):
     scale = (np.abs(x[rows].astype(np.float64)) * sx[rows][:, None]) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
     assert np.max(np.abs(Y.cpu().numpy()[rows].astype(np.float64) - ref) / scale) <= 2e-6
     assert gu.torch_cuda().equal(_run(goq, bw, act, q, tokens, xd, gu.to_dev(sx), goq.F32)[0], Y)
+
+
+@pytest.mark.parametrize("act", sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens", [30, 90])
+def test_slabs_of_large_and_tiny_products(oracle, act, bw, tokens):
+    """Slab sums at the full width the exactness claims name (W4: products up to 8, 32 or 128 beside odd
+    multiples of 2^-7; running sums to 2^10, 2^12 or 2^14): the largest state against the most
+    negative activation on one part of a slab, the smallest state against odd activations on the rest, in either
+    order, within a group of eight and across groups, and large products that cancel.  int32 partials bit for bit."""
+    import paper_2605_26092_amd as goq
+    print("large and tiny products %s bw=%d tokens=%d" % (act, bw, tokens), flush=True)
+    inn, k = 384, np.arange(128)
+    parts = [k < 64, k >= 64, k < 120, k >= 8, k < 96, k >= 32, k % 8 == 0, k % 8 != 0, k % 8 != 7, k != 127, k != 0, k % 2 == 0, k % 32 < 16, k >= 0, k < 0]
+    r = np.random.default_rng(5)
+    half = 1 << (bw - 1)
+    largest = [np.zeros(128, int), np.full(128, half), np.where(k % 2, half, 0), np.where(k < 64, 0, half)]   # +1, -1, cancelling
+    tiny = [np.full(128, 2 * half - 1), np.where(k % 2, 2 * half - 1, half - 2), r.choice([half - 2, 2 * half - 2, 2 * half - 1], 128)]
+    rows = [np.where(p, a, t) for p in parts for a in largest for t in tiny]
+    q = goq_inputs.canonical_random(bw, len(rows), inn, config_id=65, tensor_id=tokens)
+    q["codes"][:] = np.stack([np.concatenate([row, np.roll(row, 8), row[::-1]]) for row in rows])
+    bits, packer = PACKERS[act] or (8, None)
+    top = 1 << (bits - 1)
+    x = np.empty((tokens, inn), np.int8)
+    for t in range(tokens):
+        p = np.concatenate([parts[t % len(parts)], np.roll(parts[t % len(parts)], 8), parts[t % len(parts)][::-1]])
+        odd = 2 * r.integers(-(top // 2), top // 2, inn) + 1
+        x[t] = np.where(p, -top if t % 2 else top - 1, odd if t % 3 else top - 1)
+    sx = r.uniform(0.01, 0.02, tokens).astype(np.float32)
+    _, pref = oracle.gemm_a8(q, x, sx, threads=8, want_partials=True)
+    assert np.abs(pref).max() >= (top - 1) * 128 << (half - 1)     # the widest sums do occur
+    xd = gu.to_dev(getattr(goq_inputs, packer)(x) if packer else x)
+    Y, P = _run(goq, bw, act, q, tokens, xd, gu.to_dev(sx), goq.F32, partials=True)
+    assert np.array_equal(P.cpu().numpy(), pref)
+    assert gu.torch_cuda().equal(_run(goq, bw, act, q, tokens, xd, gu.to_dev(sx), goq.F32)[0], Y)
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens", [1, 5, 40])
+def test_subnormal_activations(oracle, bw, tokens):
+    """fp16 activations below 2^-14 alone, and beside ordinary ones in other slabs: no operand flushes
+    them (fp32 sums of exact products: 2e-6 of the sum of absolute products, as above)."""
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    out, inn = 130, 1152
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=66, tensor_id=tokens)
+    x = (np.random.default_rng(7).integers(-1023, 1024, (tokens, inn)) * 2.0 ** -24)
+    x[tokens // 2, 256:512] = 1.5
+    x = x.astype(np.float16)
+    ref = oracle.gemm_a16(q, x, threads=8)
+    scale = np.abs(x.astype(np.float64)) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T
+    y = _run(goq, bw, "A16", q, tokens, gu.to_dev(x), None, goq.F32)[0].cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(y - ref) / scale) <= 2e-6
+    if tokens == 1:
+        packed, yv = gu.pack_layer(goq, q), torch.full((out,), float("nan"), dtype=torch.float32, device="cuda")
+        goq.gemv(bw, goq.A16, out, inn, packed, gu.to_dev(x), None, yv, goq.F32)
+        assert np.max(np.abs(yv.cpu().numpy().astype(np.float64) - ref[0]) / scale[0]) <= 2e-6
