@@ -173,3 +173,35 @@ def test_subnormal_activations(oracle, bw, tokens):
         packed, yv = gu.pack_layer(goq, q), torch.full((out,), float("nan"), dtype=torch.float32, device="cuda")
         goq.gemv(bw, goq.A16, out, inn, packed, gu.to_dev(x), None, yv, goq.F32)
         assert np.max(np.abs(yv.cpu().numpy().astype(np.float64) - ref[0]) / scale[0]) <= 2e-6
+
+
+@pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,out,inn", [(5, 8209, 2176), (16, 8209, 1152), (16, 32785, 1152), (3, 32785, 2176), (20, 8209, 2176)])
+def test_several_row_tiles_over_several_slabs(oracle, act, bw, tokens, out, inn):
+    """Two and four row tiles per workgroup (more than 512 and, W3 with one token tile, more than 2048 row tiles), the
+    last workgroup with one of them, and wavefronts that walk one, two and three slabs.  The oracle sees sampled
+    rows of a layer that repeats every 1031 rows (a prime: a misplaced tile is another row); integers with partials bit
+    for bit; the fp32 bound of test_few_tokens_a16."""
+    import paper_2605_26092_amd as goq
+    print("row tiles %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    base = goq_inputs.canonical_random(bw, 1031, inn, config_id=67, tensor_id=tokens)
+    at = np.arange(out) % 1031
+    q = {k: v[at] if isinstance(v, np.ndarray) else v for k, v in base.items()}
+    rows = np.unique(np.r_[0:70, 1020:1040, out // 2:out // 2 + 70, out - 90:out])
+    part = {k: np.ascontiguousarray(v[rows]) if isinstance(v, np.ndarray) else v for k, v in q.items()}
+    xd, sxd, x, sx = _inputs(goq, act, tokens, inn)
+    what = np.abs(oracle.dequant(part, want=("what",))["what"]).T
+    Y, P = _run(goq, bw, act, q, tokens, xd, sxd, goq.F32, partials=act != "A16")
+    if act == "A16":
+        ref, scale = oracle.gemm_a16(part, x, threads=8), np.abs(x.astype(np.float64)) @ what
+    else:
+        ref, pref = oracle.gemm_a8(part, x, sx, threads=8, want_partials=True)
+        scale = (np.abs(x.astype(np.float64)) * sx[:, None]) @ what
+        assert np.array_equal(P.cpu().numpy()[:, rows], pref)
+        assert gu.torch_cuda().equal(_run(goq, bw, act, q, tokens, xd, sxd, goq.F32)[0], Y)
+    y = Y.cpu().numpy().astype(np.float64)
+    assert np.all(np.isfinite(y))
+    assert np.max(np.abs(y[:, rows] - ref) / (scale + 1e-30)) <= 2e-6
+    # every row: those a period apart are the same row
+    assert np.array_equal(y[:, 1031:], y[:, :out - 1031])
