@@ -429,6 +429,11 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     decode_step(wA, 0, B1, B2);
     read_a(xs0, 0, A);
 
+    // Activations that pass through registers, tiles of 64 tokens: one slab body with buffers that change places, and
+    // a full barrier.  Their loads into LDS are ordinary writes, so there is no wait to be made exact, and the three
+    // bodies of the other kernels only cost (us, three bodies / one: 8192 x 28672, 129 tokens, W4/A6 320 / 302; four
+    // layers of 14336 x 4096, 128 tokens, W4/A8 141 / 133; W3/A4 .. A6 within 1 %).
+    constexpr bool ROLL = REGSTAGE && !F8 && MS == 2;
     // One slab: its weights wd and activations xs, the next slab's weights wn (requested here) and
     // activations xn (requested a slab ago), and the buffer xf that slab g + 2 is requested into.
     auto slab = [&](int g, const Weights &wd, Weights &wn, const unsigned char *xs, const unsigned char *xn, unsigned char *xf) {
@@ -446,7 +451,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         // The requests stay here; moved near their use they would not be in flight long enough.  (64
         // tokens and fp16 operands: the compiler keeps them here by itself and schedules the slab better
         // without the barrier: 7B block, 2048 tokens, W3/A16 1400 us with, 1365 without; int8 1048 / 1084.)
-        if constexpr (MS == 1 || !F16) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!ROLL && (MS == 1 || !F16)) __builtin_amdgcn_sched_barrier(0);
 
         float c1 = 0.f, c2 = 0.f;
         if constexpr (!FOLD) coefficients(wd, c1, c2);
@@ -472,10 +477,10 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
                 } else {
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
                 }
-                if constexpr ((ACT == 1 || ACT == 3 || ACT == 5 || ACT == 7) && MS == 2) {
+                if constexpr (ROLL || (ACT == 1 && MS == 2)) {
                     // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
                     // CU: nothing is gained by looking further ahead (ViT-B block, 12608 tokens: 313.5 us, 319
-                    // with the barrier below; int4 on its way to int8, 4096 x 11008, 300 tokens: 102.4 / 104.1, int6 110.5 / 112.5)
+                    // with the barrier below)
                     __syncthreads();
                 } else {
                     // (not __syncthreads(): it would wait for the activations just requested as well.
@@ -534,6 +539,15 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
             }
         }
     };
+    if constexpr (ROLL) {
+        unsigned char *x0 = xs0, *x1 = xs1, *x2 = xs2;
+        for (int g = 0; g < a.gn; ++g) {
+            slab(g, wA, wB, x0, x1, x2);
+            wA = wB;
+            unsigned char *const t = x0;
+            x0 = x1; x1 = x2; x2 = t;
+        }
+    } else
     for (int g = 0;;) {
         slab(g, wA, wB, xs0, xs1, xs2);
         if (++g == a.gn) break;

@@ -95,9 +95,10 @@ def test_batch_of_few_and_many_tokens(act):
 
 @pytest.mark.parametrize("act", sorted(PACKERS))
 @pytest.mark.parametrize("bw", [3, 4])
-@pytest.mark.parametrize("tokens,out,inn", [(1089, 1025, 128), (700, 2050, 384), (65, 130, 256), (1100, 9000, 128)])
+@pytest.mark.parametrize("tokens,out,inn", [(1089, 1025, 128), (700, 2050, 384), (65, 130, 256), (1100, 9000, 128),
+                                            (300, 4400, 1152)])
 def test_many_tokens_integers(oracle, act, bw, tokens, out, inn):
-    """The tile kernel with every integer type, ragged in both directions, one and three slabs: int32
+    """The tile kernel with every integer type, ragged in both directions, one, three and nine slabs: int32
     slab partials bit for bit, with the extremes of the type in the first tokens, y from them, and y
     without the partials the same bits."""
     import paper_2605_26092_amd as goq
