@@ -45,7 +45,7 @@
 // waits for slab g + 1's activations only.  (With a request under a run-time condition or a plain
 // __syncthreads() the compiler waited for everything, slab g + 2 included, once per slab: a launch with
 // one workgroup per CU took 1.3 us a slab.)
-// Launches of few tiles use 32-token tiles (narrow_tiles below): 4096 x 4096, 64 tokens, W3/A16 40 -> 27 us.
+// Launches of few tiles use 32-token tiles (goq_gemm_rules.h): 4096 x 4096, 64 tokens, W3/A16 40 -> 27 us.
 // One launch covers up to GOQ_MAX_BATCH layers (goq_gemm_batch): their tiles form one grid, the
 // layers with the deepest rows first, so that a block of matrices has one tail, not one per matrix.
 // Coefficient rescale (H5) once per slab: Y += c1[n,g] * P1 + c2[n,g] * P2 in fp32, after the
@@ -58,6 +58,7 @@
 #include "goq_decode.h"
 #include "goq_activations.h"
 #include "goq_internal.h"
+#include "goq_gemm_rules.h"
 #include "goq_request.h"
 
 namespace {
@@ -68,8 +69,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int TN = 128;       // outputs per workgroup tile
-constexpr int WN = 32;        // outputs per wavefront
+constexpr int TN = GOQ_TILE_OUT;   // outputs per workgroup tile
+constexpr int WN = 32;             // outputs per wavefront
 
 struct GemmArgs {
     const uint32_t *packed;
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         }
 }
 
-// Too many tiles for one grid?  (64-token tiles: 32-token ones are for a few hundred.)
+// Too many tiles for one grid?  (Counted in 64-token tiles; there are at most twice as many of 32.)
 bool too_large(const GemmBatch &b, int n)
 {
     int64_t tiles = 0;                                                        // below 8 * 2^35
@@ -615,38 +616,15 @@ int launch_ms(hipStream_t st, GemmBatch &b, int n)
     return goq_check_launch("goq_gemm");
 }
 
-// Tokens per tile.  32-token tiles do a token's decode twice as often as 64-token ones, but a launch that
-// leaves CUs without a workgroup lasts as long as one workgroup walks its slabs, and that is where
-// half the work per slab counts.  Estimated time per slab in units of what one more resident 64-token
-// workgroup costs, from the workgroups per CU; fitted to 4096 x 4096, 11008 x 4096, 4096 x 11008 and the 7B, 70B
-// and ViT-B blocks at 40 .. 1024 tokens (us, 32 / 64 tokens per tile, W3/A16: 4096 x 4096, 64 tokens 27 / 40, 256
-// tokens 30 / 45, 512 tokens 44 / 48, 1024 tokens 79 / 71; 7B block, 64 tokens 84 / 115, 128 tokens 125 / 131).
-// bw = 4 spends more on decode, activations that pass through registers (staged) on unpacking.  A single
-// layer whose 64-token tiles give every CU one and some a second has equally long tiles, nothing that short ones
-// could fill, and takes the 64-token tiles earlier (32 / 64 tokens per tile: 2304 x 768, 1576 tokens, W3/A16, 450
-// tiles of 64: 18.9 / 17.2; W4/A16 8192 x 4096, 300 tokens, 320 tiles: 66.0 / 58.9, 4096 x 4096, 600 tokens 65.0 /
-// 59.2; at 320 tiles W3 is faster with short ones).  Results do not depend on the choice.
-bool narrow_tiles(int bw, bool staged, const GemmBatch &b, int n)
-{
-    int64_t w1 = 0, w2 = 0;
-    for (int i = 0; i < n; ++i) {
-        const int64_t nt = (b.p[i].out + TN - 1) / TN;
-        w1 += (b.p[i].tokens + 31) / 32 * nt;
-        w2 += (b.p[i].tokens + 63) / 64 * nt;
-    }
-    if (w2 > (n > 1 ? 768 : bw == 3 ? 384 : 256)) return false;
-    // beyond the first workgroup of a CU; up to two the fullest CU counts, then the average
-    auto more = [](int64_t w) { return w <= 512 ? (double)((w + 255) / 256 - 1) : (double)w / 256.0 - 1.0; };
-    const double narrow = staged ? 1.0 + 0.8 * more(w1) : bw == 3 ? 0.88 + 0.52 * more(w1) : 0.95 + 0.7 * more(w1);
-    return narrow <= 1.4 + more(w2);
-}
-
 template <int BW, int ACT>
 int launch(hipStream_t st, GemmBatch &b, int n)
 {
     // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
-    if constexpr (ACT != 4 && ACT != 8)
-        if (narrow_tiles(BW, ACT >= 2, b, n)) return launch_ms<BW, ACT, 1>(st, b, n);
+    if constexpr (ACT != 4 && ACT != 8) {
+        GoqTileProblem p[GOQ_MAX_BATCH];
+        for (int i = 0; i < n; ++i) p[i] = GoqTileProblem{b.p[i].tokens, b.p[i].out, b.p[i].gn};
+        if (goq_narrow_tiles(BW, ACT == 0, ACT >= 2, n, p)) return launch_ms<BW, ACT, 1>(st, b, n);
+    }
     return launch_ms<BW, ACT, 2>(st, b, n);
 }
 

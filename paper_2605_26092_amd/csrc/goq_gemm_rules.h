@@ -1,0 +1,56 @@
+// Which tiles a goq_gemm launch takes, decided on the host from its sizes.  Plain C++ on its own, so that the
+// choices can be checked against measured launches without a device.
+#pragma once
+#include <stdint.h>
+#include "goq_layout.h"
+
+constexpr int GOQ_TILE_OUT = 128;        // outputs per workgroup tile
+
+struct GoqTileProblem {
+    int tokens, out, gn;
+};
+
+// Tokens per tile: 32 (true) or 64.  Results do not depend on the choice.
+//
+// A CU's time is set by the workgroups it holds, K = tiles per CU: the first one costs its latency, every further
+// one its share of the issue slots.  A 32-token tile costs 0.77 (fp16, W3) to 0.89 (W4) of a 64-token one where it
+// is alone and two thirds of it where it is one of several (it decodes the same weights for half the tokens), so
+// narrow tiles win as long as there are less than one and a half times as many of them on the fullest CU: K32 /
+// K64 -> time of narrow over wide tiles, W3 with fp16, layers of more than 1024 inputs, 33 .. 2048 tokens:
+//     1/1 0.78   2/1 1.07   2/2 0.76   3/2 1.01   4/2 1.22   4/3 0.94   5/3 1.10   6/4 1.00   7/4 1.13   8/4 1.24
+// and W4 with int6 0.88, 1.26, 0.84, 1.10, 1.41, 0.97, 1.16, 1.08, 1.23, 1.37.  At one and a half W3 with fp16 or int8
+// activations gains as often as it loses (4096 x 4096, 600 tokens, int8 48.6 / 50.1 us), the others lose.
+// Layers of equal depth have tiles of equal length: K is rounded up, a second tile on one CU lasts as
+// long as on all of them.  In a launch of layers of several depths the short tiles fill what the deepest leave
+// free: K is the average in tiles of the deepest layer, and narrow tiles are free of cost up to two of them
+// per CU (W4: 1.6, with fp16 1.35): 7B block, 65 tokens, K32 = 1.68, W3/A16 96 / 106 us, ViT-B block, 197
+// tokens, K32 = 0.49, W4/A16 27.0 / 31.7, but 7B block, 128 tokens, K32 = 2.24, W3/A16 123 / 119.
+// Shallow layers pay for start-up and stores of a tile, less for a narrow one: up to 1024 inputs one tile
+// per CU more is still the faster choice (2304 x 768, 600 tokens, W3/A8, 2/1: 12.0 / 13.3 us), unless the wide
+// tiles' second half would be nearly empty (30000 x 768, 33 tokens, W4/A8, 2/1: 15.2 / 13.1).
+inline bool goq_narrow_tiles(int bw, bool fp16, bool staged, int n, const GoqTileProblem *p)
+{
+    int deepest = 0, most = 0;
+    bool equal = true;
+    for (int i = 0; i < n; ++i) {
+        equal = equal && p[i].gn == p[0].gn;
+        deepest = p[i].gn > deepest ? p[i].gn : deepest;
+        most = p[i].tokens > most ? p[i].tokens : most;
+    }
+    int64_t narrow = 0, wide = 0;        // slabs of all tiles (at most 8 * 2^19 * 2^17 * 2^17)
+    for (int i = 0; i < n; ++i) {
+        const int64_t slabs = (int64_t)((p[i].out + GOQ_TILE_OUT - 1) / GOQ_TILE_OUT) * p[i].gn;
+        narrow += (p[i].tokens + 31) / 32 * slabs;
+        wide += (p[i].tokens + 63) / 64 * slabs;
+    }
+    narrow /= deepest;                   // in tiles of the deepest layer
+    wide /= deepest;
+    if (equal) {
+        narrow = (narrow + 255) / 256;   // workgroups of the fullest CU
+        wide = (wide + 255) / 256;
+        if (deepest <= 8 && most > 48 && narrow <= wide + 1) return true;
+    } else if (narrow < (bw == 3 ? 512 : fp16 ? 346 : 410)) {
+        return true;
+    }
+    return bw == 3 && !staged ? 2 * narrow <= 3 * wide : 2 * narrow < 3 * wide;
+}

@@ -1,0 +1,72 @@
+"""goq_gemm's host-side choices against measured launches (see gemm_rules_main.cpp): single layers, layers of equal
+depth in one launch, blocks of several depths, shallow layers, a last tile with few tokens."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+BLOCK_7B = "4096x4096*4 11008x4096*2 4096x11008"
+BLOCK_13B = "5120x5120*4 13824x5120*2 5120x13824"
+VIT_B = "2304x768 768x768 3072x768 768x3072"
+VIT_L = "3072x1024 1024x1024 4096x1024 1024x4096"
+
+# layers, weight bits, activations, tokens, microseconds with 32- and with 64-token tiles: launches where the choice
+# is worth 6 % or more, measured on one MI355X
+TILES = [
+    ("8192x8192*2 1024x8192*2", 4, "a16", 128, 125.2, 112.3),
+    ("8192x8192*2 1024x8192*2", 3, "a8", 64, 67.6, 61.5),
+    (VIT_B, 4, "a16", 197, 27.0, 31.7),
+    ("13824x5120*2", 3, "a8", 128, 78.5, 63.7),
+    ("700x4096 2500x4096", 3, "a16", 1024, 72.2, 58.5),
+    ("4096x4096*3", 3, "a8", 300, 64.2, 53.8),
+    ("4096x4096*3", 3, "a16", 300, 75.4, 63.7),
+    ("3000x2048*3", 3, "a16", 600, 57.9, 48.7),
+    ("11008x4096*2", 3, "a8", 203, 80.2, 74.0),
+    ("11008x4096*2", 4, "a6", 128, 82.8, 75.1),
+    ("8192x8192", 4, "a16", 300, 125.7, 112.9),
+    ("4096x4096", 3, "a16", 64, 28.4, 36.6),
+    ("4096x4096", 3, "a16", 256, 29.3, 37.7),
+    ("4096x4096", 3, "a8", 300, 37.2, 35.0),
+    ("4096x4096", 3, "a16", 1024, 76.5, 63.9),
+    ("4096x4096", 4, "a6", 256, 43.8, 49.5),
+    (BLOCK_7B, 3, "a16", 64, 79.1, 96.7),
+    (BLOCK_7B, 3, "a16", 96, 102.1, 111.9),
+    (BLOCK_7B, 4, "a8", 64, 97.6, 110.6),
+    (BLOCK_7B, 4, "a8", 128, 155.6, 119.0),
+    (VIT_L, 3, "a4", 512, 36.4, 44.1),
+    (VIT_L, 3, "a16", 1024, 59.6, 53.2),
+    ("2304x768", 3, "a8", 600, 11.9, 13.3),
+    ("2304x768", 3, "a16", 1576, 18.9, 17.8),
+    ("30000x768", 4, "a8", 33, 15.2, 13.1),
+    ("30000x768", 3, "a8", 64, 12.6, 13.7),
+    ("768x768", 3, "a8", 2048, 11.9, 13.2),
+    ("28672x8192*2", 4, "a8", 300, 779.5, 595.5),
+    (BLOCK_13B, 3, "a16", 100, 184.2, 150.8),
+    ("4096x11008", 4, "a16", 600, 165.7, 147.0),
+    ("1024x29952", 3, "a4", 203, 223.0, 260.2),
+]
+
+
+def _layers(text):
+    got = []
+    for part in text.split():
+        shape, _, times = part.partition("*")
+        got += [tuple(int(v) for v in shape.split("x"))] * int(times or 1)
+    return got
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_tile_widths_follow_the_measurements(tmp_path):
+    exe = str(tmp_path / "gemm_rules")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", os.path.join(ROOT, "tests", "gemm_rules_main.cpp"), "-o", exe], check=True)
+    lines = []
+    for text, bw, act, tokens, _, _ in TILES:
+        staged = not (act == "a16" or (act == "a8" and bw == 3))
+        ly = _layers(text)
+        lines.append(" ".join([str(bw), str(int(act == "a16")), str(int(staged)), str(len(ly))] + ["%d %d %d" % (tokens, o, i) for o, i in ly]))
+    out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True, timeout=60).stdout.split()
+    assert len(out) == len(TILES)
+    wrong = [(case, got) for case, got in zip(TILES, out) if int(got) != (32 if case[4] < case[5] else 64)]
+    assert not wrong, wrong
