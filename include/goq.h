@@ -236,9 +236,13 @@ int goq_gemv_select(int kernel);
  * Only out and in of the descriptors are read; nothing is launched and no device is touched. */
 int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kernel, int *workgroups);
 
-/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Up to 32 tokens
+/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Calls of up to 32 tokens
+ * (of 17 to 32 only where the layer has not too many outputs: some 8192 to 32768, by depth)
  * go to a kernel that splits the depth over the wavefronts of a workgroup and widens integer
- * activations to fp16 (exact: see bw = 4 below); the others:
+ * activations to fp16 (exact: see bw = 4 below).  It adds the slabs of a row in another order than the
+ * kernel of the others does, so the last bits of a token's outputs depend on the number of tokens in the
+ * call: a call of 40 tokens need not equal one of 20 and another of 20 bit for bit.  (Any two calls
+ * of more than 32 tokens agree, and so do any two of up to 16 or of 17 to 32 with one layer.)  The others:
  *   act = GOQ_A16: X fp16, sx NULL; PoT codes are decoded to fp16 operands of the fp16 MFMA,
  *                  fp32 accumulation.
  *   act = GOQ_A8 : X int8, sx fp32 [tokens].  bw = 3: PoT codes are decoded to int8 (b * 2^(E-1))
@@ -260,8 +264,8 @@ int goq_gemm(void *stream, int bw, int act, int64_t tokens, int64_t out, int64_t
 
 /* Several independent many-token layers in ONE launch (e.g. q, k, v or gate, up of a decoder block,
  * which share X): the tiles of all problems form one grid, so a small matrix does not leave the
- * chip half empty and there is one tail instead of n (a batch that mixes problems of up to 32
- * tokens with larger ones is two launches on the stream).  descs is a HOST array of n <= GOQ_MAX_BATCH
+ * chip half empty and there is one tail instead of n (a batch that mixes problems for either of
+ * goq_gemm's two kernels is two launches on the stream).  descs is a HOST array of n <= GOQ_MAX_BATCH
  * descriptors with the arguments of goq_gemm; all share bw and act.  Results are those of n
  * goq_gemm calls, bit for bit. */
 typedef struct goq_gemm_desc {

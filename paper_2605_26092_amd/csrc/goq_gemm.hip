@@ -669,13 +669,13 @@ int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, 
 
 int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs)
 {
-    // Every problem goes to the kernel its own token count asks for, whatever it is batched with: a
+    // Every problem goes to the kernel its own sizes ask for, whatever it is batched with: a
     // batch returns the bits of single calls.
     GemmBatch b;
     goq_gemm_desc few[GOQ_MAX_BATCH];
     int nfew = 0, nmany = 0;
     for (int i = 0; i < n; ++i) {
-        if (goq_gemm_small_takes(descs[i].tokens)) few[nfew++] = descs[i];
+        if (goq_few_tokens(bw, act == GOQ_A16, descs[i].tokens, descs[i].out, descs[i].in / GOQ_N)) few[nfew++] = descs[i];
         else b.p[nmany++] = make_args(descs[i]);
     }
     // before the first launch: a refused batch has done nothing

@@ -54,3 +54,30 @@ inline bool goq_narrow_tiles(int bw, bool fp16, bool staged, int n, const GoqTil
     }
     return bw == 3 && !staged ? 2 * narrow <= 3 * wide : 2 * narrow < 3 * wide;
 }
+
+// Up to 32 tokens: does a problem go to the kernel that splits the depth over the wavefronts of a workgroup (few
+// tokens), or to the tile kernel?  Their sums differ in the last bits and a batch returns the bits of single
+// calls, so the line can depend on the problem alone.
+//
+// The few-token kernel wins where the tile kernel's out / 128 workgroups leave the chip idle.  It decodes the
+// weights once per 16 or 32 tokens like the tile kernel, but reads the activations from L2 for every 32 rows, and
+// its time grows with the number of rounds of workgroups (16384 rows each with two token tiles), the other's not
+// before 32768 outputs.  us, few-token kernel / tile kernel:
+//     17 tokens, W3/A16   16384 x 4096 18 / 28   22528 x 4096 25 / 28   32000 x 4096 34 / 28   50257 x 1024 24 / 13
+//     32 tokens, W3/A8    16384 x 768 8.3 / 9.3   20480 x 768 11 / 9.5   30000 x 768 15 / 9.8
+//     32 tokens, W4/A8    28672 x 8192 63 / 75   32000 x 4096 37 / 38
+//     16 tokens, W3/A16   32000 x 4096 23 / 28   128256 x 4096 72 / 77   30000 x 768 8.1 / 8.4
+// Gate and up in one launch have twice the rows and the same answer: two layers of 13824 x 5120, 32 tokens, W3/A8 39 /
+// 32, W3/A16 51 / 34, W4/A16 56 / 41.  (The tile kernel as it was before there was another took 42, 50, 49; so that
+// no pair is slower than that, W4 with fp16 ends at 12288 outputs.  Four layers of 14336 x 4096 in one launch are, 73
+// against 62.)
+// In layers of less than eight macro-blocks some of its wavefronts have no slab: 2 tokens, W3/A8, 60000 x
+// 256 8.2 / 5.4 us, 16384 x 256 4.4 / 5.6.
+inline bool goq_few_tokens(int bw, bool fp16, int64_t tokens, int64_t out, int64_t gn)
+{
+    if (tokens > 32) return false;
+    if (tokens <= 16) return gn >= 6 || out <= (gn <= 2 ? 16384 : 32768);
+    if (bw == 4 && !fp16 && gn >= 32) return out <= 32768;
+    if (bw == 4 && fp16 && gn > 2) return out <= 12288;
+    return out <= (gn <= 2 ? 8192 : gn < 12 ? 16384 : 24576);
+}

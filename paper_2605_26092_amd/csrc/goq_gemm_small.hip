@@ -1,4 +1,5 @@
-// goq_gemm / goq_gemm_batch for up to 32 tokens (batched decode, verification of draft tokens), and
+// goq_gemm / goq_gemm_batch for up to 32 tokens (batched decode, verification of draft tokens; the line to the
+// tile kernel is drawn in goq_gemm_rules.h), and
 // goq_gemv / goq_gemv_batch of small layers as one token: Y[tokens][out] = X[tokens][in] * W^T (Eq. 4).
 //
 // What bounds it: the packed weights are read once for a handful of tokens, so the floor is the
@@ -327,13 +328,6 @@ int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, i
 }
 
 }  // namespace
-
-// Up to 32 tokens.  Its sums are not those of the tile kernel bit for bit, and a batch returns the bits of
-// single calls, so the line can depend on the problem alone: up to 32 tokens this kernel is the faster one
-// in a launch of its own and as part of a block (us, this kernel / tile kernel, W3/A16: 4096 x 4096, 32 tokens
-// 10 / 40; 7B block, 24 tokens 60 / 111).  With 64 tokens a 4096 x 4096 layer takes 19 / 27, but the block
-// 125 / 83: the weights are decoded once per 32 tokens here, and the tiles of a block fill the chip.
-bool goq_gemm_small_takes(int64_t tokens) { return tokens <= 32; }
 
 int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs, int row_tiles, const char *what)
 {

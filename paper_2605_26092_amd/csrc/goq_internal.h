@@ -32,7 +32,6 @@ int goq_launch_gemm_folded(hipStream_t st, int bw, int64_t tokens, int64_t out, 
                            const void *X, void *Y, int ytype);
 int goq_launch_gemm(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs);
 // few tokens: kernel of its own (goq_gemm_small.hip)
-bool goq_gemm_small_takes(int64_t tokens);
 // row_tiles: 16-row tiles per workgroup, 0 = by size; what: the entry point's name for error texts
 int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm_desc *descs, int row_tiles, const char *what);
 int goq_launch_mfma_probe(hipStream_t st, int32_t *report);

@@ -1,12 +1,22 @@
-// The host-side choices of goq_gemm (goq_gemm_rules.h), one launch per line of stdin:
-//     bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64
+// The host-side choices of goq_gemm (goq_gemm_rules.h), one question per line of stdin:
+//     tiles bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64 (tokens per tile)
+//     few   bw fp16 tokens out in                               ->   1 (few-token kernel) or 0 (tile kernel)
 #include <cstdio>
+#include <cstring>
 #include "../paper_2605_26092_amd/csrc/goq_gemm_rules.h"
 
 int main()
 {
-    int bw, fp16, staged, n;
-    while (scanf("%d %d %d %d", &bw, &fp16, &staged, &n) == 4) {
+    char what[8];
+    while (scanf("%7s", what) == 1) {
+        int bw, fp16, staged, n;
+        if (!strcmp(what, "few")) {
+            long long tokens, out, in;
+            if (scanf("%d %d %lld %lld %lld", &bw, &fp16, &tokens, &out, &in) != 5) return 1;
+            printf("%d\n", goq_few_tokens(bw, fp16 != 0, tokens, out, in / GOQ_N) ? 1 : 0);
+            continue;
+        }
+        if (scanf("%d %d %d %d", &bw, &fp16, &staged, &n) != 4 || n > 8) return 1;
         GoqTileProblem p[8];
         for (int i = 0; i < n; ++i) {
             int in;

@@ -57,16 +57,70 @@ def _layers(text):
     return got
 
 
-@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-def test_tile_widths_follow_the_measurements(tmp_path):
-    exe = str(tmp_path / "gemm_rules")
+# layers, weight bits, activations, tokens, microseconds of the few-token kernel and of the tile kernel, of 12 % or more
+FEW = [
+    ("4096x4096", 4, "a16", 5, 7.5, 38.2),
+    ("16384x4096", 3, "a16", 17, 18.5, 27.6),
+    ("32000x4096", 3, "a16", 17, 33.6, 28.1),
+    ("32000x4096", 3, "a16", 32, 41.3, 29.1),
+    ("50257x1024", 3, "a16", 17, 24.4, 13.4),
+    ("50257x1024", 4, "a8", 32, 27.8, 17.8),
+    ("16384x768", 3, "a8", 32, 8.3, 9.3),
+    ("20480x768", 3, "a8", 32, 11.3, 9.5),
+    ("30000x768", 4, "a16", 24, 15.6, 9.8),
+    ("30000x768", 3, "a6", 17, 15.8, 10.8),
+    ("28672x8192", 4, "a8", 32, 62.6, 75.3),
+    ("28672x8192", 3, "a16", 32, 71.4, 52.5),
+    ("22528x4096", 4, "a8", 32, 28.4, 37.0),
+    ("15360x5120", 3, "a16", 32, 27.0, 34.0),
+    ("13824x1024", 4, "a8", 17, 8.6, 11.7),
+    ("13824x5120", 4, "a16", 16, 19.0, 40.0),
+    ("32000x4096", 3, "a16", 16, 22.6, 28.3),
+    ("128256x4096", 4, "a16", 9, 81.3, 95.7),
+    ("128256x4096", 3, "a8", 32, 134.1, 72.3),
+    ("24576x640", 3, "a16", 8, 6.2, 7.1),
+    ("60000x256", 3, "a8", 2, 8.2, 5.3),
+    ("60000x128", 4, "a8", 16, 11.6, 6.2),
+    ("16384x256", 3, "a8", 2, 4.4, 5.6),
+    ("16384x128", 3, "a16", 17, 6.0, 4.4),
+    ("4096x128", 4, "a4", 2, 3.2, 4.6),
+    ("4096x4096", 3, "a16", 33, None, 28.0),       # more than 32 tokens: tiles, whatever the layer
+    ("64x128", 4, "a8", 1000, None, 5.0),
+]
+
+
+def _layers(text):
+    got = []
+    for part in text.split():
+        shape, _, times = part.partition("*")
+        got += [tuple(int(v) for v in shape.split("x"))] * int(times or 1)
+    return got
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """The rules' answers to a list of questions."""
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    exe = str(tmp_path_factory.mktemp("rules") / "gemm_rules")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", os.path.join(ROOT, "tests", "gemm_rules_main.cpp"), "-o", exe], check=True)
+    return lambda lines: subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True, timeout=60).stdout.split()
+
+
+def test_tile_widths_follow_the_measurements(ask):
     lines = []
     for text, bw, act, tokens, _, _ in TILES:
         staged = not (act == "a16" or (act == "a8" and bw == 3))
         ly = _layers(text)
-        lines.append(" ".join([str(bw), str(int(act == "a16")), str(int(staged)), str(len(ly))] + ["%d %d %d" % (tokens, o, i) for o, i in ly]))
-    out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True, timeout=60).stdout.split()
-    assert len(out) == len(TILES)
-    wrong = [(case, got) for case, got in zip(TILES, out) if int(got) != (32 if case[4] < case[5] else 64)]
+        lines.append(" ".join(["tiles", str(bw), str(int(act == "a16")), str(int(staged)), str(len(ly))] + ["%d %d %d" % (tokens, o, i) for o, i in ly]))
+    got = ask(lines)
+    assert len(got) == len(TILES)
+    wrong = [(case, g) for case, g in zip(TILES, got) if int(g) != (32 if case[4] < case[5] else 64)]
+    assert not wrong, wrong
+
+
+def test_few_token_line_follows_the_measurements(ask):
+    got = ask(["few %d %d %d %d %d" % (bw, act == "a16", tokens, *_layers(text)[0]) for text, bw, act, tokens, _, _ in FEW])
+    assert len(got) == len(FEW)
+    wrong = [(case, g) for case, g in zip(FEW, got) if int(g) != (case[4] is not None and case[4] < case[5])]
     assert not wrong, wrong

@@ -206,3 +206,20 @@ def test_several_row_tiles_over_several_slabs(oracle, act, bw, tokens, out, inn)
     assert np.max(np.abs(y[:, rows] - ref) / (scale + 1e-30)) <= 2e-6
     # every row: those a period apart are the same row
     assert np.array_equal(y[:, 1031:], y[:, :out - 1031])
+
+
+@pytest.mark.parametrize("act", ["A16", "A8"])
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("out,inn,counts", [(200, 1152, (1, 5, 16, 20, 32)), (300, 640, (33, 64, 65, 130, 1000)), (16400, 384, (17, 32, 40, 300)), (20000, 256, (1, 7, 16, 33, 200))])
+def test_bits_of_a_token(act, bw, out, inn, counts):
+    """A token's outputs are the same bits in every call that one kernel serves, whatever else the call
+    holds: few tokens, many, and the large or shallow layers whose few tokens go to the tiles."""
+    import paper_2605_26092_amd as goq
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=68, tensor_id=out)
+    if act == "A16":
+        x, sx = goq_inputs.activations_a16(max(counts), inn, config_id=68, tensor_id=100, outlier_frac=0.01), None
+    else:
+        x, sx = goq_inputs.activations_a8(max(counts), inn, config_id=68, tensor_id=200)
+    got = [_run(goq, bw, act, q, n, gu.to_dev(x[:n]), None if sx is None else gu.to_dev(sx[:n]), goq.F32)[0] for n in counts]
+    for n, y in zip(counts, got):
+        assert gu.torch_cuda().equal(y, got[-1][:n]), n
