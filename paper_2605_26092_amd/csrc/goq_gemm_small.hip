@@ -313,8 +313,9 @@ template <int BW, int ACT>
 int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part, const char *what)
 {
     if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part, what) : launch<BW, ACT, 2, 2>(st, b, grid, part, what);
-    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part, what)
-         : rt == 2 ? launch<BW, ACT, 1, 2>(st, b, grid, part, what) : launch<BW, ACT, 1, 4>(st, b, grid, part, what);
+    if constexpr (BW == 3)
+        if (rt == 4) return launch<BW, ACT, 1, 4>(st, b, grid, part, what);
+    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part, what) : launch<BW, ACT, 1, 2>(st, b, grid, part, what);
 }
 
 template <int BW>

@@ -818,8 +818,10 @@ __global__ __launch_bounds__(256) void workspace_init_kernel(Region *ws)
 // barriers per window on staging them (us, that kernel / this: W3/A16 4096 x 4096 5.07 / 4.66, 4096 x 11008
 // 11.2 / 8.6, 1024 x 8192 7.9 / 6.8; W4/A8 4096 x 4096 6.5 / 5.9, 4096 x 11008 14.3 / 11.4).  The line: beyond 512 tiles
 // or 24576 (tile, macro-block) pairs the streaming kernel's equal pieces win where several layers
-// share a launch (W3/A16 gate + up 13.9 / 13.9, W4/A8 17.6 / 18.4, the 7B block 23.3 / 30.2); single layers of 700
-// to 1000 tiles are a tenth faster here, which the documented rule leaves aside.
+// share a launch (streaming / few-token: W3/A16 gate + up 13.9 / 13.9, W4/A8 17.6 / 18.4, the 7B block 23.3 / 30.2).
+// Single layers and small groups a little beyond it are faster in the few-token kernel (8192 x 8192 13.1 / 10.9, 11008 x 4096
+// 11.3 / 10.1, three of 4096 x 4096 11.5 / 10.2, 8192 x 8192 W4/A8 15.3 / 14.4): the line is that of the kernel this one
+// replaced, and goq_gemv_plan tells callers about it; a better one has not been drawn yet.
 constexpr int ROWS_MAX_TILES = 512;      // automatic choice: largest grid ...
 constexpr int ROWS_MAX_SLICES = 24576;   // ... and most (tile, macro-block) slices per launch
 
@@ -839,6 +841,7 @@ template <int BW, int ACT>
 __global__ __launch_bounds__(NT)
 void gemv_rows_kernel(GemvArgs a)
 {
+    static_assert(ACT >= 2, "packed activations only");
     __shared__ __attribute__((aligned(16))) unsigned char xtab[XZ + RW * XG];
     __shared__ __attribute__((aligned(16))) unsigned char stab[RW * 4];
     __shared__ __attribute__((aligned(16))) unsigned char vtab[64 * VS];
@@ -922,7 +925,7 @@ void gemv_rows_kernel(GemvArgs a)
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < NT / 16; ++i) s += red[i * 16 + tid];
-        if constexpr (ACT != 0) s *= ((const __attribute__((address_space(1))) float *)P.sx)[0];
+        s *= ((const __attribute__((address_space(1))) float *)P.sx)[0];
         const int row = R * GOQ_ROWS + 16 * j + tid;
         if (row < P.out) {
             // (global-memory pointers, said explicitly: a generic store may hit LDS as far as the
