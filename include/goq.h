@@ -236,9 +236,9 @@ int goq_gemv_select(int kernel);
  * Only out and in of the descriptors are read; nothing is launched and no device is touched. */
 int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kernel, int *workgroups);
 
-/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Calls of up to 32 tokens
- * (of 17 to 32 only where the layer has not too many outputs: some 8192 to 32768, by depth)
- * go to a kernel that splits the depth over the wavefronts of a workgroup and widens integer
+/* Many-token layer output (Eq. 4), Y[tokens][out] = X[tokens][in] * W^T.  Calls of up to 32 tokens,
+ * but for layers with too many outputs for it (17 to 32 tokens: from 8192 to 32768, by depth and types;
+ * up to 16: shallow layers of more than 16384), go to a kernel that splits the depth over the wavefronts of a workgroup and widens integer
  * activations to fp16 (exact: see bw = 4 below).  It adds the slabs of a row in another order than the
  * kernel of the others does, so the last bits of a token's outputs depend on the number of tokens in the
  * call: a call of 40 tokens need not equal one of 20 and another of 20 bit for bit.  (Any two calls

@@ -39,13 +39,13 @@
 // 128-token tile (one wavefront per SIMD) spreads the decode over more matrix instructions but
 // needs the partials in accumulator registers, which the rescale can only read through copies:
 // it measured slower.
-// Pipeline: activations of slab g + 2 are requested (global_load_lds, straight into one of three
+// Pipeline: activations of slab g + 2 are requested (buffer loads straight into one of three
 // LDS buffers) and the weights of slab g + 1 (registers) at the start of slab g; inside a slab
 // every k-step's MFMAs run on operands prepared during the previous k-step; one barrier per slab, which
 // waits for slab g + 1's activations only.  (With a request under a run-time condition or a plain
 // __syncthreads() the compiler waited for everything, slab g + 2 included, once per slab: a launch with
 // one workgroup per CU took 1.3 us a slab.)
-// Launches of few tiles use 32-token tiles (goq_gemm_rules.h): 4096 x 4096, 64 tokens, W3/A16 40 -> 27 us.
+// Launches of few tiles use 32-token tiles (goq_gemm_rules.h): 4096 x 4096, 64 tokens, W3/A16 37 -> 28 us.
 // One launch covers up to GOQ_MAX_BATCH layers (goq_gemm_batch): their tiles form one grid, the
 // layers with the deepest rows first, so that a block of matrices has one tail, not one per matrix.
 // Coefficient rescale (H5) once per slab: Y += c1[n,g] * P1 + c2[n,g] * P2 in fp32, after the
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
              : t == 4 ? w.q1.x : t == 5 ? w.q1.y : t == 6 ? w.q1.z : w.q1.w;
     };
 
-    // Activation slab -> LDS without passing through registers (global_load_lds_dwordx4): each
+    // Activation slab -> LDS without passing through registers (buffer_load_dwordx4 .. lds): each
     // instruction fills 64 consecutive 16-byte LDS slots, one per lane, from per-lane addresses.
     // Slot (row, cs) holds k-piece cs ^ f(row): the XOR swizzle makes the 16 rows a quarter of an
     // MFMA A operand read touches fall into 16 different bank groups (row stride 256 / 128 bytes).

@@ -1,5 +1,6 @@
-"""goq_gemm with up to 32 tokens (the kernel that splits the depth over wavefronts) and just beyond: edges of its 16-token and 16-row tiles, wavefronts without
-a slab of their own, one and two row tiles per workgroup; against the oracle, and batch against single calls."""
+"""goq_gemm with up to 32 tokens (the kernel that splits the depth over wavefronts) and just beyond: edges of its 16-token and
+16-row tiles, wavefronts without a slab and with several, one, two and four row tiles per workgroup; the tile
+kernel with every integer type; against the oracle, batch against single calls, and a token's bits between calls."""
 import numpy as np
 import pytest
 
