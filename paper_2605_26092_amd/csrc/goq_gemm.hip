@@ -180,6 +180,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     __shared__ __attribute__((aligned(16))) unsigned char xs1[TM * ROWB];
     __shared__ __attribute__((aligned(16))) unsigned char xs2[TM * ROWB];
     __shared__ __attribute__((aligned(16))) unsigned char xtab[64 * 16];        // exchange table
+    __shared__ float sxs[ACT == 0 ? 1 : TM];                                    // scales of the tile's tokens
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -401,17 +402,18 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         c2 = __half2float(__ushort_as_half((unsigned short)(cw >> 16)));
     };
 
-    // Prologue: slabs 0 and 1 are requested and waited for.
+    // Prologue: slabs 0 and 1 are requested and waited for, with the tokens' scales.
     Weights wA, wB, wC;
     uint4 xr[NPS * NQ];
     load_weights(0, wA);
+    if constexpr (ACT != 0)
+        if (tid < TM) sxs[tid] = a.sx[min(m0 + tid, a.tokens - 1)] * (F16 || F8 ? 1.f : 1.f / (float)(1 << ((1 << (BW - 1)) - 1)));
     if constexpr (REGSTAGE) {
+        uint4 xr1[NPS * NQ];
         fetch_x(0, xr);
+        fetch_x(min(1, a.gn - 1), xr1);
         write_x(xs0, xr);
-        if (a.gn > 1) {
-            fetch_x(1, xr);
-            write_x(xs1, xr);
-        }
+        write_x(xs1, xr1);
     } else {
         stage_x(0, xs0);
         if (a.gn > 1) stage_x(1, xs1);
@@ -557,23 +559,62 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         slab(g, wC, wA, xs2, xs0, xs1);
         if (++g == a.gn) break;
     }
-    // no load may still be on its way into LDS when the workgroup ends
+    // No load may still be on its way into LDS, and no wavefront still reading a slab, when the slabs' memory is
+    // used for the tile.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 
-    // ---- store the tile (H6)
-    const int n = n0 + ln;
+    // ---- store the tile (H6).  A lane holds single elements of 16 tokens; a wavefront turns its outputs 2 KiB at a
+    // time in LDS (no other wavefront takes part) and stores rows of 32 in 16-byte pieces.  Single elements cost eight
+    // times the store instructions, and with integer activations each waited for its token's scale, which was loaded
+    // behind the store before it: 32 round trips to memory per tile, half the time of a tile of six slabs (us, single
+    // elements / pieces: ViT-B block, 12608 tokens, W3/A8 296 / 259; 1576 tokens, W4/A4 55.0 / 44.2; two of
+    // 11008 x 4096, 203 tokens, W4/A16 96.3 / 92.2).
+    unsigned char *const turn = (wave < 2 ? xs0 : xs1) + (wave & 1) * 2048;
+    auto store_tile = [&](auto element) {
+        using T = decltype(element);
+        typedef T piece_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));   // rows begin anywhere
+        constexpr int E = 16 / sizeof(T);                  // elements of a piece
+        constexpr int PPR = 32 / E;                        // pieces of a row
+        constexpr int ROWS = 2048 / 32 / sizeof(T);        // tokens of a pass
+        constexpr int REGS = ROWS / 2;
+        T *const Y = reinterpret_cast<T *>(a.Y) + (int64_t)m0 * a.out + n0;
 #pragma unroll
-    for (int i = 0; i < MS; ++i)
+        for (int pass = 0; pass < MS * 32 / ROWS; ++pass) {
+            // register v of a pass: token 8 (v / 4) + 4 kg + v % 4, kept in row 8 (v / 4) + 2 (v % 4) + kg, so that the
+            // two lane groups write to different banks
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int m = m0 + 32 * i + 8 * (v / 4) + 4 * kg + (v % 4);
-            if (m >= a.tokens || n >= a.out) continue;
-            float y = Yacc[i][v];
-            if constexpr (ACT != 0 && !F16 && !F8) y *= a.sx[m] * (1.f / (float)(1 << ((1 << (BW - 1)) - 1)));
-            if constexpr (ACT != 0 && (F16 || F8)) y *= a.sx[m];
-            if (a.ytype == GOQ_F32) reinterpret_cast<float *>(a.Y)[(int64_t)m * a.out + n] = y;
-            else reinterpret_cast<__half *>(a.Y)[(int64_t)m * a.out + n] = __float2half(y);
+            for (int v = 0; v < REGS; ++v) {
+                const int at = pass * REGS + v;
+                float y = Yacc[at / 16][at % 16];
+                if constexpr (ACT != 0) {
+                    y *= sxs[pass * ROWS + 8 * (v / 4) + 4 * kg + v % 4];
+                    asm("" : "+v"(y));                     // (rounded to fp32 before it becomes fp16: no fused form)
+                }
+                reinterpret_cast<T *>(turn)[(8 * (v / 4) + 2 * (v % 4) + kg) * 32 + ln] = (T)y;
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int row = (r * 64 + lane) / PPR, col = lane % PPR * E;
+                const int m = pass * ROWS + (row & ~7) + 4 * (row & 1) + ((row >> 1) & 3);
+                const piece_t piece = *reinterpret_cast<const piece_t *>(turn + (r * 64 + lane) * 16);
+                if (m0 + m < a.tokens) {
+                    T *const to = Y + (int64_t)m * a.out + col;
+                    if (n0 + col + E <= a.out) {
+                        *reinterpret_cast<piece_t *>(to) = piece;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < E; ++e)
+                            if (n0 + col + e < a.out) to[e] = piece[e];
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
         }
+    };
+    if (a.ytype == GOQ_F32) store_tile(0.f);
+    else store_tile((_Float16)0.f);
 }
 
 // Too many tiles for one grid?  (Counted in 64-token tiles; there are at most twice as many of 32.)
