@@ -71,6 +71,11 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TN = GOQ_TILE_OUT;   // outputs per workgroup tile
 constexpr int WN = 32;             // outputs per wavefront
+// Where the int8 slab sums of a 128-token tile begin: the bits of an fp32 number inside [2^-3, 2^-2), whose last place is 2^-26, so
+// that START + P, read as fp32, is that number + 2^-26 P exactly (|P| <= 2^17; the binade has room for -2.2 and +6.0 million
+// last places).  The subtraction that takes P out again is exact too and takes 2 cycles where the conversion of an integer
+// takes 4; 4096 x 4096, 4096 tokens, W3/A8 148 -> 145 us.  (Tiles of 64 tokens have no 16 registers left for it.)
+constexpr int START = 0x3e22f983;
 
 struct GemmArgs {
     const uint32_t *packed;
@@ -143,9 +148,14 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
 // per register) and ONE matrix instruction per k-step and tile accumulates straight into Y.  Half
 // the matrix instructions and no rescale, but the operand is no power of two any more: every
 // weight is rounded to fp16 (2^-11 relative), which the two-basis path avoids.
-// MS: MFMA tiles along tokens per wavefront (the workgroup's tile has 32 MS tokens).
+// MS: MFMA tiles along tokens per wavefront (the workgroup's tile has 32 MS tokens).  With four of them a wavefront keeps the
+// decoded weights of the slab (32 registers) and goes through its tiles one after the other, so that two slab sums are
+// open at a time and not eight: that fits two wavefronts per SIMD, and a weight is decoded once per 128 tokens.  Worth it where
+// decode weighs most and operands are narrow, for int8 operands straight from memory and 8-bit floats (us, 64 / 128 tokens: 4096 x
+// 4096, 4096 tokens, W3/A8 170 / 145, W4/A4 182 / 152; ViT-B block, 12608 tokens, W4/A4 314 / 273; packed activations with
+// W3 lose, 183 / 191: their staging needs the registers).
 template <int BW, int ACT, bool PART, bool FOLD, int MS>
-__global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm_kernel(GemmBatch batch)
+__global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2) void gemm_kernel(GemmBatch batch)
 {
     int pi = 0;
 #pragma unroll
@@ -156,6 +166,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     static_assert(!FOLD || (ACT == 0 && !PART), "the folded product exists for fp16 activations only");
     constexpr int CH = (BW == 3) ? 4 : 5;
     constexpr int TM = 32 * MS;
+    constexpr int MA = MS == 4 ? 1 : MS;                           // MFMA tiles whose slab sums are open at a time
     // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x unpacked to
     // int8, int8 MFMA; 4 packed int4 x as 8-bit floats; 5 packed int6 x unpacked to int8, int8
     // MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x unpacked to int8, int8 MFMA; 8 packed
@@ -163,6 +174,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     constexpr bool F16 = (ACT == 0 || ACT == 2 || ACT == 6);       // fp16 MFMA
     constexpr bool F8 = (ACT == 4 || ACT == 8);                    // 8-bit-float MFMA
     constexpr bool REGSTAGE = (ACT >= 2);
+    constexpr bool BIASED = MS == 4 && ACT == 1;                   // slab sums begin at START
     constexpr bool X4 = (ACT == 3 || ACT == 4);                    // two activations per byte
     constexpr bool X6 = (ACT == 5 || ACT == 6);                    // four activations per three bytes
     constexpr bool X3 = (ACT == 7 || ACT == 8);                    // eight activations per three bytes
@@ -374,16 +386,17 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
     };
     // A operands of k-step t: token 32 i + ln, the 16-byte piece that holds the k of micro-block(s)
     // 8 kg + MPK t .. of the slab
-    auto read_a = [&](const unsigned char *xs, int t, OpT (&A)[MS]) {
+    auto read_a = [&](const unsigned char *xs, int t, int tile0, OpT (&A)[MA]) {
         const int piece = KSTEPS * kg + t;
 #pragma unroll
-        for (int i = 0; i < MS; ++i)
+        for (int i = 0; i < MA; ++i) {
+            const unsigned char *row = xs + (32 * (tile0 + i) + ln) * ROWB;          // (swz has a period of 32 rows)
             if constexpr (F8) {
-                const unsigned char *row = xs + (32 * i + ln) * ROWB;
-                const i32x4 a0 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece) ^ swz(32 * i + ln)) * 16));
-                const i32x4 a1 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece + 1) ^ swz(32 * i + ln)) * 16));
+                const i32x4 a0 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece) ^ swz(ln)) * 16));
+                const i32x4 a1 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece + 1) ^ swz(ln)) * 16));
                 A[i] = i32x8{a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-            } else A[i] = *reinterpret_cast<const OpT *>(xs + (32 * i + ln) * ROWB + ((piece ^ swz(32 * i + ln)) * 16));
+            } else A[i] = *reinterpret_cast<const OpT *>(row + ((piece ^ swz(ln)) * 16));
+        }
     };
     // coefficient pair of this lane's output channel
     auto coefficients = [&](const Weights &w, float &c1, float &c2) {
@@ -427,16 +440,86 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
 #pragma unroll
         for (int k = 0; k < 8; ++k) { cf1[k] = (_Float16)c1; cf2[k] = (_Float16)c2; }
     };
-    OpT B1, B2, A[MS];
+    OpT B1, B2, A[MA];
     if constexpr (FOLD) fold_coefficients(wA);
     decode_step(wA, 0, B1, B2);
-    read_a(xs0, 0, A);
+    read_a(xs0, 0, 0, A);
 
     // Activations that pass through registers, tiles of 64 tokens: one slab body with buffers that change places, and
     // a full barrier.  Their loads into LDS are ordinary writes, so there is no wait to be made exact, and the three
     // bodies of the other kernels only cost (us, three bodies / one: 8192 x 28672, 129 tokens, W4/A6 320 / 302; four
     // layers of 14336 x 4096, 128 tokens, W4/A8 141 / 133; W3/A4 .. A6 within 1 %).
     constexpr bool ROLL = REGSTAGE && !F8 && MS == 2;
+    auto products = [&](int t, const OpT &Ai, const OpT &B1i, const OpT &B2i, AccT &P1, AccT &P2, int i) {
+        AccT z;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z[v] = BIASED ? START : 0;
+        if constexpr (FOLD) {
+            Yacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B1i, Yacc[i], 0, 0, 0);
+        } else if constexpr (F16) {
+            P1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B1i, t == 0 ? z : P1, 0, 0, 0);
+            P2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B2i, t == 0 ? z : P2, 0, 0, 0);
+        } else if constexpr (F8) {
+            // E5M2 x E5M2, block scales 2^0
+            P1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ai, B1i, t == 0 ? z : P1, 1, 1, 0, 127, 0, 127);
+            P2 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ai, B2i, t == 0 ? z : P2, 1, 1, 0, 127, 0, 127);
+        } else {
+            P1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ai, B1i, t == 0 ? z : P1, 0, 0, 0);
+            P2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ai, B2i, t == 0 ? z : P2, 0, 0, 0);
+        }
+    };
+    // The coefficient rescale of one MFMA tile, once per slab, outside the dot-product loop (H5), and the verification
+    // output.  Register v of a 32 x 32 tile: token 8 (v / 4) + 4 kg + v % 4, output ln.
+    auto rescale = [&](int g, int i, float c1, float c2, const AccT &P1, const AccT &P2) {
+        if constexpr (!FOLD) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if constexpr (BIASED) {
+                    Yacc[i][v] = fmaf(c1, __int_as_float(P1[v]) - __int_as_float(START), Yacc[i][v]);
+                    Yacc[i][v] = fmaf(c2, __int_as_float(P2[v]) - __int_as_float(START), Yacc[i][v]);
+                } else {
+                    Yacc[i][v] = fmaf(c1, (float)P1[v], Yacc[i][v]);
+                    Yacc[i][v] = fmaf(c2, (float)P2[v], Yacc[i][v]);
+                }
+            }
+        }
+        if constexpr (PART) {
+            // exact int32 slab partials [tokens][out][in/128][2] (verification output)
+            const int n = n0 + ln;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int m = m0 + 32 * i + 8 * (v / 4) + 4 * kg + (v % 4);
+                if (m < a.tokens && n < a.out && a.partials)
+                    *reinterpret_cast<int2 *>(a.partials + (((int64_t)m * a.out + n) * a.gn + g) * 2) =
+                        F16 || F8 ? make_int2((int)((float)P1[v] * (float)(1 << ((1 << (BW - 1)) - 1))),
+                                        (int)((float)P2[v] * (float)(1 << ((1 << (BW - 1)) - 1))))
+                            : make_int2((int)P1[v], (int)P2[v]);
+            }
+        }
+    };
+    // Everything older than this slab's activation request has landed once at most NP vector-memory operations are
+    // outstanding (they return in order): slab g + 1's activations, requested a slab ago, and its weights.
+    auto slab_barrier = [&](int g, unsigned char *xf) {
+        if constexpr (REGSTAGE) {
+            // (register path: slab g + 2 is written here; its buffer was last read before the previous slab's
+            // barrier, and it is first read after the next one)
+            if (F8 || g + 2 < a.gn) write_x(xf, xr);
+        } else {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
+        }
+        if constexpr (ROLL || (ACT == 1 && MS == 2)) {
+            // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
+            // CU: nothing is gained by looking further ahead (ViT-B block, 12608 tokens: 313.5 us, 319
+            // with the barrier below)
+            __syncthreads();
+        } else {
+            // (not __syncthreads(): it would wait for the activations just requested as well.
+            // This wavefront's LDS operations are done when it arrives.)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+    };
     // One slab: its weights wd and activations xs, the next slab's weights wn (requested here) and
     // activations xn (requested a slab ago), and the buffer xf that slab g + 2 is requested into.
     auto slab = [&](int g, const Weights &wd, Weights &wn, const unsigned char *xs, const unsigned char *xn, unsigned char *xf) {
@@ -457,89 +540,47 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 ? 3 : 2) void gemm
         if constexpr (!ROLL && (MS == 1 || !F16)) __builtin_amdgcn_sched_barrier(0);
 
         float c1 = 0.f, c2 = 0.f;
-        if constexpr (!FOLD) coefficients(wd, c1, c2);
-
-        AccT P1[MS], P2[MS];
-#pragma unroll
-        for (int t = 0; t < KSTEPS; ++t) {
-            const OpT B1c = B1, B2c = B2;
-            OpT Ac[MS];
-#pragma unroll
-            for (int i = 0; i < MS; ++i) Ac[i] = A[i];
-            if (t + 1 < KSTEPS) {
-                decode_step(wd, t + 1, B1, B2);
-                read_a(xs, t + 1, A);
-            } else {
-                // last k-step of the slab.  Everything older than this slab's activation request
-                // has landed once at most NP vector-memory operations are outstanding (they return
-                // in order): slab g + 1's activations, requested a slab ago, and its weights.
-                if constexpr (REGSTAGE) {
-                    // (register path: slab g + 2 is written here; its buffer was last read before
-                    // the previous slab's barrier, and it is first read after the next one)
-                    if (F8 || g + 2 < a.gn) write_x(xf, xr);
-                } else {
-                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
-                }
-                if constexpr (ROLL || (ACT == 1 && MS == 2)) {
-                    // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
-                    // CU: nothing is gained by looking further ahead (ViT-B block, 12608 tokens: 313.5 us, 319
-                    // with the barrier below)
-                    __syncthreads();
-                } else {
-                    // (not __syncthreads(): it would wait for the activations just requested as well.
-                    // This wavefront's LDS operations are done when it arrives.)
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    __builtin_amdgcn_s_barrier();
-                    asm volatile("" ::: "memory");
-                }
-                if constexpr (FOLD) fold_coefficients(wn);
-                decode_step(wn, 0, B1, B2);
-                read_a(xn, 0, A);
+        if constexpr (!FOLD) {
+            coefficients(wd, c1, c2);
+            if constexpr (BIASED) {
+                c1 *= (float)(1 << 26);
+                c2 *= (float)(1 << 26);
             }
-#pragma unroll
-            for (int i = 0; i < MS; ++i) {
-                AccT z;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) z[v] = 0;
-                if constexpr (FOLD) {
-                    Yacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[i], B1c, Yacc[i], 0, 0, 0);
-                } else if constexpr (F16) {
-                    P1[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[i], B1c, t == 0 ? z : P1[i], 0, 0, 0);
-                    P2[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[i], B2c, t == 0 ? z : P2[i], 0, 0, 0);
-                } else if constexpr (F8) {
-                    // E5M2 x E5M2, block scales 2^0
-                    P1[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ac[i], B1c, t == 0 ? z : P1[i], 1, 1, 0, 127, 0, 127);
-                    P2[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(Ac[i], B2c, t == 0 ? z : P2[i], 1, 1, 0, 127, 0, 127);
-                } else {
-                    P1[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ac[i], B1c, t == 0 ? z : P1[i], 0, 0, 0);
-                    P2[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ac[i], B2c, t == 0 ? z : P2[i], 0, 0, 0);
-                }
-            }
+            // (fp32 from here on: the fused conversion of an fp16 factor, v_fma_mix_f32, takes 4 cycles, v_fma_f32 2)
+            asm("" : "+v"(c1), "+v"(c2));
         }
-        // ---- coefficient rescale, once per slab, outside the dot-product loop (H5).  Register v
-        //      of a 32 x 32 tile: token 8 (v / 4) + 4 kg + v % 4, output ln.
+
+        // The slab's token tiles, MA at a time; more than one group keeps the decoded weights of the whole slab.
+        constexpr int GROUPS = MS / MA;
+        OpT S1[GROUPS == 1 ? 1 : KSTEPS], S2[GROUPS == 1 ? 1 : KSTEPS];
 #pragma unroll
-        for (int i = 0; i < MS; ++i) {
-            if constexpr (!FOLD) {
+        for (int h = 0; h < GROUPS; ++h) {
+            AccT P1[MA], P2[MA];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    Yacc[i][v] = fmaf(c1, (float)P1[i][v], Yacc[i][v]);
-                    Yacc[i][v] = fmaf(c2, (float)P2[i][v], Yacc[i][v]);
+            for (int t = 0; t < KSTEPS; ++t) {
+                if constexpr (GROUPS > 1) {
+                    if (h == 0) { S1[t] = B1; S2[t] = B2; }
                 }
-            }
-            if constexpr (PART) {
-                // exact int32 slab partials [tokens][out][in/128][2] (verification output)
-                const int n = n0 + ln;
+                const OpT B1c = GROUPS > 1 ? S1[GROUPS > 1 ? t : 0] : B1, B2c = GROUPS > 1 ? S2[GROUPS > 1 ? t : 0] : B2;
+                OpT Ac[MA];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + 32 * i + 8 * (v / 4) + 4 * kg + (v % 4);
-                    if (m < a.tokens && n < a.out && a.partials)
-                        *reinterpret_cast<int2 *>(a.partials + (((int64_t)m * a.out + n) * a.gn + g) * 2) =
-                            F16 || F8 ? make_int2((int)((float)P1[i][v] * (float)(1 << ((1 << (BW - 1)) - 1))),
-                                            (int)((float)P2[i][v] * (float)(1 << ((1 << (BW - 1)) - 1))))
-                                : make_int2((int)P1[i][v], (int)P2[i][v]);
+                for (int i = 0; i < MA; ++i) Ac[i] = A[i];
+                if (t + 1 < KSTEPS) {
+                    if (h == 0) decode_step(wd, t + 1, B1, B2);
+                    read_a(xs, t + 1, MA * h, A);
+                } else if (h + 1 < GROUPS) {
+                    read_a(xs, 0, MA * (h + 1), A);
+                } else {
+                    slab_barrier(g, xf);
+                    if constexpr (FOLD) fold_coefficients(wn);
+                    decode_step(wn, 0, B1, B2);
+                    read_a(xn, 0, 0, A);
                 }
+#pragma unroll
+                for (int i = 0; i < MA; ++i) products(t, Ac[i], B1c, B2c, P1[i], P2[i], MA * h + i);
             }
+#pragma unroll
+            for (int i = 0; i < MA; ++i) rescale(g, MA * h + i, c1, c2, P1[i], P2[i]);
         }
     };
     if constexpr (ROLL) {
@@ -645,13 +686,12 @@ int lay_out(GemmBatch &b, int n, int tm)
 }
 
 template <int BW, int ACT, int MS>
-int launch_ms(hipStream_t st, GemmBatch &b, int n)
+int launch_ms(hipStream_t st, GemmBatch &b, int n, bool part)
 {
     const int grid = lay_out(b, n, 32 * MS);
-    bool part = false;
-    for (int i = 0; i < n; ++i) part = part || b.p[i].partials;
-    if (ACT != 0 && part)
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, (ACT != 0), false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
+    constexpr bool PART = ACT != 0 && MS < 4;                // (there are no tiles of 128 tokens with partials)
+    if (PART && part)
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
     else
         hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm");
@@ -660,13 +700,19 @@ int launch_ms(hipStream_t st, GemmBatch &b, int n)
 template <int BW, int ACT>
 int launch(hipStream_t st, GemmBatch &b, int n)
 {
-    // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
-    if constexpr (ACT != 4 && ACT != 8) {
-        GoqTileProblem p[GOQ_MAX_BATCH];
-        for (int i = 0; i < n; ++i) p[i] = GoqTileProblem{b.p[i].tokens, b.p[i].out, b.p[i].gn};
-        if (goq_narrow_tiles(BW, ACT == 0, ACT >= 2, n, p)) return launch_ms<BW, ACT, 1>(st, b, n);
+    constexpr bool F8 = ACT == 4 || ACT == 8;
+    GoqTileProblem p[GOQ_MAX_BATCH];
+    bool part = false;
+    for (int i = 0; i < n; ++i) {
+        p[i] = GoqTileProblem{b.p[i].tokens, b.p[i].out, b.p[i].gn};
+        part = part || b.p[i].partials;
     }
-    return launch_ms<BW, ACT, 2>(st, b, n);
+    if constexpr (F8 || ACT == 1)
+        if (!part && goq_wide_tiles(F8, n, p)) return launch_ms<BW, ACT, 4>(st, b, n, false);
+    // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
+    if constexpr (!F8)
+        if (goq_narrow_tiles(BW, ACT == 0, ACT >= 2, n, p)) return launch_ms<BW, ACT, 1>(st, b, n, part);
+    return launch_ms<BW, ACT, 2>(st, b, n, part);
 }
 
 template <int BW>

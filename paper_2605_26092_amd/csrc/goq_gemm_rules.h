@@ -10,7 +10,7 @@ struct GoqTileProblem {
     int tokens, out, gn;
 };
 
-// Tokens per tile: 32 (true) or 64.  Results do not depend on the choice.
+// Tokens per tile, of the launches that goq_wide_tiles below leaves: 32 (true) or 64.  Results do not depend on the choice.
 //
 // A CU's time is set by the workgroups it holds, K = tiles per CU: the first one costs its latency, every further
 // one its share of the issue slots.  A 32-token tile costs 0.77 (fp16, W3) to 0.89 (W4) of a 64-token one where it
@@ -53,6 +53,42 @@ inline bool goq_narrow_tiles(int bw, bool fp16, bool staged, int n, const GoqTil
         return true;
     }
     return bw == 3 && !staged ? 2 * narrow <= 3 * wide : 2 * narrow < 3 * wide;
+}
+
+// Tiles of 128 tokens (true), for the launches that have such a kernel (W3 with int8, and bw = 4 with int4 or int3:
+// f8)?  Results do not depend on the choice.
+//
+// A 128-token tile costs 1.7 (f8: 1.6) 64-token ones where a CU holds several of either, and nearly two where it is
+// alone on its CU, which runs at two wavefronts per SIMD at most instead of three (f8: two).  So wide tiles win from two per
+// CU on, if there are at least 1.75 times as many 64-token tiles on the fullest CU; K128 / K64 -> time of wide tiles
+// over the better of the other widths, layers of more than 1024 inputs, 70 .. 12608 tokens:
+//     W3/A8  1/2 1.01  2/3 1.06  2/4 0.84  3/5 1.03  3/6 0.89  4/7 0.95  5/8 1.04  5/9 0.96  6/12 0.88  10/19 0.91  14/26 0.94
+//     W4/A4  1/2 1.07  2/3 1.00  2/4 0.82  3/5 0.98  3/6 0.86  4/7 0.91  5/8 0.99  5/9 0.91  6/12 0.84  10/19 0.84  14/26 0.86
+// Shallow layers pay for start-up and stores of a tile, which no width saves: with int8, 512 to 1024 inputs 4/7 1.02, 7/14
+// 0.95, 10/19 0.95, and below that nothing is gained (256 inputs 3/5 1.18, 10/20 1.02, 31/61 0.98); W4/A4 with 256 inputs
+// 5/10 0.93, 8/16 0.90.
+// In a launch of layers of several depths K is the average in tiles of the deepest layer: ViT-B block, W3/A8, 1576 tokens
+// 0.91/1.76 1.09, 2600 1.48/2.88 0.97, 12608 6.96/13.85 0.91; 7B block, 394 tokens 2.24/3.93 1.06, 512 2.24/4.49 0.90, 1300
+// 6.17/11.78 0.93; W4/A4 from 1.12/2.25 on 0.91.
+inline bool goq_wide_tiles(bool f8, int n, const GoqTileProblem *p)
+{
+    int deepest = 0;
+    bool equal = true;
+    for (int i = 0; i < n; ++i) {
+        equal = equal && p[i].gn == p[0].gn;
+        deepest = p[i].gn > deepest ? p[i].gn : deepest;
+    }
+    int64_t wide = 0, middle = 0;        // slabs of all tiles
+    for (int i = 0; i < n; ++i) {
+        const int64_t slabs = (int64_t)((p[i].out + GOQ_TILE_OUT - 1) / GOQ_TILE_OUT) * p[i].gn;
+        wide += (p[i].tokens + 127) / 128 * slabs;
+        middle += (p[i].tokens + 63) / 64 * slabs;
+    }
+    if (!equal) return wide >= (int64_t)(f8 ? 282 : 358) * deepest && 5 * middle >= 9 * wide;
+    if (deepest < (f8 ? 2 : 4)) return false;
+    wide = (wide / deepest + 255) / 256;
+    middle = (middle / deepest + 255) / 256;
+    return wide >= 2 && (!f8 && deepest <= 8 ? 8 * middle >= 15 * wide : 4 * middle >= 7 * wide);
 }
 
 // Up to 32 tokens: does a problem go to the kernel that splits the depth over the wavefronts of a workgroup (few

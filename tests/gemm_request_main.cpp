@@ -43,7 +43,7 @@ int main()
     for (int64_t t : tokens)
         for (int64_t in : ins)
             for (int xb = 1; xb <= 2; ++xb)
-                for (int tm = 32; tm <= 64; tm += 32)
+                for (int tm = 32; tm <= (xb == 1 ? 128 : 64); tm *= 2)
                     if (check(t, in, xb, tm)) return printf("tokens %lld in %lld bytes %d tile %d\n", (long long)t, (long long)in, xb, tm), 1;
     printf("requests in range: ok (%lld pieces)\n", checked);
     return 0;

@@ -1,5 +1,6 @@
 // The host-side choices of goq_gemm (goq_gemm_rules.h), one question per line of stdin:
 //     tiles bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64 (tokens per tile)
+//     wide  bw fp16 staged n  tokens out in ..                  ->   128 or 0
 //     few   bw fp16 tokens out in                               ->   1 (few-token kernel) or 0 (tile kernel)
 #include <cstdio>
 #include <cstring>
@@ -23,7 +24,8 @@ int main()
             if (scanf("%d %d %d", &p[i].tokens, &p[i].out, &in) != 3) return 1;
             p[i].gn = in / GOQ_N;
         }
-        printf("%d\n", goq_narrow_tiles(bw, fp16 != 0, staged != 0, n, p) ? 32 : 64);
+        if (!strcmp(what, "wide")) printf("%d\n", goq_wide_tiles(bw == 4, n, p) ? 128 : 0);
+        else printf("%d\n", goq_narrow_tiles(bw, fp16 != 0, staged != 0, n, p) ? 32 : 64);
     }
     return 0;
 }

@@ -97,6 +97,46 @@ def _layers(text):
     return got
 
 
+# layers, weight bits, activations, tokens, microseconds with the better of the other tile widths and with 128-token tiles,
+# of 6 % or more
+WIDE = [
+    ("11008x4096", 4, "a4", 3152, 381.8, 324.4),
+    ("1500x1024", 4, "a4", 2600, 17.3, 19.6),
+    ("20000x256", 4, "a4", 197, 11.4, 12.3),
+    ("20000x256", 4, "a4", 2600, 65.8, 56.9),
+    ("2304x768", 4, "a4", 3152, 24.0, 20.9),
+    (VIT_B, 4, "a4", 2600, 62.2, 55.0),
+    ("3072x768", 4, "a4", 6304, 55.3, 46.8),
+    ("4096x11008", 4, "a4", 4096, 467.1, 382.5),
+    ("4096x4096", 4, "a4", 1024, 51.3, 54.7),
+    ("4096x4096", 4, "a4", 4096, 180.8, 150.7),
+    ("4096x4096*3", 4, "a4", 160, 49.7, 53.9),
+    ("4096x4096*3", 4, "a4", 1576, 228.6, 188.5),
+    (BLOCK_7B, 4, "a4", 160, 120.6, 136.4),
+    (BLOCK_7B, 4, "a4", 256, 151.8, 137.7),
+    ("6000x2048", 4, "a4", 640, 29.0, 32.3),
+    ("6000x2048", 4, "a4", 6304, 220.6, 190.8),
+    ("11008x4096", 3, "a8", 394, 62.5, 67.4),
+    ("11008x4096", 3, "a8", 2048, 227.4, 211.6),
+    ("11008x4096*2", 3, "a8", 1024, 226.7, 208.8),
+    ("1500x1024", 3, "a8", 3152, 20.3, 23.8),
+    ("20000x256", 3, "a8", 512, 14.3, 16.3),
+    ("2304x768", 3, "a8", 2048, 16.1, 17.8),
+    ("2304x768", 3, "a8", 3152, 21.4, 19.9),
+    (VIT_B, 3, "a8", 1300, 32.0, 39.8),
+    ("3072x768", 3, "a8", 2048, 16.6, 18.9),
+    ("4096x11008", 3, "a8", 1576, 217.0, 178.5),
+    ("4096x4096", 3, "a8", 1300, 65.1, 69.9),
+    ("4096x4096", 3, "a8", 2048, 87.2, 74.8),
+    ("4096x4096*3", 3, "a8", 320, 48.6, 68.9),
+    ("4096x4096*3", 3, "a8", 2048, 247.1, 214.5),
+    (BLOCK_7B, 3, "a8", 160, 112.0, 129.4),
+    (BLOCK_7B, 3, "a8", 512, 267.2, 241.0),
+    ("6000x2048", 3, "a8", 394, 25.8, 27.5),
+    ("6000x2048", 3, "a8", 9000, 292.6, 273.7),
+]
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     """The rules' answers to a list of questions."""
@@ -123,4 +163,15 @@ def test_few_token_line_follows_the_measurements(ask):
     got = ask(["few %d %d %d %d %d" % (bw, act == "a16", tokens, *_layers(text)[0]) for text, bw, act, tokens, _, _ in FEW])
     assert len(got) == len(FEW)
     wrong = [(case, g) for case, g in zip(FEW, got) if int(g) != (case[4] is not None and case[4] < case[5])]
+    assert not wrong, wrong
+
+
+def test_wide_tiles_follow_the_measurements(ask):
+    lines = []
+    for text, bw, act, tokens, _, _ in WIDE:
+        ly = _layers(text)
+        lines.append(" ".join(["wide", str(bw), "0", "0", str(len(ly))] + ["%d %d %d" % (tokens, o, i) for o, i in ly]))
+    got = ask(lines)
+    assert len(got) == len(WIDE)
+    wrong = [(case, g) for case, g in zip(WIDE, got) if int(g) != (128 if case[5] < case[4] else 0)]
     assert not wrong, wrong

@@ -224,3 +224,27 @@ def test_bits_of_a_token(act, bw, out, inn, counts):
     got = [_run(goq, bw, act, q, n, gu.to_dev(x[:n]), None if sx is None else gu.to_dev(sx[:n]), goq.F32)[0] for n in counts]
     for n, y in zip(counts, got):
         assert gu.torch_cuda().equal(y, got[-1][:n]), n
+
+
+@pytest.mark.parametrize("bw,act", [(3, "A8"), (4, "A4"), (4, "A3")])
+@pytest.mark.parametrize("tokens,out,inn", [(1023, 8191, 512), (993, 8190, 1152), (2017, 4090, 768)])
+def test_tiles_of_128_tokens(oracle, bw, act, tokens, out, inn):
+    """Launches that take 128-token tiles, ragged in both directions, with an odd and an even number of slabs and the extremes of the
+    type in the first and last tokens: the bits of calls of 33 and of 100 tokens, which take narrower tiles, and the oracle's values."""
+    import paper_2605_26092_amd as goq
+    print("wide %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    torch = gu.torch_cuda()
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=69, tensor_id=tokens)
+    q["codes"][:40] = 0                                            # all +1
+    bits, packer = PACKERS[act] or (8, None)
+    x, sx = goq_inputs.activations_int(tokens, inn, bits, config_id=69, tensor_id=200)
+    top = 1 << (bits - 1)
+    x[0], x[1], x[2, ::2], x[-1], x[-2] = -top, top - 1, -top, -top, top - 1
+    dev = lambda r: (gu.to_dev(getattr(goq_inputs, packer)(x[r]) if packer else x[r]), gu.to_dev(sx[r]))
+    Y, _ = _run(goq, bw, act, q, tokens, *dev(slice(None)), goq.F32)
+    for r in (slice(0, 100), slice(tokens - 33, tokens), slice(tokens // 2, tokens // 2 + 100)):
+        assert torch.equal(_run(goq, bw, act, q, r.stop - r.start, *dev(r), goq.F32)[0], Y[r]), r
+    rows = np.r_[0:6, tokens - 6:tokens]
+    ref, _ = oracle.gemm_a8(q, x[rows], sx[rows], threads=8, want_partials=True)
+    scale = (np.abs(x[rows].astype(np.float64)) * sx[rows][:, None]) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
+    assert np.max(np.abs(Y.cpu().numpy()[rows].astype(np.float64) - ref) / scale) <= 2e-6
