@@ -85,20 +85,30 @@ __device__ __forceinline__ void goq_decode_bytes(uint32_t w, uint32_t &lo, uint3
 template <uint32_t FLIP>
 __device__ __forceinline__ uint4 goq_exchange_entry(int v)
 {
-    const int s = (v & 3) + 1;
-    const int sg = v >> 2;
-    uint32_t mlo = 0, mhi = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int j = i ^ s;
-        const int l = i < j ? i : j;
-        const int p = (s == 1) ? (l >> 1) : (s == 4) ? l : ((l & 1) | ((l >> 2) << 1));
-        const int eta_neg = (sg >> p) & 1;
-        const int lower = i < j;
-        const uint32_t flip = (uint32_t)(eta_neg ^ lower) * FLIP;
-        if (i < 4) mlo |= flip << (8 * i);
-        else mhi |= flip << (8 * (i - 4));
-    }
-    const uint32_t srep = (uint32_t)s * 0x01010101u;
+    const uint32_t s = (uint32_t)(v & 3) + 1u, sg = (uint32_t)v >> 2;
+    // bit i: the sign bit of the pair that element i belongs to
+    const uint32_t x = (sg & 3u) | ((sg & 12u) << 2);                                          // pairs 0, 1 at 0, 1 and 2, 3 at 4, 5
+    const uint32_t z = (sg & 1u) | ((sg & 2u) << 1) | ((sg & 4u) << 2) | ((sg & 8u) << 3);     // pair p at 2 p
+    const uint32_t eta_neg = s == 1 ? 3u * z : s == 2 ? 5u * x : s == 3 ? x | ((x & 0x11u) << 3) | ((x & 0x22u) << 1) : 17u * sg;
+    const uint32_t lower = s == 1 ? 0x55u : s == 4 ? 0x0Fu : 0x33u;                            // bit i: i < i xor s
+    const uint32_t flip = eta_neg ^ lower;
+    // four bits to the low bits of four bytes
+    const uint32_t mlo = ((flip & 15u) * 0x00204081u & 0x01010101u) * FLIP;
+    const uint32_t mhi = ((flip >> 4) * 0x00204081u & 0x01010101u) * FLIP;
+    const uint32_t srep = s * 0x01010101u;
     return make_uint4(0x03020100u ^ srep, 0x07060504u ^ srep, mlo, mhi);
+}
+
+// The table in LDS, entry v at VC * 16 * v, in VC copies of 16 bytes (a lane reads copy lane % VC): every wavefront computes all
+// 64 entries, one per lane, and writes its share of the copies.  (Computed copy by copy by all threads it was 200 vector-ALU
+// instructions per wavefront at the start of every workgroup; us: 7B block, 16 tokens, W3/A16 33.4 -> 31.9; 4096 x 4096, one
+// token 4.59 -> 4.47, two such layers, W3/A6 7.7 -> 7.1.)
+template <uint32_t FLIP, int VC, int WAVES>
+__device__ __forceinline__ void goq_write_exchange_table(unsigned char *table, int wave, int lane)
+{
+    static_assert(VC % WAVES == 0, "each wavefront writes the same number of copies");
+    const uint4 e = goq_exchange_entry<FLIP>(lane);
+#pragma unroll
+    for (int i = 0; i < VC / WAVES; ++i)
+        *reinterpret_cast<uint4 *>(table + (lane * VC + (wave + WAVES * i + lane) % VC) * 16) = e;     // (16 lanes, 16 bank groups)
 }

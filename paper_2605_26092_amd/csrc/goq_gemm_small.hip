@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
 
     SlabT bufA, bufB;
     if (wave < gn) load(wave, bufA);
-    for (int t = tid; t < 64 * VC; t += NT) *reinterpret_cast<uint4 *>(vtab + t * 16) = goq_exchange_entry<0x80u>(t / VC);
+    goq_write_exchange_table<0x80u, VC, WAVES>(vtab, wave, lane);
     __syncthreads();
     const uint32_t vt = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)vtab + (lane % VC) * 16;
 

@@ -17,7 +17,7 @@
 //       exactly the 16-byte quad (chunk q, row 16 j + c) of the packed layout.
 //   A operand (activations): eight of the 16 rows hold the eight digits of the macro-block's
 //       128 activations (digit d in row 4 (d / 2) + d % 2, the other rows are zero).
-//       Activations are handed over as block fixed point, see stage_run.
+//       Activations are handed over as block fixed point, see stage_digits.
 //   D[row][c] = sum_k digit(x_k) b[row c][k]: lane (c, q) receives rows 4q .. 4q + 3, i.e. two
 //       digit sums, so the slab dot product of a row is spread over four lanes and is put
 //       together once, when the row is stored.
@@ -296,17 +296,6 @@ __device__ __forceinline__ void load_run(const void *x, int g, int r, uint32_t (
     }
 }
 
-template <int ACT>
-__device__ __forceinline__ void stage_digits(unsigned char *xt, unsigned char *st, const uint32_t (&raw)[4], int r);
-
-template <int ACT>
-__device__ __forceinline__ void stage_run(unsigned char *xt, unsigned char *st, const void *x, int g, int r)
-{
-    uint32_t raw[4];
-    load_run<ACT>(x, g, r, raw);
-    stage_digits<ACT>(xt, st, raw, r);
-}
-
 // digit table and block scales of one run (see above) from its raw words
 template <int ACT>
 __device__ __forceinline__ void stage_digits(unsigned char *xt, unsigned char *st, const uint32_t (&raw)[4], int r)
@@ -409,24 +398,28 @@ __device__ __forceinline__ Stream stream_of(const Problems<TABLE> &pb, int pi)
     return s;
 }
 
-// Digits of the units [u0, u0 + ns) of the sequence, unit s into table slot s.  Thread
+// Activations of the units [u0, u0 + ns) of the sequence, unit s for table slot s.  Thread
 // (slot = tid / 16, run = tid % 16); ns <= SW = NT / 32.  u0 lies in problem pi0, whose units end
 // at end0; units past it belong to the following problems.
 template <int ACT, bool TABLE>
-__device__ __forceinline__ void stage_window(const Problems<TABLE> &pb, int pi0, int end0, int u0, int ns,
-                                             unsigned char *xt, unsigned char *st, int tid)
+__device__ __forceinline__ void load_window(const Problems<TABLE> &pb, int pi0, int end0, int u0, int ns, int tid, uint32_t (&raw)[4])
 {
     if (tid < ns * 16) {
-        const int slot = tid >> 4;
-        const int u = u0 + slot;
+        const int u = u0 + (tid >> 4);
         int pi = pi0;
         if (u >= end0) {
             ++pi;
             while (pi + 1 < pb.n() && u >= pb[pi + 1].begin) ++pi;
         }
         const auto &P = pb[pi];
-        stage_run<ACT>(xt + slot * XG, st + slot * 4, P.x, (u - P.begin) % P.gn, tid & 15);
+        load_run<ACT>(P.x, (u - P.begin) % P.gn, tid & 15, raw);
     }
+}
+// Their digits, unit s into table slot s.
+template <int ACT>
+__device__ __forceinline__ void stage_window(int ns, unsigned char *xt, unsigned char *st, int tid, const uint32_t (&raw)[4])
+{
+    if (tid < ns * 16) stage_digits<ACT>(xt + (tid >> 4) * XG, st + (tid >> 4) * 4, raw, tid & 15);
 }
 
 // ---- one 16-row slice of a macro-block (decode, exchange, the two slab dot products) ---------
@@ -656,14 +649,27 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
     const int lane = tid & 63;
     const int wave = uniform(tid >> 6);
 
-    // the first unit's weights are requested before anything else
+    // The first window's activations are requested before anything else, the first unit's weights behind them: loads
+    // return in order, and behind the 16 MB of first units of all workgroups the activations came after 3 us, with
+    // nothing to compute until then (us: 7B block, W3/A16 22.9 -> 22.3; gate and up, W4/A8 17.6 -> 17.1; a stream of 166 MB,
+    // W3/A8 32.8 -> 32.2, with the cheaper table below).  In the W3/A16 stream it costs a spilled register: eight 7B blocks 141.5 -> 143.
+    constexpr bool EARLY = !(TABLE && BW == 3 && ACT == 0);
     UnitBuf<BW> bufA, bufB;
     constexpr bool KEEP = (BW == 3);
     Stream S = stream_of<KEEP>(pb, cur.pi);
+    uint32_t raw[4];
+    if constexpr (EARLY) {
+        load_window<ACT, TABLE>(pb, cur.pi, S.end, i0, min(SW, i1 - i0), tid, raw);
+        asm volatile("" ::: "memory");
+    }
     load_unit<BW>(S.packed, S.gn, min(cur.rg * WAVES + wave, S.rbn - 1), cur.g, lane, bufA);
 
-    for (int t = tid; t < 64 * VC; t += NT) *reinterpret_cast<uint4 *>(vtab + t * 16) = goq_exchange_entry<0x80u>(t / VC);
+    goq_write_exchange_table<0x80u, VC, WAVES>(vtab, wave, lane);
     if (tid < XZ / 4) reinterpret_cast<uint32_t *>(xtab)[tid] = 0u;
+    if constexpr (EARLY) {
+        stage_window<ACT>(min(SW, i1 - i0), xtab + XZ, stab, tid, raw);
+        __syncthreads();
+    }
 
     // A operand of this lane: row = lane % 16, k-group q = lane / 16.  Digit d sits in row
     // 4 (d / 2) + d % 2, so that every lane group receives two digit sums (D rows 4q, 4q + 1) and
@@ -685,9 +691,12 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
     auto step = [&](UnitBuf<BW> &bcur, UnitBuf<BW> &bnxt, auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
         const int slot = (idx - i0) % SW;
-        if (slot == 0) {
+        if (slot == 0 && (!EARLY || idx != i0)) {
+            const int ns = min(SW, i1 - idx);
+            uint32_t next[4];
             if (idx != i0) __syncthreads();                    // everyone is done with the old window
-            stage_window<ACT, TABLE>(pb, cur.pi, S.end, idx, min(SW, i1 - idx), xtab + XZ, stab, tid);
+            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, tid, next);
+            stage_window<ACT>(ns, xtab + XZ, stab, tid, next);
             __syncthreads();
         }
         Cursor nxt = cur;
@@ -878,10 +887,14 @@ void gemv_rows_kernel(GemvArgs a)
             if constexpr (BW == 4) s[i].md = __builtin_nontemporal_load(base + 4 * (GOQ_ROWS * 4) + q);
         }
     };
+    // (the first window's activations before the weights: loads return in order)
+    uint32_t raw[4];
+    if (tid < min(RW, gn) * 16) load_run<ACT>(P.x, tid >> 4, tid & 15, raw);
+    asm volatile("" ::: "memory");
     Slice cur[RS], nxt[RS];
     request(0, cur);
 
-    for (int t = tid; t < 64 * VC; t += NT) *reinterpret_cast<uint4 *>(vtab + t * 16) = goq_exchange_entry<0x80u>(t / VC);
+    goq_write_exchange_table<0x80u, VC, WAVES>(vtab, wave, lane);
     if (tid < XZ / 4) reinterpret_cast<uint32_t *>(xtab)[tid] = 0u;
 
     // A operand of this lane, as in the kernel above
@@ -895,8 +908,10 @@ void gemv_rows_kernel(GemvArgs a)
     float acc = 0.f;
     for (int w0 = 0; w0 < gn; w0 += RW) {
         if (w0) __syncthreads();                               // everyone is done with the old window
-        if (tid < min(RW, gn - w0) * 16)
-            stage_run<ACT>(xtab + XZ + (tid >> 4) * XG, stab + (tid >> 4) * 4, P.x, w0 + (tid >> 4), tid & 15);
+        if (tid < min(RW, gn - w0) * 16) {
+            if (w0) load_run<ACT>(P.x, w0 + (tid >> 4), tid & 15, raw);
+            stage_digits<ACT>(xtab + XZ + (tid >> 4) * XG, stab + (tid >> 4) * 4, raw, tid & 15);
+        }
         __syncthreads();
         if (w0 + RW < gn) request(w0 + RW, nxt);
 #pragma unroll
