@@ -310,7 +310,8 @@ def gemv_kernel_name(bw, shapes):
     """The kernel the library launches for these layers in one goq_gemv_batch call (goq_gemv_plan)."""
     import paper_2605_26092_amd as goq
     kernel, _ = goq.gemv_plan(bw, goq.A16, [(out, inn) for _, out, inn in shapes])
-    return ("gemm_small_kernel<%d,0,1,1>" if kernel == goq.GEMV_ROWS else "gemv_kernel<%d,0>") % bw
+    rows = "gemm_small_single_kernel<%d,0>" if len(shapes) == 1 else "gemm_small_kernel<%d,0,1,1>"
+    return (rows if kernel == goq.GEMV_ROWS else "gemv_kernel<%d,0>") % bw
 
 
 def bench_gemm_block(args, shapes, bw, act, packed, tokens, steps=10, warmup=2, folded=False):

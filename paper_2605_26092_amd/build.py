@@ -8,8 +8,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgoq.so")
 
-# per-file extras: the GEMV's leading scalar kernel arguments arrive in scalar registers
-EXTRA = {"goq_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"]}
+# per-file extras: leading scalar kernel arguments that arrive in scalar registers (the GEMV's, and those of a
+# few-token launch of one problem)
+EXTRA = {"goq_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"],
+         "goq_gemm_small.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=8"]}
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
          # packed fp32 VALU forms are kept off on the test machines

@@ -117,8 +117,9 @@ __device__ __forceinline__ void as_half(const uint32_t (&x)[XW], f16x8 (&A)[4])
     }
 }
 
+// rows: which of problem a's groups of 16 RT rows
 template <int BW, int ACT, int MT, int RT, bool PART>
-__global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel(SmallBatch batch)
+__device__ __forceinline__ void few_tokens(const SmallArgs &a, int rows)
 {
     constexpr int CH = (BW == 3) ? 4 : 5;
     constexpr int XROW = goq_block_bytes<ACT>();
@@ -131,12 +132,7 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
 
-    int pi = 0;
-#pragma unroll
-    for (int i = 1; i < GOQ_MAX_BATCH; ++i) pi += ((int)blockIdx.x >= batch.first[i]) ? 1 : 0;
-    pi = __builtin_amdgcn_readfirstlane(pi);
-    const SmallArgs &a = batch.p[pi];
-    const int rt0 = ((int)blockIdx.x - batch.first[pi]) * RT;       // first 16-row tile; RT divides 4: one row block
+    const int rt0 = rows * RT;                                      // first 16-row tile; RT divides 4: one row block
     const int gn = a.gn;
 
     // rows: lane (c, q) reads chunk q of row 16 (rt0 + r) % 64 + c (rows past `out` lie in the padding)
@@ -299,9 +295,39 @@ __global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel
     }
 }
 
+template <int BW, int ACT, int MT, int RT, bool PART>
+__global__ __launch_bounds__(NT, MT == 2 || PART ? 2 : 4) void gemm_small_kernel(SmallBatch batch)
+{
+    int pi = 0;
+#pragma unroll
+    for (int i = 1; i < GOQ_MAX_BATCH; ++i) pi += ((int)blockIdx.x >= batch.first[i]) ? 1 : 0;
+    pi = __builtin_amdgcn_readfirstlane(pi);
+    few_tokens<BW, ACT, MT, RT, PART>(batch.p[pi], (int)blockIdx.x - batch.first[pi]);
+}
+
+// One problem, one row tile per workgroup: the launches that last a few microseconds.  The problem's fields are arguments of their own, so
+// that they arrive in scalar registers with the wavefront (-amdgpu-kernarg-preload-count) and its first loads wait for no other; from a
+// SmallBatch they come by two scalar loads, one after the other (us, batch / single: 4096 x 4096, one token, W3/A16 4.5 / 4.0; 5 tokens,
+// W4/A16 5.5 / 4.9; 4096 x 11008, one token 8.6 / 8.0).
+template <int BW, int ACT>
+__global__ __launch_bounds__(NT, 4)
+void gemm_small_single_kernel(const uint32_t *packed, const void *X, const float *sx, void *Y, int tokens, int out, int gn, int ytype)
+{
+    const SmallArgs a{packed, X, sx, Y, nullptr, tokens, out, gn, ytype};
+    few_tokens<BW, ACT, 1, 1, false>(a, (int)blockIdx.x);
+}
+
 template <int BW, int ACT, int MT, int RT>
 int launch(hipStream_t st, const SmallBatch &b, int grid, bool part, const char *what)
 {
+    if constexpr (MT == 1 && RT == 1) {
+        if (b.first[1] == 0x7fffffff && !part) {
+            const SmallArgs &a = b.p[0];
+            hipLaunchKernelGGL((gemm_small_single_kernel<BW, ACT>), dim3((unsigned)grid), dim3(NT), 0, st, a.packed, a.X, a.sx, a.Y, a.tokens, a.out,
+                               a.gn, a.ytype);
+            return goq_check_launch(what);
+        }
+    }
     if (ACT != GOQ_A16 && part)
         hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, ACT != GOQ_A16>), dim3((unsigned)grid), dim3(NT), 0, st, b);
     else
