@@ -84,6 +84,7 @@ struct GemmArgs {
     void *Y;
     int32_t *partials;
     int tokens, out, in, gn, rbn, ytype;
+    int order;       // of the tiles: GOQ_TILES_*
 };
 
 // The problems of one launch: workgroups first[i] .. first[i + 1] - 1 own the tiles of problem i
@@ -200,9 +201,16 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     const int ln = lane & 31;     // MFMA column (output channel) / A row (token)
     const int kg = lane >> 5;     // k-group
 
-    const int mtiles = (a.tokens + TM - 1) / TM;
-    const int mt = tile % mtiles;
-    const int nt = tile / mtiles;
+    const int mtiles = (a.tokens + TM - 1) / TM, ntiles = (a.out + TN - 1) / TN;
+    int mt = tile % mtiles, nt = tile / mtiles;
+    if (a.order != GOQ_TILES_IN_TURN) {
+        // (workgroups are dealt to the eight XCDs in turn)
+        const int at = goq_xcd_tile(tile, mtiles * ntiles);
+        mt = a.order == GOQ_TILES_BY_TOKENS ? at / ntiles : at % mtiles;
+        nt = a.order == GOQ_TILES_BY_TOKENS ? at % ntiles : at / mtiles;
+    }
+    mt = __builtin_amdgcn_readfirstlane(mt);
+    nt = __builtin_amdgcn_readfirstlane(nt);
     const int m0 = mt * TM;
     const int n0 = nt * TN + wave * WN;
 
@@ -668,7 +676,8 @@ bool too_large(const GemmBatch &b, int n)
 
 // tiles of the problems, in launch order; returns the grid size.  The problems with the deepest rows go
 // first: their tiles take longest, and the launch should end with short ones.
-int lay_out(GemmBatch &b, int n, int tm)
+// (xblock, wblock: bytes of a macro-block of one token and of one row block)
+int lay_out(GemmBatch &b, int n, int tm, int xblock, int wblock)
 {
     for (int i = 1; i < n; ++i)
         for (int j = i; j > 0 && b.p[j].gn > b.p[j - 1].gn; --j) {
@@ -677,18 +686,20 @@ int lay_out(GemmBatch &b, int n, int tm)
             b.p[j - 1] = t;
         }
     int tiles = 0;
-    for (int i = 0; i < GOQ_MAX_BATCH; ++i) {
-        if (i >= n) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; continue; }
+    for (int i = 0; i < n; ++i) {
         b.first[i] = tiles;
         tiles += ((b.p[i].tokens + tm - 1) / tm) * ((b.p[i].out + TN - 1) / TN);
     }
+    for (int i = 0; i < n; ++i) b.p[i].order = goq_tile_order(tiles, (int64_t)b.p[i].tokens * b.p[i].gn * xblock, (int64_t)b.p[i].rbn * b.p[i].gn * wblock);
+    for (int i = n; i < GOQ_MAX_BATCH; ++i) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; }
     return tiles;
 }
 
 template <int BW, int ACT, int MS>
 int launch_ms(hipStream_t st, GemmBatch &b, int n, bool part)
 {
-    const int grid = lay_out(b, n, 32 * MS);
+    constexpr int GOQ_ACT = ACT == 0 ? GOQ_A16 : ACT <= 2 ? GOQ_A8 : ACT <= 4 ? GOQ_A4 : ACT <= 6 ? GOQ_A6 : GOQ_A3;
+    const int grid = lay_out(b, n, 32 * MS, goq_block_bytes<GOQ_ACT>(), goq_chunks(BW) * GOQ_ROWS * 16);
     constexpr bool PART = ACT != 0 && MS < 4;                // (there are no tiles of 128 tokens with partials)
     if (PART && part)
         hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
@@ -718,7 +729,7 @@ int launch(hipStream_t st, GemmBatch &b, int n)
 template <int BW>
 int launch_folded(hipStream_t st, GemmBatch &b, int n)
 {
-    const int grid = lay_out(b, n, 64);
+    const int grid = lay_out(b, n, 64, goq_block_bytes<GOQ_A16>(), goq_chunks(BW) * GOQ_ROWS * 16);
     hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm_folded");
 }
@@ -737,6 +748,7 @@ GemmArgs make_args(const goq_gemm_desc &d)
     a.gn = (int)(d.in / GOQ_N);
     a.rbn = (int)goq_row_blocks(d.out);
     a.ytype = d.ytype;
+    a.order = GOQ_TILES_IN_TURN;
     return a;
 }
 

@@ -6,6 +6,15 @@
 
 constexpr int GOQ_TILE_OUT = 128;        // outputs per workgroup tile
 
+enum { GOQ_TILES_IN_TURN = 0, GOQ_TILES_BY_TOKENS = 1, GOQ_TILES_BY_OUTPUTS = 2 };
+
+// place of workgroup `tile` of a problem's `tiles`, when every XCD has a consecutive range of places: workgroup 8 j + k gets place j of range k
+GOQ_HD int goq_xcd_tile(int tile, int tiles)
+{
+    const int k = tile % 8, rest = tiles % 8;
+    return k * (tiles / 8) + (k < rest ? k : rest) + tile / 8;
+}
+
 struct GoqTileProblem {
     int tokens, out, gn;
 };
@@ -89,6 +98,23 @@ inline bool goq_wide_tiles(bool f8, int n, const GoqTileProblem *p)
     wide = (wide / deepest + 255) / 256;
     middle = (middle / deepest + 255) / 256;
     return wide >= 2 && (!f8 && deepest <= 8 ? 8 * middle >= 15 * wide : 4 * middle >= 7 * wide);
+}
+
+// Which tiles of a problem an XCD gets.  Workgroups are dealt to the eight XCDs in turn, so in launch order (token tiles of one output
+// tile, then the next) every XCD reads all weights and all activations through its 4 MB of L2.  Where one side is
+// small enough to stay there, an XCD gets consecutive tiles instead: of a range of outputs, where the activations stay (2 MB) and the weights
+// are then read by one XCD each; of a range of tokens, where the weights stay (3 MB).  Only for launches with more tiles than the
+// chip holds at once: fewer are all in flight together, and the order changed nothing or cost up to 7 % (4096 x 11008, 40 tokens).  us, every call with weights of its own, in turn / in ranges:
+//     outputs   two of 11008 x 4096, W4/A16, 203 tokens 88.1 / 84.1   W3/A8, 400 tokens 105.0 / 101.8   20000 x 512, W4/A16, 400 23.2 / 22.8
+//     tokens    ViT-B block, W3/A8, 12608 tokens 220.5 / 210.4   3072 x 768, W3/A16, 12608 tokens 112 / 105   1500 x 1024, W3/A4, 9000 44.6 / 43.9
+// Where both sides are large neither helps (4096 x 4096, 4096 tokens, W3/A8 147 in turn, 149 and 152 in ranges; 7B block, 2048 tokens, W3/A16
+// 1336, 1345, 1380).
+inline int goq_tile_order(int64_t tiles, int64_t x_bytes, int64_t w_bytes)
+{
+    if (tiles < 512) return GOQ_TILES_IN_TURN;
+    if (x_bytes <= 2 << 20 && w_bytes > 4 << 20) return GOQ_TILES_BY_OUTPUTS;
+    if (w_bytes <= 3 << 20 && x_bytes > 4 << 20) return GOQ_TILES_BY_TOKENS;
+    return GOQ_TILES_IN_TURN;
 }
 
 // Up to 32 tokens: does a problem go to the kernel that splits the depth over the wavefronts of a workgroup (few

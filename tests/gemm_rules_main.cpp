@@ -1,9 +1,12 @@
 // The host-side choices of goq_gemm (goq_gemm_rules.h), one question per line of stdin:
 //     tiles bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64 (tokens per tile)
 //     wide  bw fp16 staged n  tokens out in ..                  ->   128 or 0
+//     order tiles x_bytes w_bytes                               ->   0, 1 or 2 (GOQ_TILES_*)
+//     deal  tiles                                               ->   1 if every place is taken once, and by XCD in ranges
 //     few   bw fp16 tokens out in                               ->   1 (few-token kernel) or 0 (tile kernel)
 #include <cstdio>
 #include <cstring>
+#include <vector>
 #include "../paper_2605_26092_amd/csrc/goq_gemm_rules.h"
 
 int main()
@@ -11,6 +14,26 @@ int main()
     char what[8];
     while (scanf("%7s", what) == 1) {
         int bw, fp16, staged, n;
+        if (!strcmp(what, "order")) {
+            long long tiles, x, w;
+            if (scanf("%lld %lld %lld", &tiles, &x, &w) != 3) return 1;
+            printf("%d\n", goq_tile_order(tiles, x, w));
+            continue;
+        }
+        if (!strcmp(what, "deal")) {
+            int tiles;
+            if (scanf("%d", &tiles) != 1) return 1;
+            std::vector<int> owner(tiles, -1);
+            bool ok = true;
+            for (int t = 0; t < tiles; ++t) {
+                const int at = goq_xcd_tile(t, tiles);
+                ok = ok && at >= 0 && at < tiles && owner[at] == -1;
+                if (ok) owner[at] = t % 8;
+            }
+            for (int t = 1; t < tiles && ok; ++t) ok = owner[t] >= owner[t - 1];
+            printf("%d\n", ok ? 1 : 0);
+            continue;
+        }
         if (!strcmp(what, "few")) {
             long long tokens, out, in;
             if (scanf("%d %d %lld %lld %lld", &bw, &fp16, &tokens, &out, &in) != 5) return 1;

@@ -175,3 +175,12 @@ def test_wide_tiles_follow_the_measurements(ask):
     assert len(got) == len(WIDE)
     wrong = [(case, g) for case, g in zip(WIDE, got) if int(g) != (128 if case[5] < case[4] else 0)]
     assert not wrong, wrong
+
+
+def test_order_of_tiles(ask):
+    MB = 1 << 20
+    # few tokens of a large layer; many of a small one; a large one; one that fits the chip at once; a small layer
+    assert ask(["order 688 %d %d" % (1.6 * MB, 28 * MB), "order 2376 %d %d" % (9 * MB, 1.2 * MB), "order 4096 %d %d" % (16 * MB, 8 * MB),
+                "order 511 %d %d" % (1 * MB, 28 * MB), "order 2000 %d %d" % (1 * MB, 1 * MB)]) == ["2", "1", "0", "0", "0"]
+    counts = list(range(1, 70)) + [511, 512, 2376, 4752, 65535]
+    assert ask(["deal %d" % n for n in counts]) == ["1"] * len(counts)

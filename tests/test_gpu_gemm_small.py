@@ -248,3 +248,20 @@ def test_tiles_of_128_tokens(oracle, bw, act, tokens, out, inn):
     ref, _ = oracle.gemm_a8(q, x[rows], sx[rows], threads=8, want_partials=True)
     scale = (np.abs(x[rows].astype(np.float64)) * sx[rows][:, None]) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
     assert np.max(np.abs(Y.cpu().numpy()[rows].astype(np.float64) - ref) / scale) <= 2e-6
+
+
+@pytest.mark.parametrize("bw,act", [(3, "A16"), (4, "A16"), (3, "A8"), (4, "A8"), (4, "A4")])
+@pytest.mark.parametrize("tokens,out,inn", [(165, 33001, 640), (9001, 1500, 512)])
+def test_tiles_in_ranges(oracle, bw, act, tokens, out, inn):
+    """Launches whose tiles are dealt to the XCDs in ranges of outputs and of tokens, ragged in both directions: every output is
+    written, and sampled rows are the oracle's."""
+    import paper_2605_26092_amd as goq
+    print("ranges %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=71, tensor_id=tokens)
+    xd, sxd, x, sx = _inputs(goq, act, tokens, inn)
+    Y, _ = _run(goq, bw, act, q, tokens, xd, sxd, goq.F32)
+    assert gu.torch_cuda().isfinite(Y).all()
+    rows = np.r_[0:3, 31:34, 63:66, 127:130, tokens // 2, tokens - 3:tokens]
+    ref = oracle.gemm_a16(q, x[rows], threads=8) if sx is None else oracle.gemm_a8(q, x[rows], sx[rows], threads=8, want_partials=True)[0]
+    scale = (np.abs(x[rows].astype(np.float64)) * (1.0 if sx is None else sx[rows][:, None])) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
+    assert np.max(np.abs(Y[rows].cpu().numpy().astype(np.float64) - ref) / scale) <= 2e-6
