@@ -651,25 +651,19 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
 
     // The first window's activations are requested before anything else, the first unit's weights behind them: loads
     // return in order, and behind the 16 MB of first units of all workgroups the activations came after 3 us, with
-    // nothing to compute until then (us: 7B block, W3/A16 22.9 -> 22.3; gate and up, W4/A8 17.6 -> 17.1; a stream of 166 MB,
-    // W3/A8 32.8 -> 32.2, with the cheaper table below).  In the W3/A16 stream it costs a spilled register: eight 7B blocks 141.5 -> 143.
-    constexpr bool EARLY = !(TABLE && BW == 3 && ACT == 0);
+    // nothing to compute until then.
     UnitBuf<BW> bufA, bufB;
     constexpr bool KEEP = (BW == 3);
     Stream S = stream_of<KEEP>(pb, cur.pi);
     uint32_t raw[4];
-    if constexpr (EARLY) {
-        load_window<ACT, TABLE>(pb, cur.pi, S.end, i0, min(SW, i1 - i0), tid, raw);
-        asm volatile("" ::: "memory");
-    }
+    load_window<ACT, TABLE>(pb, cur.pi, S.end, i0, min(SW, i1 - i0), tid, raw);
+    asm volatile("" ::: "memory");
     load_unit<BW>(S.packed, S.gn, min(cur.rg * WAVES + wave, S.rbn - 1), cur.g, lane, bufA);
 
     goq_write_exchange_table<0x80u, VC, WAVES>(vtab, wave, lane);
     if (tid < XZ / 4) reinterpret_cast<uint32_t *>(xtab)[tid] = 0u;
-    if constexpr (EARLY) {
-        stage_window<ACT>(min(SW, i1 - i0), xtab + XZ, stab, tid, raw);
-        __syncthreads();
-    }
+    stage_window<ACT>(min(SW, i1 - i0), xtab + XZ, stab, tid, raw);
+    __syncthreads();
 
     // A operand of this lane: row = lane % 16, k-group q = lane / 16.  Digit d sits in row
     // 4 (d / 2) + d % 2, so that every lane group receives two digit sums (D rows 4q, 4q + 1) and
@@ -691,12 +685,17 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
     auto step = [&](UnitBuf<BW> &bcur, UnitBuf<BW> &bnxt, auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
         const int slot = (idx - i0) % SW;
-        if (slot == 0 && (!EARLY || idx != i0)) {
+        if (slot == 0 && idx != i0) {
             const int ns = min(SW, i1 - idx);
             uint32_t next[4];
-            if (idx != i0) __syncthreads();                    // everyone is done with the old window
-            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, tid, next);
-            stage_window<ACT>(ns, xtab + XZ, stab, tid, next);
+            // The thread's slot, run and table addresses are worked out again: kept from the first window through
+            // the loop they cost 10 registers, and spills in five of the twenty instances (us, kept / again: 70B layer
+            // W3/A16 77.6 / 76.9, W4/A3 109.9 / 101.4; two of 28672 x 8192, W4/A3 63.1 / 58.0).
+            int t = tid;
+            asm("" : "+v"(t));
+            __syncthreads();                                   // everyone is done with the old window
+            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, t, next);
+            stage_window<ACT>(ns, xtab + XZ, stab, t, next);
             __syncthreads();
         }
         Cursor nxt = cur;

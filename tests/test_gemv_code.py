@@ -1,0 +1,25 @@
+"""What the compiler makes of the batch-1 kernels.  They run at the largest register count that leaves four wavefronts per SIMD, so that
+a change of a prologue shows as spills in the streaming loop, which no test of results notices."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_26092_amd import build
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """gfx950 assembly of goq_gemv.hip, compiled as the library is."""
+    out = str(tmp_path_factory.mktemp("code") / "goq_gemv.s")
+    name = "goq_gemv.hip"
+    subprocess.run(["hipcc", "-S", "--offload-device-only"] + [f for f in build.FLAGS if f != "-shared"] + build.EXTRA[name]
+                   + ["-o", out, os.path.join(build.CSRC, name)], check=True, stderr=subprocess.DEVNULL)
+    return open(out).read()
+
+
+def test_no_vector_register_is_spilled(assembly):
+    kernels = re.findall(r"\.name:\s+(\S*gemv_\S*kernel\S*)\n.*?\.vgpr_spill_count:\s+(\d+)", assembly, re.S)
+    assert len(kernels) == 26                          # streaming: 2 widths x 5 activation types x 2 forms; 6 for small layers
+    assert not [k for k in kernels if int(k[1])]
