@@ -23,3 +23,16 @@ def test_no_vector_register_is_spilled(assembly):
     kernels = re.findall(r"\.name:\s+(\S*gemv_\S*kernel\S*)\n.*?\.vgpr_spill_count:\s+(\d+)", assembly, re.S)
     assert len(kernels) == 26                          # streaming: 2 widths x 5 activation types x 2 forms; 6 for small layers
     assert not [k for k in kernels if int(k[1])]
+
+
+def test_first_weights_are_requested_while_activations_are_on_their_way(assembly):
+    """From the request of the first activations to that of the first weights (the non-temporal loads) nothing waits for the
+    activations, whatever has to be done to their bits afterwards."""
+    late, kernels = [], re.findall(r"^(_Z\S*gemv_(?:stream_|rows_)?kernel\S*):(.*?)s_endpgm", assembly, re.S | re.M)
+    assert len(kernels) == 26
+    for name, body in kernels:
+        loads = list(re.finditer(r"global_load_\S+.*", body))
+        first = next(i for i, m in enumerate(loads) if m.group(0).split(";")[0].rstrip().endswith(" nt"))
+        if "s_waitcnt vmcnt(" in body[loads[first - 1].end():loads[first].start()]:
+            late.append(name)
+    assert not late
