@@ -1,0 +1,62 @@
+"""What the compiler makes of the kernels, where a test of results notices nothing and the loss is time: registers spilled in a loop, a request
+that waits for another one, loads moved behind the work that should cover them."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_26092_amd import build
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """gfx950 assembly of a source, compiled as the library is."""
+    done = {}
+
+    def get(name):
+        if name not in done:
+            out = str(tmp_path_factory.mktemp("code") / (name + ".s"))
+            subprocess.run(["hipcc", "-S", "--offload-device-only"] + [f for f in build.FLAGS if f != "-shared"] + build.EXTRA.get(name, [])
+                           + ["-o", out, os.path.join(build.CSRC, name)], check=True, stderr=subprocess.DEVNULL)
+            done[name] = open(out).read()
+        return done[name]
+    return get
+
+
+def _bodies(text, kernel):
+    """[(mangled name, code)] of a source's kernels."""
+    return re.findall(r"^(_Z\S*%s\S*):(.*?)\.end_amdhsa_kernel" % kernel, text, re.S | re.M)
+
+
+def test_batch_1_kernels_spill_no_vector_register(assembly):
+    """They run at the largest register count that leaves four wavefronts per SIMD, so that a change of a prologue can spill in the loop."""
+    kernels = re.findall(r"\.name:\s+(\S*gemv_\S*kernel\S*)\n.*?\.vgpr_spill_count:\s+(\d+)", assembly("goq_gemv.hip"), re.S)
+    assert len(kernels) == 26                          # streaming: 2 widths x 5 activation types x 2 forms; 6 for small layers
+    assert not [k for k in kernels if int(k[1])]
+
+
+def test_first_weights_are_requested_while_activations_are_on_their_way(assembly):
+    """From the request of the first activations to that of the first weights (the non-temporal loads) nothing waits for the
+    activations, whatever has to be done to their bits afterwards."""
+    late, kernels = [], _bodies(assembly("goq_gemv.hip"), "gemv_(?:stream_|rows_)?kernel")
+    assert len(kernels) == 26
+    for name, body in kernels:
+        loads = list(re.finditer(r"global_load_\S+.*", body))
+        first = next(i for i, m in enumerate(loads) if m.group(0).split(";")[0].rstrip().endswith(" nt"))
+        if "s_waitcnt vmcnt(" in body[loads[first - 1].end():loads[first].start()]:
+            late.append(name)
+    assert not late
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+def test_next_slab_is_requested_before_the_matrix_instructions(assembly, bw):
+    """Few-token kernel, int8, two token tiles, one row tile: the loads of the next slab stand before the work on this one."""
+    (_, body), = _bodies(assembly("goq_gemm_small.hip"), "gemm_small_kernelILi%dELi1ELi2ELi1ELb0E" % bw)
+    loops = 0
+    for block in re.split(r"^\.LBB\S*:", body, flags=re.M):
+        ops = re.findall(r"^\s+(global_load|v_mfma)", block, re.M)
+        if set(ops) == {"global_load", "v_mfma"}:
+            loops += 1
+            assert "global_load" not in ops[ops.index("v_mfma"):]
+    assert loops
