@@ -295,11 +295,12 @@ __device__ __forceinline__ void few_tokens(const SmallArgs &a, int rows)
     }
 }
 
-// Two token tiles: two to four wavefronts per SIMD.  Without the upper bound the compiler takes int8 with one row tile below 100 registers, for
-// five wavefronts that no workgroup of eight can use, and moves the next slab's loads behind the matrix instructions of this one (us, 18 tokens,
-// W3/A8, W4/A8: 4096 x 11008 14.4, 16.8 -> 12.7, 13.9; three of 2048 x 5120 12.4, 14.1 -> 11.8, 13.1).
+// int8, two token tiles: two to four wavefronts per SIMD.  Without the upper bound the compiler takes the instances with one row tile below 100
+// registers, for five wavefronts that no workgroup of eight can use, and moves the next slab's loads behind the matrix instructions of this one
+// (us, 18 tokens, W3/A8, W4/A8: 4096 x 11008 14.4, 16.8 -> 12.7, 13.9; three of 2048 x 5120 12.4, 14.1 -> 11.8, 13.1).  The other types stay
+// above 110 registers by themselves; bounded, int6 gains 5 % on deep layers and loses as much on others (768 x 3072, 32 tokens 7.3 -> 7.6).
 template <int BW, int ACT, int MT, int RT, bool PART>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MT == 2 || PART ? 2 : 4, MT == 2 || PART ? 4 : 8)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MT == 2 || PART ? 2 : 4, MT == 2 && ACT == GOQ_A8 ? 4 : 8)))
 void gemm_small_kernel(SmallBatch batch)
 {
     int pi = 0;
