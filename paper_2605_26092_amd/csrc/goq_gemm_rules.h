@@ -143,3 +143,26 @@ inline bool goq_few_tokens(int bw, bool fp16, int64_t tokens, int64_t out, int64
     if (bw == 4 && fp16 && gn > 2) return out <= 12288;
     return out <= (gn <= 2 ? 8192 : gn < 12 ? 16384 : 24576);
 }
+
+// Few-token kernel, 17 to 32 tokens, one row tile per workgroup (up to 512 workgroups): does a workgroup get its CU to itself (true),
+// or may it share it with a second one?  Results do not depend on the choice.
+//
+// A workgroup goes through its layer in slabs / 8 rounds.  Where layers are alike, two on a CU hide each other's waits.  Where one layer is much
+// deeper, its workgroups are the launch's longest chain and a second one only slows them, while the short ones find room on the
+// other CUs, one after the other: if all rounds fit into the 256 CUs within the deepest layer's.  us, alone / shared:
+//     32 tokens, W3/A16   ViT-B block 8.3 / 9.7   two of 2048 x 2048 and 2048 x 5504 12.7 / 16.6   4096 x 2048 and 2048 x 4096 11.5 / 13.7
+//                         4096 x 2048 and 4000 x 4096 15.2 / 14.1   4096 x 512 and 3000 x 2048 8.7 / 7.5   4096 x 4096 and 1024 x 4608 18.5 / 18.4
+//     18 tokens, W4/A8    ViT-B block 6.5 / 7.1   6000 x 512 and 512 x 8192 10.8 / 11.0   5000 x 896 and 2000 x 1792 7.4 / 6.3
+//     18 tokens, W3/A4    ViT-B block 6.3 / 6.8   4096 x 2048 and 4000 x 4096 10.6 / 8.8   four of 1280 x 1280 and 1280 x 5120 8.1 / 9.0
+// With integers a chain of two rounds is too short to matter (ViT-S block, 32 tokens: W3/A16 5.6 / 6.2, W4/A8 5.8 / 5.3).
+inline bool goq_alone_on_cu(bool fp16, int n, const GoqTileProblem *p)
+{
+    int64_t workgroups = 0, rounds = 0, deepest = 0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t tiles = ((int64_t)p[i].out + 15) / 16, r = (p[i].gn + 7) / 8;
+        workgroups += tiles;
+        rounds += tiles * r;
+        deepest = r > deepest ? r : deepest;
+    }
+    return workgroups > 256 && deepest >= (fp16 ? 2 : 3) && rounds <= 256 * deepest;
+}

@@ -32,6 +32,7 @@
 #include "goq_decode.h"
 #include "goq_activations.h"
 #include "goq_internal.h"
+#include "goq_gemm_rules.h"
 
 namespace {
 
@@ -322,9 +323,12 @@ void gemm_small_single_kernel(const uint32_t *packed, const void *X, const float
     few_tokens<BW, ACT, 1, 1, false>(a, (int)blockIdx.x);
 }
 
+// alone: LDS that nothing uses keeps a second workgroup off the CU (goq_alone_on_cu)
 template <int BW, int ACT, int MT, int RT>
-int launch(hipStream_t st, const SmallBatch &b, int grid, bool part, const char *what)
+int launch(hipStream_t st, const SmallBatch &b, int grid, bool part, bool alone, const char *what)
 {
+    constexpr unsigned SPARE = 57 * 1024;
+    static_assert(2 * (64 * VS + WAVES * MT * RT * 1024 + SPARE) > 160 * 1024, "two workgroups do not fit");
     if constexpr (MT == 1 && RT == 1) {
         if (b.first[1] == 0x7fffffff && !part) {
             const SmallArgs &a = b.p[0];
@@ -336,27 +340,27 @@ int launch(hipStream_t st, const SmallBatch &b, int grid, bool part, const char 
     if (ACT != GOQ_A16 && part)
         hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, ACT != GOQ_A16>), dim3((unsigned)grid), dim3(NT), 0, st, b);
     else
-        hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, false>), dim3((unsigned)grid), dim3(NT), 0, st, b);
+        hipLaunchKernelGGL((gemm_small_kernel<BW, ACT, MT, RT, false>), dim3((unsigned)grid), dim3(NT), alone ? SPARE : 0, st, b);
     return goq_check_launch(what);
 }
 
 template <int BW, int ACT>
-int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part, const char *what)
+int launch_tiles(hipStream_t st, const SmallBatch &b, int grid, int mt, int rt, bool part, bool alone, const char *what)
 {
-    if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part, what) : launch<BW, ACT, 2, 2>(st, b, grid, part, what);
+    if (mt == 2) return rt == 1 ? launch<BW, ACT, 2, 1>(st, b, grid, part, alone, what) : launch<BW, ACT, 2, 2>(st, b, grid, part, alone, what);
     if constexpr (BW == 3)
-        if (rt == 4) return launch<BW, ACT, 1, 4>(st, b, grid, part, what);
-    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part, what) : launch<BW, ACT, 1, 2>(st, b, grid, part, what);
+        if (rt == 4) return launch<BW, ACT, 1, 4>(st, b, grid, part, alone, what);
+    return rt == 1 ? launch<BW, ACT, 1, 1>(st, b, grid, part, alone, what) : launch<BW, ACT, 1, 2>(st, b, grid, part, alone, what);
 }
 
 template <int BW>
-int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt, bool part, const char *what)
+int launch_act(hipStream_t st, int act, const SmallBatch &b, int grid, int mt, int rt, bool part, bool alone, const char *what)
 {
-    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt, part, what);
-    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt, part, what);
-    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt, part, what);
-    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt, part, what);
-    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt, part, what);
+    if (act == GOQ_A16) return launch_tiles<BW, GOQ_A16>(st, b, grid, mt, rt, part, alone, what);
+    if (act == GOQ_A8) return launch_tiles<BW, GOQ_A8>(st, b, grid, mt, rt, part, alone, what);
+    if (act == GOQ_A4) return launch_tiles<BW, GOQ_A4>(st, b, grid, mt, rt, part, alone, what);
+    if (act == GOQ_A6) return launch_tiles<BW, GOQ_A6>(st, b, grid, mt, rt, part, alone, what);
+    return launch_tiles<BW, GOQ_A3>(st, b, grid, mt, rt, part, alone, what);
 }
 
 }  // namespace
@@ -376,6 +380,9 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
     // (Neither choice changes a result: a row's sums are the same in every tile.)
     const int mt = most > 16 ? 2 : 1;
     const int rt = row_tiles ? row_tiles : tiles16 <= 512 ? 1 : mt == 2 || bw == 4 || tiles16 <= 2048 ? 2 : 4;
+    GoqTileProblem p[GOQ_MAX_BATCH];
+    for (int i = 0; i < n; ++i) p[i] = GoqTileProblem{(int)descs[i].tokens, (int)descs[i].out, (int)(descs[i].in / GOQ_N)};
+    const bool alone = mt == 2 && rt == 1 && goq_alone_on_cu(act == GOQ_A16, n, p);
     // the problems with the deepest rows first: the launch should end with short ones
     int order[GOQ_MAX_BATCH];
     for (int i = 0; i < n; ++i) {
@@ -401,5 +408,6 @@ int goq_launch_gemm_small(hipStream_t st, int bw, int act, int n, const goq_gemm
         a.gn = (int)(d.in / GOQ_N);
         a.ytype = d.ytype;
     }
-    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt, part, what) : launch_act<4>(st, act, b, (int)grid, mt, rt, part, what);
+    return bw == 3 ? launch_act<3>(st, act, b, (int)grid, mt, rt, part, alone, what)
+                   : launch_act<4>(st, act, b, (int)grid, mt, rt, part, alone, what);
 }

@@ -137,6 +137,34 @@ WIDE = [
 ]
 
 
+# layers, weight bits, activations, tokens, microseconds of the few-token kernel with a CU to each workgroup and with two workgroups
+# on a CU, of 4 % or more
+ALONE = [
+    (VIT_B, 3, "a16", 18, 6.7, 7.5),
+    (VIT_B, 3, "a16", 32, 8.3, 9.7),
+    (VIT_B, 4, "a8", 18, 6.5, 7.1),
+    (VIT_B, 3, "a4", 32, 6.5, 6.9),
+    ("2048x2048*2 2048x5504", 3, "a16", 32, 12.7, 16.6),
+    ("2048x2048*2 2048x5504", 4, "a8", 32, 9.6, 12.0),
+    ("4096x2048 2048x4096", 3, "a16", 18, 9.1, 10.2),
+    ("4096x2048 2048x4096", 4, "a8", 32, 9.2, 10.1),
+    ("1280x1280*4 1280x5120", 3, "a16", 32, 12.0, 14.8),
+    ("1280x1280*4 1280x5120", 3, "a4", 18, 8.1, 9.0),
+    ("6000x512 512x8192", 3, "a16", 18, 12.6, 13.5),
+    ("1152x384*4 384x384 1536x384 384x1536", 3, "a16", 32, 5.6, 6.2),
+    ("1152x384*4 384x384 1536x384 384x1536", 4, "a8", 32, 5.8, 5.3),
+    ("4096x2048 4000x4096", 3, "a16", 18, 11.6, 10.4),
+    ("4096x2048 4000x4096", 3, "a4", 32, 10.8, 9.3),
+    ("4096x512 3000x2048", 3, "a16", 32, 8.7, 7.5),
+    ("4096x512 3000x2048", 4, "a8", 18, 7.1, 5.9),
+    ("5000x896 2000x1792", 3, "a16", 18, 7.4, 6.3),
+    ("4096x4096 1024x4608", 3, "a4", 18, 12.4, 11.2),
+    ("4096x4096*2", 3, "a16", 18, 14.2, 12.8),
+    ("2304x768*2 768x768", 4, "a8", 25, 6.4, 5.2),
+    ("2048x5120*3", 3, "a16", 25, 19.2, 18.4),
+]
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     """The rules' answers to a list of questions."""
@@ -174,6 +202,17 @@ def test_wide_tiles_follow_the_measurements(ask):
     got = ask(lines)
     assert len(got) == len(WIDE)
     wrong = [(case, g) for case, g in zip(WIDE, got) if int(g) != (128 if case[5] < case[4] else 0)]
+    assert not wrong, wrong
+
+
+def test_a_cu_to_each_workgroup_follows_the_measurements(ask):
+    lines = []
+    for text, bw, act, tokens, _, _ in ALONE:
+        ly = _layers(text)
+        lines.append(" ".join(["alone", str(bw), str(int(act == "a16")), "0", str(len(ly))] + ["%d %d %d" % (tokens, o, i) for o, i in ly]))
+    got = ask(lines)
+    assert len(got) == len(ALONE)
+    wrong = [(case, g) for case, g in zip(ALONE, got) if int(g) != (case[4] < case[5])]
     assert not wrong, wrong
 
 

@@ -209,6 +209,29 @@ def test_several_row_tiles_over_several_slabs(oracle, act, bw, tokens, out, inn)
     assert np.array_equal(y[:, 1031:], y[:, :out - 1031])
 
 
+@pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,layers", [(17, [(4000, 128), (520, 3072)]), (32, [(1000, 1152), (2050, 896), (1111, 2304)])])
+def test_a_cu_to_each_workgroup(act, bw, tokens, layers):
+    """Launches whose workgroups get a CU each (257 to 512 of them, one layer much deeper): the bits of single calls, which the
+    other tests of this file hold to the oracle."""
+    import paper_2605_26092_amd as goq
+    from paper_2605_26092_amd import binding
+    print("alone %s bw=%d %d tokens %s" % (act, bw, tokens, layers), flush=True)
+    torch = gu.torch_cuda()
+    problems, single = [], []
+    for out, inn in layers:
+        q = goq_inputs.canonical_random(bw, out, inn, config_id=73, tensor_id=out)
+        xd, sxd, _, _ = _inputs(goq, act, tokens, inn)
+        single.append(_run(goq, bw, act, q, tokens, xd, sxd, goq.F16)[0])
+        Y = torch.full((tokens, out), float("nan"), dtype=torch.float16, device="cuda")
+        problems.append((tokens, out, inn, gu.pack_layer(goq, q), xd, sxd, Y, goq.F16))
+    goq.gemm_batch(bw, getattr(goq, act), binding.make_gemm_descs(problems))
+    torch.cuda.synchronize()
+    for p, y in zip(problems, single):
+        assert torch.isfinite(y).all() and torch.equal(p[6], y)
+
+
 @pytest.mark.parametrize("act", ["A16", "A8"])
 @pytest.mark.parametrize("bw", [3, 4])
 @pytest.mark.parametrize("out,inn,counts", [(200, 1152, (1, 5, 16, 20, 32)), (300, 640, (33, 64, 65, 130, 1000)), (16400, 384, (17, 32, 40, 300)), (20000, 256, (1, 7, 16, 33, 200))])
