@@ -554,8 +554,10 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
                 c1 *= (float)(1 << 26);
                 c2 *= (float)(1 << 26);
             }
-            // (fp32 from here on: the fused conversion of an fp16 factor, v_fma_mix_f32, takes 4 cycles, v_fma_f32 2)
-            asm("" : "+v"(c1), "+v"(c2));
+            // (fp32 from here on: the fused conversion of an fp16 factor, v_fma_mix_f32, takes 4 cycles, v_fma_f32 2.  Not in int8 tiles
+            // of 32 tokens: mostly alone on their CUs, where a wavefront issues one instruction per 4 cycles at best and the two
+            // conversions are two more; us, 48 tokens, W3/A8: 4096 x 11008 63.9 / 59.3, 1024 x 8192 48.0 / 44.7.)
+            if constexpr (ACT != 1 || MS != 1) asm("" : "+v"(c1), "+v"(c2));
         }
 
         // The slab's token tiles, MA at a time; more than one group keeps the decoded weights of the whole slab.

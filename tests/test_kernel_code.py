@@ -60,3 +60,12 @@ def test_next_slab_is_requested_before_the_matrix_instructions(assembly, bw):
             loops += 1
             assert "global_load" not in ops[ops.index("v_mfma"):]
     assert loops
+
+
+def test_int8_tiles_of_32_tokens_convert_coefficients_in_the_rescale(assembly):
+    """By the fused conversion of the FMA: such tiles are bound by the instructions that a single wavefront issues.  Two MFMA registers of
+    16 sums per slab, three slab bodies; the slabs of wider tiles convert beforehand."""
+    text = assembly("goq_gemm.hip")
+    mixed = {ms: len(re.findall(r"\bv_fma_mix_f32\b", body)) for ms in (1, 2)
+             for _, body in _bodies(text, "gemm_kernelILi3ELi1ELb0ELb0ELi%dE" % ms)}
+    assert mixed == {1: 96, 2: 0}
