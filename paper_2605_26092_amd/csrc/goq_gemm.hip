@@ -692,7 +692,10 @@ int lay_out(GemmBatch &b, int n, int tm, int xblock, int wblock)
         b.first[i] = tiles;
         tiles += ((b.p[i].tokens + tm - 1) / tm) * ((b.p[i].out + TN - 1) / TN);
     }
-    for (int i = 0; i < n; ++i) b.p[i].order = goq_tile_order(tiles, (int64_t)b.p[i].tokens * b.p[i].gn * xblock, (int64_t)b.p[i].rbn * b.p[i].gn * wblock);
+    for (int i = 0; i < n; ++i) {
+        GemmArgs &a = b.p[i];
+        a.order = goq_tile_order(tiles, (a.tokens + tm - 1) / tm, (int64_t)a.tokens * a.gn * xblock, (int64_t)a.rbn * a.gn * wblock, (int64_t)a.tokens * a.out);
+    }
     for (int i = n; i < GOQ_MAX_BATCH; ++i) { b.first[i] = 0x7fffffff; b.p[i] = b.p[0]; }
     return tiles;
 }

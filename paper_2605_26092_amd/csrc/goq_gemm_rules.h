@@ -103,17 +103,25 @@ inline bool goq_wide_tiles(bool f8, int n, const GoqTileProblem *p)
 // Which tiles of a problem an XCD gets.  Workgroups are dealt to the eight XCDs in turn, so in launch order (token tiles of one output
 // tile, then the next) every XCD reads all weights and all activations through its 4 MB of L2.  Where one side is
 // small enough to stay there, an XCD gets consecutive tiles instead: of a range of outputs, where the activations stay (2 MB) and the weights
-// are then read by one XCD each; of a range of tokens, where the weights stay (3 MB).  Only for launches with more tiles than the
-// chip holds at once: fewer are all in flight together, and the order changed nothing or cost up to 7 % (4096 x 11008, 40 tokens).  us, every call with weights of its own, in turn / in ranges:
-//     outputs   two of 11008 x 4096, W4/A16, 203 tokens 88.1 / 84.1   W3/A8, 400 tokens 105.0 / 101.8   20000 x 512, W4/A16, 400 23.2 / 22.8
-//     tokens    ViT-B block, W3/A8, 12608 tokens 220.5 / 210.4   3072 x 768, W3/A16, 12608 tokens 112 / 105   1500 x 1024, W3/A4, 9000 44.6 / 43.9
+// are then read by one XCD each; of a range of tokens, where the weights stay (3 MB).  Only for launches of two tiles per CU and more
+// (below, the order changed nothing or cost up to 7 %: 4096 x 11008, 40 tokens); from there it pays as well where three workgroups
+// fit a CU and all tiles are in flight together (39 launches of 512 to 767 tiles, W3 with fp16 and int8: 1.6 % faster on average, none
+// slower by more than 0.8 %).  us, every call with weights of its own, in turn / in ranges:
+//     outputs   two of 11008 x 4096, W4/A16, 203 tokens 100 / 98   W3/A8, 400 tokens 120 / 118   30000 x 512, W3/A4, 300 tokens 24.8 / 22.9
+//               50257 x 1024, W4/A4, 1280 tokens 236 / 207
+//     tokens    ViT-B block, W3/A8, 12608 tokens 232 / 228   768 x 768, W4/A16, 12608 tokens 39.3 / 34.4   3072 x 768, W3/A16 119 / 115
+// Where the token tiles are a multiple of eight, launch order already gives an XCD token tiles of its own, an eighth of the activations.
+// Ranges of tokens then read no less (768 x 768, W4/A16, 8192 tokens 23.0 / 23.9, 2048 x 1024 71.8 / 74.7) unless the activations are
+// large (1024 x 1024, W4/A16, 24576 tokens, 48 MB, 116 / 106), and ranges of outputs lose for 32 and more token tiles or large outputs (30000 x 512,
+// W4/A4, 4000 tokens 286 / 308; 50257 x 1024, 2048 tokens W4/A4 344 / 363, W3/A6 367 / 386), not for 8 and 16 (1 to 2 % faster).
 // Where both sides are large neither helps (4096 x 4096, 4096 tokens, W3/A8 147 in turn, 149 and 152 in ranges; 7B block, 2048 tokens, W3/A16
 // 1336, 1345, 1380).
-inline int goq_tile_order(int64_t tiles, int64_t x_bytes, int64_t w_bytes)
+inline int goq_tile_order(int64_t tiles, int64_t token_tiles, int64_t x_bytes, int64_t w_bytes, int64_t outputs)
 {
+    const bool own = token_tiles % 8 == 0;
     if (tiles < 512) return GOQ_TILES_IN_TURN;
-    if (x_bytes <= 2 << 20 && w_bytes > 4 << 20) return GOQ_TILES_BY_OUTPUTS;
-    if (w_bytes <= 3 << 20 && x_bytes > 4 << 20) return GOQ_TILES_BY_TOKENS;
+    if (x_bytes <= 2 << 20 && w_bytes > 4 << 20) return own && (token_tiles >= 32 || outputs > 64 << 20) ? GOQ_TILES_IN_TURN : GOQ_TILES_BY_OUTPUTS;
+    if (w_bytes <= 3 << 20 && x_bytes > 4 << 20) return own && x_bytes < 32 << 20 ? GOQ_TILES_IN_TURN : GOQ_TILES_BY_TOKENS;
     return GOQ_TILES_IN_TURN;
 }
 

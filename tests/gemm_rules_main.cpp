@@ -2,7 +2,7 @@
 //     tiles bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64 (tokens per tile)
 //     wide  bw fp16 staged n  tokens out in ..                  ->   128 or 0
 //     alone bw fp16 staged n  tokens out in ..                  ->   1 or 0 (one few-token workgroup per CU)
-//     order tiles x_bytes w_bytes                               ->   0, 1 or 2 (GOQ_TILES_*)
+//     order tiles token_tiles x_bytes w_bytes outputs           ->   0, 1 or 2 (GOQ_TILES_*)
 //     deal  tiles                                               ->   1 if every place is taken once, and by XCD in ranges
 //     few   bw fp16 tokens out in                               ->   1 (few-token kernel) or 0 (tile kernel)
 #include <cstdio>
@@ -16,9 +16,9 @@ int main()
     while (scanf("%7s", what) == 1) {
         int bw, fp16, staged, n;
         if (!strcmp(what, "order")) {
-            long long tiles, x, w;
-            if (scanf("%lld %lld %lld", &tiles, &x, &w) != 3) return 1;
-            printf("%d\n", goq_tile_order(tiles, x, w));
+            long long tiles, own, x, w, y;
+            if (scanf("%lld %lld %lld %lld %lld", &tiles, &own, &x, &w, &y) != 5) return 1;
+            printf("%d\n", goq_tile_order(tiles, own, x, w, y));
             continue;
         }
         if (!strcmp(what, "deal")) {

@@ -216,10 +216,51 @@ def test_a_cu_to_each_workgroup_follows_the_measurements(ask):
     assert not wrong, wrong
 
 
+# layer, weight bits, activations, tokens, tokens per tile, microseconds of single layers with the tiles in turn and in ranges, of 3 % or more
+ORDER = [
+    ("1024x1024", 3, "a16", 16000, 64, 70.0, 64.6),
+    ("1024x512", 3, "a8", 20000, 128, 36.5, 34.1),
+    ("1500x1024", 4, "a16", 12608, 64, 93.3, 87.4),
+    ("768x768", 4, "a16", 12608, 64, 39.3, 34.4),
+    ("768x768", 3, "a8", 25216, 128, 46.1, 43.0),
+    ("768x3072", 3, "a16", 12608, 64, 114.8, 108.4),
+    ("3072x768", 4, "a16", 12608, 64, 132.1, 123.4),
+    ("1024x1024", 4, "a16", 24576, 64, 115.8, 106.5),
+    ("30000x512", 3, "a8", 300, 64, 23.9, 22.1),
+    ("50257x1024", 3, "a4", 400, 64, 81.6, 76.8),
+    ("50257x1024", 4, "a4", 384, 128, 64.6, 61.4),
+    ("50257x1024", 3, "a8", 1576, 128, 252.8, 230.5),
+    ("50257x1024", 4, "a3", 1920, 128, 274.3, 259.4),
+    ("768x768", 3, "a8", 8192, 64, 16.9, 17.4),
+    ("768x768", 4, "a16", 8192, 64, 23.0, 23.9),
+    ("1024x512", 3, "a6", 16384, 64, 32.3, 33.3),
+    ("2048x1024", 4, "a16", 8192, 64, 71.8, 74.7),
+    ("30000x512", 4, "a16", 2048, 64, 155.7, 160.1),
+    ("30000x512", 3, "a8", 4000, 128, 224.0, 243.2),
+    ("30000x512", 4, "a3", 4000, 128, 284.4, 300.8),
+    ("50257x1024", 3, "a6", 2048, 64, 367.0, 385.8),
+    ("50257x1024", 4, "a4", 2048, 128, 343.5, 362.1),
+]
+
+
+def _order_question(out, inn, bw, act, tokens, tile, tiles=None):
+    """What goq_gemm asks for a layer of a launch of `tiles` tiles (a single layer: its own)."""
+    own, gn = -(-tokens // tile), inn // 128
+    return "order %d %d %d %d %d" % (tiles or own * -(-out // 128), own, tokens * gn * {"a16": 256, "a8": 128, "a6": 96, "a4": 64, "a3": 48}[act],
+                                     -(-out // 64) * gn * 1024 * (4 if bw == 3 else 5), tokens * out)
+
+
+def test_order_of_tiles_follows_the_measurements(ask):
+    got = ask([_order_question(*_layers(text)[0], bw, act, tokens, tile) for text, bw, act, tokens, tile, _, _ in ORDER])
+    assert len(got) == len(ORDER)
+    wrong = [(case, g) for case, g in zip(ORDER, got) if (g != "0") != (case[6] < case[5])]
+    assert not wrong, wrong
+
+
 def test_order_of_tiles(ask):
-    MB = 1 << 20
-    # few tokens of a large layer; many of a small one; a large one; one that fits the chip at once; a small layer
-    assert ask(["order 688 %d %d" % (1.6 * MB, 28 * MB), "order 2376 %d %d" % (9 * MB, 1.2 * MB), "order 4096 %d %d" % (16 * MB, 8 * MB),
-                "order 511 %d %d" % (1 * MB, 28 * MB), "order 2000 %d %d" % (1 * MB, 1 * MB)]) == ["2", "1", "0", "0", "0"]
+    # two of 11008 x 4096, 203 tokens; a ViT-B block's layers, 12608 tokens; 4096 x 4096, 4096 tokens; less than two tiles per CU; both sides small
+    lines = [_order_question(11008, 4096, 4, "a16", 203, 64, 688)] + [_order_question(o, i, 3, "a8", 12608, 128, 5346) for o, i in _layers(VIT_B)]
+    lines += [_order_question(4096, 4096, 3, "a8", 4096, 128), _order_question(8064, 4096, 3, "a8", 500, 64), _order_question(2048, 512, 3, "a4", 4096, 64)]
+    assert ask(lines) == ["2"] + ["1"] * 4 + ["0"] * 3
     counts = list(range(1, 70)) + [511, 512, 2376, 4752, 65535]
     assert ask(["deal %d" % n for n in counts]) == ["1"] * len(counts)
