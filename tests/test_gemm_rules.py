@@ -250,6 +250,17 @@ def _order_question(out, inn, bw, act, tokens, tile, tiles=None):
                                      -(-out // 64) * gn * 1024 * (4 if bw == 3 else 5), tokens * out)
 
 
+def launch(ask, bw, act, tokens, layers):
+    """(tokens per tile, orders) of a launch of more than 32 tokens."""
+    float8 = bw == 4 and act in ("a4", "a3")
+    staged = not float8 and act != "a16" and (bw, act) != (3, "a8")
+    sizes = " ".join(["%d" % len(layers)] + ["%d %d %d" % (tokens, o, i) for o, i in layers])
+    wide, tile = ask(["wide %d 0 0 %s" % (bw, sizes), "tiles %d %d %d %s" % (bw, act == "a16", staged, sizes)])
+    tile = 128 if wide == "128" and (float8 or (bw, act) == (3, "a8")) else 64 if float8 else int(tile)
+    tiles = sum(-(-tokens // tile) * -(-o // 128) for o, _ in layers)
+    return tile, ask([_order_question(o, i, bw, act, tokens, tile, tiles) for o, i in layers])
+
+
 def test_order_of_tiles_follows_the_measurements(ask):
     got = ask([_order_question(*_layers(text)[0], bw, act, tokens, tile) for text, bw, act, tokens, tile, _, _ in ORDER])
     assert len(got) == len(ORDER)

@@ -6,6 +6,7 @@ import pytest
 
 import goq_inputs
 from tests import gpu_util as gu
+from tests.test_gemm_rules import ask, launch                      # (ask: a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -274,10 +275,11 @@ def test_tiles_of_128_tokens(oracle, bw, act, tokens, out, inn):
 
 
 @pytest.mark.parametrize("bw,act", [(3, "A16"), (4, "A16"), (3, "A8"), (4, "A8"), (4, "A4")])
-@pytest.mark.parametrize("tokens,out,inn", [(165, 33001, 640), (9001, 1500, 512)])
-def test_tiles_in_ranges(oracle, bw, act, tokens, out, inn):
+@pytest.mark.parametrize("tokens,out,inn,order", [(165, 33001, 640, "2"), (16950, 1500, 512, "1")])
+def test_tiles_in_ranges(oracle, ask, bw, act, tokens, out, inn, order):
     """Launches whose tiles are dealt to the XCDs in ranges of outputs and of tokens, ragged in both directions: every output is
     written, and sampled rows are the oracle's."""
+    assert launch(ask, bw, act.lower(), tokens, [(out, inn)]) == (128 if act == "A4" and order == "1" else 64, [order])
     import paper_2605_26092_amd as goq
     print("ranges %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
     q = goq_inputs.canonical_random(bw, out, inn, config_id=71, tensor_id=tokens)
@@ -288,3 +290,27 @@ def test_tiles_in_ranges(oracle, bw, act, tokens, out, inn):
     ref = oracle.gemm_a16(q, x[rows], threads=8) if sx is None else oracle.gemm_a8(q, x[rows], sx[rows], threads=8, want_partials=True)[0]
     scale = (np.abs(x[rows].astype(np.float64)) * (1.0 if sx is None else sx[rows][:, None])) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30
     assert np.max(np.abs(Y[rows].cpu().numpy().astype(np.float64) - ref) / scale) <= 2e-6
+
+
+@pytest.mark.parametrize("bw,act", [(3, "A16"), (3, "A8"), (4, "A8"), (4, "A4")])
+@pytest.mark.parametrize("tokens,layers,order", [(165, [(33001, 640), (20001, 512)], "2"), (16950, [(1500, 640), (1000, 512)], "1")])
+def test_ranges_of_a_second_layer(ask, bw, act, tokens, layers, order):
+    """A batch whose second layer does not begin at a multiple of eight workgroups, so that its ranges belong to other XCDs than the
+    first one's: the bits of single calls."""
+    import paper_2605_26092_amd as goq
+    from paper_2605_26092_amd import binding
+    print("ranges of two %s bw=%d %d tokens %s" % (act, bw, tokens, layers), flush=True)
+    tile, orders = launch(ask, bw, act.lower(), tokens, layers)
+    assert orders == [order] * 2 and -(-tokens // tile) * -(-layers[0][0] // 128) % 8
+    torch = gu.torch_cuda()
+    problems, single = [], []
+    for out, inn in layers:
+        q = goq_inputs.canonical_random(bw, out, inn, config_id=74, tensor_id=out)
+        xd, sxd, _, _ = _inputs(goq, act, tokens, inn)
+        single.append(_run(goq, bw, act, q, tokens, xd, sxd, goq.F16)[0])
+        Y = torch.full((tokens, out), float("nan"), dtype=torch.float16, device="cuda")
+        problems.append((tokens, out, inn, gu.pack_layer(goq, q), xd, sxd, Y, goq.F16))
+    goq.gemm_batch(bw, getattr(goq, act), binding.make_gemm_descs(problems))
+    torch.cuda.synchronize()
+    for p, y in zip(problems, single):
+        assert torch.equal(p[6], y)
