@@ -93,7 +93,7 @@ def _stream(stream):
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
-def _current_stream():
+def _first_current_stream():
     """The current stream of the current device.  The first call goes through torch's stream object, which initialises the
     device; later ones ask for the handle itself (2.9 -> 0.2 us; goq.gemm of a small layer 8.0 -> 5.5 us of host time, which
     bounded 4096 x 4096 with 5 tokens: 6.9 -> 5.4 us)."""
@@ -104,6 +104,16 @@ def _current_stream():
     if raw is not None and device is not None:
         _current_stream = lambda: raw(device())
     return handle
+
+
+def _forget_current_stream():
+    global _current_stream
+    _current_stream = _first_current_stream
+
+
+_current_stream = _first_current_stream
+# (a forked child has no usable device: torch says so when it is asked for a stream, the raw handle would just be launched on)
+os.register_at_fork(after_in_child=_forget_current_stream)
 
 
 def _check(rc):
