@@ -703,13 +703,14 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
         if (slot == 0 && idx != i0) {
             const int ns = min(SW, i1 - idx);
             uint32_t next[4];
-            // The thread's slot, run and table addresses are worked out again: kept from the first window through
-            // the loop they cost 10 registers, and spills in five of the twenty instances (us, kept / again: 70B layer
-            // W3/A16 77.6 / 76.9, W4/A3 109.9 / 101.4; two of 28672 x 8192, W4/A3 63.1 / 58.0).
+            __syncthreads();                                   // everyone is done with the old window
+            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, tid, next);
+            // The thread's addresses in the digit table are worked out again: kept from the first window through the loop
+            // they cost registers that five of the twenty instances did not have (us, kept / again: 70B layer W3/A16 77.0 / 75.4,
+            // W4/A3 109.7 / 99.7; two of 28672 x 8192, W4/A3 63.1 / 58.0).  With the addresses of the loads worked out again as
+            // well there are fewer registers in use, but the 7B block, W3/A16, takes 22.9 instead of 22.5.
             int t = tid;
             asm("" : "+v"(t));
-            __syncthreads();                                   // everyone is done with the old window
-            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, t, next);
             stage_window<ACT>(ns, xtab + XZ, stab, t, next);
             __syncthreads();
         }
