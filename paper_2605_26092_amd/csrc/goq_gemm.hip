@@ -28,17 +28,17 @@
 // takes micro-block 8 kg + t of lane group kg.  The activation tile of the slab is staged in LDS
 // (XOR-swizzled 16-byte pieces against bank conflicts) and read as the MFMA A operand.
 //
-// Tiling: workgroup = 4 wavefronts, tile 64 (or 32) tokens x 128 outputs; each wavefront owns 64 tokens x
-// 32 outputs = two MFMA tiles of 32 x 32, with three accumulator sets: the slab partials P1, P2
-// (restarted every slab by feeding C = 0 to the slab's first MFMA) and the output Y.  That fits
-// three wavefronts per SIMD.  Measured on this chip with a probe of the same instruction mix:
+// Tiling: workgroup = 4 wavefronts, tile 32, 64 or 128 tokens x 128 outputs (chosen per launch, goq_gemm_rules.h); with 64 each
+// wavefront owns 64 tokens x 32 outputs = two MFMA tiles of 32 x 32, with three accumulator sets: the slab partials P1, P2
+// (restarted every slab by feeding C = 0 to the slab's first MFMA) and the output Y.  That fits three wavefronts per SIMD for W3
+// with fp16 or int8 activations, two for the other types; tiles of 128 tokens run at two.  Measured on this chip with a probe of the same instruction mix:
 // vector-ALU instructions hide only to a small extent behind matrix instructions, whatever the
 // program order (about five per 32x32x16 instruction; every further one costs nearly its full
 // four cycles), so the rate is set by vector-ALU and LDS instructions per matrix instruction.
 // The 32x32x16 instruction halves both per flop compared with 16x16x32 at the same tile.  A
-// 128-token tile (one wavefront per SIMD) spreads the decode over more matrix instructions but
-// needs the partials in accumulator registers, which the rescale can only read through copies:
-// it measured slower.
+// 128-token tile spreads the decode over more matrix instructions, but with all its slab partials open at a time it
+// runs at one wavefront per SIMD with partials in accumulator registers, which the rescale can only read through copies: slower.
+// With two open at a time (MS = 4 below) it is the fastest form where the operands are narrow.
 // Pipeline: activations of slab g + 2 are requested (buffer loads straight into one of three
 // LDS buffers) and the weights of slab g + 1 (registers) at the start of slab g; inside a slab
 // every k-step's MFMAs run on operands prepared during the previous k-step; one barrier per slab, which
@@ -73,7 +73,8 @@ constexpr int TN = GOQ_TILE_OUT;   // outputs per workgroup tile
 constexpr int WN = 32;             // outputs per wavefront
 // Where the int8 slab sums of a 128-token tile begin: the bits of an fp32 number inside [2^-3, 2^-2), whose last place is 2^-26, so
 // that START + P, read as fp32, is that number + 2^-26 P exactly (|P| <= 2^17; the binade has room for -2.2 and +6.0 million
-// last places).  The subtraction that takes P out again is exact too and takes 2 cycles where the conversion of an integer
+// last places).  Of the numbers there this one, 1 / (2 pi), is an inline constant of the instruction set: the subtraction needs neither
+// a register nor a literal for it.  It is exact too and takes 2 cycles where the conversion of an integer
 // takes 4; 4096 x 4096, 4096 tokens, W3/A8 148 -> 145 us.  (Tiles of 64 tokens have no 16 registers left for it.)
 constexpr int START = 0x3e22f983;
 
@@ -151,7 +152,8 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
 // weight is rounded to fp16 (2^-11 relative), which the two-basis path avoids.
 // MS: MFMA tiles along tokens per wavefront (the workgroup's tile has 32 MS tokens).  With four of them a wavefront keeps the
 // decoded weights of the slab (32 registers) and goes through its tiles one after the other, so that two slab sums are
-// open at a time and not eight: that fits two wavefronts per SIMD, and a weight is decoded once per 128 tokens.  Worth it where
+// open at a time and not eight: that fits two wavefronts per SIMD (W3 249 registers; W4 all 256 and seven spilled, six of them for the end of the
+// tile, one read back once in three slabs), and a weight is decoded once per 128 tokens.  Worth it where
 // decode weighs most and operands are narrow, for int8 operands straight from memory and 8-bit floats (us, 64 / 128 tokens: 4096 x
 // 4096, 4096 tokens, W3/A8 170 / 145, W4/A4 182 / 152; ViT-B block, 12608 tokens, W4/A4 314 / 273; packed activations with
 // W3 lose, 183 / 191: their staging needs the registers).
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     __syncthreads();
 
     // ---- store the tile (H6).  A lane holds single elements of 16 tokens; a wavefront turns its outputs 2 KiB at a
-    // time in LDS (no other wavefront takes part) and stores rows of 32 in 16-byte pieces.  Single elements cost eight
+    // time in LDS (no other wavefront takes part) and stores rows of 32 in 16-byte pieces.  Single elements cost eight (fp32: four)
     // times the store instructions, and with integer activations each waited for its token's scale, which was loaded
     // behind the store before it: 32 round trips to memory per tile, half the time of a tile of six slabs (us, single
     // elements / pieces: ViT-B block, 12608 tokens, W3/A8 296 / 259; 1576 tokens, W4/A4 55.0 / 44.2; two of

@@ -139,8 +139,8 @@ inline int goq_tile_order(int64_t tiles, int64_t token_tiles, int64_t x_bytes, i
 //     16 tokens, W3/A16   32000 x 4096 23 / 28   128256 x 4096 72 / 77   30000 x 768 8.1 / 8.4
 // Gate and up in one launch have twice the rows and the same answer: two layers of 13824 x 5120, 32 tokens, W3/A8 39 /
 // 32, W3/A16 51 / 34, W4/A16 56 / 41.  (The tile kernel as it was before there was another took 42, 50, 49; so that
-// no pair is slower than that, W4 with fp16 ends at 12288 outputs.  Four layers of 14336 x 4096 in one launch are, 73
-// against 62.)
+// no pair is slower than that, W4 with fp16 ends at 12288 outputs.  Four layers of 14336 x 4096 in one launch are: 32 tokens,
+// W3/A16 72, the tile kernel with 33 tokens 60.)
 // In layers of less than eight macro-blocks some of its wavefronts have no slab: 2 tokens, W3/A8, 60000 x
 // 256 8.2 / 5.4 us, 16384 x 256 4.4 / 5.6.
 inline bool goq_few_tokens(int bw, bool fp16, int64_t tokens, int64_t out, int64_t gn)

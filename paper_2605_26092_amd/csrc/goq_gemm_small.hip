@@ -20,7 +20,7 @@
 //       from global memory (every workgroup reads all of X, which L2 holds), so nothing is
 //       staged and no barrier stands before the final sum.
 // Measured against the tile kernel (one launch, us, weights of three copies in turn): 4096 x 4096, 5 tokens,
-// W4/A16: 38.2 -> 7.4; the seven matrices of a LLaMA-2-7B block, 16 tokens, W3/A16: 105 -> 33.3.
+// W4/A16: 38.2 -> 4.8; the seven matrices of a LLaMA-2-7B block, 16 tokens, W3/A16: 105 -> 32.4.
 // (Tried: activations through LDS in whole rows, 36 us for the block; micro-block 4 t + q per lane, so that
 // lanes of a load lie side by side but weights come in dwords: 52 us; four wavefronts: no gain.)
 // Integer activations are widened to fp16 in registers; int8 values and powers of two down to 2^-7

@@ -839,21 +839,22 @@ __global__ __launch_bounds__(256) void workspace_init_kernel(Region *ws)
 // GEMMs (goq_gemm_small.hip) with one token: a workgroup owns 16 output rows over the whole depth,
 // its eight wavefronts take the macro-blocks round-robin and add up in LDS.  It reads x straight into fp16
 // matrix operands; a kernel of the same shape on the digits of this file spent half a microsecond and two
-// barriers per window on staging them (us, that kernel / this: W3/A16 4096 x 4096 5.07 / 4.66, 4096 x 11008
-// 11.2 / 8.6, 1024 x 8192 7.9 / 6.8; W4/A8 4096 x 4096 6.5 / 5.9, 4096 x 11008 14.3 / 11.4).  The line: beyond 512 tiles
+// barriers per window on staging them (us, that kernel / this, when it was replaced: W3/A16 4096 x 4096 5.07 / 4.66, 4096 x 11008
+// 11.2 / 8.6; the streaming kernel / this now: W3/A16 4096 x 4096 9.0 / 4.3, 4096 x 11008 19.7 / 8.3, 1024 x 8192 12.3 / 6.2; W4/A8
+// 4096 x 4096 9.5 / 5.4, 4096 x 11008 21.6 / 11.4).  The line: beyond 512 tiles
 // or 24576 (tile, macro-block) pairs the streaming kernel's equal pieces win where several layers
-// share a launch (streaming / few-token: W3/A16 gate + up 13.9 / 13.9, W4/A8 17.6 / 18.4, the 7B block 23.3 / 30.2).
-// Single layers and small groups a little beyond it are faster in the few-token kernel (8192 x 8192 13.1 / 10.9, 11008 x 4096
-// 11.3 / 10.1, three of 4096 x 4096 11.5 / 10.2, 8192 x 8192 W4/A8 15.3 / 14.4): the line is that of the kernel this one
+// share a launch (streaming / few-token: gate + up W3/A16 14.5 / 16.3, W4/A8 18.4 / 20.5, the 7B block 22.8 / 31.9).
+// Single layers and small groups beyond it are 10 to 27 % faster in the few-token kernel (8192 x 8192 13.3 / 11.0, W4/A8 15.8 / 14.2,
+// 11008 x 4096 11.8 / 8.6, W4/A8 13.9 / 11.1, three of 4096 x 4096 12.0 / 10.1): the line is that of the kernel this one
 // replaced, and goq_gemv_plan tells callers about it; a better one has not been drawn yet.
 constexpr int ROWS_MAX_TILES = 512;      // automatic choice: largest grid ...
 constexpr int ROWS_MAX_SLICES = 24576;   // ... and most (tile, macro-block) slices per launch
 
 // Packed activations (int6, int4, int3) keep a kernel of that split on the digits, gemv_rows_kernel: in the
 // few-token kernel all 16 token lanes of an operand unpack the one token there is, here a thread unpacks a run of 8
-// once per workgroup (us, digits / few-token kernel: W3/A6 8192 x 4096 7.6 / 9.4, 4096 x 4096 5.7 / 6.3, 1024 x 29952
-// 22.9 / 28.1; W3/A4 8192 x 4096 7.5 / 8.2; W4/A3 2048 x 16384 17.5 / 18.5; only W4/A4 gains at some depths, 4096 x
-// 11008 14.6 / 12.2, and loses at full grids, three layers of 444 tiles 8.9 / 9.4).
+// once per workgroup (us, digits / few-token kernel: W3/A6 8192 x 4096 6.5 / 8.8, 4096 x 4096 4.8 / 5.7, 1024 x 29952
+// 22.5 / 27.5; W3/A4 8192 x 4096 6.6 / 7.5; W4/A3 2048 x 16384 16.9 / 17.7; only W4/A4 gains at some depths, 4096 x
+// 11008 13.4 / 11.6, and loses at full grids, three of 2368 x 4096 8.0 / 9.2).
 constexpr int RW = NT / 16;              // macro-blocks staged per window: one run per thread
 constexpr int RS = RW / WAVES;           // slices per wavefront and window
 struct Slice {
