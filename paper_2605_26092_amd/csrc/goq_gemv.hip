@@ -286,6 +286,7 @@ __device__ __forceinline__ void load_run(const void *x, int g, int r, uint32_t (
         // dword only when they start at byte 2 or 3 of theirs (never for the last run)
         const gptr p = (gptr)x + ((int64_t)g * 12 + ((3 * r) >> 2));
         raw[0] = p[0];
+        raw[1] = 0u;
         if (((3 * r) & 3) > 1) raw[1] = p[1];
     } else {
         // the run's 6 bytes start at byte 6 r of the macro-block's 96: in the two dwords from dword
