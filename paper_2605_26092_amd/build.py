@@ -14,7 +14,7 @@ EXTRA = {"goq_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"],
          "goq_gemm_small.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=8"]}
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
-         # packed fp32 VALU forms are kept off on the test machines
+         # packed fp32 VALU forms stay off: some of them have given wrong results on this chip
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 
