@@ -413,20 +413,32 @@ __device__ __forceinline__ Stream stream_of(const Problems<TABLE> &pb, int pi)
 }
 
 // Activations of the units [u0, u0 + ns) of the sequence, unit s for table slot s.  Thread
-// (slot = tid / 16, run = tid % 16); ns <= SW = NT / 32.  u0 lies in problem pi0, whose units end
-// at end0; units past it belong to the following problems.
-template <int ACT, bool TABLE>
-__device__ __forceinline__ void load_window(const Problems<TABLE> &pb, int pi0, int end0, int u0, int ns, int tid, uint32_t (&raw)[4])
+// (slot = tid / 16, run = tid % 16); ns <= SW = NT / 32.  u0 lies in problem pi0 = S; units past its end belong
+// to the following problems.  A FIRST window inside one problem takes that problem's fields as scalars: looked up by each thread, the
+// activations are requested a round trip later, and so are the weights behind them (us, looked up / scalars: 20480 x 2048 W3/A16 10.4 / 9.8, W4/A4
+// 12.2 / 11.8; three of 4096 x 4096 W3/A6 12.3 / 12.0; 17184 x 1152, two layers, W3/A6 10.8 / 9.9; 7B block and streams within 1 %).  Later windows have the
+// unit in work to hide that, and scalars there gained nothing.
+template <int ACT, bool TABLE, bool FIRST>
+__device__ __forceinline__ void load_window(const Problems<TABLE> &pb, int pi0, const Stream &S, int u0, int ns, int tid, uint32_t (&raw)[4])
 {
+    const uint64_t px = FIRST ? (uint64_t)pb[pi0].x : 0;
+    const void *x = (const void *)(((uint64_t)(uint32_t)uniform((int)(px >> 32)) << 32) | (uint32_t)uniform((int)px));
     if (tid < ns * 16) {
         const int u = u0 + (tid >> 4);
-        int pi = pi0;
-        if (u >= end0) {
-            ++pi;
-            while (pi + 1 < pb.n() && u >= pb[pi + 1].begin) ++pi;
+        int g;
+        if (FIRST && u0 + ns <= S.end) {
+            g = (u - S.begin) % S.gn;
+        } else {
+            int pi = pi0;
+            if (u >= S.end) {
+                ++pi;
+                while (pi + 1 < pb.n() && u >= pb[pi + 1].begin) ++pi;
+            }
+            const auto &P = pb[pi];
+            x = P.x;
+            g = (u - P.begin) % P.gn;
         }
-        const auto &P = pb[pi];
-        load_run<ACT>(P.x, (u - P.begin) % P.gn, tid & 15, raw);
+        load_run<ACT>(x, g, tid & 15, raw);
     }
 }
 // Their digits, unit s into table slot s.
@@ -672,7 +684,7 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
     constexpr bool KEEP = (BW == 3);
     Stream S = stream_of<KEEP>(pb, cur.pi);
     uint32_t raw[4];
-    load_window<ACT, TABLE>(pb, cur.pi, S.end, i0, min(SW, i1 - i0), tid, raw);
+    load_window<ACT, TABLE, true>(pb, cur.pi, S, i0, min(SW, i1 - i0), tid, raw);
     asm volatile("" ::: "memory");
     load_unit<BW>(S.packed, S.gn, min(cur.rg * WAVES + wave, S.rbn - 1), cur.g, lane, bufA);
 
@@ -705,7 +717,7 @@ __device__ __forceinline__ void stream_piece(const Problems<TABLE> &pb, const Pi
             const int ns = min(SW, i1 - idx);
             uint32_t next[4];
             __syncthreads();                                   // everyone is done with the old window
-            load_window<ACT, TABLE>(pb, cur.pi, S.end, idx, ns, tid, next);
+            load_window<ACT, TABLE, false>(pb, cur.pi, S, idx, ns, tid, next);
             // The thread's addresses in the digit table are worked out again: kept from the first window through the loop
             // they cost registers that five of the twenty instances did not have (us, kept / again: 70B layer W3/A16 77.0 / 75.4,
             // W4/A3 109.7 / 99.7; two of 28672 x 8192, W4/A3 63.1 / 58.0).  With the addresses of the loads worked out again as

@@ -49,6 +49,47 @@ def test_first_weights_are_requested_while_activations_are_on_their_way(assembly
     assert not late
 
 
+def _first_weights_follow_activations(body):
+    """Is there a way from the start of a kernel to its first non-temporal load (of weights) on which another load, of activations, is
+    on its way and no load has been waited for?"""
+    code, at = [], {}
+    for line in body.splitlines():
+        line = line.split(";")[0].strip()
+        if line.endswith(":"):
+            at[line[:-1]] = len(code)
+        elif line and not line.startswith("."):
+            code.append(line)
+    todo, seen = [(0, False)], set()
+    while todo:
+        i, pending = todo.pop()
+        while (i, pending) not in seen and i < len(code):
+            seen.add((i, pending))
+            op = code[i]
+            if op.startswith("global_load"):
+                if op.endswith(" nt"):
+                    if pending:
+                        return True
+                    break
+                pending = True
+            elif op.startswith("s_waitcnt") and "vmcnt" in op and pending or op.startswith("s_endpgm"):
+                break
+            elif op.startswith("s_branch"):
+                i = at[op.split()[1]]
+                continue
+            elif op.startswith("s_cbranch"):
+                todo.append((at[op.split()[1]], pending))
+            i += 1
+    return False
+
+
+def test_first_window_of_one_problem_is_requested_without_a_look_up(assembly):
+    """Where the first window lies inside one problem no thread reads the problem's fields for itself: weights requested behind the
+    activations would come two round trips later."""
+    kernels = _bodies(assembly("goq_gemv.hip"), "gemv_(?:stream_)?kernel")
+    assert len(kernels) == 20
+    assert not [name for name, body in kernels if not _first_weights_follow_activations(body)]
+
+
 @pytest.mark.parametrize("bw", [3, 4])
 def test_next_slab_is_requested_before_the_matrix_instructions(assembly, bw):
     """Few-token kernel, int8, two token tiles, one row tile: the loads of the next slab stand before the work on this one."""
