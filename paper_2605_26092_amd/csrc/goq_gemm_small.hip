@@ -155,6 +155,10 @@ __device__ __forceinline__ void few_tokens(const SmallArgs &a, int rows)
         gbytes xg = xbase + (int64_t)g * XROW;
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
+            // (W4 with int3, one row tile: the order of the requests is kept.  Left alone the compiler puts some of them behind half of this
+            // slab's matrix instructions; us, 17 to 31 tokens: 2133 x 2048 and 342 x 2048 6.4 / 6.15, 3026 x 1664 6.6 / 6.4, 756 x 1920 6.1 / 5.9.
+            // Two row tiles lose by it, 11862 x 1536 11.7 / 12.0; int8 is held by its registers, see below.)
+            if constexpr (BW == 4 && ACT == GOQ_A3 && MT == 2 && RT == 1) asm volatile("" ::: "memory");
             if constexpr (SlabT::XW % 4 == 0) {
 #pragma unroll
                 for (int i = 0; i < SlabT::XW / 4; ++i) {

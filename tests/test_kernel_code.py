@@ -90,10 +90,10 @@ def test_first_window_of_one_problem_is_requested_without_a_look_up(assembly):
     assert not [name for name, body in kernels if not _first_weights_follow_activations(body)]
 
 
-@pytest.mark.parametrize("bw", [3, 4])
-def test_next_slab_is_requested_before_the_matrix_instructions(assembly, bw):
-    """Few-token kernel, int8, two token tiles, one row tile: the loads of the next slab stand before the work on this one."""
-    (_, body), = _bodies(assembly("goq_gemm_small.hip"), "gemm_small_kernelILi%dELi1ELi2ELi1ELb0E" % bw)
+@pytest.mark.parametrize("bw,act", [(3, 1), (4, 1), (4, 4)])
+def test_next_slab_is_requested_before_the_matrix_instructions(assembly, bw, act):
+    """Few-token kernel, int8 and W4 with int3, two token tiles, one row tile: the loads of the next slab stand before the work on this one."""
+    (_, body), = _bodies(assembly("goq_gemm_small.hip"), "gemm_small_kernelILi%dELi%dELi2ELi1ELb0E" % (bw, act))
     loops = 0
     for block in re.split(r"^\.LBB\S*:", body, flags=re.M):
         ops = re.findall(r"^\s+(global_load|v_mfma)", block, re.M)
