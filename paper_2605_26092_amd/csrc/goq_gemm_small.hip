@@ -155,10 +155,11 @@ __device__ __forceinline__ void few_tokens(const SmallArgs &a, int rows)
         gbytes xg = xbase + (int64_t)g * XROW;
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-            // (W4 with int3, one row tile: the order of the requests is kept.  Left alone the compiler puts some of them behind half of this
-            // slab's matrix instructions; us, 17 to 31 tokens: 2133 x 2048 and 342 x 2048 6.4 / 6.15, 3026 x 1664 6.6 / 6.4, 756 x 1920 6.1 / 5.9.
-            // Two row tiles lose by it, 11862 x 1536 11.7 / 12.0; int8 is held by its registers, see below.)
-            if constexpr (BW == 4 && ACT == GOQ_A3 && MT == 2 && RT == 1) asm volatile("" ::: "memory");
+            // (One row tile, W4 with int3 and W3 with int8: the order of the requests is kept.  Left alone the compiler puts some of them behind half of
+            // this slab's matrix instructions, or behind the wait for all of this slab; us, 17 to 31 tokens: W4/A3 2133 x 2048 and 342 x 2048 6.4 / 6.15,
+            // 3026 x 1664 6.6 / 6.4; W3/A8 4734 x 2816 8.5 / 8.4, 5865 x 10112 20.3 / 20.2.  Two row tiles lose by it, W4/A3 11862 x 1536 11.7 / 12.0; W4 with
+            // int8 needs 130 registers for it, so that no two workgroups fit a CU.)
+            if constexpr ((BW == 4 ? ACT == GOQ_A3 : ACT == GOQ_A8) && MT == 2 && RT == 1) asm volatile("" ::: "memory");
             if constexpr (SlabT::XW % 4 == 0) {
 #pragma unroll
                 for (int i = 0; i < SlabT::XW / 4; ++i) {
