@@ -853,12 +853,12 @@ __global__ __launch_bounds__(256) void workspace_init_kernel(Region *ws)
 // its eight wavefronts take the macro-blocks round-robin and add up in LDS.  It reads x straight into fp16
 // matrix operands; a kernel of the same shape on the digits of this file spent half a microsecond and two
 // barriers per window on staging them (us, that kernel / this, when it was replaced: W3/A16 4096 x 4096 5.07 / 4.66, 4096 x 11008
-// 11.2 / 8.6; the streaming kernel / this now: W3/A16 4096 x 4096 9.0 / 4.3, 4096 x 11008 19.7 / 8.3, 1024 x 8192 12.3 / 6.2; W4/A8
-// 4096 x 4096 9.5 / 5.4, 4096 x 11008 21.6 / 11.4).  The line: beyond 512 tiles
+// 11.2 / 8.6; the streaming kernel / this now: W3/A16 4096 x 4096 8.8 / 4.4, 4096 x 11008 20.3 / 8.3, 1024 x 8192 12.2 / 6.2; W4/A8
+// 4096 x 4096 9.5 / 5.5, 4096 x 11008 21.5 / 11.5).  The line: beyond 512 tiles
 // or 24576 (tile, macro-block) pairs the streaming kernel's equal pieces win where several layers
-// share a launch (streaming / few-token: gate + up W3/A16 14.5 / 16.3, W4/A8 18.4 / 20.5, the 7B block 22.8 / 31.9).
-// Single layers and small groups beyond it are 10 to 27 % faster in the few-token kernel (8192 x 8192 13.3 / 11.0, W4/A8 15.8 / 14.2,
-// 11008 x 4096 11.8 / 8.6, W4/A8 13.9 / 11.1, three of 4096 x 4096 12.0 / 10.1): the line is that of the kernel this one
+// share a launch (streaming / few-token: gate + up W3/A16 14.4 / 16.6, W4/A8 18.4 / 20.8, the 7B block 23.6 / 32.5).
+// Single layers and small groups beyond it are 6 to 25 % faster in the few-token kernel (8192 x 8192 13.5 / 11.1, W4/A8 15.6 / 14.7,
+// 11008 x 4096 11.5 / 8.6, W4/A8 13.6 / 11.0, three of 4096 x 4096 11.7 / 9.8): the line is that of the kernel this one
 // replaced, and goq_gemv_plan tells callers about it; a better one has not been drawn yet.
 constexpr int ROWS_MAX_TILES = 512;      // automatic choice: largest grid ...
 constexpr int ROWS_MAX_SLICES = 24576;   // ... and most (tile, macro-block) slices per launch
