@@ -11,13 +11,13 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 
-def _run(goq, bw, w16):
+def _run(goq, bw, w16, offset=0):
+    """offset: of pattern and signs from where an allocation begins"""
     torch = gu.torch_cuda()
     out, inn = w16.shape
     wd = gu.to_dev(w16.view(np.uint16))
     codes = torch.full((out, inn), 255, dtype=torch.uint8, device="cuda")
-    pat = torch.full((out, inn // 8), 255, dtype=torch.uint8, device="cuda")
-    sg = torch.full((out, inn // 8), 255, dtype=torch.uint8, device="cuda")
+    pat, sg = (torch.full((out * inn // 8 + offset,), 255, dtype=torch.uint8, device="cuda")[offset:].view(out, -1) for _ in range(2))
     c1 = torch.full((out, inn // 128), -1, dtype=torch.int16, device="cuda")
     c2 = torch.full((out, inn // 128), -1, dtype=torch.int16, device="cuda")
     goq.quantize(bw, out, inn, wd, codes, pat, sg, c1, c2)
@@ -113,3 +113,23 @@ def test_quantize_signs_of_zero(oracle, bw):
     w = np.where(kind < 0.4, sign * 0.0, np.where(kind < 0.6, sign * 2.0 ** r.integers(-24, -8, kind.shape), w))
     w = w.astype(np.float16)
     _same(_run(goq, bw, w), oracle.quantize_geo(bw, w, threads=4))
+
+
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("shape", [(1, 128), (2, 640), (189, 16640), (199, 16640)])
+def test_quantize_coefficients_at_midpoints(oracle, bw, shape):
+    """Coefficients on and next to midpoints of two fp16 numbers: half a macro-block's weights one fp16 step above the other
+    half, and a few small ones that move the quotient by less than fp32 can tell.  Last groups of one to four macro-blocks, one
+    and two groups per round (24570 and 25870 macro-blocks), patterns and signs that begin at any byte."""
+    import paper_2605_26092_amd as goq
+    out, inn = shape
+    print("midpoints bw=%d out=%d in=%d" % (bw, out, inn), flush=True)
+    r = np.random.default_rng(out)
+    n = out * inn // 128
+    base = r.uniform(0.6, 0.95, (n, 1)).astype(np.float16)
+    step = np.spacing(base)
+    w = np.where(np.arange(128) % 2 == 0, base, base + step)
+    small = r.random((n, 128)) < r.choice([0.0, 0.0, 0.02, 0.1], size=(n, 1))
+    w = np.where(small & (np.arange(128) < 126), w * 2.0 ** -r.integers(1, 4, (n, 128)) * r.uniform(0.9, 1.1, (n, 128)), w) * 2.0 ** -r.integers(0, 18, (n, 1))
+    w = (w * np.where(r.random((n, 1)) < 0.5, 1, r.choice([-1, 1], (n, 128)))).astype(np.float16).reshape(out, inn)
+    _same(_run(goq, bw, w, offset=out % 4), oracle.quantize_geo(bw, w, threads=8))
