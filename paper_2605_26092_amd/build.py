@@ -11,6 +11,7 @@ LIB = os.path.join(HERE, "libgoq.so")
 # per-file extras: leading scalar kernel arguments that arrive in scalar registers (the GEMV's, and those of a
 # few-token launch of one problem)
 EXTRA = {"goq_gemv.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"],
+         "goq_gemv_short.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=9"],
          "goq_gemm_small.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=8"]}
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

@@ -1,0 +1,336 @@
+// What the batch-1 kernels share: the problems of a launch, activations as digits, and a 16-row slice of a macro-block
+// against them (goq_gemv.hip says why they look like this).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+#include <stdint.h>
+#include "goq_layout.h"
+#include "goq_decode.h"
+#include "goq_internal.h"
+
+struct GemvProblem {
+    const uint32_t *packed;
+    const void *x;
+    const float *sx;
+    void *y;
+    int out;
+    int gn;          // macro-blocks per row
+    int ytype;
+    int rbn;         // row blocks
+    int rgroups;     // row groups
+    int begin;       // first unit of this problem in the linear unit sequence
+    int bb;          // first 16-row block of this problem in the launch
+    int cost;        // (16-row block, macro-block) slices of the launch before this problem
+};
+
+// Launches of a few projections up to a decoder block (goq_gemv_short.hip): does this one go there?  p: with bb and cost filled in.
+bool goq_gemv_short(int bw, int act, int n, const GemvProblem *p);
+// table: the problems in device memory, or NULL to pass them as arguments
+int goq_launch_gemv_short(hipStream_t st, int bw, int act, int n, const GemvProblem *p, const GemvProblem *table);
+
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// (explicitly global-memory pointers: generic ones would turn loads into flat loads, which the LDS
+// wait counter has to wait for as well)
+typedef const __attribute__((address_space(1))) uint32_t *gptr;
+typedef const __attribute__((address_space(1))) u32x4 *gptr4;
+
+constexpr int XG = 1024;                 // bytes of digits per macro-block: 4 k-groups x 8 digits x 32
+constexpr int XZ = 256;                  // zero bytes in front of the digit table
+#ifndef GOQ_VCOPIES
+#define GOQ_VCOPIES 16
+#endif
+constexpr int VC = GOQ_VCOPIES;          // copies of the exchange table in LDS (a lane uses copy lane % VC)
+constexpr int VS = VC * 16;              // bytes from one entry to the next
+
+// Where the problems of a launch live: in the kernel arguments (up to GOQ_MAX_BATCH) or in a
+// table in device memory.
+template <bool TABLE>
+struct Problems;
+// (Kernel arguments are read through the kernel-argument segment pointer: indexing the by-value
+// argument struct with a run-time index inside loops makes the compiler copy it to scratch.)
+template <>
+struct Problems<false> {
+    typedef const __attribute__((address_space(4))) GemvProblem Entry;
+    Entry *t;
+    int cnt;
+    __device__ __forceinline__ Entry &operator[](int i) const { return t[i]; }
+    __device__ __forceinline__ int n() const { return cnt; }
+};
+template <>
+struct Problems<true> {
+    const GemvProblem *__restrict__ t;
+    int cnt;
+    __device__ __forceinline__ const GemvProblem &operator[](int i) const { return t[i]; }
+    __device__ __forceinline__ int n() const { return cnt; }
+};
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// ---- activation digits ----------------------------------------------------------------------
+// The 8-bit-float matrix instruction adds the products of 8 consecutive k on a grid that ends 13
+// binary places below the largest exponent sum of the 8 (measured); anything lower is cut off.
+// Floating-point pieces of x (own exponent per element) would therefore lose bits whenever a
+// micro-block mixes large and small activations.  So x is handed over as block FIXED point: for
+// each block of 32 activations that share an MFMA block scale, with largest exponent E, |x_k| is
+// written with 24 bits below 2^(E+1) -- every fp16 value within 2^13 of the block maximum exactly,
+// smaller ones truncated at 2^(E-23), the same footing as an fp32 sum -- and cut into 8 digits of
+// 3 bits.  Digit i of the block is an E5M2 operand (0..7 are exact in E5M2) with the block scale
+// 2^(E-2-3i), applied by the MFMA's per-lane E8M0 scale.  Inside a micro-block all products are
+// now (3-bit digit) x (power of two >= 2^-7): at most 13 binary places, so the instruction's grid
+// keeps every bit, and D = sum_k digit_k b_k is exact.
+//
+// Which 32 activations share a block scale is fixed by the instruction (measured): the scale a
+// lane of lane-group Q supplies covers, of the A row it holds, register halves (bytes 0..15 for
+// Q = 0, 1; bytes 16..31 for Q = 2, 3) of the two k-groups 2 (Q % 2) and 2 (Q % 2) + 1.  In
+// micro-blocks m = 0..15 of the macro-block that is block Q = {m : m / 8 == Q % 2, (m / 2) % 2 ==
+// Q / 2}, i.e. micro-blocks b, b+1, b+4, b+5 with b = 0, 8, 2, 10.
+//
+// One run = 8 consecutive activations (one micro-block), handled by one thread.  Digit table of a
+// macro-block: the 32 bytes of (k-group h, digit i) at h * 256 + i * 32; scale byte (E + 110) of
+// block Q at st[Q], where E + 15 is the largest biased fp16 exponent of the block (subnormals
+// count as 1).
+// The 8 activations of run r as four registers of two fp16 each, from the run's raw words:
+// raw[0..3] (fp16), raw[0..1] (int8), raw[0] (packed int4: element i in nibble i) or the low 48
+// bits of raw[1]:raw[0] (packed int6: element i in bits 6 i .. 6 i + 5) or the low 24 bits of raw[0]
+// (packed int3: element i in bits 3 i .. 3 i + 2).  Integer activations are exact in fp16.
+template <int ACT>
+__device__ __forceinline__ void run_as_half(const uint32_t (&raw)[4], uint32_t (&v)[4])
+{
+    if constexpr (ACT == 0) {
+        v[0] = raw[0]; v[1] = raw[1]; v[2] = raw[2]; v[3] = raw[3];
+    } else if constexpr (ACT == 1) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int e0 = (int)(int8_t)(raw[d >> 1] >> (16 * (d & 1)));
+            const int e1 = (int)(int8_t)(raw[d >> 1] >> (16 * (d & 1) + 8));
+            const goq_half2 hv = {(_Float16)e0, (_Float16)e1};     // exact: |e| <= 128
+            v[d] = __builtin_bit_cast(uint32_t, hv);
+        }
+    } else if constexpr (ACT == 2) {
+        const uint32_t q = raw[0];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int e0 = (int)(q << (28 - 8 * d)) >> 28;         // sign-extended nibble 2 d
+            const int e1 = (int)(q << (24 - 8 * d)) >> 28;         // nibble 2 d + 1
+            const goq_half2 hv = {(_Float16)e0, (_Float16)e1};
+            v[d] = __builtin_bit_cast(uint32_t, hv);
+        }
+    } else if constexpr (ACT == 4) {
+        const uint32_t q = raw[0];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int e0 = (int)(q << (29 - 6 * d)) >> 29;         // sign-extended field 2 d
+            const int e1 = (int)(q << (26 - 6 * d)) >> 29;         // field 2 d + 1
+            const goq_half2 hv = {(_Float16)e0, (_Float16)e1};
+            v[d] = __builtin_bit_cast(uint32_t, hv);
+        }
+    } else {
+        // fields 0..4 lie in raw[0], field 5 straddles the two words, 6 and 7 lie in raw[1]
+        const uint32_t lo = raw[0], hi = (raw[0] >> 30) | (raw[1] << 2);     // hi: fields 5, 6, 7 from bit 0
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int k0 = 2 * d, k1 = 2 * d + 1;
+            const int e0 = k0 < 5 ? (int)(lo << (26 - 6 * k0)) >> 26 : (int)(hi << (26 - 6 * (k0 - 5))) >> 26;
+            const int e1 = k1 < 5 ? (int)(lo << (26 - 6 * k1)) >> 26 : (int)(hi << (26 - 6 * (k1 - 5))) >> 26;
+            const goq_half2 hv = {(_Float16)e0, (_Float16)e1};
+            v[d] = __builtin_bit_cast(uint32_t, hv);
+        }
+    }
+}
+
+// The dwords that hold run r of macro-block g of x in global memory.  Loads only: what comes next are the requests for weights, and shifting
+// the run into place here made those wait for the activations (int6 and int3; us, shifted here / in align_run: 16384 x 2048 W4/A6 10.8 / 10.3,
+// three of 4096 x 4096 W4/A6 14.5 / 14.2, W4/A3 14.5 / 14.2).
+template <int ACT>
+__device__ __forceinline__ void load_run(const void *x, int g, int r, uint32_t (&raw)[4])
+{
+    raw[0] = raw[1] = raw[2] = raw[3] = 0u;
+    if constexpr (ACT == 0) {
+        const u32x4 q = ((gptr4)x)[(int64_t)g * 16 + r];
+        raw[0] = q.x; raw[1] = q.y; raw[2] = q.z; raw[3] = q.w;
+    } else if constexpr (ACT == 1) {
+        raw[0] = ((gptr)x)[(int64_t)g * 32 + 2 * r];
+        raw[1] = ((gptr)x)[(int64_t)g * 32 + 2 * r + 1];
+    } else if constexpr (ACT == 2) {
+        raw[0] = ((gptr)x)[(int64_t)g * 16 + r];
+    } else if constexpr (ACT == 4) {
+        // the run's 3 bytes start at byte 3 r of the macro-block's 48; they reach into the next
+        // dword only when they start at byte 2 or 3 of theirs (never for the last run)
+        const gptr p = (gptr)x + ((int64_t)g * 12 + ((3 * r) >> 2));
+        raw[0] = p[0];
+        raw[1] = 0u;
+        if (((3 * r) & 3) > 1) raw[1] = p[1];
+    } else {
+        // the run's 6 bytes start at byte 6 r of the macro-block's 96: in the two dwords from dword
+        // 3 r / 2, at byte offset 0 (r even) or 2 (r odd)
+        const gptr p = (gptr)x + ((int64_t)g * 24 + ((3 * r) >> 1));
+        raw[0] = p[0];
+        raw[1] = p[1];
+    }
+}
+
+// the run's own bits, from bit 0 on, out of those dwords
+template <int ACT>
+__device__ __forceinline__ void align_run(const uint32_t (&dwords)[4], int r, uint32_t (&raw)[4])
+{
+    raw[0] = dwords[0]; raw[1] = dwords[1]; raw[2] = dwords[2]; raw[3] = dwords[3];
+    if constexpr (ACT == 3 || ACT == 4) {
+        const uint32_t sh = ACT == 3 ? (uint32_t)(r & 1) * 16u : (uint32_t)((3 * r) & 3) * 8u;
+        raw[0] = __builtin_amdgcn_alignbit(dwords[1], dwords[0], sh);
+        raw[1] = dwords[1] >> sh;
+    }
+}
+
+// digit table and block scales of one run (see above) from its raw words
+template <int ACT>
+__device__ __forceinline__ void stage_digits(unsigned char *xt, unsigned char *st, const uint32_t (&dwords)[4], int r)
+{
+    uint32_t raw[4], v[4];
+    align_run<ACT>(dwords, r, raw);
+    run_as_half<ACT>(raw, v);
+    // largest biased exponent of the run (subnormals count as 1), then of the scale block
+    int emax = 1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        emax = max(emax, max((int)((v[d] >> 10) & 31u), (int)((v[d] >> 26) & 31u)));
+    emax = max(emax, __shfl_xor(emax, 1));              // runs r, r^1, r^4, r^5 form one scale block
+    emax = max(emax, __shfl_xor(emax, 4));
+    // 24-bit fixed point below 2^(emax - 14), truncated: |x| 2^(38 - emax) is an integer part of at
+    // most 24 bits, exact in fp32, and the conversion to integer truncates
+    uint32_t fx[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const unsigned short hb = (unsigned short)((v[k >> 1] >> (16 * (k & 1))) & 0x7FFFu);
+        fx[k] = (uint32_t)ldexpf((float)__builtin_bit_cast(_Float16, hb), 38 - emax);
+    }
+    // sign bytes of elements 0..3 and 4..7
+    const uint32_t slo = goq_perm(v[1], v[0], 0x07050301u) & 0x80808080u;
+    const uint32_t shi = goq_perm(v[3], v[2], 0x07050301u) & 0x80808080u;
+    unsigned char *dst = xt + (r >> 2) * 256 + (r & 3) * 8;
+    // Digit i of an element is bits 23 - 3 i .. 21 - 3 i of its fixed-point value.  The three bytes
+    // of the values are first gathered across four elements (one element per byte), so that a digit
+    // of four elements is a shift and a mask of one register.
+    uint32_t dg[2][8];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        uint32_t pl[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const uint32_t sel = 0x0c0c0400u + (uint32_t)b * 0x0101u;              // byte b of both sources
+            pl[b] = goq_perm(goq_perm(fx[4 * hf + 3], fx[4 * hf + 2], sel), goq_perm(fx[4 * hf + 1], fx[4 * hf], sel), 0x05040100u);
+        }
+        const uint32_t M = 0x07070707u;
+        dg[hf][0] = (pl[2] >> 5) & M;
+        dg[hf][1] = (pl[2] >> 2) & M;
+        dg[hf][2] = ((pl[2] << 1) & 0x06060606u) | ((pl[1] >> 7) & 0x01010101u);
+        dg[hf][3] = (pl[1] >> 4) & M;
+        dg[hf][4] = (pl[1] >> 1) & M;
+        dg[hf][5] = ((pl[1] << 2) & 0x04040404u) | ((pl[0] >> 6) & 0x03030303u);
+        dg[hf][6] = (pl[0] >> 3) & M;
+        dg[hf][7] = pl[0] & M;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        // E5M2 of 0..7: 00 3C 40 42 44 45 46 47
+        const uint32_t lo = goq_perm(0x47464544u, 0x42403C00u, dg[0][i]) | slo;
+        const uint32_t hi = goq_perm(0x47464544u, 0x42403C00u, dg[1][i]) | shi;
+        *reinterpret_cast<uint2 *>(dst + i * 32) = make_uint2(lo, hi);
+    }
+    if ((r & 5) == 0) st[(r & 2) | (r >> 3)] = (unsigned char)(emax + 110);
+}
+
+// ---- one 16-row slice of a macro-block (decode, exchange, the two slab dot products) ---------
+// quad: the lane's quad (chunk q, row c of the slice); md (bw = 4): the metadata dword of that
+// chunk and row; vt: LDS address of this lane's copy of the exchange table; A, sa: the
+// macro-block's digits (this lane's A row and k-group) and their block scale.  D1, D2: the
+// matrix instruction's results against b1 and b2; this lane group's two digit sums of row c are
+// elements 0 and 1.
+template <int BW>
+__device__ __forceinline__ void slice_products(const uint4 &quad, uint32_t md, uint32_t vt,
+                                               const v8i &A, int sa, v4f &D1, v4f &D2)
+{
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t dw[4] = {quad.x, quad.y, quad.z, quad.w};
+    // LA exchange-table entries are requested ahead, so that the look-ups are in flight while the
+    // primary codes are decoded (bw = 4 has fewer registers to spare)
+    constexpr int LA = (BW == 3) ? 4 : 2;
+    u32x4 ev[4];
+    auto address = [&](int k) {            // LDS address of the entry: vt + VS * (pattern | signs << 2)
+        if constexpr (BW == 3) {
+            // a_0 (bits 6..7), a_1 (14..15), a_2 (22..23) are the top two bits of bytes 0..2: a
+            // byte dot product with weights 1, 4, 16 gives 64 (a_0 + 4 a_1 + 16 a_2); the weights
+            // are scaled to the entry stride VS
+            return __builtin_amdgcn_udot4(dw[k] & 0x00C0C0C0u, 0x00100401u * (VS / 64), vt, false);
+        } else {
+            return vt + ((md >> (6 * k)) & 63u) * VS;
+        }
+    };
+    auto fetch = [&](int k, uint32_t eo) {
+        ev[k] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>(eo);
+    };
+    auto request = [&](int k) { fetch(k, address(k)); };
+    {
+        // the addresses first, then the reads: a dot-product result needs a few cycles before an
+        // LDS instruction may use it as address, which the other address computations cover
+        uint32_t eo[LA];
+#pragma unroll
+        for (int k = 0; k < LA; ++k) eo[k] = address(k);
+#pragma unroll
+        for (int k = 0; k < LA; ++k) __builtin_amdgcn_sched_group_barrier(0x002, BW == 3 ? 2 : 3, 0);   // VALU
+        __builtin_amdgcn_sched_group_barrier(0x100, LA, 0);                                            // DS read
+#pragma unroll
+        for (int k = 0; k < LA; ++k) fetch(k, eo[k]);
+    }
+    v8i B1, B2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t lo, hi;
+        goq_decode_bytes<BW, 0>(dw[k], lo, hi);                      // code -> E5M2 byte
+        B1[2 * k] = (int)lo;
+        B1[2 * k + 1] = (int)hi;
+    }
+    // E5M2 x E5M2, fp32 accumulation; block scale sa on the activation side, 2^0 on the weight side
+    D1 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B1, zero, 1, 1, 0, sa, 0, 127);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t lo = (uint32_t)B1[2 * k], hi = (uint32_t)B1[2 * k + 1];
+        B2[2 * k] = (int)(goq_perm(hi, lo, ev[k].x) ^ ev[k].z);       // Theorem 1 exchange + sign XOR
+        B2[2 * k + 1] = (int)(goq_perm(hi, lo, ev[k].y) ^ ev[k].w);
+        if (k + LA < 4) request(k + LA);
+    }
+    D2 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B2, zero, 1, 1, 0, sa, 0, 127);
+}
+
+// A row's coefficient word is spread over what its four lanes (c, 0..3) load, one byte each: two
+// bits in each of the quad's dwords (bw = 3), the top byte of the metadata dword (bw = 4).
+// position: the byte of the word this lane holds.
+template <int BW>
+__device__ __forceinline__ uint32_t coefficient_byte(const uint4 &quad, uint32_t md)
+{
+    if constexpr (BW == 3) {
+        uint32_t cw = quad.x >> 30;
+        cw = __builtin_amdgcn_alignbit(cw, quad.y, 30);
+        cw = __builtin_amdgcn_alignbit(cw, quad.z, 30);
+        cw = __builtin_amdgcn_alignbit(cw, quad.w, 30);
+        return cw;
+    } else {
+        return md >> 24;
+    }
+}
+template <int BW>
+__device__ __forceinline__ int coefficient_byte_position(int q) { return BW == 3 ? 3 - q : q; }
+
+// Coefficient rescale (Eq. 4), once per slab, outside the dot-product loop: the two digit sums
+// this lane group received for each basis, times the slab's coefficient pair.
+__device__ __forceinline__ float rescale(uint32_t cword, const v4f &D1, const v4f &D2, float acc)
+{
+    const float c1 = __half2float(__ushort_as_half((unsigned short)(cword & 0xffffu)));
+    const float c2 = __half2float(__ushort_as_half((unsigned short)(cword >> 16)));
+    return fmaf(c2, D2[0] + D2[1], fmaf(c1, D1[0] + D1[1], acc));
+}
+
+}  // namespace

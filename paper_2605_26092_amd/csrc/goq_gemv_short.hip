@@ -1,0 +1,312 @@
+// goq_gemv_batch / goq_gemv_stream, launches between the small ones (goq_gemm_small.hip, gemv_rows_kernel) and long streams: a few
+// projections or a decoder block of one token.
+//
+// What bounds them: start and end.  The streaming kernel of goq_gemv.hip cuts such a launch into 512 pieces of three to seven
+// units, and every piece ends with a combine through memory that all its neighbours have to wait for.  Here a workgroup owns
+// whole outputs: one workgroup of 16 wavefronts per CU takes a range of 16-row tiles over their whole depth, its wavefronts take
+// equal contiguous runs of the range's (tile, macro-block) slices, and the parts of a tile meet in LDS: no scratch memory, no atomics, one
+// barrier before the loop and one behind it.
+//   activations  x as digits (goq_gemv.h), the whole depth staged once per workgroup and kept for all its tiles; layers that
+//                follow each other with the same x and depth (q, k, v; gate, up) share the staging.
+//   weights      a slice is 16 rows of a macro-block: four (bw = 3) or five registers.  DEPTH slices are in flight per wavefront,
+//                requested before the digits are staged: 12 MB on the chip.
+//   balance      ranges of tiles have equal numbers of slices but for one tile; inside a range the wavefronts' runs are equal to one slice.
+// Sums are added in a fixed order: a wavefront's slices in turn, then the wavefronts in turn.
+// Timing-only builds (us; 11008 x 4096, W3/A16, 9.1 in all): a launch that ends at once 2.0, with the ranges found 2.3, x staged 3.2, the first slices there
+// 5.2, everything but the matrix products 7.6.  What the products add is the work on the last slices in flight, 16 wavefronts' at a
+// time.  goq_gemv_rules.h says which launches come here, and what they gain.
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+#include <stddef.h>
+#include "goq_gemv.h"
+#include "goq_gemv_rules.h"
+
+namespace {
+
+constexpr int WAVES = 16;
+constexpr int NT = WAVES * 64;
+constexpr int WGS = GOQ_SHORT_WGS;               // one workgroup per CU
+constexpr int DEPTH = 3;                         // slices in flight per wavefront (us, 2 / 3 / 4 / 6 / 8: 8192 x 8192 W3/A16 11.5 / 11.4 / 11.3 / 12.4 / 15)
+constexpr int MAX_GN = GOQ_SHORT_GN;
+constexpr int PARTS = GOQ_SHORT_TILES / WAVES + 2;   // tiles that a wavefront's run touches
+static_assert(MAX_GN <= 2 * NT / 16, "a thread holds two runs of x");
+
+struct ShortArgs {
+    int n;
+    GemvProblem p[GOQ_MAX_BATCH];
+};
+
+// LDS, in this order; the zeros and digits come last, as many as the deepest layer needs
+struct ShortLds {
+    unsigned char vtab[64 * VS];                 // exchange table
+    float red[WAVES][PARTS][16];                 // sums of 16 rows: a wavefront's k-th tile
+    int first[WAVES], count[WAVES];              // a wavefront's first tile in the range, and how many it has touched
+    unsigned char cwx[WAVES][64];                // coefficient bytes on their way to their rows' lanes
+    unsigned char stab[MAX_GN * 4];              // block scales
+    unsigned char xtab[XZ];                      // zeros, then the digits
+};
+
+template <int BW>
+struct Slice {
+    u32x4 q;
+    uint32_t md;
+};
+
+// Tiles [t, t1) of the launch; problem pi holds tile t.
+template <int BW, int ACT, bool TABLE>
+__device__ __forceinline__ void tile_range(const Problems<TABLE> &pb, int t, int t1, int pi, ShortLds &lds)
+{
+    constexpr int CH = (BW == 3) ? 4 : 5;
+    constexpr int UNIT = CH * GOQ_ROWS * 4;      // dwords of a row block's macro-block
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = uniform(tid >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int n = pb.n();
+
+    // A operand of this lane: row = lane % 16; digit d sits in row 4 (d / 2) + d % 2, the other rows are zero
+    const bool live = (c & 3) < 2;
+    const int digit = 2 * (c >> 2) + (c & 1);
+    const uint32_t abase = live ? (uint32_t)(XZ + q * 256 + digit * 32) : 0u;
+    const uint32_t amask = live ? ~0u : 0u;
+    const uint32_t vt = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds.vtab + (lane % VC) * 16;
+    const uint32_t lane_quad = (uint32_t)(q * (GOQ_ROWS * 4) + c * 4) * 4u, lane_meta = (uint32_t)(4 * (GOQ_ROWS * 4) + c * 4 + q) * 4u;   // bytes
+
+    bool again = false;
+    while (t < t1) {
+        // the layers from pi on that share x
+        const int gn = uniform(pb[pi].gn);
+        const void *const x = pb[pi].x;
+        int pe = pi + 1;
+        while (pe < n && pb[pe].bb < t1 && pb[pe].x == x && pb[pe].gn == gn) ++pe;
+        const int end = uniform(min(t1, pb[pe - 1].bb + (pb[pe - 1].out + 15) / 16));
+        const int total = (end - t) * gn;
+        const int a = uniform(wave * total / WAVES), b = uniform((wave + 1) * total / WAVES);
+
+        uint32_t raw[2][4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (i * (NT / 16) + (tid >> 4) < gn) load_run<ACT>(x, i * (NT / 16) + (tid >> 4), tid & 15, raw[i]);
+        asm volatile("" ::: "memory");
+
+        // where the next request goes: slice `at`, macro-block g of tile `tile`, which problem pj holds up to `last`
+        int at = min(a, total - 1);
+        int tile = t + at / gn, g = at % gn, pj = pi;
+        while (pj + 1 < pe && tile >= pb[pj + 1].bb) ++pj;
+        const uint32_t *packed = pb[pj].packed;
+        int bb = pb[pj].bb, last = pj + 1 < pe ? pb[pj + 1].bb : end;
+        auto place = [&] { return packed + ((int64_t)((tile - bb) >> 2) * gn + g) * UNIT + ((tile - bb) & 3) * 64; };
+        const uint32_t *from = place();
+        auto request = [&](Slice<BW> &s) {
+            const __attribute__((address_space(1))) char *const base = (const __attribute__((address_space(1))) char *)from;
+            s.q = __builtin_nontemporal_load((gptr4)(base + lane_quad));
+            s.md = 0u;
+            if constexpr (BW == 4) s.md = __builtin_nontemporal_load((gptr)(base + lane_meta));
+            if (at + 1 < b) {                    // (past the end of the run the last slice again, not used)
+                ++at;
+                from += UNIT;
+                if (++g == gn) {
+                    g = 0;
+                    if (++tile == last) {
+                        ++pj;
+                        packed = pb[pj].packed;
+                        bb = pb[pj].bb;
+                        last = pj + 1 < pe ? pb[pj + 1].bb : end;
+                    }
+                    from = place();
+                }
+            }
+        };
+        Slice<BW> s[DEPTH];
+        const int la = a / gn;                   // first tile of the run
+        int cg = a % gn;                         // macro-block of the next slice to compute
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) request(s[i]);
+
+        if (!again) {
+            // (a sixteenth of the table each)
+            goq_write_exchange_table<0x80u, VC, WAVES>(lds.vtab, wave, lane);
+            if (tid < XZ / 4) reinterpret_cast<uint32_t *>(lds.xtab)[tid] = 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = i * (NT / 16) + (tid >> 4);
+            if (m < gn) stage_digits<ACT>(lds.xtab + XZ + m * XG, lds.stab + m * 4, raw[i], tid & 15);
+        }
+        again = true;
+        __syncthreads();
+
+        unsigned char *const cwx = lds.cwx[wave];
+        float acc = 0.f;
+        int k = 0;
+        v4f D1 = {0.f, 0.f, 0.f, 0.f}, D2 = D1;
+        uint32_t cw = 0u;
+        // the sum of a tile's rows over this run, into LDS
+        auto put = [&] {
+            acc = rescale(cw, D1, D2, acc);
+            const uint32_t v = __float_as_uint(acc);
+            const auto u = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            const uint32_t h = __float_as_uint(__uint_as_float(u[0]) + __uint_as_float(u[1]));
+            const auto w = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+            if (lane < 16) lds.red[wave][k][c] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+            ++k;
+            acc = 0.f;
+            D1 = D2 = v4f{0.f, 0.f, 0.f, 0.f};
+        };
+        // One slice; the coefficients of the one before are applied behind its matrix instructions.
+        auto compute = [&](const Slice<BW> &w) {
+            if (cg == gn) {
+                put();
+                cg = 0;
+            }
+            const v8i A = *reinterpret_cast<const v8i *>(lds.xtab + abase + ((uint32_t)(cg * XG) & amask));
+            const uint32_t sc = *reinterpret_cast<const uint32_t *>(lds.stab + cg * 4);
+            const int sa = (int)((sc >> (8 * q)) & 0xFFu) - 3 * digit;
+            const uint4 quad = make_uint4(w.q.x, w.q.y, w.q.z, w.q.w);
+            v4f E1, E2;
+            // the row's coefficient word: each of its four lanes holds one byte of it (LDS operations of a wavefront execute in order)
+            cwx[c * 4 + coefficient_byte_position<BW>(q)] = (unsigned char)coefficient_byte<BW>(quad, w.md);
+            asm volatile("" ::: "memory");
+            slice_products<BW>(quad, w.md, vt, A, sa, E1, E2);
+            acc = rescale(cw, D1, D2, acc);
+            D1 = E1;
+            D2 = E2;
+            cw = *reinterpret_cast<const uint32_t *>(cwx + c * 4);
+            ++cg;
+        };
+        int i = a;
+        for (; i + 2 * DEPTH <= b; i += DEPTH)
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                compute(s[d]);
+                request(s[d]);
+            }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (i + d < b) {
+                compute(s[d]);
+                if (i + DEPTH + d < b) request(s[d]);
+            }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (i + DEPTH + d < b) compute(s[d]);
+        if (a < b) put();
+        if (lane == 0) {
+            lds.first[wave] = la;
+            lds.count[wave] = k;
+        }
+        __syncthreads();
+
+        // H6: the parts of a row, in wavefront order
+        for (int e = tid; e < (end - t) * 16; e += NT) {
+            float y = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const int part = (e >> 4) - lds.first[w];
+                const bool has = (unsigned)part < (unsigned)lds.count[w];
+                const float v = lds.red[w][has ? part : 0][e & 15];
+                y += has ? v : 0.f;
+            }
+            int pr = pi;
+            const int at16 = t + (e >> 4);
+            while (pr + 1 < pe && at16 >= pb[pr + 1].bb) ++pr;
+            const auto &P = pb[pr];
+            const int row = (at16 - P.bb) * 16 + (e & 15);
+            if (row < P.out) {
+                if constexpr (ACT != 0) y *= ((const __attribute__((address_space(1))) float *)P.sx)[0];
+                if (P.ytype == GOQ_F32) ((__attribute__((address_space(1))) float *)P.y)[row] = y;
+                else ((__attribute__((address_space(1))) unsigned short *)P.y)[row] = __half_as_ushort(__float2half(y));
+            }
+        }
+        t = end;
+        pi = pe;
+        if (t < t1) __syncthreads();             // the parts have been read, and no wavefront reads digits any more
+    }
+}
+
+// cq, cr: slices of the launch / WGS, % WGS; c1 .. c7: slices before problems 1 .. 7 (INT_MAX: there is no such problem).  They arrive in scalar
+// registers (-amdgpu-kernarg-preload-count), a round trip before the problems' fields.
+template <int BW, int ACT, bool TABLE>
+__global__ __launch_bounds__(NT)
+void gemv_short_kernel(int cq, int cr, int c1, int c2, int c3, int c4, int c5, int c6, int c7, int tiles, const GemvProblem *table, ShortArgs a)
+{
+    extern __shared__ __attribute__((aligned(256))) unsigned char memory[];
+    const Problems<TABLE> pb = [&] {
+        if constexpr (TABLE) {
+            return Problems<true>{table, a.n};
+        } else {
+            // `a` follows ten ints and a pointer
+            constexpr int KARG_P = 48 + (int)offsetof(ShortArgs, p);
+            const __attribute__((address_space(4))) char *kseg = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+            return Problems<false>{(const __attribute__((address_space(4))) GemvProblem *)(kseg + KARG_P), a.n};
+        }
+    }();
+    // The launch is cut behind the tile that ends nearest to an equal share of the slices.
+    const int before[GOQ_MAX_BATCH] = {0, c1, c2, c3, c4, c5, c6, c7};
+    int cut[2], pi = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = (int)blockIdx.x + i, at = goq_short_share(k, cq, cr);
+        int p = 0, b = 0;
+#pragma unroll
+        for (int j = 1; j < GOQ_MAX_BATCH; ++j) {
+            p += at >= before[j] ? 1 : 0;
+            b = at >= before[j] ? before[j] : b;
+        }
+        p = uniform(p);
+        const int gn = uniform(pb[p].gn);
+        cut[i] = k == WGS ? tiles : uniform(goq_short_cut(at, b, pb[p].bb, gn));
+        if (i == 0) pi = p;
+    }
+    if (pi + 1 < a.n && cut[0] >= pb[pi + 1].bb) ++pi;
+    tile_range<BW, ACT, TABLE>(pb, cut[0], cut[1], pi, *reinterpret_cast<ShortLds *>(memory));
+}
+
+template <int BW, int ACT>
+int launch(hipStream_t st, int n, const GemvProblem *p, const GemvProblem *table)
+{
+    ShortArgs a;
+    int before[GOQ_MAX_BATCH], deepest = 0, total = 0, tiles = 0;
+    for (int i = 0; i < GOQ_MAX_BATCH; ++i) {
+        a.p[i] = p[i < n ? i : 0];
+        before[i] = i < n ? p[i].cost : 0x7fffffff;
+        if (i >= n) continue;
+        const int t = (p[i].out + 15) / 16;
+        deepest = p[i].gn > deepest ? p[i].gn : deepest;
+        total += t * p[i].gn;
+        tiles += t;
+    }
+    a.n = n;
+    const unsigned lds = sizeof(ShortLds) + deepest * XG;
+    if (table)
+        hipLaunchKernelGGL((gemv_short_kernel<BW, ACT, true>), dim3(WGS), dim3(NT), lds, st, total / WGS, total % WGS, before[1], before[2], before[3],
+                           before[4], before[5], before[6], before[7], tiles, table, a);
+    else
+        hipLaunchKernelGGL((gemv_short_kernel<BW, ACT, false>), dim3(WGS), dim3(NT), lds, st, total / WGS, total % WGS, before[1], before[2], before[3],
+                           before[4], before[5], before[6], before[7], tiles, table, a);
+    return goq_check_launch("goq_gemv");
+}
+
+}  // namespace
+
+bool goq_gemv_short(int bw, int act, int n, const GemvProblem *p)
+{
+    if (n > GOQ_MAX_BATCH) return false;
+    GoqRows rows[GOQ_MAX_BATCH];
+    for (int i = 0; i < n; ++i) rows[i] = GoqRows{p[i].out, p[i].gn};
+    return goq_short(bw, act == GOQ_A8, n, rows);
+}
+
+int goq_launch_gemv_short(hipStream_t st, int bw, int act, int n, const GemvProblem *p, const GemvProblem *table)
+{
+    if (bw == 3 && act == GOQ_A16) return launch<3, 0>(st, n, p, table);
+    if (bw == 3 && act == GOQ_A8) return launch<3, 1>(st, n, p, table);
+    if (bw == 4 && act == GOQ_A8) return launch<4, 1>(st, n, p, table);
+    if (bw == 3 && act == GOQ_A4) return launch<3, 2>(st, n, p, table);
+    if (bw == 4 && act == GOQ_A4) return launch<4, 2>(st, n, p, table);
+    if (bw == 3 && act == GOQ_A6) return launch<3, 3>(st, n, p, table);
+    if (bw == 4 && act == GOQ_A6) return launch<4, 3>(st, n, p, table);
+    if (bw == 3 && act == GOQ_A3) return launch<3, 4>(st, n, p, table);
+    if (bw == 4 && act == GOQ_A3) return launch<4, 4>(st, n, p, table);
+    return launch<4, 0>(st, n, p, table);
+}

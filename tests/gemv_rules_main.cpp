@@ -1,0 +1,54 @@
+// The host-side arithmetic of short batch-1 launches (goq_gemv_rules.h), one question per line of stdin:
+//     short bw int8 n  out in  out in ..   ->   1 (ranges of tiles) or 0 (streaming kernel)
+//     cuts  n  out in  out in ..           ->   fewest and most tiles, most slices of a workgroup; -1 if ranges do not follow each other
+#include <cstdio>
+#include <cstring>
+#include "../paper_2605_26092_amd/csrc/goq_gemv_rules.h"
+
+int main()
+{
+    char what[8];
+    while (scanf("%7s", what) == 1) {
+        int bw = 3, int8 = 0, n;
+        const bool asked = !strcmp(what, "short");
+        if (asked && scanf("%d %d", &bw, &int8) != 2) return 1;
+        if (scanf("%d", &n) != 1 || n < 1 || n > 8) return 1;
+        GoqRows p[8];
+        int first[9] = {0}, before[9] = {0};
+        for (int i = 0; i < n; ++i) {
+            int in;
+            if (scanf("%d %d", &p[i].out, &in) != 2) return 1;
+            p[i].gn = in / GOQ_N;
+            first[i + 1] = first[i] + (p[i].out + 15) / 16;
+            before[i + 1] = before[i] + (p[i].out + 15) / 16 * p[i].gn;
+        }
+        if (asked) {
+            printf("%d\n", goq_short(bw, int8 != 0, n, p) ? 1 : 0);
+            continue;
+        }
+        const int total = before[n], each = total / GOQ_SHORT_WGS, rest = total % GOQ_SHORT_WGS;
+        auto cut = [&](int k) {
+            const int at = goq_short_share(k, each, rest);
+            int i = 0;
+            while (i + 1 < n && at >= before[i + 1]) ++i;
+            return k == GOQ_SHORT_WGS ? first[n] : goq_short_cut(at, before[i], first[i], p[i].gn);
+        };
+        auto slices = [&](int tile) {
+            int i = 0;
+            while (i + 1 < n && tile >= first[i + 1]) ++i;
+            return before[i] + (tile - first[i]) * p[i].gn;
+        };
+        int least = 1 << 30, most = 0, longest = 0;
+        bool follow = cut(0) == 0;
+        for (int k = 0; k < GOQ_SHORT_WGS; ++k) {
+            const int a = cut(k), b = cut(k + 1);
+            follow = follow && a <= b && b <= first[n];
+            least = b - a < least ? b - a : least;
+            most = b - a > most ? b - a : most;
+            longest = slices(b) - slices(a) > longest ? slices(b) - slices(a) : longest;
+        }
+        if (follow) printf("%d %d %d\n", least, most, longest);
+        else printf("-1 -1 -1\n");
+    }
+    return 0;
+}

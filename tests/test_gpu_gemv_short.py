@@ -1,0 +1,75 @@
+"""Batch-1 launches that go to ranges of tiles (goq_gemv_short.hip) against the oracle, as a batch, with a workspace of the caller's, and
+as a stream: the three take the same ranges, so their bits are equal.  fp32 outputs within 2e-6 of the sum of absolute products
+(2^-24 per rounding, at most some ten of them on a path from a product to y, and x cut off 24 binary places below its block's maximum)."""
+import numpy as np
+import pytest
+
+import goq_inputs
+from tests import gpu_util as gu
+from tests.test_gemv_rules import _words, ask                      # (ask: a fixture)
+
+pytestmark = pytest.mark.gpu
+
+PACKERS = {"A8": None, "A4": (4, "pack_int4"), "A6": (6, "pack_int6"), "A3": (3, "pack_int3")}
+
+# one macro-block, a ragged last tile, layers that share x and layers that do not, depths that change within a workgroup's range, the deepest
+# that is taken, workgroups with one tile and with many, wavefronts with no slice and with several tiles
+LAUNCHES = [
+    [(8209, 128, 0)],
+    [(17000, 256, 0), (300, 256, 1), (1, 256, 1)],
+    [(3001, 2048, 0), (3001, 2048, 0), (2999, 2048, 0)],
+    [(5000, 1024, 0), (4100, 1024, 1), (90, 1024, 2)],
+    [(2459, 4992, 0), (2459, 4992, 0), (5263, 640, 1), (7, 640, 2), (40, 640, 2)],
+    [(1100, 256, i) for i in range(8)],
+    [(4096, 16384, 0)],
+]
+
+
+@pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("launch", range(len(LAUNCHES)))
+def test_ranges_of_tiles(oracle, ask, launch, bw, act):
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    layers = LAUNCHES[launch]
+    if layers[0][1] > 4096 and (bw, act) not in ((3, "A16"), (4, "A6")):
+        pytest.skip("the deepest launch with two types only")
+    assert ask(["short %d %d %s" % (bw, act == "A8", _words([l[:2] for l in layers]))]) == ["1"]
+    print("ranges of tiles bw=%d %s %s" % (bw, act, layers), flush=True)
+    probs, refs, xs = [], [], {}
+    for i, (out, inn, which) in enumerate(layers):
+        q = goq_inputs.canonical_random(bw, out, inn, config_id=81, tensor_id=i)
+        if (which, inn) not in xs:
+            if act == "A16":
+                x = goq_inputs.activations_a16(1, inn, config_id=81, tensor_id=100 + which, outlier_frac=0.01)
+                xs[which, inn] = x.astype(np.float64), gu.to_dev(x.reshape(-1)), None, x
+            else:
+                bits, packer = PACKERS[act] or (8, None)
+                x, sx = goq_inputs.activations_int(1, inn, bits, config_id=81, tensor_id=100 + which)
+                xs[which, inn] = x * sx[:, None].astype(np.float64), gu.to_dev(getattr(goq_inputs, packer)(x) if packer else x), gu.to_dev(sx), (x, sx)
+        x64, xd, sxd, xh = xs[which, inn]
+        ref = oracle.gemm_a16(q, xh, threads=8)[0] if act == "A16" else oracle.gemm_a8(q, *xh, threads=8)[0][0]
+        refs.append((ref, np.abs(x64) @ np.abs(oracle.dequant(q, want=("what",))["what"]).T + 1e-30))
+        y = torch.full((out,), float("nan"), dtype=torch.float16 if i % 3 == 2 else torch.float32, device="cuda")
+        probs.append((out, inn, gu.pack_layer(goq, q), xd, sxd, y, goq.F16 if i % 3 == 2 else goq.F32))
+    goq.gemv_batch(bw, getattr(goq, act), probs)
+    torch.cuda.synchronize()
+    first = [p[5].clone() for p in probs]
+    for y, (ref, scale) in zip(first, refs):
+        y = y.double().cpu().numpy()
+        half = 2.0 ** -11 * np.abs(ref) + 2.0 ** -25 if len(first) > 2 else 0.0
+        assert np.all(np.abs(y - ref) <= 2e-6 * scale[0] + half)
+
+    def again(call):
+        for p in probs:
+            p[5].fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, p[5]) for a, p in zip(first, probs))
+
+    ws = torch.empty(goq.gemv_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    goq.gemv_workspace_init(ws)
+    again(lambda: goq.gemv_batch_ws(bw, getattr(goq, act), probs, ws))
+    table, size = goq.gemv_stream_table(bw, getattr(goq, act), probs)
+    on_device = torch.frombuffer(bytearray(bytes(table)[:size]), dtype=torch.uint8).cuda()
+    again(lambda: goq.gemv_stream(table, on_device, ws))
