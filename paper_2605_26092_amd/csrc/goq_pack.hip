@@ -3,18 +3,18 @@
 #include <hip/hip_runtime.h>
 #include "goq_layout.h"
 #include "goq_internal.h"
+#include "goq_gemm_rules.h"
 
 namespace {
 
 // Packing moves 1.8 (bw = 3) or 1.9 bytes per weight and computes next to nothing, so it is laid out
-// for memory: a workgroup takes a row block of 64 rows and PG consecutive macro-blocks, thread
+// for memory: a workgroup takes a row block of 64 rows and one macro-block, thread
 // (row, h) the 32 codes of chunk h.  The four threads of a row read 128 consecutive bytes of codes, a wavefront
-// writes 256-byte runs of each chunk, and the PG macro-blocks use up the 64-byte pieces of the
-// pattern and sign rows (16 bytes per macro-block) that a workgroup touches.  With one thread per
-// (row, macro-block) reading single bytes, rows apart, a 4096 x 11008 layer took 220 us.
+// writes 256-byte runs of each chunk.  Of a line of patterns, signs or coefficients a workgroup uses an eighth and less, so neighbours along the
+// row belong on one XCD, whose L2 then reads the line once: every XCD takes a range of workgroups instead of every eighth.  (us, 4096 x 11008, bw = 3 / 4, one box:
+// eight macro-blocks per workgroup and no ranges 24.7 / 24.7, two 23.1 / 22.5, two and ranges 19.0 / 18.5, one and ranges 18.6 / 18.3; 1500 x 1024 6.4, 5.0, 5.1, 5.0;
+// with one thread per (row, macro-block) reading single bytes 220.)
 // WIDE: the codes are 16-byte, pattern and signs 4-byte aligned; else they are read byte by byte.
-constexpr int PG = 8;
-
 template <bool WIDE>
 __device__ __forceinline__ uint4 load16(const uint8_t *p)
 {
@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *p)
 }
 
 template <int BW, bool WIDE>
-__global__ __launch_bounds__(256) void pack_kernel(int64_t out, int64_t in, int64_t groups,
+__global__ __launch_bounds__(256) void pack_kernel(int64_t out, int64_t in, int units,
                                                    const uint8_t *__restrict__ codes,
                                                    const uint8_t *__restrict__ pattern,
                                                    const uint8_t *__restrict__ signs,
@@ -41,23 +41,19 @@ __global__ __launch_bounds__(256) void pack_kernel(int64_t out, int64_t in, int6
                                                    uint32_t *__restrict__ packed)
 {
     constexpr int CH = (BW == 3) ? 4 : 5;
-    const int64_t gn = in / GOQ_N;
-    const int64_t R = blockIdx.x / groups;
-    const int64_t g0 = blockIdx.x % groups * PG;
+    const int gn = (int)(in / GOQ_N);
     const int r = threadIdx.x >> 2, h = threadIdx.x & 3;
-    const int64_t row = R * GOQ_ROWS + r;
-    const bool live = row < out;
+    for (int unit = (int)blockIdx.x; unit < units; unit += (int)gridDim.x) {
+        const int at = goq_xcd_tile(unit, units);
+        const int R = at / gn, g = at % gn;
+        const int64_t row = (int64_t)R * GOQ_ROWS + r;
 
-#pragma unroll 4
-    for (int i = 0; i < PG; ++i) {
-        const int64_t g = g0 + i;
-        if (g >= gn) break;
         // padding rows: zero codes, pattern 0, signs 0, zero coefficients
         uint32_t c[8], pat = 0, sg = 0, cw = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) c[k] = (uint32_t)goq_zero_code(BW) * 0x01010101u;
-        if (live) {
-            const int64_t k0 = row * in + g * GOQ_N + 32 * h;
+        if (row < out) {
+            const int64_t k0 = row * in + (int64_t)g * GOQ_N + 32 * h;
             const uint4 a = load16<WIDE>(codes + k0), b = load16<WIDE>(codes + k0 + 16);
             c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w; c[4] = b.x; c[5] = b.y; c[6] = b.z; c[7] = b.w;
             pat = load4<WIDE>(pattern + k0 / GOQ_G);
@@ -146,13 +142,13 @@ int goq_launch_pack(hipStream_t st, int bw, int64_t out, int64_t in, const uint8
                     const uint8_t *pattern, const uint8_t *signs, const uint16_t *c1,
                     const uint16_t *c2, void *packed)
 {
-    const int64_t groups = (in / GOQ_N + PG - 1) / PG;
-    const int64_t grid = goq_row_blocks(out) * groups;
-    if (grid > 0x7fffffff) return goq_set_error(GOQ_ESHAPE, "goq_pack: layer too large for one launch");
+    const int64_t units = goq_row_blocks(out) * (in / GOQ_N);
+    const int64_t grid = units < 1 << 22 ? units : 1 << 22;      // (a launch has less than 2^32 threads)
+    if (units > 0x7fffffff - grid) return goq_set_error(GOQ_ESHAPE, "goq_pack: layer too large for one launch");
     const bool wide = ((uintptr_t)codes & 15) == 0 && (((uintptr_t)pattern | (uintptr_t)signs) & 3) == 0;
     const auto kernel = bw == 3 ? (wide ? pack_kernel<3, true> : pack_kernel<3, false>)
                                 : (wide ? pack_kernel<4, true> : pack_kernel<4, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, out, in, groups, codes, pattern, signs, c1, c2,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, out, in, (int)units, codes, pattern, signs, c1, c2,
                        (uint32_t *)packed);
     return goq_check_launch("goq_pack");
 }
