@@ -64,13 +64,13 @@
 namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TN = GOQ_TILE_OUT;   // outputs per workgroup tile
-constexpr int WN = 32;             // outputs per wavefront
 // Where the int8 slab sums of a 128-token tile begin: the bits of an fp32 number inside [2^-3, 2^-2), whose last place is 2^-26, so
 // that START + P, read as fp32, is that number + 2^-26 P exactly (|P| <= 2^17; the binade has room for -2.2 and +6.0 million
 // last places).  Of the numbers there this one, 1 / (2 pi), is an inline constant of the instruction set: the subtraction needs neither
@@ -150,15 +150,18 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
 // per register) and ONE matrix instruction per k-step and tile accumulates straight into Y.  Half
 // the matrix instructions and no rescale, but the operand is no power of two any more: every
 // weight is rounded to fp16 (2^-11 relative), which the two-basis path avoids.
-// MS: MFMA tiles along tokens per wavefront (the workgroup's tile has 32 MS tokens).  With four of them a wavefront keeps the
+// WN: outputs per wavefront.  16 (32-token tiles only): the tile's 128 outputs on eight wavefronts, for launches that leave CUs with one workgroup.  There a
+// wavefront's chain of instructions per slab is the time, and half the outputs are half the chain; the activations are read from LDS twice as often, so it loses as soon as
+// workgroups share CUs (goq_sixteen_outputs).  us, 32 / 16 outputs, 4096 x 4096, 203 tokens: W3/A8 29.0 / 23.2, W4/A16 34.6 / 29.3, W3/A16 28.1 / 26.8, W3/A6 44.1 / 30, W4/A4 44.6 / 27.6.
+// MS: MFMA tiles of 32 tokens per wavefront (the workgroup's tile has 32 MS tokens).  With four of them a wavefront keeps the
 // decoded weights of the slab (32 registers) and goes through its tiles one after the other, so that two slab sums are
 // open at a time and not eight: that fits two wavefronts per SIMD (W3 249 registers; W4 all 256 and seven spilled, six of them for the end of the
 // tile, one read back once in three slabs), and a weight is decoded once per 128 tokens.  Worth it where
 // decode weighs most and operands are narrow, for int8 operands straight from memory and 8-bit floats (us, 64 / 128 tokens: 4096 x
 // 4096, 4096 tokens, W3/A8 170 / 145, W4/A4 182 / 152; ViT-B block, 12608 tokens, W4/A4 314 / 273; packed activations with
 // W3 lose, 183 / 191: their staging needs the registers).
-template <int BW, int ACT, bool PART, bool FOLD, int MS>
-__global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2) void gemm_kernel(GemmBatch batch)
+template <int BW, int ACT, bool PART, bool FOLD, int MS, int WN>
+__global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2) void gemm_kernel(GemmBatch batch)
 {
     int pi = 0;
 #pragma unroll
@@ -169,7 +172,16 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     static_assert(!FOLD || (ACT == 0 && !PART), "the folded product exists for fp16 activations only");
     constexpr int CH = (BW == 3) ? 4 : 5;
     constexpr int TM = 32 * MS;
-    constexpr int MA = MS == 4 ? 1 : MS;                           // MFMA tiles whose slab sums are open at a time
+    constexpr bool NARROW = WN == 16;                              // 16 x 16 MFMA tiles, eight wavefronts
+    static_assert(WN == 32 || (NARROW && MS == 1 && !FOLD && !PART), "16 outputs per wavefront: 32 tokens");
+    // 16 x 16 tiles with fp16 activations take k in the order of the 32 x 32 instruction: that one adds eight products of lane group 0, then of lane
+    // group 1, this one of groups 0 to 3 (both measured: two 32x32x16 in a row and one 16x16x32 on the same k give the same bits), so k-step t has
+    // micro-blocks 2 t, 8 + 2 t, 2 t + 1, 9 + 2 t and a sum does not depend on the tile.  Integer sums are exact in any order.
+    constexpr bool IN_ORDER = NARROW && ACT == 0;
+    constexpr int THREADS = TN / WN * 64;
+    constexpr int MT = TM / WN;                                    // MFMA tiles along tokens
+    constexpr int MA = MS == 4 ? 1 : MT;                           // of these, whose slab sums are open at a time
+    constexpr int ACCS = WN * WN / 64;                             // accumulators of an MFMA tile per lane
     // ACT: 0 fp16 x; 1 int8 x, int8 MFMA; 2 int8 x widened to fp16; 3 packed int4 x unpacked to
     // int8, int8 MFMA; 4 packed int4 x as 8-bit floats; 5 packed int6 x unpacked to int8, int8
     // MFMA; 6 packed int6 x widened to fp16; 7 packed int3 x unpacked to int8, int8 MFMA; 8 packed
@@ -185,8 +197,9 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     constexpr int WACT = F16 || F8 ? 0 : 1;            // how the weights are decoded
     constexpr int XB = F16 ? 2 : 1;                    // bytes per activation in LDS
     constexpr int ROWB = GOQ_N * XB;                   // LDS row stride (XOR-swizzled, not padded)
-    constexpr int KSTEPS = F16 ? 8 : F8 ? 2 : 4;       // MFMA k-steps per slab (16 / 64 / 32 k each)
-    using AccT = typename std::conditional<F16 || F8, f32x16, i32x16>::type;
+    constexpr int KSTEPS = (F16 ? 8 : F8 ? 2 : 4) / (NARROW ? 2 : 1);       // MFMA k-steps per slab (16 / 64 / 32 k each, twice as many with 16 outputs)
+    using YT = typename std::conditional<NARROW, f32x4, f32x16>::type;
+    using AccT = typename std::conditional<F16 || F8, YT, typename std::conditional<NARROW, i32x4, i32x16>::type>::type;
     using OpT = typename std::conditional<F16, f16x8, typename std::conditional<F8, i32x8, i32x4>::type>::type;   // one MFMA operand
 
     // three activation slabs (arrays of their own: the compiler makes a read of an array wait for the
@@ -196,12 +209,13 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     __shared__ __attribute__((aligned(16))) unsigned char xs2[TM * ROWB];
     __shared__ __attribute__((aligned(16))) unsigned char xtab[64 * 16];        // exchange table
     __shared__ float sxs[ACT == 0 ? 1 : TM];                                    // scales of the tile's tokens
+    __shared__ __attribute__((aligned(16))) unsigned char spare[NARROW && !F16 ? 4096 : 16];   // small slabs: for pieces that do not exist, and two wavefronts' outputs
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ln = lane & 31;     // MFMA column (output channel) / A row (token)
-    const int kg = lane >> 5;     // k-group
+    const int ln = lane % WN;     // MFMA column (output channel) / A row (token)
+    const int kg = lane / WN;     // k-group
 
     const int mtiles = (a.tokens + TM - 1) / TM, ntiles = (a.out + TN - 1) / TN;
     int mt = tile % mtiles, nt = tile / mtiles;
@@ -218,30 +232,37 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
 
     if (tid < 64) *reinterpret_cast<uint4 *>(xtab + tid * 16) = goq_exchange_entry<(WACT == 0 ? 0x80u : 0xFFu)>(tid);
 
-    f32x16 Yacc[MS];
+    YT Yacc[MT];
 #pragma unroll
-    for (int i = 0; i < MS; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) Yacc[i][v] = 0.f;
+        for (int v = 0; v < ACCS; ++v) Yacc[i][v] = 0.f;
 
     // the two quads this lane reads per slab: row n0 + ln, chunks 2 kg and 2 kg + 1 (micro-blocks
-    // 8 kg .. 8 kg + 7).  Rows past the last row block are redirected to the last one (their
+    // 8 kg .. 8 kg + 7); with 16 outputs per wavefront one quad, chunk kg (micro-blocks 4 kg .. 4 kg + 3).  Rows past the last row block are redirected to the last one (their
     // outputs are never stored), so that every lane always issues the same loads.
+    const int chunk = IN_ORDER ? 2 * (kg & 1) + (kg >> 1) : (NARROW ? 1 : 2) * kg;
     int wrow = n0 + ln;
     wrow = (wrow / GOQ_ROWS) < a.rbn ? wrow : a.rbn * GOQ_ROWS - 1;
-    const uint32_t *wq = a.packed + goq_quad_index(CH, a.gn, wrow / GOQ_ROWS, 0, 2 * kg, wrow % GOQ_ROWS);
+    const uint32_t *wq = a.packed + goq_quad_index(CH, a.gn, wrow / GOQ_ROWS, 0, chunk, wrow % GOQ_ROWS);
     const int64_t gstride = (int64_t)CH * GOQ_ROWS * 4;     // dwords between macro-blocks
 
     struct Weights {
         uint4 q0, q1;     // micro-blocks 8 kg .. 8 kg + 3 and 8 kg + 4 .. 8 kg + 7
-        uint4 meta;       // bw = 4: metadata dwords of the two chunks (x, y), coefficient word (w)
+        uint4 meta;       // bw = 4: metadata dwords of the two chunks (x, y), coefficient word (w); 16 outputs, integers: the one dword of the chunk (x)
     };
     auto load_weights = [&](int g, Weights &w) {
         const uint32_t *p = wq + g * gstride;
         w.q0 = *reinterpret_cast<const uint4 *>(p);
-        w.q1 = *reinterpret_cast<const uint4 *>(p + GOQ_ROWS * 4);
-        w.meta = make_uint4(0, 0, 0, 0);
-        if constexpr (BW == 4) {
+        w.q1 = w.meta = make_uint4(0, 0, 0, 0);
+        if constexpr (!NARROW) w.q1 = *reinterpret_cast<const uint4 *>(p + GOQ_ROWS * 4);
+        if constexpr (BW == 4 && IN_ORDER) {
+            const uint2 two = *reinterpret_cast<const uint2 *>(p + (4 - chunk) * GOQ_ROWS * 4 + 2 * (kg & 1));
+            w.meta.x = two.x;
+            w.meta.y = two.y;
+        } else if constexpr (BW == 4 && NARROW) {
+            w.meta.x = p[(4 - kg) * GOQ_ROWS * 4 + kg];
+        } else if constexpr (BW == 4) {
             // chunk 4 of the same row: one metadata dword per chunk, each with a byte of the
             // coefficient word on top
             const uint4 mq = *reinterpret_cast<const uint4 *>(p + (4 - 2 * kg) * GOQ_ROWS * 4);
@@ -249,6 +270,15 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
             w.meta = make_uint4(kg ? mq.z : mq.x, kg ? mq.w : mq.y, 0, cw);
         }
     };
+    // Activations that pass through registers are fetched three slabs ahead and unpacked a slab later, where a slab is short (16 outputs per wavefront; us, fetched and
+    // unpacked in the same slab / this: 4096 x 4608, 58 tokens, W4/A4 42.5 / 29.4; 4045 x 6656 twice, 38 tokens, W3/A3 53.9 / 42.9).
+    // Elsewhere it costs (two of 11008 x 4096, 203 tokens, W4/A8 99 / 104; ViT-B block, 12608 tokens, W3/A6
+    // 289 / 320, W4/A3 237 / 259, where it spills).
+    constexpr bool EARLY = REGSTAGE && NARROW;
+    constexpr int NW = (NARROW ? 1 : 2) + (BW == 4 ? 1 : 0);       // vector-memory instructions of a request
+    // Weights are requested so many slabs ahead.  (16 outputs per wavefront: a slab takes 0.5 to 0.8 us, less than memory does; 203 tokens, 4096 x 4096, one / two: W3/A8
+    // 31.3 / 23.2, W3/A16 28.5 / 26.0, W4/A16 31.7 / 29.3 us.)
+    constexpr int AHEAD = NARROW ? 2 : 1;
     auto word_of = [](const Weights &w, int t) {
         return t == 0 ? w.q0.x : t == 1 ? w.q0.y : t == 2 ? w.q0.z : t == 3 ? w.q0.w
              : t == 4 ? w.q1.x : t == 5 ? w.q1.y : t == 6 ? w.q1.z : w.q1.w;
@@ -262,14 +292,15 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     // them is per-lane, which the range check counts.
     constexpr int PIECES = TM * GOQ_N * XB / 16;
     constexpr int PER_ROW = GOQ_N * XB / 16;
-    constexpr int NP = PIECES / 256;
+    constexpr int NP = (PIECES + THREADS - 1) / THREADS;
+    constexpr bool HALF = NP * THREADS > PIECES;       // half of the wavefronts have no piece: they request zeros from outside the window
     auto swz = [](int row) { return F16 ? (row & 15) : ((row >> 1) & 7); };
     const uint32_t xline = (uint32_t)a.in * XB;
     uint32_t xoff[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        const int row = i * (256 / PER_ROW) + tid / PER_ROW;
-        xoff[i] = goq_piece_offset(row, (tid % PER_ROW) ^ swz(row), xline);
+        const int row = i * (THREADS / PER_ROW) + tid / PER_ROW;
+        xoff[i] = HALF && row >= TM ? 0x7fffffffu : goq_piece_offset(row, (tid % PER_ROW) ^ swz(row), xline);
     }
     const uint64_t xtile = (uint64_t)(uintptr_t)a.X + (uint64_t)m0 * xline;
     uint32_t xbytes = goq_tile_bytes(a.tokens - m0, TM, xline);
@@ -280,7 +311,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
 #pragma unroll
         for (int i = 0; i < NP; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsrc, (__attribute__((address_space(3))) void *)(buf + (i * 256 + wave * 64) * 16), 16, (int)xoff[i], 0, 0, 0);
+                rsrc, (__attribute__((address_space(3))) void *)(HALF && wave * 64 >= PIECES ? spare : buf + (i * THREADS + wave * 64) * 16), 16, (int)xoff[i], 0, 0, 0);
     };
     // Register staging (ACT >= 2): integer activations pass through registers and are unpacked /
     // widened on their way into LDS.  A thread moves NPS 16-byte pieces per slab; a piece holds
@@ -290,14 +321,14 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     constexpr int SRCROW = X4 ? GOQ_N / 2 : X6 ? GOQ_N * 3 / 4 : X3 ? GOQ_N * 3 / 8 : GOQ_N;   // bytes of a slab row in memory
     constexpr int SRCP = X6 ? 24 : X3 ? 12 : 16;                   // bytes of a source piece
     constexpr int SPR = SRCROW / SRCP;                             // source pieces per row
-    constexpr int NPS = (TM * SPR + 255) / 256;
+    constexpr int NPS = (TM * SPR + THREADS - 1) / THREADS;
     constexpr int NQ = X6 ? 2 : 1;                                 // uint4 registers per source piece (int6: 6 of 8 words used)
     constexpr int OUTP = ROWB / SPR / 16;                          // LDS pieces per source piece
     const int64_t xpitch = X4 ? a.in / 2 : X6 ? a.in / 4 * 3 : X3 ? a.in / 8 * 3 : a.in;   // bytes of a token row in memory
     uint32_t soff[NPS];
 #pragma unroll
     for (int i = 0; i < NPS; ++i) {
-        const int S = i * 256 + tid;
+        const int S = i * THREADS + tid;
         int m = m0 + S / SPR;
         m = m < a.tokens ? m : a.tokens - 1;
         soff[i] = (uint32_t)(m - m0) * (uint32_t)xpitch + (S % SPR) * SRCP;
@@ -323,9 +354,9 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     auto write_x = [&](unsigned char *buf, const uint4 (&r)[NPS * NQ]) {
 #pragma unroll
         for (int i = 0; i < NPS; ++i) {
-            const int S = i * 256 + tid;
+            const int S = i * THREADS + tid;
             const int row = S / SPR, cs = S % SPR;
-            if (NPS * 256 > TM * SPR && S >= TM * SPR) continue;
+            if (NPS * THREADS > TM * SPR && S >= TM * SPR) continue;
             uint32_t o[16];                                        // the source piece's LDS pieces
             if constexpr (X6) {
                 // 6 dwords = 8 groups of 24 bits; group j starts at bit 24 j
@@ -367,12 +398,24 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
                     make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
         }
     };
+    // IN_ORDER: lanes of groups 0 and 2 (1 and 3) have loaded chunks 0 and 1 (2 and 3) of the same rows; they swap dwords so that group 0 (1) has the even
+    // micro-blocks of both chunks and group 2 (3) the odd ones.
+    auto arrange = [&](Weights &w) {
+        if constexpr (IN_ORDER) {
+            const auto a = __builtin_amdgcn_permlane32_swap(w.q0.x, w.q0.y, false, false), b = __builtin_amdgcn_permlane32_swap(w.q0.z, w.q0.w, false, false);
+            w.q0 = make_uint4(a[0], b[0], a[1], b[1]);
+        }
+    };
     // decoded B operands (b1 and b2) of k-step t of a slab (H2, H4); cf (FOLD): the slab's
     // coefficients (c1, c2) as fp16, both halves of a register alike
     f16x8 cf1, cf2;
     auto decode_step = [&](const Weights &w, int t, OpT &B1, OpT &B2) {
         if constexpr (F16) {
             uint32_t l1, h1, l2, h2;
+            if constexpr (IN_ORDER) {
+                const uint4 m = make_uint4(w.meta.x >> (6 * (kg >> 1)), w.meta.y >> (6 * (kg >> 1)), 0, 0);
+                decode_pair<BW, WACT>(word_of(w, t), m, 2 * t, xtab, l1, h1, l2, h2);
+            } else
             decode_pair<BW, WACT>(word_of(w, t), w.meta, t, xtab, l1, h1, l2, h2);
             B1 = widen8(l1, h1);
             B2 = widen8(l2, h2);
@@ -397,10 +440,10 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     // A operands of k-step t: token 32 i + ln, the 16-byte piece that holds the k of micro-block(s)
     // 8 kg + MPK t .. of the slab
     auto read_a = [&](const unsigned char *xs, int t, int tile0, OpT (&A)[MA]) {
-        const int piece = KSTEPS * kg + t;
+        const int piece = IN_ORDER ? 8 * (kg & 1) + 2 * t + (kg >> 1) : KSTEPS * kg + t;
 #pragma unroll
         for (int i = 0; i < MA; ++i) {
-            const unsigned char *row = xs + (32 * (tile0 + i) + ln) * ROWB;          // (swz has a period of 32 rows)
+            const unsigned char *row = xs + (WN * (tile0 + i) + ln) * ROWB;          // (swz has a period of 16 rows)
             if constexpr (F8) {
                 const i32x4 a0 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece) ^ swz(ln)) * 16));
                 const i32x4 a1 = *reinterpret_cast<const i32x4 *>(row + (((2 * piece + 1) ^ swz(ln)) * 16));
@@ -411,7 +454,28 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     // coefficient pair of this lane's output channel
     auto coefficients = [&](const Weights &w, float &c1, float &c2) {
         uint32_t cw;
-        if constexpr (BW == 3) {
+        if constexpr (IN_ORDER && BW == 4) {
+            // lane groups 0 and 2 have c1, 1 and 3 c2
+            cw = ((w.meta.x >> 24) | (w.meta.y >> 24) << 8) << (16 * (kg & 1));
+            const auto v = __builtin_amdgcn_permlane16_swap(cw, cw, false, false);
+            cw = v[0] | v[1];
+        } else if constexpr (NARROW) {
+            // each of a row's four lanes has one byte, IN_ORDER every other pair of bits
+            if constexpr (IN_ORDER) {
+                cw = (word_of(w, 0) >> 30 << 12 | word_of(w, 1) >> 30 << 8 | word_of(w, 2) >> 30 << 4 | word_of(w, 3) >> 30) << (18 - 2 * (kg >> 1) - 16 * (kg & 1));
+            } else if constexpr (BW == 3) {
+                cw = word_of(w, 0) >> 30;
+#pragma unroll
+                for (int t = 1; t < 4; ++t) cw = __builtin_amdgcn_alignbit(cw, word_of(w, t), 30);
+                cw <<= 8 * (3 - kg);
+            } else {
+                cw = (w.meta.x >> 24) << (8 * kg);
+            }
+            const auto u = __builtin_amdgcn_permlane32_swap(cw, cw, false, false);
+            cw = u[0] | u[1];
+            const auto v = __builtin_amdgcn_permlane16_swap(cw, cw, false, false);
+            cw = v[0] | v[1];
+        } else if constexpr (BW == 3) {
             // a lane's 8 dwords carry 16 of the 32 bits (lane group 0: c2, lane group 1: c1)
             uint32_t part = 0;
 #pragma unroll
@@ -429,6 +493,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     Weights wA, wB, wC;
     uint4 xr[NPS * NQ];
     load_weights(0, wA);
+    if constexpr (AHEAD == 2) load_weights(min(1, a.gn - 1), wB);
     if constexpr (ACT != 0)
         if (tid < TM) sxs[tid] = a.sx[min(m0 + tid, a.tokens - 1)] * (F16 || F8 ? 1.f : 1.f / (float)(1 << ((1 << (BW - 1)) - 1)));
     if constexpr (REGSTAGE) {
@@ -437,6 +502,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
         fetch_x(min(1, a.gn - 1), xr1);
         write_x(xs0, xr);
         write_x(xs1, xr1);
+        if constexpr (EARLY) fetch_x(min(2, a.gn - 1), xr);
     } else {
         stage_x(0, xs0);
         if (a.gn > 1) stage_x(1, xs1);
@@ -452,6 +518,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     };
     OpT B1, B2, A[MA];
     if constexpr (FOLD) fold_coefficients(wA);
+    arrange(wA);
     decode_step(wA, 0, B1, B2);
     read_a(xs0, 0, 0, A);
 
@@ -463,9 +530,18 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     auto products = [&](int t, const OpT &Ai, const OpT &B1i, const OpT &B2i, AccT &P1, AccT &P2, int i) {
         AccT z;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) z[v] = BIASED ? START : 0;
+        for (int v = 0; v < ACCS; ++v) z[v] = BIASED ? START : 0;
         if constexpr (FOLD) {
             Yacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B1i, Yacc[i], 0, 0, 0);
+        } else if constexpr (NARROW && F16) {
+            P1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ai, B1i, t == 0 ? z : P1, 0, 0, 0);
+            P2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ai, B2i, t == 0 ? z : P2, 0, 0, 0);
+        } else if constexpr (NARROW && F8) {
+            P1 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(Ai, B1i, t == 0 ? z : P1, 1, 1, 0, 127, 0, 127);
+            P2 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(Ai, B2i, t == 0 ? z : P2, 1, 1, 0, 127, 0, 127);
+        } else if constexpr (NARROW) {
+            P1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(Ai, B1i, t == 0 ? z : P1, 0, 0, 0);
+            P2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(Ai, B2i, t == 0 ? z : P2, 0, 0, 0);
         } else if constexpr (F16) {
             P1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B1i, t == 0 ? z : P1, 0, 0, 0);
             P2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ai, B2i, t == 0 ? z : P2, 0, 0, 0);
@@ -483,7 +559,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     auto rescale = [&](int g, int i, float c1, float c2, const AccT &P1, const AccT &P2) {
         if constexpr (!FOLD) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
+            for (int v = 0; v < ACCS; ++v) {
                 if constexpr (BIASED) {
                     Yacc[i][v] = fmaf(c1, __int_as_float(P1[v]) - __int_as_float(START), Yacc[i][v]);
                     Yacc[i][v] = fmaf(c2, __int_as_float(P2[v]) - __int_as_float(START), Yacc[i][v]);
@@ -510,12 +586,13 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     // Everything older than this slab's activation request has landed once at most NP vector-memory operations are
     // outstanding (they return in order): slab g + 1's activations, requested a slab ago, and its weights.
     auto slab_barrier = [&](int g, unsigned char *xf) {
-        if constexpr (REGSTAGE) {
+        if constexpr (EARLY) {
+        } else if constexpr (REGSTAGE) {
             // (register path: slab g + 2 is written here; its buffer was last read before the previous slab's
             // barrier, and it is first read after the next one)
             if (F8 || g + 2 < a.gn) write_x(xf, xr);
         } else {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NP + (AHEAD == 2 ? NW : 0)) : "memory");
         }
         if constexpr (ROLL || (ACT == 1 && MS == 2)) {
             // int8 tiles of 64 tokens are bound by vector-ALU issue with three workgroups per
@@ -532,13 +609,18 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     };
     // One slab: its weights wd and activations xs, the next slab's weights wn (requested here) and
     // activations xn (requested a slab ago), and the buffer xf that slab g + 2 is requested into.
-    auto slab = [&](int g, const Weights &wd, Weights &wn, const unsigned char *xs, const unsigned char *xn, unsigned char *xf) {
+    auto slab = [&](int g, const Weights &wd, Weights &wn, Weights &wf, const unsigned char *xs, const unsigned char *xn, unsigned char *xf) {
         // (The weight request is on a clamped slab index, past the last slab the result is not used; the
         // activation request comes last and is unconditional -- past the last slab it lies outside the
         // buffer and touches no memory -- so that the wait below and the compiler's own for the weights
         // are exact: under a run-time condition it waits for everything.)
-        load_weights(min(g + 1, a.gn - 1), wn);
-        if constexpr (REGSTAGE) {
+        if constexpr (EARLY) {
+            write_x(xf, xr);
+            fetch_x(min(g + 3, a.gn - 1), xr);
+        }
+        load_weights(min(g + AHEAD, a.gn - 1), AHEAD == 2 ? wf : wn);
+        if constexpr (EARLY) {
+        } else if constexpr (REGSTAGE) {
             // (8-bit floats: unconditional too, unpacking a slab too much at the end costs less than the waits)
             if (F8 || g + 2 < a.gn) fetch_x(min(g + 2, a.gn - 1), xr);
         } else {
@@ -563,7 +645,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
         }
 
         // The slab's token tiles, MA at a time; more than one group keeps the decoded weights of the whole slab.
-        constexpr int GROUPS = MS / MA;
+        constexpr int GROUPS = MT / MA;
         OpT S1[GROUPS == 1 ? 1 : KSTEPS], S2[GROUPS == 1 ? 1 : KSTEPS];
 #pragma unroll
         for (int h = 0; h < GROUPS; ++h) {
@@ -585,6 +667,7 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
                 } else {
                     slab_barrier(g, xf);
                     if constexpr (FOLD) fold_coefficients(wn);
+                    arrange(wn);
                     decode_step(wn, 0, B1, B2);
                     read_a(xn, 0, 0, A);
                 }
@@ -598,18 +681,19 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     if constexpr (ROLL) {
         unsigned char *x0 = xs0, *x1 = xs1, *x2 = xs2;
         for (int g = 0; g < a.gn; ++g) {
-            slab(g, wA, wB, x0, x1, x2);
+            slab(g, wA, wB, wC, x0, x1, x2);
             wA = wB;
+            if constexpr (AHEAD == 2) wB = wC;
             unsigned char *const t = x0;
             x0 = x1; x1 = x2; x2 = t;
         }
     } else
     for (int g = 0;;) {
-        slab(g, wA, wB, xs0, xs1, xs2);
+        slab(g, wA, wB, wC, xs0, xs1, xs2);
         if (++g == a.gn) break;
-        slab(g, wB, wC, xs1, xs2, xs0);
+        slab(g, wB, wC, wA, xs1, xs2, xs0);
         if (++g == a.gn) break;
-        slab(g, wC, wA, xs2, xs0, xs1);
+        slab(g, wC, wA, wB, xs2, xs0, xs1);
         if (++g == a.gn) break;
     }
     // No load may still be on its way into LDS, and no wavefront still reading a slab, when the slabs' memory is
@@ -623,36 +707,40 @@ __global__ __launch_bounds__(256, BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2)
     // behind the store before it: 32 round trips to memory per tile, half the time of a tile of six slabs (us, single
     // elements / pieces: ViT-B block, 12608 tokens, W3/A8 296 / 259; 1576 tokens, W4/A4 55.0 / 44.2; two of
     // 11008 x 4096, 203 tokens, W4/A16 96.3 / 92.2).
-    unsigned char *const turn = (wave < 2 ? xs0 : xs1) + (wave & 1) * 2048;
+    // 2 KiB of a wavefront: tokens x its outputs; 16 x 16 tiles: register v of lane group kg is token 4 kg + v.
+    constexpr int TURNS = NARROW ? TM * ROWB / 2048 : 2;   // wavefronts whose 2 KiB one slab's memory holds
+    unsigned char *const turn = (wave / TURNS == 0 ? xs0 : !NARROW || wave / TURNS == 1 ? xs1 : wave / TURNS == 2 ? xs2 : spare) + (wave % TURNS) * 2048;
     auto store_tile = [&](auto element) {
         using T = decltype(element);
         typedef T piece_t __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));   // rows begin anywhere
         constexpr int E = 16 / sizeof(T);                  // elements of a piece
-        constexpr int PPR = 32 / E;                        // pieces of a row
-        constexpr int ROWS = 2048 / 32 / sizeof(T);        // tokens of a pass
-        constexpr int REGS = ROWS / 2;
+        constexpr int PPR = WN / E;                        // pieces of a row
+        constexpr int ROWS = 2048 / WN / sizeof(T);        // tokens of a pass (fp16 with 16 outputs: twice the tile's, half a pass)
+        constexpr int REGS = ROWS * WN / 64;
         T *const Y = reinterpret_cast<T *>(a.Y) + (int64_t)m0 * a.out + n0;
 #pragma unroll
-        for (int pass = 0; pass < MS * 32 / ROWS; ++pass) {
+        for (int pass = 0; pass < (NARROW ? (TM + ROWS - 1) / ROWS : TM / ROWS); ++pass) {
             // register v of a pass: token 8 (v / 4) + 4 kg + v % 4, kept in row 8 (v / 4) + 2 (v % 4) + kg, so that the
             // two lane groups write to different banks
 #pragma unroll
             for (int v = 0; v < REGS; ++v) {
                 const int at = pass * REGS + v;
-                float y = Yacc[at / 16][at % 16];
+                if (at / ACCS >= MT) break;
+                float y = Yacc[at / ACCS][at % ACCS];
+                const int token = NARROW ? 16 * (v / 4) + 4 * kg + v % 4 : 8 * (v / 4) + 4 * kg + v % 4;      // of the pass
                 if constexpr (ACT != 0) {
-                    y *= sxs[pass * ROWS + 8 * (v / 4) + 4 * kg + v % 4];
+                    y *= sxs[pass * ROWS + token];
                     asm("" : "+v"(y));                     // (rounded to fp32 before it becomes fp16: no fused form)
                 }
-                reinterpret_cast<T *>(turn)[(8 * (v / 4) + 2 * (v % 4) + kg) * 32 + ln] = (T)y;
+                reinterpret_cast<T *>(turn)[(NARROW ? token : 8 * (v / 4) + 2 * (v % 4) + kg) * WN + ln] = (T)y;
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const int row = (r * 64 + lane) / PPR, col = lane % PPR * E;
-                const int m = pass * ROWS + (row & ~7) + 4 * (row & 1) + ((row >> 1) & 3);
+                const int m = pass * ROWS + (NARROW ? row : (row & ~7) + 4 * (row & 1) + ((row >> 1) & 3));
                 const piece_t piece = *reinterpret_cast<const piece_t *>(turn + (r * 64 + lane) * 16);
-                if (m0 + m < a.tokens) {
+                if (m0 + m < a.tokens && (!NARROW || m < TM)) {
                     T *const to = Y + (int64_t)m * a.out + col;
                     if (n0 + col + E <= a.out) {
                         *reinterpret_cast<piece_t *>(to) = piece;
@@ -709,9 +797,20 @@ int launch_ms(hipStream_t st, GemmBatch &b, int n, bool part)
     const int grid = lay_out(b, n, 32 * MS, goq_block_bytes<GOQ_ACT>(), goq_chunks(BW) * GOQ_ROWS * 16);
     constexpr bool PART = ACT != 0 && MS < 4;                // (there are no tiles of 128 tokens with partials)
     if (PART && part)
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
     else
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
+    return goq_check_launch("goq_gemm");
+}
+
+// alone: LDS that nothing uses keeps a second workgroup off the CU (goq_sixteen_outputs)
+template <int BW, int ACT>
+int launch_sixteen(hipStream_t st, GemmBatch &b, int n, bool alone)
+{
+    constexpr int GOQ_ACT = ACT == 0 ? GOQ_A16 : ACT <= 2 ? GOQ_A8 : ACT <= 4 ? GOQ_A4 : ACT <= 6 ? GOQ_A6 : GOQ_A3;
+    constexpr unsigned SPARE = 72 * 1024;
+    const int grid = lay_out(b, n, 32, goq_block_bytes<GOQ_ACT>(), goq_chunks(BW) * GOQ_ROWS * 16);
+    hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, 1, 16>), dim3((unsigned)grid), dim3(512), alone ? SPARE : 0, st, b);
     return goq_check_launch("goq_gemm");
 }
 
@@ -725,6 +824,9 @@ int launch(hipStream_t st, GemmBatch &b, int n)
         p[i] = GoqTileProblem{b.p[i].tokens, b.p[i].out, b.p[i].gn};
         part = part || b.p[i].partials;
     }
+    static_assert(GOQ_MAX_TILE_PROBLEMS == GOQ_MAX_BATCH, "the rules' arrays");
+    const int sixteen = part ? 0 : goq_sixteen_outputs(n, p);
+    if (sixteen) return launch_sixteen<BW, ACT>(st, b, n, sixteen == 2);
     if constexpr (F8 || ACT == 1)
         if (!part && goq_wide_tiles(F8, n, p)) return launch_ms<BW, ACT, 4>(st, b, n, false);
     // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
@@ -737,7 +839,7 @@ template <int BW>
 int launch_folded(hipStream_t st, GemmBatch &b, int n)
 {
     const int grid = lay_out(b, n, 64, goq_block_bytes<GOQ_A16>(), goq_chunks(BW) * GOQ_ROWS * 16);
-    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2>), dim3((unsigned)grid), dim3(256), 0, st, b);
+    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm_folded");
 }
 

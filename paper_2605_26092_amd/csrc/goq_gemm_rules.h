@@ -15,11 +15,12 @@ GOQ_HD int goq_xcd_tile(int tile, int tiles)
     return k * (tiles / 8) + (k < rest ? k : rest) + tile / 8;
 }
 
+constexpr int GOQ_MAX_TILE_PROBLEMS = 8;
 struct GoqTileProblem {
     int tokens, out, gn;
 };
 
-// Tokens per tile, of the launches that goq_wide_tiles below leaves: 32 (true) or 64.  Results do not depend on the choice.
+// Tokens per tile, of the launches that goq_sixteen_outputs and goq_wide_tiles below leave: 32 (true) or 64.  Results do not depend on the choice.
 //
 // A CU's time is set by the workgroups it holds, K = tiles per CU: the first one costs its latency, every further
 // one its share of the issue slots.  A 32-token tile costs 0.77 (fp16, W3) to 0.89 (W4) of a 64-token one where it
@@ -98,6 +99,53 @@ inline bool goq_wide_tiles(bool f8, int n, const GoqTileProblem *p)
     wide = (wide / deepest + 255) / 256;
     middle = (middle / deepest + 255) / 256;
     return wide >= 2 && (!f8 && deepest <= 8 ? 8 * middle >= 15 * wide : 4 * middle >= 7 * wide);
+}
+
+// 32-token tiles on eight wavefronts of 16 outputs each, or one of the kernels with 32 outputs per wavefront?  Results do not depend on the choice.
+//
+// Half the chain of instructions per slab where a workgroup has its CU to itself; where CUs hold two and more, the chains hide each other and the second reading of the
+// activations from LDS costs.  So for up to one tile per CU.  300 launches, time over the best of the other widths, up to 256 tiles / one to two per CU:
+//     W3/A16 0.92 .. 0.99 / 1.04 .. 1.24   W4/A16 0.81 .. 0.95 / 1.05 .. 1.20   W3/A8 0.76 .. 0.91 / 0.98 .. 1.07   W4/A8 0.77 .. 0.91 / 1.03 .. 1.32
+//     W3 with int6 and int3 0.61 .. 0.92 / 0.94 .. 1.16   W4/A6 0.79 .. 0.96 / 1.0 .. 1.4   W4/A4 0.59 .. 0.84 / 1.02 .. 1.12
+// In a launch of layers of several depths the short tiles fill what the deepest leave free: up to one and an eighth per CU, counted in tiles of the deepest layer (ViT-B
+// block, 197 tokens, 0.49, W4/A8 30.5 / 24.7 us, W4/A4 35.2 / 22.2; 7B block, 64 tokens, 1.12, W3/A16 81.0 / 78.7, W3/A8 75.9 / 61.2; ViT-B block, 500 tokens, 1.125,
+// W3/A16 25.9 / 26.6; 4096 x 2048 and 2048 x 4096, 260 tokens, 1.125, W4/A16 35.0 / 37.6).
+// More than 112 tiles of more than half the deepest layer's depth leave the short ones too few CUs of their own (4096 x 2048 and 2048 x 4096, 230 tokens, W3/A16 28.1 / 30.2;
+// 1126 x 4224 and 567 x 6016, 589 tokens 44.0 / 51.8).
+//
+// 0: no, 1: yes, 2: yes, and a workgroup gets its CU to itself: launches of layers of several depths, more tiles than CUs, where the short tiles can go through the CUs that the deepest
+// leave, one after the other, before those end; a tile costs five slabs more than it has.  us, shared / alone: ViT-B block, 197 tokens, W4/A6 29.8 / 28.1, 330 tokens 30.4 / 36.1;
+// 4096 x 2048 and 2048 x 4096, 200 tokens, W4/A16 35.7 / 31.1; 7B block, 40 tokens, W3/A16 72.6 / 93.4.
+inline int goq_sixteen_outputs(int n, const GoqTileProblem *p)
+{
+    int64_t deepest = 0, tiles[GOQ_MAX_TILE_PROBLEMS], all = 0, slabs = 0, cost = 0, deep = 0, tall = 0, rounds = 0;
+    bool equal = true;
+    for (int i = 0; i < n; ++i) {
+        tiles[i] = ((int64_t)p[i].tokens + 31) / 32 * ((p[i].out + GOQ_TILE_OUT - 1) / GOQ_TILE_OUT);
+        all += tiles[i];
+        slabs += tiles[i] * p[i].gn;
+        cost += tiles[i] * (p[i].gn + 5);
+        deepest = p[i].gn > deepest ? p[i].gn : deepest;
+        equal = equal && p[i].gn == p[0].gn;
+    }
+    if (all <= 256) return 1;
+    if (equal || slabs >= 288 * deepest) return 0;
+    for (int i = 0; i < n; ++i) {
+        deep += p[i].gn == deepest ? tiles[i] : 0;
+        tall += 2 * p[i].gn > deepest ? tiles[i] : 0;
+    }
+    if (deep < 256 && cost <= 256 * (deepest + 5)) {
+        for (int i = 0; i < n; ++i) {                // (layers of one depth go through together)
+            int64_t alike = 0;
+            for (int j = 0; j < n; ++j) {
+                if (p[j].gn == p[i].gn && j < i) break;
+                alike += p[j].gn == p[i].gn ? tiles[j] : 0;
+            }
+            if (p[i].gn < deepest) rounds += (alike + 255 - deep) / (256 - deep) * (p[i].gn + 5);
+        }
+        if (100 * rounds <= 114 * (deepest + 5)) return 2;
+    }
+    return tall <= 112 ? 1 : 0;
 }
 
 // Which tiles of a problem an XCD gets.  Workgroups are dealt to the eight XCDs in turn, so in launch order (token tiles of one output

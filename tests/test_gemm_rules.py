@@ -165,6 +165,20 @@ ALONE = [
 ]
 
 
+# layers, weight bits, activations, tokens, microseconds of the best other width, of 16 outputs per wavefront with two workgroups on a CU and
+# with one, of 4 % or more
+SIXTEEN = [
+    ("4096x4096", 4, "a16", 203, 34.6, 29.3, 29.3), ("4096x4096", 3, "a8", 64, 27.8, 22.2, 22.2), ("543x5504", 3, "a16", 40, 33.6, 32.0, 32.0),
+    ("11666x11264", 3, "a16", 69, 88.0, 104.0, 104.0), ("10930x1408", 4, "a16", 191, 23.2, 27.4, 27.4), ("7732x4096", 4, "a6", 147, 47.4, 63.9, 63.9),
+    ("10331x1536*2", 4, "a4", 155, 27.4, 40.7, 40.7), ("1553x8960*2", 4, "a16", 75, 70.1, 57.2, 57.2),
+    (VIT_B, 4, "a4", 197, 35.2, 22.7, 22.2), (VIT_B, 4, "a6", 197, 34.7, 29.8, 28.1), (VIT_B, 3, "a8", 330, 22.3, 19.7, 23.8), (VIT_B, 4, "a16", 430, 27.9, 25.4, 30.4),
+    (BLOCK_7B, 3, "a8", 64, 75.9, 61.2, 78.6), (BLOCK_7B, 3, "a16", 40, 76.2, 72.6, 93.4), ("4096x2048 2048x4096", 4, "a16", 200, 35.4, 35.7, 31.1),
+    ("4096x2048 2048x4096", 4, "a16", 260, 35.0, 37.6, 43.6), ("2048x2048*2 2048x5504", 4, "a6", 250, 57.7, 52.9, 46.2), (VIT_L, 3, "a16", 330, 33.0, 31.6, 36.9),
+    ("3000x1024*3 1024x3072", 4, "a6", 300, 35.0, 37.5, 44.4), ("4096x2048 2048x4096", 3, "a16", 230, 28.1, 30.2, 40.0),
+    ("1126x4224 567x6016", 3, "a16", 589, 44.0, 51.8, 51.8), ("3072x1024 1024x1024 4096x1024 1024x4096", 3, "a16", 230, 31.2, 28.8, 27.7),
+]
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     """The rules' answers to a list of questions."""
@@ -203,6 +217,15 @@ def test_wide_tiles_follow_the_measurements(ask):
     assert len(got) == len(WIDE)
     wrong = [(case, g) for case, g in zip(WIDE, got) if int(g) != (128 if case[5] < case[4] else 0)]
     assert not wrong, wrong
+
+
+def test_sixteen_outputs_follow_the_measurements(ask):
+    lines = []
+    for text, bw, act, tokens, _, _, _ in SIXTEEN:
+        layers = _layers(text)
+        lines.append("half %d %d %d %d %s" % (bw, act == "a16", act != "a16", len(layers), " ".join("%d %d %d" % ((tokens,) + l) for l in layers)))
+    for answer, (text, bw, act, tokens, *us) in zip(ask(lines), SIXTEEN):
+        assert us[int(answer)] <= 1.01 * min(us), (text, bw, act, tokens, answer, us)
 
 
 def test_a_cu_to_each_workgroup_follows_the_measurements(ask):

@@ -1,0 +1,77 @@
+"""goq_gemm launches with 16 outputs per wavefront (those that leave CUs with one workgroup): the bits of the kernels with 32, which the
+same problem takes in a batch with a larger one, and the oracle's values."""
+import numpy as np
+import pytest
+
+import goq_inputs
+from tests import gpu_util as gu
+from tests.test_gemm_rules import ask                              # (ask: a fixture)
+from tests.test_gpu_gemm_small import PACKERS, _inputs
+
+pytestmark = pytest.mark.gpu
+
+# edges of 32 tokens, of 16 and 128 outputs; one to nine slabs (the buffers change places every third)
+SHAPES = [(33, 1, 128), (64, 17, 256), (65, 129, 384), (100, 300, 512), (96, 250, 1152), (257, 1000, 640)]
+
+
+def _half(ask, problems):
+    return ask(["half 3 0 0 %d %s" % (len(problems), " ".join("%d %d %d" % p for p in problems))])[0]
+
+
+def _problem(goq, bw, act, tokens, out, inn, ytype, seed):
+    torch = gu.torch_cuda()
+    q = goq_inputs.canonical_random(bw, out, inn, config_id=83, tensor_id=seed)
+    xd, sxd, x, sx = _inputs(goq, act, tokens, inn)
+    Y = torch.full((tokens, out), float("nan"), dtype=torch.float32 if ytype == goq.F32 else torch.float16, device="cuda")
+    return q, x, sx, (tokens, out, inn, gu.pack_layer(goq, q), xd, sxd, Y, ytype)
+
+
+@pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,out,inn", SHAPES)
+def test_bits_do_not_depend_on_the_width(oracle, ask, act, bw, tokens, out, inn):
+    """fp32 outputs within 2e-6 of the sum of absolute products (2^-24 per rounding, at most some ten of them on a path)."""
+    import paper_2605_26092_amd as goq
+    from paper_2605_26092_amd import binding
+    torch = gu.torch_cuda()
+    print("sixteen %s bw=%d %dx%dx%d" % (act, bw, tokens, out, inn), flush=True)
+    large = (700, 6000, inn)
+    assert _half(ask, [(tokens, out, inn)]) == "1" and _half(ask, [(tokens, out, inn), large]) == "0"
+    for ytype in (goq.F32, goq.F16):
+        q, x, sx, p = _problem(goq, bw, act, tokens, out, inn, ytype, out)
+        goq.gemm(bw, getattr(goq, act), *p)
+        torch.cuda.synchronize()
+        alone = p[6].clone()
+        p[6].fill_(float("nan"))
+        goq.gemm_batch(bw, getattr(goq, act), binding.make_gemm_descs([_problem(goq, bw, act, *large, goq.F16, 1)[3], p]))
+        torch.cuda.synchronize()
+        assert torch.isfinite(alone).all() and torch.equal(alone, p[6])
+        if ytype == goq.F32:
+            what = np.abs(oracle.dequant(q, want=("what",))["what"]).T
+            ref = oracle.gemm_a16(q, x, threads=8) if sx is None else oracle.gemm_a8(q, x, sx, threads=8)[0]
+            scale = (np.abs(x.astype(np.float64)) * (1.0 if sx is None else sx[:, None])) @ what + 1e-30
+            assert np.max(np.abs(alone.cpu().numpy().astype(np.float64) - ref) / scale) <= 2e-6
+
+
+@pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
+@pytest.mark.parametrize("bw", [3, 4])
+@pytest.mark.parametrize("tokens,layers,answer", [(300, [(3000, 128), (520, 3072)], "2"), (1700, [(3000, 128), (200, 3072)], "1"), (40, [(700, 384), (1000, 640), (33, 128)], "1")])
+def test_layers_of_several_depths(ask, act, bw, tokens, layers, answer):
+    """More tiles than CUs, with a workgroup on each CU and with two: the bits of single calls."""
+    import paper_2605_26092_amd as goq
+    from paper_2605_26092_amd import binding
+    torch = gu.torch_cuda()
+    print("sixteen, depths %s bw=%d %d tokens %s" % (act, bw, tokens, layers), flush=True)
+    assert _half(ask, [(tokens,) + l for l in layers]) == answer
+    problems, single = [], []
+    for out, inn in layers:
+        p = _problem(goq, bw, act, tokens, out, inn, goq.F16, out)[3]
+        goq.gemm(bw, getattr(goq, act), *p)
+        torch.cuda.synchronize()
+        single.append(p[6].clone())
+        p[6].fill_(float("nan"))
+        problems.append(p)
+    goq.gemm_batch(bw, getattr(goq, act), binding.make_gemm_descs(problems))
+    torch.cuda.synchronize()
+    for p, y in zip(problems, single):
+        assert torch.isfinite(y).all() and torch.equal(p[6], y)
