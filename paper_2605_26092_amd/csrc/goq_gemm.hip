@@ -271,10 +271,10 @@ __global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : BW == 3 && !PART && AC
         }
     };
     // Activations that pass through registers are fetched three slabs ahead and unpacked a slab later, where a slab is short (16 outputs per wavefront; us, fetched and
-    // unpacked in the same slab / this: 4096 x 4608, 58 tokens, W4/A4 42.5 / 29.4; 4045 x 6656 twice, 38 tokens, W3/A3 53.9 / 42.9).
-    // Elsewhere it costs (two of 11008 x 4096, 203 tokens, W4/A8 99 / 104; ViT-B block, 12608 tokens, W3/A6
+    // unpacked in the same slab / this: 4096 x 4608, 58 tokens, W4/A4 42.5 / 29.4; 4045 x 6656 twice, 38 tokens, W3/A3 53.9 / 42.9) and in
+    // tiles of 128 tokens with int4 (ViT-B block, 12608 tokens 234 / 229, 8192 x 8192, 1024 tokens 160 / 153).  Elsewhere it costs (two of 11008 x 4096, 203 tokens, W4/A8 99 / 104; ViT-B block, 12608 tokens, W3/A6
     // 289 / 320, W4/A3 237 / 259, where it spills).
-    constexpr bool EARLY = REGSTAGE && NARROW;
+    constexpr bool EARLY = REGSTAGE && (NARROW || (MS == 4 && ACT == 4));
     constexpr int NW = (NARROW ? 1 : 2) + (BW == 4 ? 1 : 0);       // vector-memory instructions of a request
     // Weights are requested so many slabs ahead.  (16 outputs per wavefront: a slab takes 0.5 to 0.8 us, less than memory does; 203 tokens, 4096 x 4096, one / two: W3/A8
     // 31.3 / 23.2, W3/A16 28.5 / 26.0, W4/A16 31.7 / 29.3 us.)
