@@ -31,7 +31,8 @@
 // Tiling: workgroup = 4 wavefronts, tile 32, 64 or 128 tokens x 128 outputs (chosen per launch, goq_gemm_rules.h); with 64 each
 // wavefront owns 64 tokens x 32 outputs = two MFMA tiles of 32 x 32, with three accumulator sets: the slab partials P1, P2
 // (restarted every slab by feeding C = 0 to the slab's first MFMA) and the output Y.  That fits three wavefronts per SIMD for W3
-// with fp16 or int8 activations, two for the other types; tiles of 128 tokens run at two.  Measured on this chip with a probe of the same instruction mix:
+// with fp16 or int8 activations and, in launches with work for them (goq_three_wavefronts), for 8-bit floats, two for the
+// other types; tiles of 128 tokens run at two.  A workgroup with its CU to itself has eight wavefronts of 16 outputs instead.  Measured on this chip with a probe of the same instruction mix:
 // vector-ALU instructions hide only to a small extent behind matrix instructions, whatever the
 // program order (about five per 32x32x16 instruction; every further one costs nearly its full
 // four cycles), so the rate is set by vector-ALU and LDS instructions per matrix instruction.
@@ -45,7 +46,8 @@
 // waits for slab g + 1's activations only.  (With a request under a run-time condition or a plain
 // __syncthreads() the compiler waited for everything, slab g + 2 included, once per slab: a launch with
 // one workgroup per CU took 1.3 us a slab.)
-// Launches of few tiles use 32-token tiles (goq_gemm_rules.h): 4096 x 4096, 64 tokens, W3/A16 37 -> 28 us.
+// Launches of few tiles use 32-token tiles (goq_gemm_rules.h): 4096 x 4096, 64 tokens, W3/A16 37 -> 28 us; with 16 outputs per
+// wavefront (WN below) W3/A8 27.8 -> 22.2.
 // One launch covers up to GOQ_MAX_BATCH layers (goq_gemm_batch): their tiles form one grid, the
 // layers with the deepest rows first, so that a block of matrices has one tail, not one per matrix.
 // Coefficient rescale (H5) once per slab: Y += c1[n,g] * P1 + c2[n,g] * P2 in fp32, after the
@@ -160,8 +162,9 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
 // decode weighs most and operands are narrow, for int8 operands straight from memory and 8-bit floats (us, 64 / 128 tokens: 4096 x
 // 4096, 4096 tokens, W3/A8 170 / 145, W4/A4 182 / 152; ViT-B block, 12608 tokens, W4/A4 314 / 273; packed activations with
 // W3 lose, 183 / 191: their staging needs the registers).
-template <int BW, int ACT, bool PART, bool FOLD, int MS, int WN>
-__global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : BW == 3 && !PART && ACT < 2 && MS < 4 ? 3 : 2) void gemm_kernel(GemmBatch batch)
+// THREE (8-bit floats, 64 tokens): one slab body instead of three, so that three wavefronts fit a SIMD (goq_three_wavefronts).
+template <int BW, int ACT, bool PART, bool FOLD, int MS, int WN, bool THREE>
+__global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : THREE || (BW == 3 && !PART && ACT < 2 && MS < 4) ? 3 : 2) void gemm_kernel(GemmBatch batch)
 {
     int pi = 0;
 #pragma unroll
@@ -189,6 +192,7 @@ __global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : BW == 3 && !PART && AC
     constexpr bool F16 = (ACT == 0 || ACT == 2 || ACT == 6);       // fp16 MFMA
     constexpr bool F8 = (ACT == 4 || ACT == 8);                    // 8-bit-float MFMA
     constexpr bool REGSTAGE = (ACT >= 2);
+    static_assert(!THREE || (F8 && MS == 2 && WN == 32), "three wavefronts per SIMD: 8-bit floats, 64 tokens");
     constexpr bool BIASED = MS == 4 && ACT == 1;                   // slab sums begin at START
     constexpr bool X4 = (ACT == 3 || ACT == 4);                    // two activations per byte
     constexpr bool X6 = (ACT == 5 || ACT == 6);                    // four activations per three bytes
@@ -526,7 +530,7 @@ __global__ __launch_bounds__(TN / WN * 64, WN == 16 ? 2 : BW == 3 && !PART && AC
     // a full barrier.  Their loads into LDS are ordinary writes, so there is no wait to be made exact, and the three
     // bodies of the other kernels only cost (us, three bodies / one: 8192 x 28672, 129 tokens, W4/A6 320 / 302; four
     // layers of 14336 x 4096, 128 tokens, W4/A8 141 / 133; W3/A4 .. A6 within 1 %).
-    constexpr bool ROLL = REGSTAGE && !F8 && MS == 2;
+    constexpr bool ROLL = THREE || (REGSTAGE && !F8 && MS == 2);
     auto products = [&](int t, const OpT &Ai, const OpT &B1i, const OpT &B2i, AccT &P1, AccT &P2, int i) {
         AccT z;
 #pragma unroll
@@ -790,16 +794,16 @@ int lay_out(GemmBatch &b, int n, int tm, int xblock, int wblock)
     return tiles;
 }
 
-template <int BW, int ACT, int MS>
+template <int BW, int ACT, int MS, bool THREE = false>
 int launch_ms(hipStream_t st, GemmBatch &b, int n, bool part)
 {
     constexpr int GOQ_ACT = ACT == 0 ? GOQ_A16 : ACT <= 2 ? GOQ_A8 : ACT <= 4 ? GOQ_A4 : ACT <= 6 ? GOQ_A6 : GOQ_A3;
     const int grid = lay_out(b, n, 32 * MS, goq_block_bytes<GOQ_ACT>(), goq_chunks(BW) * GOQ_ROWS * 16);
     constexpr bool PART = ACT != 0 && MS < 4;                // (there are no tiles of 128 tokens with partials)
     if (PART && part)
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, PART, false, MS, 32, false>), dim3((unsigned)grid), dim3(256), 0, st, b);
     else
-        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, MS, 32, THREE>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm");
 }
 
@@ -810,7 +814,7 @@ int launch_sixteen(hipStream_t st, GemmBatch &b, int n, bool alone)
     constexpr int GOQ_ACT = ACT == 0 ? GOQ_A16 : ACT <= 2 ? GOQ_A8 : ACT <= 4 ? GOQ_A4 : ACT <= 6 ? GOQ_A6 : GOQ_A3;
     constexpr unsigned SPARE = 72 * 1024;
     const int grid = lay_out(b, n, 32, goq_block_bytes<GOQ_ACT>(), goq_chunks(BW) * GOQ_ROWS * 16);
-    hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, 1, 16>), dim3((unsigned)grid), dim3(512), alone ? SPARE : 0, st, b);
+    hipLaunchKernelGGL((gemm_kernel<BW, ACT, false, false, 1, 16, false>), dim3((unsigned)grid), dim3(512), alone ? SPARE : 0, st, b);
     return goq_check_launch("goq_gemm");
 }
 
@@ -832,6 +836,8 @@ int launch(hipStream_t st, GemmBatch &b, int n)
     // (the 8-bit-float form has half the matrix work per tile and is no faster with 32 tokens anywhere)
     if constexpr (!F8)
         if (goq_narrow_tiles(BW, ACT == 0, ACT >= 2, n, p)) return launch_ms<BW, ACT, 1>(st, b, n, part);
+    if constexpr (F8)
+        if (!part && goq_three_wavefronts(n, p)) return launch_ms<BW, ACT, 2, true>(st, b, n, false);
     return launch_ms<BW, ACT, 2>(st, b, n, part);
 }
 
@@ -839,7 +845,7 @@ template <int BW>
 int launch_folded(hipStream_t st, GemmBatch &b, int n)
 {
     const int grid = lay_out(b, n, 64, goq_block_bytes<GOQ_A16>(), goq_chunks(BW) * GOQ_ROWS * 16);
-    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2, 32>), dim3((unsigned)grid), dim3(256), 0, st, b);
+    hipLaunchKernelGGL((gemm_kernel<BW, 0, false, true, 2, 32, false>), dim3((unsigned)grid), dim3(256), 0, st, b);
     return goq_check_launch("goq_gemm_folded");
 }
 

@@ -101,6 +101,29 @@ inline bool goq_wide_tiles(bool f8, int n, const GoqTileProblem *p)
     return wide >= 2 && (!f8 && deepest <= 8 ? 8 * middle >= 15 * wide : 4 * middle >= 7 * wide);
 }
 
+// 8-bit floats, launches of 64-token tiles: three wavefronts per SIMD (true) or two?  Results do not depend on the choice.
+//
+// Three fit with one slab body where two have three bodies with buffers at fixed places, which waits for everything once per slab: slower as long as a CU has no third
+// workgroup to fill that.  80 launches, W4 with int4 and int3, time of three over two wavefronts: layers of equal depth, up to two tiles on the fullest CU 1.00 .. 1.09, three 0.86 ..
+// 0.96, five 0.91 .. 0.94 (two of 11008 x 4096, 203 tokens 89.2 / 79.1 us).  Layers of several depths, tiles of the deepest layer per CU: below 1.4 1.05 .. 1.13; 1.4 to 2.25 0.95 .. 1.00
+// where the deepest layer has at most 192 tiles (ViT-B block, 1576 tokens 42.3 / 40.2) and up to 1.10 where it has more (two of 5650 x 4736 and 4238 x 1408, 262 tokens 62.6 / 68.3);
+// above 0.93 .. 1.00 (7B block, 400 tokens 261 / 244).
+inline bool goq_three_wavefronts(int n, const GoqTileProblem *p)
+{
+    int64_t tiles = 0, slabs = 0, deepest = 0, deep = 0;
+    bool equal = true;
+    for (int i = 0; i < n; ++i) deepest = p[i].gn > deepest ? p[i].gn : deepest;
+    for (int i = 0; i < n; ++i) {
+        const int64_t t = ((int64_t)p[i].tokens + 63) / 64 * ((p[i].out + GOQ_TILE_OUT - 1) / GOQ_TILE_OUT);
+        tiles += t;
+        slabs += t * p[i].gn;
+        deep += p[i].gn == deepest ? t : 0;
+        equal = equal && p[i].gn == p[0].gn;
+    }
+    if (equal) return tiles > 512;
+    return 100 * slabs >= (deep <= 192 ? 140 : 225) * 256 * deepest;
+}
+
 // 32-token tiles on eight wavefronts of 16 outputs each, or one of the kernels with 32 outputs per wavefront?  Results do not depend on the choice.
 //
 // Half the chain of instructions per slab where a workgroup has its CU to itself; where CUs hold two and more, the chains hide each other and the second reading of the

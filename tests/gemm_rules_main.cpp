@@ -2,6 +2,7 @@
 //     tiles bw fp16 staged n  tokens out in  tokens out in ..   ->   32 or 64 (tokens per tile)
 //     wide  bw fp16 staged n  tokens out in ..                  ->   128 or 0
 //     alone bw fp16 staged n  tokens out in ..                  ->   1 or 0 (one few-token workgroup per CU)
+//     three bw fp16 staged n  tokens out in ..                  ->   1 or 0 (8-bit floats: three wavefronts per SIMD)
 //     half  bw fp16 staged n  tokens out in ..                  ->   0, or with 16 outputs per wavefront 1, 2 if a workgroup has its CU to itself
 //     order tiles token_tiles x_bytes w_bytes outputs           ->   0, 1 or 2 (GOQ_TILES_*)
 //     deal  tiles                                               ->   1 if every place is taken once, and by XCD in ranges
@@ -50,6 +51,7 @@ int main()
             p[i].gn = in / GOQ_N;
         }
         if (!strcmp(what, "wide")) printf("%d\n", goq_wide_tiles(bw == 4, n, p) ? 128 : 0);
+        else if (!strcmp(what, "three")) printf("%d\n", goq_three_wavefronts(n, p) ? 1 : 0);
         else if (!strcmp(what, "half")) printf("%d\n", goq_sixteen_outputs(n, p));
         else if (!strcmp(what, "alone")) printf("%d\n", goq_alone_on_cu(fp16 != 0, n, p) ? 1 : 0);
         else printf("%d\n", goq_narrow_tiles(bw, fp16 != 0, staged != 0, n, p) ? 32 : 64);

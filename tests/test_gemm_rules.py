@@ -179,6 +179,14 @@ SIXTEEN = [
 ]
 
 
+# layers, tokens, microseconds with two and with three wavefronts per SIMD, W4 with int4 or int3, of 4 % or more
+THREE = [
+    ("4096x4096*3", 150, 53.1, 58.0), ("4017x9600*3", 204, 121.1, 131.5), ("4624x6784*3", 312, 137.9, 120.4), ("24354x1792", 168, 42.7, 36.9), ("11008x4096*2", 203, 89.2, 79.1),
+    ("18222x3712", 478, 121.7, 111.8), (VIT_B, 1000, 30.1, 34.0), (VIT_B, 1300, 37.7, 35.7), (VIT_B, 1576, 42.3, 40.2), (BLOCK_7B, 100, 111.0, 124.8), (BLOCK_7B, 300, 194.8, 185.7),
+    (BLOCK_7B, 400, 261.4, 243.9), ("11930x512 1354x6528", 1645, 90.3, 95.5), ("5650x4736*2 4238x1408", 262, 62.6, 68.3), ("3181x896*3 1338x640", 402, 24.0, 22.5),
+]
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     """The rules' answers to a list of questions."""
@@ -217,6 +225,11 @@ def test_wide_tiles_follow_the_measurements(ask):
     assert len(got) == len(WIDE)
     wrong = [(case, g) for case, g in zip(WIDE, got) if int(g) != (128 if case[5] < case[4] else 0)]
     assert not wrong, wrong
+
+
+def test_three_wavefronts_follow_the_measurements(ask):
+    lines = ["three 4 0 1 %d %s" % (len(_layers(text)), " ".join("%d %d %d" % ((tokens,) + l) for l in _layers(text))) for text, tokens, _, _ in THREE]
+    assert ask(lines) == [str(int(three < two)) for _, _, two, three in THREE]
 
 
 def test_sixteen_outputs_follow_the_measurements(ask):

@@ -53,6 +53,24 @@ def test_bits_do_not_depend_on_the_width(oracle, ask, act, bw, tokens, out, inn)
             assert np.max(np.abs(alone.cpu().numpy().astype(np.float64) - ref) / scale) <= 2e-6
 
 
+@pytest.mark.parametrize("act", ["A4", "A3"])
+@pytest.mark.parametrize("tokens,out,inn", [(200, 20000, 256), (129, 24000, 640), (650, 6500, 128)])
+def test_three_wavefronts_per_simd(ask, act, tokens, out, inn):
+    """8-bit floats, more than two tiles of 64 tokens per CU: the bits of calls of 33 tokens, which have 16 outputs per wavefront or two wavefronts
+    per SIMD."""
+    import paper_2605_26092_amd as goq
+    torch = gu.torch_cuda()
+    print("three %s %dx%dx%d" % (act, tokens, out, inn), flush=True)
+    assert ask(["three 4 0 1 1 %d %d %d" % (tokens, out, inn), "wide 4 0 1 1 %d %d %d" % (tokens, out, inn), "three 4 0 1 1 33 %d %d" % (out, inn)]) == ["1", "0", "0"]
+    p = _problem(goq, 4, act, tokens, out, inn, goq.F32, out)[3]
+    goq.gemm(4, getattr(goq, act), *p)
+    Y = torch.full((33, out), float("nan"), dtype=torch.float32, device="cuda")
+    for at in (0, tokens - 33):
+        goq.gemm(4, getattr(goq, act), 33, out, inn, p[3], p[4][at:at + 33], p[5][at:at + 33], Y, goq.F32)
+        torch.cuda.synchronize()
+        assert torch.isfinite(Y).all() and torch.equal(Y, p[6][at:at + 33])
+
+
 @pytest.mark.parametrize("act", ["A16"] + sorted(PACKERS))
 @pytest.mark.parametrize("bw", [3, 4])
 @pytest.mark.parametrize("tokens,layers,answer", [(300, [(3000, 128), (520, 3072)], "2"), (1700, [(3000, 128), (200, 3072)], "1"), (40, [(700, 384), (1000, 640), (33, 128)], "1")])
