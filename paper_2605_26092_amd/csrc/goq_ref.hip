@@ -7,12 +7,12 @@
 // all output channels share:
 //     A^T A = [b1 b2]^T S_g [b1 b2],   A^T Y = [b1 b2]^T S_g w,
 // so the tokens are reduced once per macro-block (kernel 1) instead of once per output channel, and
-// kernel 2 needs, per (o, g), the two products S_g b1 and S_g b2 and five dot products.  Both are
+// kernel 2 needs, per (o, g), products with the upper triangle of S_g and five dot products.  Both are
 // fp64 contractions and run on v_mfma_f64_16x16x4: it has the rate of the vector ALU (one 16 x 16 x 4
 // product in 64 cycles) but takes one operand register pair per 16 fused multiply-adds of a lane, so that
 // loads, conversions and address arithmetic hide behind it, which bound the same sums on the vector ALU
-// (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now 16 and 141).  Everything is fp64 with
-// fixed summation orders (tokens ascending; columns, then rows), so the result is a pure function of
+// (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now 16 and 127).  Everything is fp64 with
+// fixed summation orders (tokens ascending; columns, then rows of a 16-row tile, then tiles), so the result is a pure function of
 // the inputs.  It differs from a token-by-token evaluation of Eq. 3 only by fp64 rounding, far below
 // the fp16 quantum of the stored coefficients.
 //
@@ -20,6 +20,7 @@
 // B[l / 16][l % 16], element v of D is D[4 v + l / 16][l % 16].
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "goq_layout.h"
 #include "goq_decode.h"
 #include "goq_internal.h"
@@ -28,23 +29,27 @@
 namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int RT = 256;                  // threads per workgroup (both kernels): four wavefronts
 constexpr int TT = 64;                   // tokens per LDS tile of the Gram kernel
-constexpr int XP = GOQ_N + 16;           // halfs per LDS row: the four tokens of an operand in different banks
+constexpr int XP = GOQ_N + 16;           // floats per LDS row: the four tokens of an operand in different banks
 constexpr int OB = 64;                   // output channels per workgroup of the solve kernel, 16 per wavefront
-constexpr int TILES = 36;                // 16 x 16 tiles of S_g on and below the diagonal
+constexpr int TILES = 36;                // 16 x 16 tiles of S_g on and above the diagonal
+constexpr int H = 4;                     // row tiles of M^T that the solve kernel takes at a time
 
 __device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ double half_to_double(_Float16 h) { return (double)(float)h; }
 
-// ---- kernel 1: S_g = X_q^T X_q.  Workgroup (g, y): wavefront w owns tile 4 y + w of the lower triangle
-// over all tokens, so that 32 macro-blocks already fill the chip with one tile per SIMD; the tile's
-// mirror image is stored beside it.
+// ---- kernel 1: S_g = X_q^T X_q.  Workgroup (g, y): wavefront w owns tile 4 y + w of the upper triangle
+// over all tokens, so that 32 macro-blocks already fill the chip with one tile per SIMD.  What is stored is M_g: the tiles on the
+// diagonal as they are, those above it twice (exact), nothing below.  A tile of 64 tokens takes 1.3 us where its products
+// take 0.43; what takes the rest has not been found (four tiles of X in flight instead of one, two or four accumulators in turn: no faster).
 __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X, int tokens, int64_t in,
-                                                  double *__restrict__ S)
+                                                  double *__restrict__ M)
 {
-    __shared__ __attribute__((aligned(16))) _Float16 xt[TT][XP];
+    __shared__ __attribute__((aligned(16))) float xt[TT][XP];
     const int g = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, k = lane >> 4;
@@ -52,47 +57,69 @@ __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X
     int ti = 0;
     while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
     const int tj = tile - ti * (ti + 1) / 2;
-    // 64 tokens x 128 halfs = 1024 pieces of 16 bytes, four per thread; rows past the end are zero
-    auto load = [&](int t0, uint4 (&v)[4]) {
+    // 64 tokens x 128 halfs = 1024 pieces of 16 bytes, four per thread (rows past the end: the last one, which becomes zeros in LDS)
+    const uint16_t *rows = X + (int64_t)g * GOQ_N + (tid & 15) * 8;
+    f16x8 v[4];
+    auto load = [&](int64_t t0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f16x8 *>(rows + min(t0 + 16 * i + (tid >> 4), (int64_t)tokens - 1) * in);
+    };
+    // operands of four products, and the next four's on their way
+    float f[2][2][4];
+    double d[2][4];
+    auto read = [&](int t, float (&o)[2][4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int t = t0 + 16 * i + (tid >> 4);
-            v[i] = make_uint4(0, 0, 0, 0);
-            if (t < tokens) v[i] = *reinterpret_cast<const uint4 *>(X + (int64_t)t * in + (int64_t)g * GOQ_N + (tid & 15) * 8);
+            o[0][i] = xt[t + 4 * i + k][16 * tj + n];
+            o[1][i] = xt[t + 4 * i + k][16 * ti + n];
         }
     };
-    uint4 v[4];
-    load(0, v);
+    load(0);
     f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int t0 = 0; t0 < tokens; t0 += TT) {
+    for (int64_t t0 = 0; t0 < tokens; t0 += TT) {
         __syncthreads();                                       // the previous tile has been used
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(&xt[16 * i + (tid >> 4)][(tid & 15) * 8]) = v[i];
+        for (int i = 0; i < 4; ++i) {
+            float *o = &xt[16 * i + (tid >> 4)][(tid & 15) * 8];
+            const f16x8 x = t0 + 16 * i + (tid >> 4) < tokens ? v[i] : f16x8{};
+            *reinterpret_cast<f32x4 *>(o) = f32x4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
+            *reinterpret_cast<f32x4 *>(o + 4) = f32x4{(float)x[4], (float)x[5], (float)x[6], (float)x[7]};
+        }
         __syncthreads();
-        if (t0 + TT < tokens) load(t0 + TT, v);
+        load(t0 + TT);
+        read(0, f[0]);
 #pragma unroll
-        for (int t = 0; t < TT; t += 4)
-            acc = mfma(half_to_double(xt[t + k][16 * ti + n]), half_to_double(xt[t + k][16 * tj + n]), acc);
-    }
-    double *Sg = S + (int64_t)g * GOQ_N * GOQ_N;
+        for (int b = 0; b < TT / 16; ++b) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int i = 16 * ti + 4 * e + k, j = 16 * tj + n;
-        Sg[i * GOQ_N + j] = acc[e];
-        if (ti != tj) Sg[j * GOQ_N + i] = acc[e];
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[c][i] = (double)f[b & 1][c][i];
+            if (b + 1 < TT / 16) read(16 * (b + 1), f[(b + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);                 // (left alone, the reads move behind the products)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = mfma(d[0][i], d[1][i], acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    double *Mg = M + (int64_t)g * GOQ_N * GOQ_N + (16 * tj + k) * GOQ_N + 16 * ti + n;
+    const double scale = ti == tj ? 1.0 : 2.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Mg[4 * e * GOQ_N] = scale * acc[e];
 }
 
-// ---- kernel 2: per (g, block of OB output channels).  A wavefront forms u1 = S_g b1 and u2 = S_g b2 of
-// its 16 output channels (columns of B), all 128 rows: eight 16-row tiles and two bases of
-// accumulators, one read of a row of S_g (symmetric: column j is read as the contiguous row j, from
-// L2, the next four rows in flight) for all of them.  Then its share of the five dot products per lane, the four
-// lanes of a channel are added in order and the 2 x 2 system is solved.  b1, b2 and w are staged as
-// fp16, which holds them exactly.
+// ---- kernel 2: per (g, block of OB output channels).  With M = D + 2 U (diagonal tiles of S and twice those above) and any a, b
+//     a^T S b = (a^T M b + b^T M a) / 2,
+// so the five dot products need M^T b1, M^T b2 and M^T w: 3 x 36 tile products instead of the 2 x 64 of S b1 and S b2.  A wavefront forms
+// them for its 16 output channels (columns of B), H 16-row tiles of M^T at a time (column j of M^T is the contiguous row j of M, from L2, two steps of four in flight),
+// and adds their share of the dot products per lane; the four lanes of a channel are added in order and the 2 x 2 system is solved.  b1, b2 and w are
+// staged as fp16, which holds them exactly.  Bound by the fp64 matrix rate (4096 x 4096, 512 tokens, both kernels, us: both products with S 158.4, H = 2 at
+// three wavefronts per SIMD 145.8, H = 4 142.1 with six registers spilled, at two without 140.9; states staged as the upper halves of doubles, so
+// that a shift converts them, 143.4; the last but one with dot products per row tile, as now, 140.9 .. 141.2).  Error of the unrounded pairs against extended
+// precision, rms over 256 to 700 channels, six sets of inputs: with S 6.5e-16 .. 7.7e-16, now 4.9e-16 .. 6.3e-16 (dot products as one chain of additions, two sets, up to 8.5e-16).
 template <int BW>
 __global__ __launch_bounds__(RT, 2) void ref_solve_kernel(const uint16_t *__restrict__ w, const uint8_t *__restrict__ codes,
                                                        const uint8_t *__restrict__ pattern, const uint8_t *__restrict__ signs,
-                                                       const double *__restrict__ S, int64_t out, int64_t in, double lambda,
+                                                       const double *__restrict__ M, int64_t out, int64_t in, double lambda,
                                                        double *__restrict__ craw, uint16_t *__restrict__ c1,
                                                        uint16_t *__restrict__ c2)
 {
@@ -144,48 +171,69 @@ __global__ __launch_bounds__(RT, 2) void ref_solve_kernel(const uint16_t *__rest
 
     const int lane = tid & 63, n = lane & 15, k = lane >> 4;
     const int oo = (tid >> 6) * 16 + n;                        // this lane's channel
-    const double *Sg = S + (int64_t)g * GOQ_N * GOQ_N + k * GOQ_N + n;
-    f64x4 u1[8], u2[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { u1[i] = f64x4{0.0, 0.0, 0.0, 0.0}; u2[i] = f64x4{0.0, 0.0, 0.0, 0.0}; }
-    // rows 4 t + k of S_g, column 16 i + n
-    auto load = [&](int t, double (&a)[8]) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = Sg[4 * t * GOQ_N + 16 * i];
-    };
-    auto products = [&](int t, const double (&a)[8]) {
-        const double b1 = half_to_double(vb1[oo][4 * t + k]), b2 = half_to_double(vb2[oo][4 * t + k]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            u1[i] = mfma(a[i], b1, u1[i]);
-            u2[i] = mfma(a[i], b2, u2[i]);
-        }
-    };
-    double a0[8], a1[8];
-    load(0, a0);
-    for (int t = 0; t < 30; t += 2) {
-        load(t + 1, a1);
-        products(t, a0);
-        load(t + 2, a0);
-        products(t + 1, a1);
-    }
-    load(31, a1);
-    products(30, a0);
-    products(31, a1);
-
+    const double *Mg = M + (int64_t)g * GOQ_N * GOQ_N + k * GOQ_N + n;
     double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int p = 0; p < 8 / H; ++p) {
+        f64x4 u[H][3];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = 16 * i + 4 * e + k;
-            const double b1 = half_to_double(vb1[oo][r]), b2 = half_to_double(vb2[oo][r]), wr = half_to_double(vw[oo][r]);
-            q[0] = fma(b1, u1[i][e], q[0]);
-            q[1] = fma(b2, u1[i][e], q[1]);
-            q[2] = fma(b2, u2[i][e], q[2]);
-            q[3] = fma(wr, u1[i][e], q[3]);
-            q[4] = fma(wr, u2[i][e], q[4]);
+            for (int c = 0; c < 3; ++c) u[h][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+        const double *rows = Mg + 16 * H * p;
+        auto load = [&](int t, double (&a)[H]) {               // columns 4 t .. 4 t + 3 (below the diagonal: not used)
+#pragma unroll
+            for (int h = 0; h < H; ++h) a[h] = rows[4 * t * GOQ_N + 16 * h];
+        };
+        auto products = [&](int t, const double (&a)[H], auto first) {   // for row tiles first .. H - 1
+            const double b[3] = {half_to_double(vb1[oo][4 * t + k]), half_to_double(vb2[oo][4 * t + k]), half_to_double(vw[oo][4 * t + k])};
+#pragma unroll
+            for (int h = first; h < H; ++h)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) u[h][c] = mfma(a[h], b[c], u[h][c]);
+        };
+        double a[2][H];
+        load(0, a[0]);
+        load(1, a[1]);
+        const int square = 4 * H * p;                          // steps that all row tiles have; then one column of tiles at a time ends
+        for (int t = 0; t < square; t += 2)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                products(t + i, a[i], std::integral_constant<int, 0>());
+                load(t + i + 2, a[i]);
+            }
+        auto triangle = [&](auto first) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                products(square + 4 * first + i, a[i % 2], first);
+                if (first < H - 1 || i < 2) load(square + 4 * first + i + 2, a[i % 2]);
+            }
+        };
+        triangle(std::integral_constant<int, 0>());
+        triangle(std::integral_constant<int, 1>());
+        if constexpr (H == 4) {
+            triangle(std::integral_constant<int, 2>());
+            triangle(std::integral_constant<int, 3>());
         }
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};           // of a row tile: short chains of roundings
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 16 * (H * p + h) + 4 * e + k;
+                const double b1 = half_to_double(vb1[oo][r]), b2 = half_to_double(vb2[oo][r]), wr = half_to_double(vw[oo][r]);
+                const double u1 = u[h][0][e], u2 = u[h][1][e], uw = u[h][2][e];
+                s[0] = fma(b1, u1, s[0]);
+                s[1] = fma(b1, u2, fma(b2, u1, s[1]));
+                s[2] = fma(b2, u2, s[2]);
+                s[3] = fma(b1, uw, fma(wr, u1, s[3]));
+                s[4] = fma(b2, uw, fma(wr, u2, s[4]));
+            }
+#pragma unroll
+            for (int c = 0; c < 5; ++c) q[c] += s[c];
+        }
+    }
+    q[1] *= 0.5; q[3] *= 0.5; q[4] *= 0.5;
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
         q[c] += __shfl_xor(q[c], 16);
@@ -216,15 +264,15 @@ int goq_launch_ref(hipStream_t st, int bw, int64_t tokens, int64_t out, int64_t 
     const int64_t ob = (out + OB - 1) / OB;
     if (gn > 0x7fffffff || ob > 65535 || tokens > 0x7fffffff)
         return goq_set_error(GOQ_ESHAPE, "goq_ref_coefficients: layer too large for one launch");
-    double *S = reinterpret_cast<double *>(workspace);
-    hipLaunchKernelGGL(gram_kernel, dim3((unsigned)gn, TILES / 4), dim3(RT), 0, st, X, (int)tokens, in, S);
+    double *M = reinterpret_cast<double *>(workspace);
+    hipLaunchKernelGGL(gram_kernel, dim3((unsigned)gn, TILES / 4), dim3(RT), 0, st, X, (int)tokens, in, M);
     int rc = goq_check_launch("goq_ref_coefficients");
     if (rc) return rc;
     if (bw == 3)
         hipLaunchKernelGGL(ref_solve_kernel<3>, dim3((unsigned)gn, (unsigned)ob), dim3(RT), 0, st, w, codes, pattern, signs,
-                           S, out, in, lambda, craw, c1, c2);
+                           M, out, in, lambda, craw, c1, c2);
     else
         hipLaunchKernelGGL(ref_solve_kernel<4>, dim3((unsigned)gn, (unsigned)ob), dim3(RT), 0, st, w, codes, pattern, signs,
-                           S, out, in, lambda, craw, c1, c2);
+                           M, out, in, lambda, craw, c1, c2);
     return goq_check_launch("goq_ref_coefficients");
 }

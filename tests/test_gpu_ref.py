@@ -71,6 +71,25 @@ def test_ref_tile_edges_and_weights_at_any_address(oracle, tokens):
     assert np.array_equal(c2.cpu().numpy().view(np.uint16), aligned[2])
 
 
+@pytest.mark.parametrize("bw", [3, 4])
+def test_ref_every_tile_of_the_gram_matrix(oracle, bw):
+    """Only the upper triangle of a macro-block's Gram matrix is kept, in 16 x 16 tiles: macro-block g of these inputs has nonzero columns in
+    the two column tiles of the g-th pair only, so each of the 36 tiles decides a macro-block's pairs."""
+    import paper_2605_26092_amd as goq
+    pairs = [(a, b) for a in range(8) for b in range(a, 8)]
+    tokens, out, inn = 9, 65, 128 * len(pairs)
+    print("ref tiles bw=%d" % bw, flush=True)
+    W = goq_inputs.weights(out, inn, config_id=54, tensor_id=bw)
+    q = oracle.quantize_geo(bw, W, threads=8)
+    X = goq_inputs.activations_a16(tokens, inn, config_id=54, tensor_id=100, outlier_frac=0.01)
+    for g, (a, b) in enumerate(pairs):
+        keep = np.zeros(128, dtype=bool)
+        keep[16 * a + 3:16 * a + 16:5] = keep[16 * b:16 * b + 16:7] = True
+        X[:, 128 * g:128 * g + 128][:, ~keep] = 0
+    ref, rc = oracle.ref_coefficients(q, W, X, lam=1e-4, threads=8)
+    _compare(*_run(goq, q, W, X, 1e-4), ref, rc)
+
+
 def test_ref_special_cases(oracle):
     """identity inputs with and without a ridge (the GEO coefficients), weights in the span of the
     bases (exact recovery), a single token (rank-one system, ridge only), an all-zero macro-block."""
