@@ -82,7 +82,8 @@ int goq_packed_bytes(int bw, int64_t out, int64_t in, size_t *bytes);
  * (Eq. 1); per 8-weight micro-block the pattern s* = argmax_s sum_pairs |x_i r_j - x_j r_i| (ties:
  * smallest s) with pair signs eta = sgn(x_i r_j - x_j r_i) (+1 at zero) (Sec. 3.3); b2 by the
  * Theorem 1 exchange; c1 = <w,b1>/||b1||^2, c2 = <w,b2>/||b2||^2 (Eq. 2) rounded to fp16.  An
- * all-zero macro-block gets zero codes, pattern 0, signs 0, c1 = c2 = 0.  Arithmetic is fp64; the
+ * all-zero macro-block gets zero codes, pattern 0, signs 0, c1 = c2 = 0.  The outputs are those of
+ * fp64 arithmetic (fp32 decides where its error bound allows); the
  * sums are exact (every term is a multiple of 2^-31 and the totals stay below 2^22), so the
  * outputs are a pure function of w and equal a sequential evaluation in ascending k.  codes must be
  * 8-byte aligned.  Weights must be finite. */
@@ -121,7 +122,7 @@ int goq_unpack(void *stream, int bw, int64_t out, int64_t in, const void *packed
  *   act = GOQ_A4 : x is packed int4 [in / 2 bytes], sx as for GOQ_A8.
  *   act = GOQ_A6 : x is packed int6 [3 in / 4 bytes], sx as for GOQ_A8.
  *   act = GOQ_A3 : x is packed int3 [3 in / 8 bytes], sx as for GOQ_A8.
- *   y is [out] of ytype.  Large launches stream (see goq_gemv_select): the PoT codes are decoded to
+ *   y is [out] of ytype.  Larger launches stream (see goq_gemv_select): the PoT codes are decoded to
  *   8-bit floats (a power of two is exact in E5M2) and b2 is rebuilt from b1 by a byte permute and a
  *   sign flip; the two slab dot products run on the 8-bit-float matrix instruction against x written
  *   as block fixed point (24 bits below the largest exponent of each 32-activation block: exact for
@@ -129,6 +130,8 @@ int goq_unpack(void *stream, int bw, int64_t out, int64_t in, const void *packed
  *   Small launches hand x to the fp16 matrix instruction as it is.  Coefficients are applied per slab
  *   in fp32.  Results are deterministic (no floating-point atomics).  x must be finite (Inf / NaN
  *   inputs give unspecified finite or non-finite outputs).
+ *   Streaming launches of a few projections run 256 workgroups that own whole outputs instead, on the
+ *   same digits; they take a scratch region all the same.
  *   Row groups split over several workgroups are combined through one of the library's 8 static
  *   scratch regions on the device (2.1 MB each), one region per stream: launches on one stream run
  *   one after the other and may follow each other without limit.  A 9th stream takes over the
@@ -178,7 +181,7 @@ int goq_gemv_batch_ws(void *stream, int bw, int act, int n, const goq_gemv_desc 
  * stream): e.g. all projections of all decoder blocks of a model.  The units (512 output rows x
  * one 128-wide slab) of all n <= GOQ_MAX_STREAM problems form one sequence that is cut into equal
  * contiguous pieces, one per workgroup, so start-up and tail of the launch are paid once per
- * stream instead of once per block.  The problems are independent: the library orders nothing
+ * stream instead of once per block (a few projections: see goq_gemv_select).  The problems are independent: the library orders nothing
  * between them (x of every problem must be ready before the launch).
  *   goq_gemv_stream_table writes the problem table (goq_gemv_stream_table_bytes(n) bytes) into a
  *   HOST buffer, 8-byte aligned; the caller copies those bytes to device memory (16-byte aligned)
@@ -222,7 +225,9 @@ int goq_mfma_rate_probe(void *stream, int kind, int workgroups, int iters, float
  *                   problem's rows rounded up to 16) and at most 24576 (tile, macro-block)
  *                   pairs -- 48 Mi weights -- go to the row-owner kernel, everything else streams;
  *   GOQ_GEMV_STREAM the streaming kernel: equal contiguous pieces of the launch's weight bytes
- *                   per workgroup, split row groups combined through the scratch area;
+ *                   per workgroup, split row groups combined through the scratch area; where
+ *                   that is faster (a few projections, no row longer than 16384 weights) ranges of
+ *                   16-row tiles of about equal bytes instead, one per workgroup, without a combine;
  *   GOQ_GEMV_ROWS   the row-owner kernel: one workgroup per 16 output rows over the whole depth,
  *                   partial sums combined in LDS (no scratch).  fp16 and int8 activations: the kernel
  *                   of goq_gemm with few tokens, x goes to the fp16 matrix instruction as it is
@@ -232,7 +237,8 @@ enum { GOQ_GEMV_AUTO = 0, GOQ_GEMV_STREAM = 1, GOQ_GEMV_ROWS = 2 };
 int goq_gemv_select(int kernel);
 
 /* What a goq_gemv_batch call with these shapes would launch under the current selection: *kernel
- * receives GOQ_GEMV_STREAM or GOQ_GEMV_ROWS, *workgroups the grid size (both host pointers).
+ * receives GOQ_GEMV_STREAM or GOQ_GEMV_ROWS, *workgroups the grid size (both host pointers); for
+ * GOQ_GEMV_STREAM that of the form with pieces (ranges of tiles: 256 workgroups of 1024 threads).
  * Only out and in of the descriptors are read; nothing is launched and no device is touched. */
 int goq_gemv_plan(int bw, int act, int n, const goq_gemv_desc *descs, int *kernel, int *workgroups);
 

@@ -157,8 +157,8 @@ __device__ __forceinline__ f16x8 widen8(uint32_t lo, uint32_t hi)
 // workgroups share CUs (goq_sixteen_outputs).  us, 32 / 16 outputs, 4096 x 4096, 203 tokens: W3/A8 29.0 / 23.2, W4/A16 34.6 / 29.3, W3/A16 28.1 / 26.8, W3/A6 44.1 / 30, W4/A4 44.6 / 27.6.
 // MS: MFMA tiles of 32 tokens per wavefront (the workgroup's tile has 32 MS tokens).  With four of them a wavefront keeps the
 // decoded weights of the slab (32 registers) and goes through its tiles one after the other, so that two slab sums are
-// open at a time and not eight: that fits two wavefronts per SIMD (W3 249 registers; W4 all 256 and seven spilled, six of them for the end of the
-// tile, one read back once in three slabs), and a weight is decoded once per 128 tokens.  Worth it where
+// open at a time and not eight: that fits two wavefronts per SIMD (W3 248 registers; W4 all 256, and with int3
+// five spilled), and a weight is decoded once per 128 tokens.  Worth it where
 // decode weighs most and operands are narrow, for int8 operands straight from memory and 8-bit floats (us, 64 / 128 tokens: 4096 x
 // 4096, 4096 tokens, W3/A8 170 / 145, W4/A4 182 / 152; ViT-B block, 12608 tokens, W4/A4 314 / 273; packed activations with
 // W3 lose, 183 / 191: their staging needs the registers).

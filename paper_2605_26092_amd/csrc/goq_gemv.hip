@@ -31,7 +31,7 @@
 //
 // (Launches of a few hundred 16-row tiles at most -- single layers -- go to the kernel of few-token GEMMs,
 // goq_gemm_small.hip, or, with packed activations, to gemv_rows_kernel of this file: one workgroup per 16 rows
-// over the whole depth, no combine.)
+// over the whole depth, no combine.  Launches between those and long streams go to goq_gemv_short.hip where goq_gemv_rules.h says so.)
 //
 // Where a piece boundary falls inside a row group, each wavefront publishes the partial sums of
 // its 64 rows to a workspace and the LAST wavefront to arrive (an atomic counter per boundary
