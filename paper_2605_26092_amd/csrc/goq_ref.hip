@@ -12,7 +12,7 @@
 // product in 64 cycles) but takes one operand register pair per 16 fused multiply-adds of a lane, so that
 // loads, conversions and address arithmetic hide behind it, which bound the same sums on the vector ALU
 // (4096 x 4096, 512 tokens: Gram matrices 120 us, solve 272 us; now 16 and 127).  Everything is fp64 with
-// fixed summation orders (tokens ascending; columns, then rows of a 16-row tile, then tiles), so the result is a pure function of
+// fixed summation orders (tokens ascending, in one or two parts by the layer's size; columns, then rows of a 16-row tile, then tiles), so the result is a pure function of
 // the inputs.  It differs from a token-by-token evaluation of Eq. 3 only by fp64 rounding, far below
 // the fp16 quantum of the stored coefficients.
 //
@@ -32,7 +32,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int RT = 256;                  // threads per workgroup (both kernels): four wavefronts
+constexpr int RT = 256;                  // threads per workgroup of the solve kernel: four wavefronts
 constexpr int TT = 64;                   // tokens per LDS tile of the Gram kernel
 constexpr int XP = GOQ_N + 16;           // floats per LDS row: the four tokens of an operand in different banks
 constexpr int OB = 64;                   // output channels per workgroup of the solve kernel, 16 per wavefront
@@ -43,15 +43,20 @@ __device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) { return __bu
 __device__ __forceinline__ double half_to_double(_Float16 h) { return (double)(float)h; }
 
 // ---- kernel 1: S_g = X_q^T X_q.  Workgroup (g, y): wavefront w owns tile 4 y + w of the upper triangle
-// over all tokens, so that 32 macro-blocks already fill the chip with one tile per SIMD.  What is stored is M_g: the tiles on the
+// over all tokens (or its part of them), so that 32 macro-blocks already fill the chip with one tile per SIMD.  What is stored is M_g: the tiles on the
 // diagonal as they are, those above it twice (exact), nothing below.  A tile of 64 tokens takes 1.3 us where its products
 // take 0.43; what takes the rest has not been found (four tiles of X in flight instead of one, two or four accumulators in turn: no faster).
-__global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X, int tokens, int64_t in,
+// PARTS: of the tokens, each with four wavefronts of the workgroup and an LDS tile of its own.  Two where there is a tile for either and at most two
+// workgroups per CU, so that wavefronts cover each other's waits (both kernels, us, one part / two: 512 tokens, 4096 x 4096 140.7 / 139.6, 4096 x 11008, 774 workgroups, 358.8 /
+// 361.4; 4096 tokens, 768 x 768 93.2 / 82.7; 64 tokens, 2304 x 768 23.0 / 23.8).
+template <int PARTS>
+__global__ __launch_bounds__(256 * PARTS) void gram_kernel(const uint16_t *__restrict__ X, int tokens, int64_t in,
                                                   double *__restrict__ M)
 {
-    __shared__ __attribute__((aligned(16))) float xt[TT][XP];
+    __shared__ __attribute__((aligned(16))) float staged[PARTS][TT][XP];
     const int g = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255, lane = tid & 63;
+    float (&xt)[TT][XP] = staged[part];
     const int n = lane & 15, k = lane >> 4;
     const int tile = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (tid >> 6));
     int ti = 0;
@@ -74,9 +79,10 @@ __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X
             o[1][i] = xt[t + 4 * i + k][16 * ti + n];
         }
     };
-    load(0);
+    load(part * TT);
     f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t t0 = 0; t0 < tokens; t0 += TT) {
+    for (int64_t first = 0; first < tokens; first += PARTS * TT) {
+        const int64_t t0 = first + part * TT;                  // (a part without tokens adds zeros)
         __syncthreads();                                       // the previous tile has been used
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X
             *reinterpret_cast<f32x4 *>(o + 4) = f32x4{(float)x[4], (float)x[5], (float)x[6], (float)x[7]};
         }
         __syncthreads();
-        load(t0 + TT);
+        load(t0 + PARTS * TT);
         read(0, f[0]);
 #pragma unroll
         for (int b = 0; b < TT / 16; ++b) {
@@ -100,6 +106,14 @@ __global__ __launch_bounds__(RT) void gram_kernel(const uint16_t *__restrict__ X
             for (int i = 0; i < 4; ++i) acc = mfma(d[0][i], d[1][i], acc);
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    if constexpr (PARTS == 2) {
+        __syncthreads();
+        f64x4 *sums = reinterpret_cast<f64x4 *>(staged[0]);
+        if (part) sums[tid] = acc;
+        __syncthreads();
+        if (part) return;
+        acc += sums[tid];
     }
     double *Mg = M + (int64_t)g * GOQ_N * GOQ_N + (16 * tj + k) * GOQ_N + 16 * ti + n;
     const double scale = ti == tj ? 1.0 : 2.0;
@@ -265,7 +279,10 @@ int goq_launch_ref(hipStream_t st, int bw, int64_t tokens, int64_t out, int64_t 
     if (gn > 0x7fffffff || ob > 65535 || tokens > 0x7fffffff)
         return goq_set_error(GOQ_ESHAPE, "goq_ref_coefficients: layer too large for one launch");
     double *M = reinterpret_cast<double *>(workspace);
-    hipLaunchKernelGGL(gram_kernel, dim3((unsigned)gn, TILES / 4), dim3(RT), 0, st, X, (int)tokens, in, M);
+    if (tokens > TT && gn * (TILES / 4) <= 512)
+        hipLaunchKernelGGL(gram_kernel<2>, dim3((unsigned)gn, TILES / 4), dim3(512), 0, st, X, (int)tokens, in, M);
+    else
+        hipLaunchKernelGGL(gram_kernel<1>, dim3((unsigned)gn, TILES / 4), dim3(256), 0, st, X, (int)tokens, in, M);
     int rc = goq_check_launch("goq_ref_coefficients");
     if (rc) return rc;
     if (bw == 3)

@@ -71,6 +71,27 @@ def test_ref_tile_edges_and_weights_at_any_address(oracle, tokens):
     assert np.array_equal(c2.cpu().numpy().view(np.uint16), aligned[2])
 
 
+@pytest.mark.parametrize("tokens", [64, 65, 128, 129, 191, 193])
+@pytest.mark.parametrize("gn", [2, 56, 57])
+def test_ref_two_parts_of_the_tokens(oracle, tokens, gn):
+    """More than 64 tokens and at most 56 macro-blocks: the Gram matrices are added from two halves of the workgroup, 64 tokens in turn.  Inputs
+    are small integers, so Gram matrices are exact in any order: a macro-block's pairs have the same bits in a layer of 57."""
+    import paper_2605_26092_amd as goq
+    out, inn = 5, 128 * gn
+    print("ref parts tokens=%d gn=%d" % (tokens, gn), flush=True)
+    W = goq_inputs.weights(out, 128 * 57, config_id=55, tensor_id=1)[:, :inn].copy()
+    q = oracle.quantize_geo(3, W, threads=8)
+    X = np.random.default_rng(tokens).integers(-9, 10, (tokens, 128 * 57)).astype(np.float16)
+    Xg = np.ascontiguousarray(X[:, :inn])
+    ref, rc = oracle.ref_coefficients(q, W, Xg, lam=1e-4, threads=8)
+    got = _run(goq, q, W, Xg, 1e-4)
+    _compare(*got, ref, rc)
+    wide = np.concatenate([W] * (57 // gn + 1), axis=1)[:, :128 * 57].copy()
+    Xw = np.concatenate([Xg] * (57 // gn + 1), axis=1)[:, :128 * 57].copy()
+    craw = _run(goq, oracle.quantize_geo(3, wide, threads=8), wide, Xw, 1e-4)[0]
+    assert np.array_equal(craw[:, :gn], got[0])
+
+
 @pytest.mark.parametrize("bw", [3, 4])
 def test_ref_every_tile_of_the_gram_matrix(oracle, bw):
     """Only the upper triangle of a macro-block's Gram matrix is kept, in 16 x 16 tiles: macro-block g of these inputs has nonzero columns in
